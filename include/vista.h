@@ -105,7 +105,10 @@ typedef struct {
  * attention form alone: the history is cut into 256 k equal segments, k the
  * smallest count that keeps a segment at or below 8192 items -- 1024 k segments
  * of at most 2048 items for VISTA_ATTN_QLA, whose workgroups are small; at
- * least 256 items); 0 if the descriptor is invalid.
+ * least 256 items); 0 if the descriptor is invalid.  Where the size is left open
+ * (segment_items = 0) the matrix-core path of the softmax and SiLU forms fits its
+ * segments to the launch instead (multiples of 32 from 128 to 32768 items, a
+ * function of the descriptor alone); a size that is given is always kept.
  */
 int32_t vista_summarize_segment_items(const vista_summarize_desc* desc);
 
@@ -155,10 +158,15 @@ size_t vista_summarize_workspace_bytes(const vista_summarize_desc* desc);
  *   workspace        device, >= vista_summarize_workspace_bytes(desc), 256-byte aligned
  *
  * Supported: bf16 with (d, H) = (128, 4) or (256, 8), S in {64, 128, 256, 512} (MFMA path);
- * any dtype with d/H <= 64, d <= 512, S <= 512 (plain fp32-ALU path).
+ * bf16 softmax with (d, H) = (64, 2), (128, 4) or (256, 8) and any other S (MFMA path whose K, V
+ * and weights keep 16 significant bits; history 16-byte, queries and out 8-byte aligned, else the
+ * plain path); any dtype with d/H <= 64, d <= 512, S <= 512 (plain fp32-ALU path).
  * The workspace grows with the user count as well as with the history: the MFMA
- * path keeps (G + B) partial records of H * S * 144 bytes (G = segments), the
- * plain path the same count of H * S * (d/H + 2) * 4 bytes plus fp32 K and V.
+ * path keeps (G + B) partial records of H * S * 144 bytes (G = segments; S rounded
+ * up to 32), the plain path the same count of H * S * (d/H + 2) * 4 bytes plus fp32
+ * K and V.  A workspace that holds what the segments of
+ * vista_summarize_segment_items take (on the plain path, outside the MFMA seed
+ * counts) is accepted even where the stated size is larger: the call then uses those.
  */
 vista_status vista_summarize(const vista_summarize_desc* desc,
                              const void* history_emb,

@@ -62,6 +62,21 @@ __host__ __device__ __forceinline__ int find_user(const int64_t* __restrict__ of
   return lo;
 }
 
+// The same search by a whole wave (all lanes active, `row` wave-uniform): 64 probes a step, so up to 64
+// users take one round trip to memory and 4096 take two.  Any offsets keep the answer in [0, B).
+__device__ __forceinline__ int find_user_wave(const int64_t* __restrict__ offsets, int B, int64_t row) {
+  int lo = 0, n = B;                     // the answer lies in [lo, lo + n)
+  while (n > 1) {
+    const int step = (n + 63) / 64;
+    const int at = int(threadIdx.x & 63) * step;                    // lane i looks at user lo + i step
+    const bool below = at > 0 && at < n && offsets[lo + at] <= row; // lane 0 holds by the invariant
+    const int last = 63 - __builtin_clzll(__builtin_amdgcn_ballot_w64(below) | 1ull);   // last lane not beyond the row
+    lo += last * step;
+    n = n - last * step < step ? n - last * step : step;
+  }
+  return __builtin_amdgcn_readfirstlane(lo);
+}
+
 struct Piece {
   int user;
   int64_t begin, end;  // flat rows [begin, end)
@@ -164,6 +179,7 @@ struct SummarizeArgs {
   int seg;            // resolved segment size
   int64_t G;          // segments
   const int* seg_user; // [G] first user of each segment (written by the plan kernel); null: found in the kernel
+  bool offsets_checked; // the host mirror has been checked: the device need not
   float scale_log2;   // scale * log2(e)
   float scale_plain;  // scale
   const void* X;
@@ -183,6 +199,8 @@ hipError_t launch_self_kv(const vista_summarize_desc& d, const void* Q, const vo
                           float* Vs, hipStream_t s);
 vista_status generic_summarize(const SummarizeArgs& a);
 bool mfma_summarize_supported(const vista_summarize_desc& d);
+bool mfma_split_supported(const vista_summarize_desc& d);
+int mfma_summarize_segment(const vista_summarize_desc& d);
 size_t mfma_summarize_workspace(const vista_summarize_desc& d, int seg);
 vista_status mfma_summarize(const SummarizeArgs& a);
 

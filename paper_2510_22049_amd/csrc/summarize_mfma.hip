@@ -16,8 +16,18 @@
 // The projection of tile t+1 rides along with the attention over tile t, and
 // the tiles of all pieces (user x segment) of the segment form one stream.
 // Where a pair would leave a wave with more than four query blocks (S = 512) or
-// with too few waves per compute unit (D = 256), a head gets four waves instead:
-// the K and V waves plus two that only attend, a quarter of the queries each.
+// with too few waves per compute unit (D = 256), a head gets more waves instead:
+// the K and V waves plus others that only attend, the queries shared by all.
+// (Sixteen waves of two query blocks and 128 registers each, four to a SIMD, were 7 to 10 %
+// slower than eight of four: twice the operand reads from LDS and idle attend-only waves.)
+//
+// SPLIT.  The fixed seed counts keep K, V and the softmax weights as bf16 operands.  Any other seed
+// count (and d = 64) carries them as a bf16 value plus a bf16 remainder, 16 significant bits: scores
+// take two products (the seeds are bf16 already), P V three, the scale is applied to the fp32 keys,
+// and what is left against fp64 is the rounding of the bf16 output.  Twice the matrix work of the
+// plain operands and five more vector instructions per weight pair; against one thread per query on
+// the vector unit, which these shapes used to take: 48 users, 300 007 items, d = 64, S = 100 from
+// 9 800 to 51 us, 3 users, 20 000 items, d = 256, S = 100 from 2 717 to 34 us.
 //
 // Softmax reference.  Scores are kept in base-2 units.  While every score of a
 // tile is provably inside [-60, 60] (Cauchy-Schwarz: |q| |k| <= 60) the
@@ -47,13 +57,14 @@ constexpr int kRecFloats = kRecRows * 64;
 struct MfmaSummarizeParams {
   const uint16_t* X;
   const int64_t* offsets;
-  const int* seg_user;
   const uint16_t* Q;
   int64_t q_user_stride;
   const uint16_t* Wk;
   const uint16_t* Wv;
   float* partials;
   int B, S, H;
+  int nqb;        // query blocks = ceil(S / 32)
+  int wph;        // waves per head (the workgroup has HPW wph of them)
   int64_t N;
   int seg;
   int nhg;        // head groups = H / HPW
@@ -93,17 +104,56 @@ __device__ __forceinline__ void lds_barrier() {
 // Register i of a lane in half hf holds row 4 hf + acc_row0(i) of the 32x32 accumulator.
 __device__ __forceinline__ constexpr int acc_row0(int i) { return 8 * (i / 4) + (i % 4); }
 
+// One 32-wide operand of a tile: the two k-halves of its bf16 value and, where values are kept to 16
+// significant bits (SPLIT), of the bf16 remainder.
+template <bool SPLIT>
+struct Operand {
+  Pack8 hi[2];
+  Pack8 lo[SPLIT ? 2 : 1];
+};
+
+// bf16 pair of (a, b) and of what that pair leaves of them
+__device__ __forceinline__ void split_pk(float a, float b, uint32_t& hi, uint32_t& lo) {
+  hi = cvt_pk_bf16(a, b);
+  lo = cvt_pk_bf16(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xFFFF0000u));
+}
+
+// acc += A B with A = hi (+ lo) and B exact (bf16)
+template <bool SPLIT>
+__device__ __forceinline__ f32x16 mma_exact_b(const Operand<SPLIT>& a, const bf16x8 (&b)[2], f32x16 acc) {
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi[0].v, b[0], acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi[1].v, b[1], acc, 0, 0, 0);
+  if constexpr (SPLIT) {
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.lo[0].v, b[0], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.lo[1].v, b[1], acc, 0, 0, 0);
+  }
+  return acc;
+}
+
+// acc += A B, both hi (+ lo); the product of the two remainders (2^-18 of the value) is left out
+template <bool SPLIT>
+__device__ __forceinline__ f32x16 mma(const Operand<SPLIT>& a, const Operand<SPLIT>& b, f32x16 acc) {
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi[q].v, b.hi[q].v, acc, 0, 0, 0);
+    if constexpr (SPLIT) {
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.lo[q].v, b.hi[q].v, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi[q].v, b.lo[q].v, acc, 0, 0, 0);
+    }
+  }
+  return acc;
+}
+
 // One block of 32 queries against one tile of 32 items.  `general` and `masked`
 // are wave-uniform; the MFMAs sit on the common path so the accumulators keep
 // one register assignment whichever route a tile takes.
-__device__ __forceinline__ void attend_block(const bf16x8& kop0, const bf16x8& kop1, const bf16x8& vop0,
-                                             const bf16x8& vop1, const bf16x8& q0, const bf16x8& q1,
-                                             f32x16& o, float& l, float& m, bool general, bool masked,
-                                             int nvl) {
+template <bool SPLIT>
+__device__ __forceinline__ void attend_block(const Operand<SPLIT>& k, const Operand<SPLIT>& v,
+                                             const bf16x8 (&q)[2], f32x16& o, float& l, float& m, bool general,
+                                             bool masked, int nvl) {
   // nvl = valid items of the tile minus 4 hf: register i is valid iff acc_row0(i) < nvl
   f32x16 s = {0};
-  s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kop0, q0, s, 0, 0, 0);
-  s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kop1, q1, s, 0, 0, 0);
+  s = mma_exact_b<SPLIT>(k, q, s);
   if (general) {
 #pragma unroll
     for (int i = 0; i < 16; ++i)
@@ -128,15 +178,19 @@ __device__ __forceinline__ void attend_block(const bf16x8& kop0, const bf16x8& k
     for (int i = 0; i < 16; ++i)
       if (acc_row0(i) >= nvl) s[i] = 0.f;
   }
-  Pack8 p0, p1;
+  Operand<SPLIT> p;
 #pragma unroll
   for (int i = 0; i < 16; i += 2) {
-    const uint32_t pk = cvt_pk_bf16(s[i], s[i + 1]);
-    l = dot2_ones(pk, l);
-    if (i < 8) p0.w[i / 2] = pk; else p1.w[(i - 8) / 2] = pk;
+    if constexpr (SPLIT) {
+      split_pk(s[i], s[i + 1], p.hi[i / 8].w[(i % 8) / 2], p.lo[i / 8].w[(i % 8) / 2]);
+      l += s[i] + s[i + 1];
+    } else {
+      const uint32_t pk = cvt_pk_bf16(s[i], s[i + 1]);
+      l = dot2_ones(pk, l);
+      p.hi[i / 8].w[(i % 8) / 2] = pk;
+    }
   }
-  o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vop0, p0.v, o, 0, 0, 0);
-  o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vop1, p1.v, o, 0, 0, 0);
+  o = mma<SPLIT>(v, p, o);
 }
 
 template <int V>
@@ -144,21 +198,18 @@ struct Int { static constexpr int value = V; };
 
 constexpr int kXBuf = 3;             // ring depth of the X tiles and of the projected tiles in LDS
 
-// Where a projecting wave keeps its 2 x (D x 32) weight operands: in registers at D = 128 (32 of
-// them; it saves half of the operand reads of a projection), in LDS at D = 256 (64 would not fit).
-__host__ __device__ constexpr bool weights_in_registers(int D) { return D == 128; }
-
-// Shared memory of one workgroup.
-template <int D, int HPW>
+// Shared memory of one workgroup.  WREG: a projecting wave keeps its D x 32 weight operands in
+// registers (D / 4 of them; it saves half of the operand reads of a projection) instead of in LDS.
+template <int D, int HPW, bool WREG, bool SPLIT>
 struct SummarizeLds {
   uint4 xbuf[kXBuf][(D / 8) * 32];    // X tiles: [16-byte chunk][item], filled by direct global->LDS loads
-  uint4 kvbuf[kXBuf][HPW][2][2][64];  // projected tiles: [ring slot][head][K|V][half of the 16 registers][lane]
+  uint4 kvbuf[kXBuf][HPW][2][SPLIT ? 4 : 2][64];   // projected tiles: [ring slot][head][K|V][half of the 16 registers (, of the remainders)][lane]
   float knorm[kXBuf][HPW][64];        // squared norm of the scaled key rows (half per lane)
-  uint4 wop[weights_in_registers(D) ? 1 : HPW * 2 * (D / 16) * 64];   // projection weights as MFMA operands (D = 256): [head][K|V][k-slice][lane]
+  uint4 wop[WREG ? 1 : HPW * 2 * (D / 16) * 64];   // projection weights as MFMA operands: [head][K|V][k-slice][lane]
 };
 
 // Body of one wave; ROLE 0 forms K^T, ROLE 1 forms V, ROLE 2 forms nothing and only attends
-// (the third and fourth wave of a head when its queries are spread over four waves: WPH = 4).  The tile loop is
+// (the further waves of a head when its queries are spread over more than two).  The tile loop is
 // software-pipelined: while the wave attends over tile t (VALU-heavy) it also
 // issues the projection MFMAs of tile t+1, and the X rows of tiles t+2 / t+3 are
 // on their way from HBM (registers) into the LDS buffer tile t has vacated.  One
@@ -168,19 +219,18 @@ struct SummarizeLds {
 // denominator, no norm test; the key weights then carry -scale*log2(e), so a score leaves the
 // MFMA as t = -s log2(e) and SiLU(s) = -ln(2) t / (1 + 2^t); the weight handed to the second
 // product is t / (1 + 2^t) and the constant joins the 1/L_b of the merge.
-template <int D, int NQB, int HPW, int ROLE, int WPH = 2, int ATTN = VISTA_ATTN_SOFTMAX>
-__device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, SummarizeLds<D, HPW>& sm,
+template <int D, int NQB, int HPW, int FW, bool WREG, bool SPLIT, int ROLE, int ATTN>
+__device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, SummarizeLds<D, HPW, WREG, SPLIT>& sm,
                                                int64_t g, int h, int hl, int qslot, int64_t seg_begin,
                                                int64_t seg_end) {
   constexpr bool PROJ = ROLE < 2;        // this wave projects
   constexpr bool SILU = ATTN == VISTA_ATTN_SILU;
   constexpr int WR = PROJ ? ROLE : 0;    // its slot in the weight and K/V buffers (unused otherwise)
-  constexpr int NT = HPW * WPH * 64;     // threads
+  constexpr int NT = FW * 64;            // threads that move X: the first FW waves
   constexpr int CH = D / 8;              // 16-byte chunks per row
   constexpr int KS = D / 16;             // k-slices of the projection
-  constexpr int CPT = kTile * CH / NT;   // X chunks a thread moves per tile
-  static_assert(kTile * CH % NT == 0, "tile must split evenly over the workgroup");
-  static_assert(KS % NQB == 0 || NQB % KS == 0, "projection slices are spread over the query blocks");
+  constexpr int CPT = kTile * CH / NT;   // X chunks each of them moves per tile
+  static_assert(kTile * CH % NT == 0, "tile must split evenly over the fetching waves");
   constexpr int KPB = (KS + NQB - 1) / NQB;   // projection k-slices issued per query block
 
   const int tid = threadIdx.x;
@@ -192,63 +242,125 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
   // (each wave reads back only what it wrote).  Element j of slice ks is
   // W[16 ks + 8 hf + j][32 h + l32]; the key weights carry scale*log2(e), so the
   // scores leave the MFMA in base-2 units.
-  constexpr bool WREG = weights_in_registers(D);
   bf16x8 wreg[WREG ? KS : 1];
-  if constexpr (PROJ) {
-    const uint16_t* W = ROLE ? p.Wv : p.Wk;
+  auto keep_weights = [&](int ks, const uint4& u) __attribute__((always_inline)) {
+    Pack8 t;
+    t.u = u;
+    if constexpr (WREG) wreg[ks] = t.v; else sm.wop[((hl * 2 + WR) * KS + ks) * 64 + lane] = t.u;
+  };
+  // Rows of 32 columns are read 16 bytes a lane and turned by the matrix core: a 32 x 32 block times a
+  // 0/1 selector lands in accumulator layout with the lane on the block's column.  The lane picks its
+  // row so that registers 0..7 and 8..15 come out as two operands (row of register i, half hf:
+  // 16 (i / 8) + 8 hf + i % 8).  Two loads a block instead of sixteen 2-byte ones; bit for bit the
+  // same operands (a product with 1.0 is exact).
+  const uint16_t* W = ROLE ? p.Wv : p.Wk;
+  const bool wide_rows = (reinterpret_cast<uintptr_t>(W) & 15) == 0;
+  Pack8 wraw[PROJ ? KS / 2 : 1][2];
+  auto request_weights = [&]() __attribute__((always_inline)) {
+    if constexpr (PROJ) {
+      if (wide_rows) {
+        const int row = (l32 & 16) | ((l32 & 4) << 1) | ((l32 & 8) >> 1) | (l32 & 3);
+        const uint16_t* src = W + row * D + 32 * h + 8 * hf;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      Pack8 t;
+        for (int b = 0; b < KS / 2; ++b)
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const uint16_t w = W[(16 * ks + 8 * hf + j) * D + 32 * h + l32];
-        t.h[j] = ROLE ? w : f32_to_bf16_bits(__uint_as_float(uint32_t(w) << 16) * p.c);
+          for (int q = 0; q < 2; ++q) wraw[b][q].u = *reinterpret_cast<const uint4*>(src + 32 * b * D + 16 * q);
       }
-      if constexpr (WREG) wreg[ks] = t.v; else sm.wop[((hl * 2 + WR) * KS + ks) * 64 + lane] = t.u;
     }
-  }
+  };
+  auto settle_weights = [&]() __attribute__((always_inline)) {
+    if constexpr (PROJ) {
+      if (wide_rows) {
+        Pack8 sel[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+          for (int j = 0; j < 8; ++j) sel[q].h[j] = (l32 == 16 * q + 8 * hf + j) ? 0x3F80 : 0;
+        const float c = ROLE || SPLIT ? 1.f : p.c;
+#pragma unroll
+        for (int b = 0; b < KS / 2; ++b) {
+          f32x16 t = {0};
+          t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wraw[b][0].v, sel[0].v, t, 0, 0, 0);
+          t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wraw[b][1].v, sel[1].v, t, 0, 0, 0);
+#pragma unroll
+          for (int q = 0; q < 2; ++q)
+            keep_weights(2 * b + q,
+                         make_uint4(cvt_pk_bf16(t[8 * q] * c, t[8 * q + 1] * c), cvt_pk_bf16(t[8 * q + 2] * c, t[8 * q + 3] * c),
+                                    cvt_pk_bf16(t[8 * q + 4] * c, t[8 * q + 5] * c), cvt_pk_bf16(t[8 * q + 6] * c, t[8 * q + 7] * c)));
+        }
+      } else {
+#pragma unroll 1
+        for (int ks = 0; ks < KS; ++ks) {
+          Pack8 t;
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const uint16_t w = W[(16 * ks + 8 * hf + j) * D + 32 * h + l32];
+            t.h[j] = ROLE || SPLIT ? w : f32_to_bf16_bits(__uint_as_float(uint32_t(w) << 16) * p.c);
+          }
+          if constexpr (WREG) {
+#pragma unroll
+            for (int k2 = 0; k2 < KS; ++k2)
+              if (k2 == ks) wreg[k2] = t.v;
+          } else {
+            keep_weights(ks, t.u);
+          }
+        }
+      }
+    }
+  };
 
   const int qbase = qslot * (NQB * 32);  // first query of this wave (qslot = ROLE when a head has two waves)
   bf16x8 qop[NQB][2];
   float qmax2 = 0.f;
-  auto load_queries = [&](int user) __attribute__((always_inline)) {
-    const char* Qb = reinterpret_cast<const char*>(p.Q + p.q_user_stride * user + int64_t(qbase) * D + 32 * h);
-    const uint32_t qoff = uint32_t(l32) * (D * 2) + uint32_t(hf) * 8;
-    float worst = 0.f;
+  auto request_queries = [&](int user) __attribute__((always_inline)) {
+    const char* Qb = reinterpret_cast<const char*>(p.Q + p.q_user_stride * user + 32 * h) + 8 * hf;
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb) {
-      const char* row = Qb + qb * 32 * D * 2;
-      float n2 = 0.f;
+      int q = qbase + qb * 32 + l32;
+      if (q > p.S - 1) q = p.S - 1;              // columns past the last query repeat it; never read back
+      const char* row = Qb + q * (D * 2);
 #pragma unroll
       for (int part = 0; part < 2; ++part) {
         Pack8 t;
         // dh index of element j: 16 part + 4 hf + 8 (j / 4) + j % 4 -> two runs of four
-        const uint2 a = *reinterpret_cast<const uint2*>(row + 32 * part + qoff);
-        const uint2 b = *reinterpret_cast<const uint2*>(row + 32 * part + 16 + qoff);
+        const uint2 a = *reinterpret_cast<const uint2*>(row + 32 * part);
+        const uint2 b = *reinterpret_cast<const uint2*>(row + 32 * part + 16);
         t.w[0] = a.x; t.w[1] = a.y; t.w[2] = b.x; t.w[3] = b.y;
         qop[qb][part] = t.v;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          float f = __uint_as_float(uint32_t(t.h[j]) << 16);
-          n2 = fmaf(f, f, n2);
-        }
       }
-      n2 += __shfl_xor(n2, 32, 64);
-      worst = fmaxf(worst, n2);
     }
-#pragma unroll
-    for (int off = 16; off >= 1; off >>= 1) worst = fmaxf(worst, __shfl_xor(worst, off, 64));
-    qmax2 = worst;
   };
-  if (p.q_user_stride == 0) load_queries(0);
+  auto settle_queries = [&]() __attribute__((always_inline)) {
+    if constexpr (!SILU) {
+      float worst = 0.f;
+#pragma unroll
+      for (int qb = 0; qb < NQB; ++qb) {
+        float n2 = 0.f;
+#pragma unroll
+        for (int part = 0; part < 2; ++part) {
+          Pack8 t;
+          t.v = qop[qb][part];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            float f = __uint_as_float(uint32_t(t.h[j]) << 16);
+            n2 = fmaf(f, f, n2);
+          }
+        }
+        n2 += __shfl_xor(n2, 32, 64);
+        worst = fmaxf(worst, n2);
+      }
+#pragma unroll
+      for (int off = 16; off >= 1; off >>= 1) worst = fmaxf(worst, __shfl_xor(worst, off, 64));
+      qmax2 = worst;
+    }
+  };
 
   // ---- the segment as one stream of tiles (TileCursor: scalar state, offsets read through
   // uniform loads).  `ca` names the tile being attended over, `cf` runs three tiles ahead
   // and names the tile whose rows are requested from HBM.
   using Cursor = TileCursor;
   auto cursor_init = [&](Cursor& c) __attribute__((always_inline)) {
-    const int first = p.seg_user ? __builtin_amdgcn_readfirstlane(p.seg_user[g]) : find_user(p.offsets, p.B, seg_begin);
-    c.init(p.offsets, p.B, first, seg_begin, seg_end);
+    c.init(p.offsets, p.B, find_user_wave(p.offsets, p.B, seg_begin), seg_begin, seg_end);
   };
   auto cursor_advance = [&](Cursor& c) __attribute__((always_inline)) { c.advance(p.offsets, p.B, seg_end); };
 
@@ -284,6 +396,7 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
   // load has two tile periods.  Rows past the piece are clamped to its last row.
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   auto fetch = [&](const Cursor& c, int xb) __attribute__((always_inline)) {
+    if (SPLIT && wave >= FW) return;                       // (elsewhere every wave fetches)
     const int last = (c.tiles_left == 1 ? c.tail : kTile) - 1;   // last valid row of the tile
     const char* base = reinterpret_cast<const char*>(p.X) + c.row * (D * 2);
 #pragma unroll
@@ -315,19 +428,28 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
       }
     }
   };
-  // hand the projected tile to the partner wave: bf16 operand halves (+ key norms)
+  // hand the projected tile to the partner waves: bf16 operand halves (+ key norms)
   auto publish = [&](int buf, const f32x16& acc) __attribute__((always_inline)) {
     if constexpr (PROJ) {
-      Pack8 r0, r1;
+      Operand<SPLIT> r;
       float n2 = 0.f;
 #pragma unroll
       for (int i = 0; i < 16; i += 2) {
-        const uint32_t pk = cvt_pk_bf16(acc[i], acc[i + 1]);
+        uint32_t pk;
+        if constexpr (SPLIT) {
+          const float c = ROLE ? 1.f : p.c;      // the keys' scale, in fp32
+          split_pk(acc[i] * c, acc[i + 1] * c, pk, r.lo[i / 8].w[(i % 8) / 2]);
+        } else {
+          pk = cvt_pk_bf16(acc[i], acc[i + 1]);
+        }
         if (ROLE == 0 && !SILU) n2 = dot2_self(pk, n2);
-        if (i < 8) r0.w[i / 2] = pk; else r1.w[(i - 8) / 2] = pk;
+        r.hi[i / 8].w[(i % 8) / 2] = pk;
       }
-      sm.kvbuf[buf][hl][WR][0][lane] = r0.u;
-      sm.kvbuf[buf][hl][WR][1][lane] = r1.u;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        sm.kvbuf[buf][hl][WR][q][lane] = r.hi[q].u;
+        if constexpr (SPLIT) sm.kvbuf[buf][hl][WR][2 + q][lane] = r.lo[q].u;
+      }
       if (ROLE == 0 && !SILU) sm.knorm[buf][hl][lane] = n2;
     }
   };
@@ -336,6 +458,9 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
     return __builtin_amdgcn_ballot_w64(kn2 * qmax2 > kSafeBound2) != 0;
   };
 
+  // everything the workgroup starts from is requested before any of it is waited for
+  request_weights();
+  if (p.q_user_stride == 0) request_queries(0);
   Cursor ca, cf;
   cursor_init(ca);
   cf = ca;
@@ -343,21 +468,26 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
   // Common case: a full tile, bounded scores, another tile behind it.  Straight-line
   // code (one scheduling region per tile): two projection MFMAs of the next tile ride
   // along with every query block of this one.
-  Pack8 k0, k1, v0, v1;     // K/V operands of the tile being attended over
+  Operand<SPLIT> kk, vv;    // K/V operands of the tile being attended over
   float kn2 = 0.f;          // its squared key norm (this lane's item)
   // Operands of tile t+1 (ring slot i1) come out of LDS while tile t is still being worked on,
   // into the registers tile t has just finished with: K (and the norms) once the last scores
   // of the tile are issued, V after its last P.V product.  They were published one tile ago
   // and the barrier at the start of tile t made them visible, so by the next barrier they
   // are in registers and the next tile starts without a round trip to LDS.
+  auto read_operand = [&](Operand<SPLIT>& r, int i1, int which) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      r.hi[q].u = sm.kvbuf[i1][hl][which][q][lane];
+      if constexpr (SPLIT) r.lo[q].u = sm.kvbuf[i1][hl][which][2 + q][lane];
+    }
+  };
   auto read_k = [&](int i1) __attribute__((always_inline)) {
-    k0.u = sm.kvbuf[i1][hl][0][0][lane];
-    k1.u = sm.kvbuf[i1][hl][0][1][lane];
+    read_operand(kk, i1, 0);
     if constexpr (!SILU) kn2 = sm.knorm[i1][hl][lane] + sm.knorm[i1][hl][lane ^ 32];
   };
   auto read_v = [&](int i1) __attribute__((always_inline)) {
-    v0.u = sm.kvbuf[i1][hl][1][0][lane];
-    v1.u = sm.kvbuf[i1][hl][1][1][lane];
+    read_operand(vv, i1, 1);
   };
   auto fast_tile = [&](int r) __attribute__((always_inline)) {   // r = tile index mod 3
     const int i1 = r == kXBuf - 1 ? 0 : r + 1;
@@ -365,19 +495,17 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
     f32x16 acc = {0};
     // scores run one query block ahead of the exponentials that consume them
     f32x16 nx = {0};
-    nx = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0.v, qop[0][0], nx, 0, 0, 0);
-    nx = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k1.v, qop[0][1], nx, 0, 0, 0);
+    nx = mma_exact_b<SPLIT>(kk, qop[0], nx);
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb) {
       if (qb == NQB - 1) read_k(i1);     // the last scores of this tile are already issued
       const f32x16 sc = nx;
       if (qb + 1 < NQB) {
         const f32x16 z = {0};
-        nx = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0.v, qop[qb + 1][0], z, 0, 0, 0);
-        nx = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k1.v, qop[qb + 1][1], nx, 0, 0, 0);
+        nx = mma_exact_b<SPLIT>(kk, qop[qb + 1], z);
       }
-      if (qb * KPB < KS) project(i2, qb * KPB, qb * KPB + KPB, acc);
-      Pack8 p0, p1;
+      if (qb * KPB < KS) project(i2, qb * KPB, qb * KPB + KPB < KS ? qb * KPB + KPB : KS, acc);
+      Operand<SPLIT> pp;
 #pragma unroll
       for (int i = 0; i < 16; i += 2) {
         float ea = __builtin_amdgcn_exp2f(sc[i]), eb = __builtin_amdgcn_exp2f(sc[i + 1]);
@@ -385,26 +513,27 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
           ea = sc[i] * __builtin_amdgcn_rcpf(1.f + ea);
           eb = sc[i + 1] * __builtin_amdgcn_rcpf(1.f + eb);
         }
-        const uint32_t pk = cvt_pk_bf16(ea, eb);
-        if (i < 8) p0.w[i / 2] = pk; else p1.w[(i - 8) / 2] = pk;
+        if constexpr (SPLIT)
+          split_pk(ea, eb, pp.hi[i / 8].w[(i % 8) / 2], pp.lo[i / 8].w[(i % 8) / 2]);
+        else
+          pp.hi[i / 8].w[(i % 8) / 2] = cvt_pk_bf16(ea, eb);
       }
       // The denominator on the matrix core: a 4x4x4 product (16 blocks, one per four lanes)
       // whose A block has ones in row qb adds a lane's own four packed weights into register
       // qb of that lane -- the lane-local partial sum a chain of adds would form, taken over
-      // the bf16 weights the numerator uses.  It issues like one plain vector instruction
-      // for four weights; two accumulators take turns so that consecutive products do not
-      // wait for each other.
+      // the bf16 weights (and remainders) the numerator uses.  It issues like one plain vector
+      // instruction for four weights; two accumulators take turns so that consecutive products
+      // do not wait for each other.
       if constexpr (!SILU) {
         const i16x4 sel = __builtin_bit_cast(i16x4, onesrow[qb]);
 #pragma unroll
-        for (int part = 0; part < 4; ++part) {
-          const uint2 pw = part < 2 ? make_uint2(p0.w[2 * part], p0.w[2 * part + 1])
-                                    : make_uint2(p1.w[2 * part - 4], p1.w[2 * part - 3]);
+        for (int part = 0; part < (SPLIT ? 8 : 4); ++part) {
+          const Pack8& src = SPLIT && part >= 4 ? pp.lo[SPLIT ? part / 2 - 2 : 0] : pp.hi[(part / 2) & 1];
+          const uint2 pw = make_uint2(src.w[2 * (part & 1)], src.w[2 * (part & 1) + 1]);
           lacc[part & 1] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(sel, __builtin_bit_cast(i16x4, pw), lacc[part & 1], 0, 0, 0);
         }
       }
-      o[qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v0.v, p0.v, o[qb], 0, 0, 0);
-      o[qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v1.v, p1.v, o[qb], 0, 0, 0);
+      o[qb] = mma<SPLIT>(vv, pp, o[qb]);
     }
     read_v(i1);
     publish(i2, acc);
@@ -425,20 +554,17 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
 #pragma unroll
       for (int qb = 0; qb < NQB; ++qb) {
         f32x16 sc = {0};
-        sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0.v, qop[qb][0], sc, 0, 0, 0);
-        sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k1.v, qop[qb][1], sc, 0, 0, 0);
-        Pack8 p0, p1;
+        sc = mma_exact_b<SPLIT>(kk, qop[qb], sc);
+        Operand<SPLIT> pp;
 #pragma unroll
         for (int i = 0; i < 16; i += 2) {
           float wa = sc[i] * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(sc[i]));
           float wb = sc[i + 1] * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(sc[i + 1]));
           if (acc_row0(i) >= nvl) wa = 0.f;
           if (acc_row0(i + 1) >= nvl) wb = 0.f;
-          const uint32_t pk = cvt_pk_bf16(wa, wb);
-          if (i < 8) p0.w[i / 2] = pk; else p1.w[(i - 8) / 2] = pk;
+          pp.hi[i / 8].w[(i % 8) / 2] = cvt_pk_bf16(wa, wb);
         }
-        o[qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v0.v, p0.v, o[qb], 0, 0, 0);
-        o[qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v1.v, p1.v, o[qb], 0, 0, 0);
+        o[qb] = mma<SPLIT>(vv, pp, o[qb]);
       }
       mode = 1;
     } else {
@@ -451,7 +577,7 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
     const bool masked = nvalid < kTile;
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb)
-      attend_block(k0.v, k1.v, v0.v, v1.v, qop[qb][0], qop[qb][1], o[qb], l[qb], m[qb], general, masked, nvl);
+      attend_block<SPLIT>(kk, vv, qop[qb], o[qb], l[qb], m[qb], general, masked, nvl);
     }
     read_k(i1);
     read_v(i1);
@@ -464,11 +590,11 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
   // partial record of a finished piece: slot = segment + user
   auto write_partial = [&](int user) __attribute__((always_inline)) {
     const int64_t slot = g + user;
-    char* rec = reinterpret_cast<char*>(p.partials +
-                                        ((slot * p.H + h) * (p.S / 32) + (qbase / 32)) * kRecFloats);
+    char* rec = reinterpret_cast<char*>(p.partials + ((slot * p.H + h) * p.nqb + (qbase / 32)) * kRecFloats);
     const uint32_t lane_off = uint32_t(lane) * 4;
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb) {
+      if (qbase / 32 + qb >= p.nqb) break;               // a block past the last query has no record
       char* r = rec + size_t(qb) * kRecFloats * 4;       // scalar
 #pragma unroll
       for (int i = 0; i < 16; ++i) *reinterpret_cast<float*>(r + i * 256 + lane_off) = o[qb][i];
@@ -479,7 +605,6 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
 
   if (!ca.valid) return;               // only with invalid offsets (whole workgroup)
   reset_state();
-  if (p.q_user_stride != 0) load_queries(ca.user);
 
   // Waits until at most `pending` of this wave's newest vector-memory operations
   // are outstanding (s_waitcnt vmcnt only; the other counters are left alone).
@@ -499,6 +624,9 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
   cursor_advance(cf);
   fetch(cf, 2);
   cursor_advance(cf);
+  if (p.q_user_stride != 0) request_queries(ca.user);
+  settle_weights();
+  settle_queries();
   wait_vm(Int<CPT>{});
   lds_barrier();
   {
@@ -566,7 +694,10 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
     if (last_in_piece) {
       write_partial(done_user);
       reset_state();
-      if (p.q_user_stride != 0 && ca.valid) load_queries(ca.user);
+      if (p.q_user_stride != 0 && ca.valid) {
+        request_queries(ca.user);
+        settle_queries();
+      }
       drain = true;
     }
     r = r == kXBuf - 1 ? 0 : r + 1;
@@ -576,11 +707,17 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
   }
 }
 
-template <int D, int NQB, int HPW, int ATTN>
-__global__ __launch_bounds__(HPW * 128) void summarize_mfma_kernel(MfmaSummarizeParams p) {
-  __shared__ SummarizeLds<D, HPW> sm;
+// MAXT: largest workgroup of the instantiation (it bounds the registers of a wave).  FW waves fetch X.
+template <int D, int NQB, int HPW, int FW, bool WREG, bool SPLIT, int MAXT, int ATTN>
+__global__ __launch_bounds__(MAXT) void summarize_mfma_kernel(MfmaSummarizeParams p) {
+  __shared__ SummarizeLds<D, HPW, WREG, SPLIT> sm;
+
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform, kept scalar
-  const int hl = wave >> 1;
+  const int hl = wave / p.wph;
+  // slot 0 projects K, slot 1 projects V, the others only attend; the slots of successive heads are
+  // turned by two so that every SIMD (wave id mod 4) gets its share of projecting waves
+  int slot = wave - hl * p.wph + 2 * hl;
+  while (slot >= p.wph) slot -= p.wph;
 
   // XCD-aware block -> (segment, head group): the head groups of one segment
   // share an XCD (and its L2) because their block ids differ by multiples of 8.
@@ -593,70 +730,61 @@ __global__ __launch_bounds__(HPW * 128) void summarize_mfma_kernel(MfmaSummarize
   const int64_t seg_begin = g * p.seg;
   if (seg_begin >= p.N) return;          // padding blocks of the last group (whole workgroup)
   const int64_t seg_end = (seg_begin + p.seg < p.N) ? seg_begin + p.seg : p.N;
-  // Both roles run the same sequence of barriers; only the MFMA operand order differs.
-  if (wave & 1)
-    summarize_wave<D, NQB, HPW, 1, 2, ATTN>(p, sm, g, h, hl, 1, seg_begin, seg_end);
-  else
-    summarize_wave<D, NQB, HPW, 0, 2, ATTN>(p, sm, g, h, hl, 0, seg_begin, seg_end);
-}
-
-// Four waves per head (two heads per workgroup): the K and V waves project as above, two more
-// waves only attend, each of the four with a quarter of the queries.  With S = 512 this keeps a
-// wave at 4 query blocks, i.e. inside 256 vector registers and at two waves per SIMD.  Wave
-// w serves head w / 4 in slot (w + 2 (w / 4)) % 4, so that each SIMD (wave id mod 4) gets one
-// projecting and one attend-only wave.
-template <int D, int NQB, int ATTN>
-__global__ __launch_bounds__(512) void summarize_mfma4_kernel(MfmaSummarizeParams p) {
-  constexpr int HPW = 2;
-  __shared__ SummarizeLds<D, HPW> sm;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int hl = wave >> 2;
-  const int slot = (wave + 2 * hl) & 3;
-  const int64_t id = blockIdx.x;
-  const int64_t grp = id / (8 * p.nhg);
-  const int idl = int(id - grp * 8 * p.nhg);
-  const int64_t g = grp * 8 + (idl & 7);
-  const int hg = idl >> 3;
-  const int h = hg * HPW + hl;
-  const int64_t seg_begin = g * p.seg;
-  if (seg_begin >= p.N) return;          // padding blocks of the last group (whole workgroup)
-  const int64_t seg_end = (seg_begin + p.seg < p.N) ? seg_begin + p.seg : p.N;
+  // All roles run the same sequence of barriers; only the MFMA operand order differs.
   if (slot == 0)
-    summarize_wave<D, NQB, HPW, 0, 4, ATTN>(p, sm, g, h, hl, 0, seg_begin, seg_end);
+    summarize_wave<D, NQB, HPW, FW, WREG, SPLIT, 0, ATTN>(p, sm, g, h, hl, 0, seg_begin, seg_end);
   else if (slot == 1)
-    summarize_wave<D, NQB, HPW, 1, 4, ATTN>(p, sm, g, h, hl, 1, seg_begin, seg_end);
-  else
-    summarize_wave<D, NQB, HPW, 2, 4, ATTN>(p, sm, g, h, hl, slot, seg_begin, seg_end);
+    summarize_wave<D, NQB, HPW, FW, WREG, SPLIT, 1, ATTN>(p, sm, g, h, hl, 1, seg_begin, seg_end);
+  else if constexpr (MAXT != HPW * 128)      // (two waves per head: there is no third slot)
+    summarize_wave<D, NQB, HPW, FW, WREG, SPLIT, 2, ATTN>(p, sm, g, h, hl, slot, seg_begin, seg_end);
 }
 
-// Merge of a user's partial records, ascending segment order (fixed, so the
-// result is bitwise reproducible).  Softmax form: with m the running maximum of the m_c,
+// Merge of a user's partial records in a fixed order, so the result is bitwise reproducible.
+// Softmax form: with m the running maximum of the m_c,
 // out = sum_c 2^(m_c - m) O_c / sum_c 2^(m_c - m) l_c; the self term (Ks != null) is one more
 // record (m = own score, l = 1, O = own value), taken last.  SiLU form: out =
 // (-ln 2 sum_c O_c + SiLU(own score) own value) / L_b (the records hold sums of
-// t / (1 + 2^t) v with t = -s log2 e).  One block per (user, head, query block), 256 threads:
-// wave w owns accumulator registers 4w..4w+3, i.e. channels 8w + 4 hf + 0..3.
-template <bool SILU>
+// t / (1 + 2^t) v with t = -s log2 e).  Four waves per (user, head, query block): wave w owns
+// accumulator registers 4w..4w+3, i.e. channels 8w + 4 hf + 0..3.
+// RG = 1: the four are one block and walk the user's records in ascending order.
+// RG = 4: each of the four is a block of four waves; wave r takes the r-th run of the records,
+// ascending, and the runs' sums are combined in ascending order.  (No codec: its scale spans the four.)
+// Columns past the last query are computed and not stored.
+template <bool SILU, int RG>
 __global__ __launch_bounds__(256) void merge_mfma_kernel(const float* __restrict__ partials,
-                                                         const int64_t* __restrict__ offsets, int S, int d,
-                                                         int H, int seg, int64_t G,
-                                                         uint16_t* __restrict__ out, int* status,
-                                                         const uint16_t* __restrict__ Q, int64_t q_user_stride,
-                                                         const float* __restrict__ Ks,
-                                                         const float* __restrict__ Vs, float scale,
-                                                         float* __restrict__ out_scales) {
+                                                              const int64_t* __restrict__ offsets, int B, int S, int d,
+                                                              int H, int seg, int64_t N, int64_t G,
+                                                              uint16_t* __restrict__ out, int* status,
+                                                              int check_offsets, const uint16_t* __restrict__ Q,
+                                                              int64_t q_user_stride, const float* __restrict__ Ks,
+                                                              const float* __restrict__ Vs, float scale,
+                                                              float* __restrict__ out_scales) {
   __shared__ float amax_part[8][32];
-  const int nqb = S / 32;
-  const int qb = blockIdx.x % nqb, h = (blockIdx.x / nqb) % H, b = blockIdx.x / (nqb * H);
-  // without a plan kernel in front (offsets checked on the host) the status word is cleared here
-  if (status && qb == 0 && h == 0 && b == 0 && threadIdx.x == 0) *status = VISTA_OK;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  __shared__ float group[RG > 1 ? RG - 1 : 1][6][64];       // (m, l, o0..o3) of the later groups
+  const int nqb = (S + 31) / 32;
+  const int blk = RG > 1 ? blockIdx.x >> 2 : blockIdx.x;
+  const int qb = blk % nqb, h = (blk / nqb) % H, b = blk / (nqb * H);
+  // The first block publishes the status word: the offsets are checked here unless the host has.
+  if (blockIdx.x == 0) {
+    int bad = 0;
+    if (check_offsets)
+      for (int u = threadIdx.x; u <= B; u += blockDim.x) {
+        const int64_t o = offsets[u];
+        bad |= (u == 0 && o != 0) || (u == B && o != N) || (u < B && offsets[u + 1] < o);
+      }
+    bad = __syncthreads_or(bad);
+    if (threadIdx.x == 0) *status = bad ? int(VISTA_ERR_OFFSETS) : int(VISTA_OK);
+  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int w = RG > 1 ? blockIdx.x & 3 : wave, rg = RG > 1 ? wave : 0;
   const int hf = lane >> 5, l32 = lane & 31;
+  const bool live = rg == 0 && qb * 32 + l32 < S;           // this lane stores
   const int64_t begin = offsets[b], end = offsets[b + 1];
   uint16_t* dst = out + (int64_t(b) * S + qb * 32 + l32) * d + 32 * h + 8 * w + 4 * hf;
   // cache codec (out_scales != null): `out` holds int8 codes, one scale per (token, head)
   int8_t* dst8 = reinterpret_cast<int8_t*>(out) + (int64_t(b) * S + qb * 32 + l32) * d + 32 * h + 8 * w + 4 * hf;
   if (end <= begin) {
+    if (!live) return;
     if (out_scales) {
       *reinterpret_cast<uint32_t*>(dst8) = 0u;
       if (w == 0 && hf == 0) out_scales[(int64_t(b) * S + qb * 32 + l32) * H + h] = 0.f;
@@ -671,7 +799,7 @@ __global__ __launch_bounds__(256) void merge_mfma_kernel(const float* __restrict
   // the query's own key and value (self term): score in the units of the records' m
   float s_self = 0.f, vs[4] = {0.f, 0.f, 0.f, 0.f};
   if (Ks) {
-    const int i = qb * 32 + l32;
+    const int i = qb * 32 + l32 < S ? qb * 32 + l32 : S - 1;
     const uint16_t* q = Q + q_user_stride * b + int64_t(i) * d + 32 * h;
     const int64_t srow = (q_user_stride ? int64_t(b) * S : 0) + i;
     const float* ks = Ks + srow * d + 32 * h;
@@ -684,9 +812,12 @@ __global__ __launch_bounds__(256) void merge_mfma_kernel(const float* __restrict
   auto rec = [&](int64_t g) __attribute__((always_inline)) { return partials + (((g + b) * H + h) * nqb + qb) * kRecFloats + lane; };
   // One pass with a running maximum (rescale when it moves); loads are issued kBatch
   // records at a time so a long user is not a chain of dependent round trips.
-  constexpr int kBatch = 8;
+  constexpr int kBatch = RG > 1 ? 4 : 8;
   float m = -INFINITY, l = 0.f, o0 = 0.f, o1 = 0.f, o2 = 0.f, o3 = 0.f;
-  for (int64_t g = g0; g <= g1; g += kBatch) {
+  const int64_t run = (g1 - g0 + RG) / RG;                  // records per group
+  const int64_t r0 = g0 + rg * run;
+  if (g1 > r0 + run - 1) g1 = r0 + run - 1;
+  for (int64_t g = r0; g <= g1; g += kBatch) {
     float v[kBatch][6];
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
@@ -720,6 +851,30 @@ __global__ __launch_bounds__(256) void merge_mfma_kernel(const float* __restrict
       m = mn;
     }
   }
+  if (RG > 1) {
+    if (rg > 0) {
+      float* x = &group[rg - 1][0][lane];
+      x[0] = m; x[64] = l; x[128] = o0; x[192] = o1; x[256] = o2; x[320] = o3;
+    }
+    __syncthreads();
+    if (rg > 0) return;
+#pragma unroll
+    for (int r = 0; r < RG - 1; ++r) {
+      const float* x = &group[r][0][lane];
+      float keep = 1.f, wgt = 1.f;
+      if (!SILU) {
+        const float mn = fmaxf(m, x[0]);
+        keep = exp2f(m - mn);               // group 0 is never empty: mn is finite
+        wgt = exp2f(x[0] - mn);             // 0 for an empty group (m = -inf)
+        m = mn;
+      }
+      l = fmaf(x[64], wgt, l * keep);
+      o0 = fmaf(x[128], wgt, o0 * keep);
+      o1 = fmaf(x[192], wgt, o1 * keep);
+      o2 = fmaf(x[256], wgt, o2 * keep);
+      o3 = fmaf(x[320], wgt, o3 * keep);
+    }
+  }
   float inv;
   if (SILU) {
     inv = 1.f / float(end - begin);
@@ -740,7 +895,7 @@ __global__ __launch_bounds__(256) void merge_mfma_kernel(const float* __restrict
     }
     inv = 1.f / l;
   }
-  if (out_scales) {
+  if (RG == 1 && out_scales) {
     // Sec. 3.1's quantisation, fused: the head's 32 channels of a token sit in this block's
     // eight (wave, half) groups of four; their largest magnitude goes through LDS.
     const float y0 = o0 * inv, y1 = o1 * inv, y2 = o2 * inv, y3 = o3 * inv;
@@ -753,10 +908,12 @@ __global__ __launch_bounds__(256) void merge_mfma_kernel(const float* __restrict
     auto code = [&](float y) __attribute__((always_inline)) {
       return uint32_t(int(fminf(fmaxf(rintf(y * q), -127.f), 127.f))) & 0xFFu;
     };
+    if (!live) return;
     *reinterpret_cast<uint32_t*>(dst8) = code(y0) | (code(y1) << 8) | (code(y2) << 16) | (code(y3) << 24);
     if (w == 0 && hf == 0) out_scales[(int64_t(b) * S + qb * 32 + l32) * H + h] = amax > 0.f ? amax / 127.f : 0.f;
     return;
   }
+  if (!live) return;
   uint2 pk;
   pk.x = uint32_t(f32_to_bf16_bits(o0 * inv)) | (uint32_t(f32_to_bf16_bits(o1 * inv)) << 16);
   pk.y = uint32_t(f32_to_bf16_bits(o2 * inv)) | (uint32_t(f32_to_bf16_bits(o3 * inv)) << 16);
@@ -765,18 +922,52 @@ __global__ __launch_bounds__(256) void merge_mfma_kernel(const float* __restrict
 
 // ------------------------------------------------------------------ host side
 
-static bool shape_d128(const vista_summarize_desc& d) { return d.d == 128 && d.H == 4; }
-static bool shape_d256(const vista_summarize_desc& d) { return d.d == 256 && d.H == 8; }
-
+// The shapes whose K, V and softmax weights are bf16 operands.
 bool mfma_summarize_supported(const vista_summarize_desc& d) {
   if (d.dtype != VISTA_BF16 || d.attn == VISTA_ATTN_QLA) return false;
-  if (!(shape_d128(d) || shape_d256(d))) return false;
+  if (!(d.d == 128 && d.H == 4) && !(d.d == 256 && d.H == 8)) return false;
   return d.S == 64 || d.S == 128 || d.S == 256 || d.S == 512;
+}
+
+// The other bf16 softmax shapes of the same head width: any seed count, K, V and weights as split
+// operands (a bf16 value and a bf16 remainder, 16 significant bits).
+bool mfma_split_supported(const vista_summarize_desc& d) {
+  if (d.dtype != VISTA_BF16 || d.attn != VISTA_ATTN_SOFTMAX || mfma_summarize_supported(d)) return false;
+  return (d.d == 64 && d.H == 2) || (d.d == 128 && d.H == 4) || (d.d == 256 && d.H == 8);
+}
+
+// Head groups (workgroups per segment) and workgroups resident on a compute unit, as launched below.
+static int head_groups(const vista_summarize_desc& d) {
+  const int nqb = (d.S + 31) / 32;
+  if (mfma_summarize_supported(d)) return d.d == 256 ? 4 : nqb > 8 ? 2 : 1;
+  if (d.d == 256) return 8;
+  return nqb > 8 ? d.H : d.H / 2;
+}
+static int resident_workgroups(const vista_summarize_desc& d) {
+  return mfma_split_supported(d) && d.d != 256 && d.S <= 128 ? 2 : 1;
+}
+
+// Segment size of the matrix-core kernels where the caller leaves it open: the history is cut so that
+// the workgroups fill the chip k times, k the smallest count that keeps a segment at or below 32768
+// items, a multiple of 32, at least 128.  Longer segments mean fewer records to write and merge: 8
+// users of a million items (d = 128, S = 256) take 1641 us at this limit, 1655 at 16384 and 1683 at
+// 8192; two layers at d = 256, S = 512 over 14 M items 24.4, 24.8 and 25.0 ms.  Below 128 items a
+// workgroup's set-up and record outweigh its tiles: one user of 7001 items takes 35.1 us at 64, 30.5
+// at 96 and 29.0 at 128.
+int mfma_summarize_segment(const vista_summarize_desc& d) {
+  const int64_t N = d.total_items;
+  const int64_t units = 256 * resident_workgroups(d) / head_groups(d);
+  constexpr int64_t kMost = 32768, kLeast = 128;
+  int64_t k = (N + units * kMost - 1) / (units * kMost);
+  if (k < 1) k = 1;
+  int64_t s = (N + units * k - 1) / (units * k);
+  s = (s + 31) / 32 * 32;
+  return int(s < kLeast ? kLeast : s);
 }
 
 static size_t partial_bytes(const vista_summarize_desc& d, int seg) {
   int64_t G = (d.total_items + seg - 1) / seg;
-  return size_t(G + d.B) * d.H * (d.S / 32) * kRecFloats * sizeof(float);
+  return size_t(G + d.B) * d.H * ((d.S + 31) / 32) * kRecFloats * sizeof(float);
 }
 
 // [header][seg_user][partial records][K' of the seeds][V' of the seeds]
@@ -785,39 +976,55 @@ size_t mfma_summarize_workspace(const vista_summarize_desc& d, int seg) {
   return kHeaderBytes + plan_bytes(G) + ((partial_bytes(d, seg) + 255) & ~size_t(255)) + 2 * self_kv_bytes(d);
 }
 
-template <int D, int NQB, int ATTN>
-static hipError_t launch_main4(const MfmaSummarizeParams& p, int64_t G, hipStream_t s) {
+template <int D, int NQB, int HPW, int FW, bool WREG, bool SPLIT, int MAXT, int ATTN>
+static hipError_t launch_main(MfmaSummarizeParams& p, int wph, int64_t G, hipStream_t s) {
+  p.wph = wph;
+  p.nhg = p.H / HPW;
   const int64_t groups = (G + 7) / 8;
   const int64_t blocks = groups * 8 * p.nhg;
-  return launch(summarize_mfma4_kernel<D, NQB, ATTN>, dim3(unsigned(blocks)), dim3(512), 0, s, p);
-}
-
-template <int D, int NQB, int HPW, int ATTN>
-static hipError_t launch_main(const MfmaSummarizeParams& p, int64_t G, hipStream_t s) {
-  const int64_t groups = (G + 7) / 8;
-  const int64_t blocks = groups * 8 * p.nhg;
-  return launch(summarize_mfma_kernel<D, NQB, HPW, ATTN>, dim3(unsigned(blocks)), dim3(HPW * 128), 0, s, p);
+  return launch(summarize_mfma_kernel<D, NQB, HPW, FW, WREG, SPLIT, MAXT, ATTN>, dim3(unsigned(blocks)),
+                dim3(HPW * wph * 64), 0, s, p);
 }
 
 template <int ATTN>
-static hipError_t launch_for_shape(MfmaSummarizeParams& p, const vista_summarize_desc& d, int64_t G,
-                                   hipStream_t s) {
-  if (shape_d128(d)) {
-    p.nhg = 1;
-    switch (d.S) {
-      case 64: return launch_main<128, 1, 4, ATTN>(p, G, s);
-      case 128: return launch_main<128, 2, 4, ATTN>(p, G, s);
-      case 256: return launch_main<128, 4, 4, ATTN>(p, G, s);
-      default: p.nhg = 2; return launch_main4<128, 4, ATTN>(p, G, s);
-    }
+static hipError_t launch_for_shape(MfmaSummarizeParams& p, int d, int64_t G, hipStream_t s) {
+  if (d == 128) {
+    if (p.nqb <= 2) return launch_main<128, 1, 4, 8, true, false, 512, ATTN>(p, 2, G, s);
+    if (p.nqb <= 4) return launch_main<128, 2, 4, 8, true, false, 512, ATTN>(p, 2, G, s);
+    if (p.nqb <= 8) return launch_main<128, 4, 4, 8, true, false, 512, ATTN>(p, 2, G, s);
+    return launch_main<128, 4, 2, 8, true, false, 512, ATTN>(p, 4, G, s);
   }
-  p.nhg = 4;
-  switch (d.S) {
-    case 64: return launch_main<256, 1, 2, ATTN>(p, G, s);
-    case 128: return launch_main4<256, 1, ATTN>(p, G, s);
-    case 256: return launch_main4<256, 2, ATTN>(p, G, s);
-    default: return launch_main4<256, 4, ATTN>(p, G, s);
+  if (p.nqb <= 2) return launch_main<256, 1, 2, 4, false, false, 256, ATTN>(p, 2, G, s);
+  if (p.nqb <= 4) return launch_main<256, 1, 2, 8, false, false, 512, ATTN>(p, 4, G, s);
+  if (p.nqb <= 8) return launch_main<256, 2, 2, 8, false, false, 512, ATTN>(p, 4, G, s);
+  return launch_main<256, 4, 2, 8, false, false, 512, ATTN>(p, 4, G, s);
+}
+
+static hipError_t launch_split(MfmaSummarizeParams& p, int d, int64_t G, hipStream_t s) {
+  constexpr int A = VISTA_ATTN_SOFTMAX;
+  const int w1 = p.nqb < 4 ? 4 : p.nqb, w2 = p.nqb < 3 ? 2 : (p.nqb + 1) / 2;   // waves per head at one, two query blocks
+  if (d == 64) {
+    if (p.nqb <= 2) return launch_main<64, 1, 2, 4, true, true, 512, A>(p, 2, G, s);
+    if (p.nqb <= 8) return launch_main<64, 2, 2, 4, true, true, 512, A>(p, w2, G, s);
+    return launch_main<64, 2, 1, 4, true, true, 512, A>(p, w2, G, s);
   }
+  if (d == 128) {
+    if (p.nqb <= 2) return launch_main<128, 1, 2, 4, true, true, 512, A>(p, 2, G, s);
+    if (p.nqb <= 8) return launch_main<128, 2, 2, 4, true, true, 512, A>(p, w2, G, s);
+    return launch_main<128, 2, 1, 4, true, true, 512, A>(p, w2, G, s);
+  }
+  if (p.nqb <= 8) return launch_main<256, 1, 1, 4, false, true, 512, A>(p, w1, G, s);
+  return launch_main<256, 2, 1, 4, false, true, 512, A>(p, w2, G, s);
+}
+
+template <bool SILU, int RG>
+static hipError_t launch_merge(const MfmaSummarizeParams& p, const SummarizeArgs& a, const float* Ks, const float* Vs,
+                               int64_t blocks) {
+  const vista_summarize_desc& d = a.desc;
+  return launch(merge_mfma_kernel<SILU, RG>, dim3(unsigned(RG > 1 ? 4 * blocks : blocks)), dim3(256), 0, a.stream, p.partials, a.offsets,
+                d.B, d.S, d.d, d.H, a.seg, d.total_items, a.G, static_cast<uint16_t*>(a.out),
+                reinterpret_cast<int*>(a.workspace), a.offsets_checked ? 0 : 1, p.Q, d.q_user_stride, Ks, Vs,
+                SILU ? a.scale_plain : a.scale_log2, a.out_scales);
 }
 
 vista_status mfma_summarize(const SummarizeArgs& a) {
@@ -831,10 +1038,9 @@ vista_status mfma_summarize(const SummarizeArgs& a) {
   p.Wk = static_cast<const uint16_t*>(a.Wk);
   p.Wv = static_cast<const uint16_t*>(a.Wv);
   p.partials = reinterpret_cast<float*>(a.workspace + kHeaderBytes + plan_bytes(a.G));
-  p.seg_user = a.seg_user;
-
   p.B = d.B;
   p.S = d.S;
+  p.nqb = (d.S + 31) / 32;
   p.H = d.H;
   p.N = d.total_items;
   p.seg = a.seg;
@@ -846,23 +1052,20 @@ vista_status mfma_summarize(const SummarizeArgs& a) {
     Vs = Ks + self_kv_bytes(d) / sizeof(float);
     if (launch_self_kv(d, a.Q, a.Wk, a.Wv, Ks, Vs, a.stream) != hipSuccess) return VISTA_ERR_HIP;
   }
-  const int64_t merge_blocks = int64_t(d.B) * d.H * (d.S / 32);
-  if ((a.G + 7) / 8 * 8 * 4 > 0x7FFFFFFF || merge_blocks > 0x7FFFFFFF) return VISTA_ERR_UNSUPPORTED;
+  const int64_t merge_blocks = int64_t(d.B) * d.H * p.nqb;
+  if ((a.G + 7) / 8 * 8 * 8 > 0x7FFFFFFF || merge_blocks > 0x7FFFFFFF) return VISTA_ERR_UNSUPPORTED;
   if (a.G > 0) {
-    const hipError_t e = silu ? launch_for_shape<VISTA_ATTN_SILU>(p, d, a.G, a.stream)
-                              : launch_for_shape<VISTA_ATTN_SOFTMAX>(p, d, a.G, a.stream);
+    const hipError_t e = mfma_split_supported(d) ? launch_split(p, d.d, a.G, a.stream)
+                         : silu          ? launch_for_shape<VISTA_ATTN_SILU>(p, d.d, a.G, a.stream)
+                                         : launch_for_shape<VISTA_ATTN_SOFTMAX>(p, d.d, a.G, a.stream);
     if (e != hipSuccess) return VISTA_ERR_HIP;
   }
-  int* status = a.seg_user ? nullptr : reinterpret_cast<int*>(a.workspace);
-  if (silu)
-    VISTA_LAUNCH(merge_mfma_kernel<true>, dim3(unsigned(merge_blocks)), dim3(256), 0, a.stream, p.partials, a.offsets,
-                 d.S, d.d, d.H, a.seg, a.G, static_cast<uint16_t*>(a.out), status, p.Q, d.q_user_stride, Ks, Vs,
-                 a.scale_plain, a.out_scales);
-  else
-    VISTA_LAUNCH(merge_mfma_kernel<false>, dim3(unsigned(merge_blocks)), dim3(256), 0, a.stream, p.partials, a.offsets,
-                 d.S, d.d, d.H, a.seg, a.G, static_cast<uint16_t*>(a.out), status, p.Q, d.q_user_stride, Ks, Vs,
-                 a.scale_log2, a.out_scales);
-  return VISTA_OK;
+  // Few blocks: four times as many, and four waves to a user's records.  A merge is bound by what a
+  // compute unit can read (about 20 GB/s each when all do), so it wants them all.
+  const bool wide = merge_blocks <= 512 && !a.out_scales;
+  const hipError_t e = silu ? (wide ? launch_merge<true, 4>(p, a, Ks, Vs, merge_blocks) : launch_merge<true, 1>(p, a, Ks, Vs, merge_blocks))
+                            : (wide ? launch_merge<false, 4>(p, a, Ks, Vs, merge_blocks) : launch_merge<false, 1>(p, a, Ks, Vs, merge_blocks));
+  return e == hipSuccess ? VISTA_OK : VISTA_ERR_HIP;
 }
 
 }  // namespace vista

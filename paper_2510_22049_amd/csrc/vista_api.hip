@@ -46,6 +46,41 @@ int32_t resolve_segment(const vista_summarize_desc* d) {
   return int32_t(s);
 }
 
+// How a call is carried out: the kernel family, its segment size and the workspace it needs.
+enum class Route { kMfma, kSplit, kGeneric };
+struct Work {
+  Route route;
+  int32_t seg;
+  size_t need;
+};
+
+// The plain path at the default segment size: what a bf16 softmax shape outside the fixed seed counts
+// falls back to when the workspace or a pointer's alignment does not suit the matrix-core kernel.
+Work base_work(const vista_summarize_desc& d) {
+  const int32_t seg = resolve_segment(&d);
+  if (mfma_summarize_supported(d)) return {Route::kMfma, seg, mfma_summarize_workspace(d, seg)};
+  return {Route::kGeneric, seg, generic_summarize_workspace(d, seg)};
+}
+
+// The preferred way, a function of the descriptor alone: the segments fitted to the launch where the
+// caller leaves their size open.  Finer segments mean more records; where these would no longer fit
+// the static scratch (or what the base schedule takes, if that is more) the base schedule stays, so
+// that the static entry point and the one with a workspace always do the same.
+Work best_work(const vista_summarize_desc& d) {
+  const Work base = base_work(d);
+  const bool split = mfma_split_supported(d);
+  if (base.route == Route::kGeneric && !split) return base;
+  const Route route = split ? Route::kSplit : Route::kMfma;
+  const size_t limit = base.need > size_t(VISTA_STATIC_SCRATCH_BYTES) ? base.need : size_t(VISTA_STATIC_SCRATCH_BYTES);
+  if (d.segment_items == 0) {
+    const int32_t seg = mfma_summarize_segment(d);
+    const size_t need = mfma_summarize_workspace(d, seg);
+    if (need <= limit) return {route, seg, need};
+  }
+  const Work w = {route, base.seg, mfma_summarize_workspace(d, base.seg)};
+  return w.need <= limit ? w : base;
+}
+
 // Scratch of vista_summarize_static: one array per GPU the library runs on, held until the
 // process ends.  In host code the name below only stands for the symbol; the array's device
 // address is looked up once per device and kept in static_scratch_ptr.
@@ -122,9 +157,8 @@ int64_t vista_summarize_schedule(const vista_summarize_desc* desc, const int64_t
 
 size_t vista_summarize_workspace_bytes(const vista_summarize_desc* desc) {
   if (check_summarize_desc(desc) != VISTA_OK) return 0;
-  int seg = resolve_segment(desc);
-  return mfma_summarize_supported(*desc) ? mfma_summarize_workspace(*desc, seg)
-                                         : generic_summarize_workspace(*desc, seg);
+  const size_t base = base_work(*desc).need, best = best_work(*desc).need;
+  return best > base ? best : base;
 }
 
 static vista_status summarize_impl(const vista_summarize_desc* desc, const void* history_emb,
@@ -141,13 +175,21 @@ static vista_status summarize_impl(const vista_summarize_desc* desc, const void*
     for (int b = 0; b < desc->B; ++b)
       if (offsets_host[b + 1] < offsets_host[b]) return VISTA_ERR_OFFSETS;
   }
-  const size_t need = vista_summarize_workspace_bytes(desc);
-  if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0 || workspace_bytes < need)
+  // a workspace that holds the base schedule only gets the base schedule
+  Work w = best_work(*desc);
+  const Work base = base_work(*desc);
+  if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0 || workspace_bytes < base.need)
     return VISTA_ERR_WORKSPACE;
+  if (workspace_bytes < w.need) w = base;
+  // the split kernels load 16 bytes of history, 8 of the seeds and store 8 of the output at a time;
+  // the plain kernels of these shapes take any element-aligned pointer
+  if (w.route == Route::kSplit &&
+      ((reinterpret_cast<uintptr_t>(history_emb) & 15) || ((reinterpret_cast<uintptr_t>(virtual_queries) | reinterpret_cast<uintptr_t>(out)) & 7)))
+    w = base;
 
   SummarizeArgs a;
   a.desc = *desc;
-  a.seg = resolve_segment(desc);
+  a.seg = w.seg;
   a.G = (desc->total_items + a.seg - 1) / a.seg;
   if (a.G + desc->B > 0x7FFFFFFF) return VISTA_ERR_UNSUPPORTED;
   // default scale: 1/sqrt(d_h) for the softmax form, none for the pointwise forms (as printed)
@@ -166,22 +208,19 @@ static vista_status summarize_impl(const vista_summarize_desc* desc, const void*
   a.workspace = static_cast<char*>(workspace);
   a.stream = static_cast<hipStream_t>(hip_stream);
 
-  // Offsets already checked on the host: the MFMA path finds each segment's first user
-  // itself and its merge kernel clears the status word, so the plan kernel is not needed.
-  if (offsets_host && mfma_summarize_supported(*desc)) {
-    a.seg_user = nullptr;
-    return mfma_summarize(a);
-  }
-  if (offsets_host && mfma_qla_supported(*desc)) {     // likewise; the finishing kernel clears the status word
-    a.seg_user = nullptr;
-    return generic_summarize(a);
-  }
+  a.offsets_checked = offsets_host != nullptr;
+  a.seg_user = nullptr;
+  // the matrix-core kernels find each segment's first user themselves and their merge kernel checks
+  // the offsets (unless that was done above) and writes the status word: no plan kernel
+  if (w.route != Route::kGeneric) return mfma_summarize(a);
+  // likewise; the finishing kernel clears the status word
+  if (offsets_host && mfma_qla_supported(*desc)) return generic_summarize(a);
   int* seg_user = reinterpret_cast<int*>(a.workspace + kHeaderBytes);
   a.seg_user = seg_user;
   if (launch_plan(offsets, desc->B, desc->total_items, a.seg, a.G, reinterpret_cast<int*>(workspace), seg_user,
                   a.stream) != hipSuccess)
     return VISTA_ERR_HIP;
-  return mfma_summarize_supported(*desc) ? mfma_summarize(a) : generic_summarize(a);
+  return generic_summarize(a);
 }
 
 vista_status vista_summarize(const vista_summarize_desc* desc, const void* history_emb,
@@ -239,6 +278,7 @@ vista_status vista_qla_backward(const vista_summarize_desc* desc, const void* hi
   a.seg = resolve_segment(desc);
   a.G = (desc->total_items + a.seg - 1) / a.seg;
   if (a.G + desc->B > 0x7FFFFFFF) return VISTA_ERR_UNSUPPORTED;
+  a.offsets_checked = offsets_host != nullptr;
   a.scale_log2 = kLog2e;
   a.scale_plain = 1.f;
   a.X = history_emb;
@@ -270,8 +310,7 @@ vista_status vista_summarize_static(const vista_summarize_desc* desc, const void
                                     void* hip_stream) {
   vista_status st = check_summarize_desc(desc);
   if (st != VISTA_OK) return st;
-  const size_t need = vista_summarize_workspace_bytes(desc);
-  if (need > size_t(VISTA_STATIC_SCRATCH_BYTES)) return VISTA_ERR_SCRATCH;
+  if (base_work(*desc).need > size_t(VISTA_STATIC_SCRATCH_BYTES)) return VISTA_ERR_SCRATCH;
   void* ws = static_scratch();
   if (!ws) return VISTA_ERR_HIP;
   // Nothing in the scratch has to start at zero: every record the merge reads and the status

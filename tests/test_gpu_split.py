@@ -1,0 +1,106 @@
+"""GPU parity of the matrix-core path with split operands (bf16 softmax shapes outside the fixed seed
+counts): K, V and weights keep 16 significant bits, so what separates a result from the oracle is the
+rounding of the bf16 output."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import vista_oracle as O
+from paper_2510_22049_amd import binding as V
+from paper_2510_22049_amd import inputs as I
+from tests.helpers import dev, host64
+
+pytestmark = pytest.mark.gpu
+LENS = [700, 0, 1, 31, 32, 33, 2100, 64, 0, 95, 1029]
+
+
+def problem(seed, d, S, per_user=False, xscale=1.0, lens=LENS):
+    g = np.random.default_rng(seed)
+    off = I.offsets_from_lengths(lens)
+    r = lambda shape, s=1.0: I.round_to((g.normal(size=shape) * s).astype(np.float32), "bf16")
+    return r((off[-1], d), xscale), off, r((len(lens), S, d) if per_user else (S, d)), r((d, d), d ** -0.5), r((d, d), d ** -0.5)
+
+
+def check(got, want, path_error):
+    """Half a bf16 ulp of the value (2^-8 of it) plus the path's own error relative to the block."""
+    top = np.abs(want).reshape(want.shape[0], -1).max(axis=1)[:, None, None]
+    assert np.all(np.isfinite(got))
+    assert np.all(np.abs(got - want) <= 2.0 ** -8 * np.abs(want) + path_error * top)
+
+
+def run(X, off, Q, Wk, Wv, H, **kw):
+    out = torch.full((len(off) - 1,) + Q.shape[-2:], float("nan"), device="cuda", dtype=torch.bfloat16)
+    ws = V.vista_summarize(dev(X, "bf16"), torch.from_numpy(off).cuda(), dev(Q, "bf16"), dev(Wk, "bf16"), dev(Wv, "bf16"),
+                           out, H=H, **kw)
+    torch.cuda.synchronize()
+    assert int(ws[:4].view(torch.int32).item()) == 0
+    return host64(out)
+
+
+# one case on each side of every change of block count per wave and waves per head
+@pytest.mark.parametrize("d,H,S", [(64, 2, 1), (64, 2, 64), (64, 2, 65), (64, 2, 100), (64, 2, 161), (64, 2, 257), (64, 2, 512),
+                                   (128, 4, 16), (128, 4, 33), (128, 4, 127), (128, 4, 129), (128, 4, 255), (128, 4, 300), (128, 4, 511),
+                                   (256, 8, 31), (256, 8, 100), (256, 8, 250), (256, 8, 257), (256, 8, 500)])
+@pytest.mark.parametrize("seg,per_user,self_term", [(0, False, False), (64, True, True)])
+def test_split_matches_oracle(d, H, S, seg, per_user, self_term):
+    X, off, Q, Wk, Wv = problem(S, d, S, per_user)
+    got = run(X, off, Q, Wk, Wv, H, segment_items=seg, self_term=self_term)
+    want = O.summarize(X, off, Q, Wk, Wv, H, self_term=self_term)
+    check(got, want, 1e-4)               # remainders of 2^-17, scores up to ten: 1e-4
+    assert np.all(got[1] == 0) and np.all(got[8] == 0)
+
+
+def test_split_running_maximum():
+    """Scores of several tens: tiles beyond the norm bound take the running maximum; the keys' 2^-17
+    becomes 2^-17 of a score of about 100 in the exponent."""
+    X, off, Q, Wk, Wv = problem(3, 128, 100, xscale=12.0, lens=[300, 77, 1500])
+    check(run(X, off, Q, Wk, Wv, 4, segment_items=256), O.summarize(X, off, Q, Wk, Wv, 4), 4e-3)
+
+
+def test_split_shapes_keep_what_the_plain_path_took():
+    """An odd element offset of the history, and a workspace of the plain path's size only."""
+    d, H, S = 64, 2, 100
+    X, off, Q, Wk, Wv = problem(5, d, S)
+    want = O.summarize(X, off, Q, Wk, Wv, H)
+    flat = torch.empty(X.size + 1, device="cuda", dtype=torch.bfloat16)
+    Xo = flat[1:].view(X.shape)
+    Xo.copy_(dev(X, "bf16"))
+    a = [torch.from_numpy(off).cuda(), dev(Q, "bf16"), dev(Wk, "bf16"), dev(Wv, "bf16")]
+    out = torch.full((len(LENS), S, d), float("nan"), device="cuda", dtype=torch.bfloat16)
+    V.vista_summarize(Xo, *a, out, H=H)
+    check(host64(out), want, 1e-4)
+    B, N, seg = len(LENS), int(off[-1]), 256
+    G = (N + seg - 1) // seg
+    up = lambda n: (n + 255) // 256 * 256
+    plain = 256 + up(4 * G) + up((G + B) * S * (d + 2 * H) * 4) + 2 * up(N * d * 4)
+    out.fill_(float("nan"))
+    V.vista_summarize(dev(X, "bf16"), *a, out, H=H, workspace=torch.empty(plain, dtype=torch.uint8, device="cuda"))
+    check(host64(out), want, 1e-4)
+    with pytest.raises(V.VistaError):
+        V.vista_summarize(dev(X, "bf16"), *a, out, H=H, workspace=torch.empty(plain - 1, dtype=torch.uint8, device="cuda"))
+
+
+@pytest.mark.parametrize("B", [1, 3, 64, 65, 200])
+def test_first_user_of_a_segment(B):
+    """Indexing: Q = 0 and W_v = I make every output the mean of its user's rows; users of 0 to 40 rows
+    in segments of 32, so a segment's first user lies anywhere (and behind runs of empty users)."""
+    g = np.random.default_rng(B)
+    lens = g.integers(0, 41, size=B)
+    lens[g.random(B) < 0.3] = 0
+    lens[-1] = 5
+    off, d, S = I.offsets_from_lengths(lens), 64, 5
+    X = np.zeros((off[-1], d), np.float32)
+    X[:, 0] = np.repeat(np.arange(B), lens)
+    eye = np.eye(d, dtype=np.float32)
+    got = run(X, off, np.zeros((S, d), np.float32), eye, eye, 2, segment_items=32)
+    assert np.array_equal(got[:, :, 0], np.where(lens > 0, np.arange(B), 0)[:, None].repeat(S, 1))
+
+
+@pytest.mark.parametrize("bad", [[0, 70, 40, 100], [1, 50, 60, 100], [0, 50, 60, 99], [0, -5, 300, 100]])
+def test_offsets_are_checked_on_the_device(bad):
+    d, S = 128, 64
+    out = torch.zeros((3, S, d), device="cuda", dtype=torch.bfloat16)
+    z = lambda *s: torch.zeros(s, device="cuda", dtype=torch.bfloat16)
+    ws = V.vista_summarize(z(100, d), torch.tensor(bad, device="cuda"), z(S, d), z(d, d), z(d, d), out, H=4)
+    torch.cuda.synchronize()
+    assert int(ws[:4].view(torch.int32).item()) == V.VISTA_ERR_OFFSETS
