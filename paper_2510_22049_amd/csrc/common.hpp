@@ -197,6 +197,9 @@ size_t generic_summarize_workspace(const vista_summarize_desc& d, int seg);
 size_t self_kv_bytes(const vista_summarize_desc& d);
 hipError_t launch_self_kv(const vista_summarize_desc& d, const void* Q, const void* Wk, const void* Wv, float* Ks,
                           float* Vs, hipStream_t s);
+bool mfma_self_kv_supported(const vista_summarize_desc& d, const void* Q, const void* Wk, const void* Wv);
+hipError_t mfma_self_kv(const vista_summarize_desc& d, const void* Q, const void* Wk, const void* Wv, float* Ks,
+                        float* Vs, hipStream_t s);
 vista_status generic_summarize(const SummarizeArgs& a);
 bool mfma_summarize_supported(const vista_summarize_desc& d);
 bool mfma_split_supported(const vista_summarize_desc& d);

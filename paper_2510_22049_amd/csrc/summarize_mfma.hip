@@ -920,7 +920,79 @@ __global__ __launch_bounds__(256) void merge_mfma_kernel(const float* __restrict
   *reinterpret_cast<uint2*>(dst) = pk;
 }
 
+// Self term: K' = Q W_k and V' = Q W_v of the seeds in fp32 (bf16 inputs, products exact, fp32 sums).
+// One wave forms 32 seeds x 32 channels of both, the seeds' rows read once as the A operand, the
+// weights 16 bytes a lane and turned by the matrix core as in the main kernel.  The whole of it is a
+// few launches' worth of latency: one thread per output walking 2-byte loads took 33 us for 128 seeds
+// of width 128, this takes 4.
+__global__ __launch_bounds__(256) void self_kv_mfma_kernel(const uint16_t* __restrict__ Q,
+                                                           const uint16_t* __restrict__ Wk,
+                                                           const uint16_t* __restrict__ Wv, float* __restrict__ Ks,
+                                                           float* __restrict__ Vs, int64_t rows, int d) {
+  const int64_t unit = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
+  const int nc = d / 32;
+  const int64_t r0 = unit / nc * 32;
+  const int c0 = int(unit % nc) * 32;
+  if (r0 >= rows) return;
+  const int lane = threadIdx.x & 63, hf = lane >> 5, l32 = lane & 31;
+  const int64_t qrow = r0 + l32 < rows ? r0 + l32 : rows - 1;   // rows past the end repeat the last; not stored
+  const uint16_t* q = Q + qrow * d + 8 * hf;
+  const int wrow = (l32 & 16) | ((l32 & 4) << 1) | ((l32 & 8) >> 1) | (l32 & 3);
+  const uint16_t* src[2] = {Wk + wrow * d + c0 + 8 * hf, Wv + wrow * d + c0 + 8 * hf};
+  Pack8 sel[2];
+#pragma unroll
+  for (int e = 0; e < 2; ++e)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) sel[e].h[j] = (l32 == 16 * e + 8 * hf + j) ? 0x3F80 : 0;
+  f32x16 acc[2] = {{0}, {0}};
+#pragma unroll 4
+  for (int k = 0; k < d; k += 32) {
+    Pack8 x[2], raw[2][2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      x[e].u = *reinterpret_cast<const uint4*>(q + k + 16 * e);
+#pragma unroll
+      for (int m = 0; m < 2; ++m) raw[m][e].u = *reinterpret_cast<const uint4*>(src[m] + k * d + 16 * e);
+    }
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      f32x16 t = {0};
+      t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(raw[m][0].v, sel[0].v, t, 0, 0, 0);
+      t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(raw[m][1].v, sel[1].v, t, 0, 0, 0);
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        Pack8 w;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) w.w[j] = cvt_pk_bf16(t[8 * e + 2 * j], t[8 * e + 2 * j + 1]);
+        acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[e].v, w.v, acc[m], 0, 0, 0);
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int64_t r = r0 + acc_row0(i) + 4 * hf;
+    if (r < rows) {
+      Ks[r * d + c0 + l32] = acc[0][i];
+      Vs[r * d + c0 + l32] = acc[1][i];
+    }
+  }
+}
+
 // ------------------------------------------------------------------ host side
+
+// 16-byte loads of seeds and weights; other alignments and types keep one thread per output.
+bool mfma_self_kv_supported(const vista_summarize_desc& d, const void* Q, const void* Wk, const void* Wv) {
+  return d.dtype == VISTA_BF16 && d.d % 32 == 0 &&
+         ((reinterpret_cast<uintptr_t>(Q) | reinterpret_cast<uintptr_t>(Wk) | reinterpret_cast<uintptr_t>(Wv)) & 15) == 0;
+}
+
+hipError_t mfma_self_kv(const vista_summarize_desc& d, const void* Q, const void* Wk, const void* Wv, float* Ks,
+                        float* Vs, hipStream_t s) {
+  const int64_t rows = d.q_user_stride ? int64_t(d.B) * d.S : d.S;
+  const int64_t units = (rows + 31) / 32 * (d.d / 32);
+  return launch(self_kv_mfma_kernel, dim3(unsigned((units + 3) / 4)), dim3(256), 0, s, static_cast<const uint16_t*>(Q),
+                static_cast<const uint16_t*>(Wk), static_cast<const uint16_t*>(Wv), Ks, Vs, rows, d.d);
+}
 
 // The shapes whose K, V and softmax weights are bf16 operands.
 bool mfma_summarize_supported(const vista_summarize_desc& d) {
