@@ -194,6 +194,16 @@ struct SummarizeArgs {
 };
 
 size_t generic_summarize_workspace(const vista_summarize_desc& d, int seg);
+// fp32 matrix instructions (plain_mfma.hip); the merge is the plain path's
+bool f32_history_supported(const vista_summarize_desc& d);
+bool f32_history_aligned(const vista_summarize_desc& d, const void* X, const void* Q, const void* Wk, const void* Wv);
+int f32_history_segment(const vista_summarize_desc& d);
+hipError_t f32_history(const SummarizeArgs& a, float* partials);
+size_t f32_summarize_workspace(const vista_summarize_desc& d, int seg);
+vista_status f32_summarize(const SummarizeArgs& a);
+bool f32_candidates_supported(const vista_attend_desc& d, const void* cand, const void* summ, const void* out);
+hipError_t f32_candidates(const vista_attend_desc& d, float scale_log2, const void* cand, const void* summ, void* out,
+                          hipStream_t s);
 size_t self_kv_bytes(const vista_summarize_desc& d);
 hipError_t launch_self_kv(const vista_summarize_desc& d, const void* Q, const void* Wk, const void* Wv, float* Ks,
                           float* Vs, hipStream_t s);

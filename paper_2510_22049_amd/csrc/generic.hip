@@ -164,64 +164,137 @@ hipError_t launch_self_kv(const vista_summarize_desc& d, const void* Q, const vo
 }
 
 // ------------------------------------------------------- stage 1: merge
-// Combines a user's partial slots in ascending segment order.
+// Combines a user's partial slots in a fixed order.
 //   softmax:  m = max m_c,  l = sum l_c 2^(m_c - m),  O = sum O_c 2^(m_c - m),  out = O / l;
 //             the self term is one more slot: m = own score, l = 1, O = own value;
 //   SiLU form: out = (sum O_c [+ SiLU(own score) own value]) / L_b.
-// grid (B, H); threads stride over (query, channel).  scale_log2 / scale as in the main kernel.
-template <typename T, bool SILU>
-__global__ void merge_kernel(const float* __restrict__ partials, const int64_t* __restrict__ offsets,
-                             int S, int d, int H, int seg, int64_t G, T* __restrict__ out,
-                             const T* __restrict__ Q, int64_t q_user_stride, const float* __restrict__ Ks,
-                             const float* __restrict__ Vs, float scale_log2) {
+// One thread per (query, channel), 256 / RG of them a block, all of one (user, head); RG threads share an
+// element, each taking a run of the user's records, ascending, eight loads in flight; the runs are
+// combined in ascending order.  Four runs where users hold eight records or more: one user's 16
+// records of a 1024-item history took 10.5 us in one block of dependent loads.
+// With `status` the first block publishes the status word, after a check of the offsets where
+// check_offsets says that nobody has.  scale: as in the main kernel.
+template <typename T, bool SILU, int RG>
+__global__ __launch_bounds__(256) void merge_kernel(const float* __restrict__ partials,
+                                                    const int64_t* __restrict__ offsets, int B, int S, int d, int H,
+                                                    int seg, int64_t N, int64_t G, T* __restrict__ out, int* status,
+                                                    int check_offsets, const T* __restrict__ Q, int64_t q_user_stride,
+                                                    const float* __restrict__ Ks, const float* __restrict__ Vs,
+                                                    float scale) {
+  constexpr int kPer = 256 / RG, kBatch = 8;
+  __shared__ float group[RG][3][kPer];
+  if (status && blockIdx.x == 0) {
+    int bad = 0;
+    if (check_offsets)
+      for (int u = threadIdx.x; u <= B; u += blockDim.x) {
+        const int64_t v = offsets[u];
+        bad |= (u == 0 && v != 0) || (u == B && v != N) || (u < B && offsets[u + 1] < v);
+      }
+    bad = __syncthreads_or(bad);
+    if (threadIdx.x == 0) *status = bad ? int(VISTA_ERR_OFFSETS) : int(VISTA_OK);
+  }
   const int dh = d / H;
-  const int b = blockIdx.x, h = blockIdx.y;
+  const int ne = (S * dh + kPer - 1) / kPer;
+  const int eb = blockIdx.x % ne, h = blockIdx.x / ne % H, b = blockIdx.x / ne / H;
+  const int rg = threadIdx.x / kPer, el = threadIdx.x % kPer;
+  const bool live = eb * kPer + el < S * dh;
+  const int e = live ? eb * kPer + el : S * dh - 1;
+  const int i = e / dh, t = e % dh;
   const int64_t begin = offsets[b], end = offsets[b + 1];
-  T* dst = out + int64_t(b) * S * d + h * dh;
+  T* dst = out + (int64_t(b) * S + i) * d + h * dh + t;
   if (end <= begin) {
-    for (int e = threadIdx.x; e < S * dh; e += blockDim.x) store_as(dst + int64_t(e / dh) * d + (e % dh), 0.f);
+    if (live && rg == 0) store_as(dst, 0.f);
     return;
   }
   int64_t g0 = begin / seg, g1 = (end - 1) / seg;
   if (g0 < 0) g0 = 0;
   if (g1 > G - 1) g1 = G - 1;
-  const int64_t srow0 = q_user_stride ? int64_t(b) * S : 0;     // first row of this user's K', V'
-  for (int e = threadIdx.x; e < S * dh; e += blockDim.x) {
-    const int i = e / dh, t = e % dh;
-    float s_self = 0.f, v_self = 0.f;
-    if (Ks) {
-      const T* q = Q + q_user_stride * b + int64_t(i) * d + h * dh;
-      const float* ks = Ks + (srow0 + i) * d + h * dh;
-      for (int c = 0; c < dh; ++c) s_self = fmaf(to_f32(q[c]), ks[c], s_self);
-      s_self *= scale_log2;
-      v_self = Vs[(srow0 + i) * d + h * dh + t];
+  const int64_t run = (g1 - g0 + RG) / RG;
+  const int64_t r0 = g0 + rg * run;
+  const int64_t r1 = g1 < r0 + run - 1 ? g1 : r0 + run - 1;
+  float m = -INFINITY, l = 0.f, o = 0.f;
+  for (int64_t g = r0; g <= r1; g += kBatch) {
+    float v[kBatch][3];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const bool on = g + u <= r1;
+      const float* p = partials + (((on ? g + u : r1) + b) * H + h) * int64_t(S) * (dh + 2) + int64_t(i) * (dh + 2);
+      v[u][0] = on ? p[dh + 1] : -INFINITY;
+      v[u][1] = p[dh];
+      v[u][2] = on || !SILU ? p[t] : 0.f;
     }
-    if (SILU) {
-      float o = 0.f;
-      for (int64_t g = g0; g <= g1; ++g) o += partials[(((g + b) * H + h) * S + i) * (dh + 2) + t];
-      if (Ks) o = fmaf(s_self / (1.f + expf(-s_self)), v_self, o);
-      store_as(dst + int64_t(i) * d + t, o / float(end - begin));
-      continue;
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      if (SILU) {
+        o += v[u][2];
+        continue;
+      }
+      const float mn = fmaxf(m, v[u][0]);
+      const float keep = exp2f(m - mn), w = exp2f(v[u][0] - mn);    // keep = 0 on the first, w = 0 for padding
+      l = fmaf(v[u][1], w, l * keep);
+      o = fmaf(v[u][2], w, o * keep);
+      m = mn;
     }
-    float m = Ks ? s_self : -INFINITY;
-    for (int64_t g = g0; g <= g1; ++g) {
-      const float* p = partials + (((g + b) * H + h) * S + i) * (dh + 2);
-      m = fmaxf(m, p[dh + 1]);
-    }
-    float l = 0.f, o = 0.f;
-    for (int64_t g = g0; g <= g1; ++g) {
-      const float* p = partials + (((g + b) * H + h) * S + i) * (dh + 2);
-      float w = exp2f(p[dh + 1] - m);
-      l = fmaf(p[dh], w, l);
-      o = fmaf(p[t], w, o);
-    }
-    if (Ks) {
-      const float w = exp2f(s_self - m);
-      l += w;
-      o = fmaf(v_self, w, o);
-    }
-    store_as(dst + int64_t(i) * d + t, o / l);
   }
+  if (RG > 1) {
+    group[rg][0][el] = m;
+    group[rg][1][el] = l;
+    group[rg][2][el] = o;
+    __syncthreads();
+    if (rg > 0) return;
+#pragma unroll
+    for (int r = 1; r < RG; ++r) {
+      const float m2 = group[r][0][el], l2 = group[r][1][el], o2 = group[r][2][el];
+      if (SILU) {
+        o += o2;
+        continue;
+      }
+      const float mn = fmaxf(m, m2);                                // run 0 is never empty: finite
+      const float keep = exp2f(m - mn), w = exp2f(m2 - mn);
+      l = fmaf(l2, w, l * keep);
+      o = fmaf(o2, w, o * keep);
+      m = mn;
+    }
+  }
+  if (!live) return;
+  float s_self = 0.f, v_self = 0.f;
+  if (Ks) {
+    const int64_t srow = (q_user_stride ? int64_t(b) * S : 0) + i;
+    const T* q = Q + q_user_stride * b + int64_t(i) * d + h * dh;
+    const float* ks = Ks + srow * d + h * dh;
+    for (int c = 0; c < dh; ++c) s_self = fmaf(to_f32(q[c]), ks[c], s_self);
+    s_self *= scale;
+    v_self = Vs[srow * d + h * dh + t];
+  }
+  if (SILU) {
+    if (Ks) o = fmaf(s_self / (1.f + expf(-s_self)), v_self, o);
+    store_as(dst, o / float(end - begin));
+    return;
+  }
+  if (Ks) {
+    const float mn = fmaxf(m, s_self);
+    const float keep = exp2f(m - mn), w = exp2f(s_self - mn);
+    l = fmaf(l, keep, w);
+    o = fmaf(v_self, w, o * keep);
+  }
+  store_as(dst, o / l);
+}
+
+template <typename T>
+static hipError_t launch_merge(const SummarizeArgs& a, const float* partials, const float* Ks, const float* Vs, int* status) {
+  const vista_summarize_desc& d = a.desc;
+  const bool silu = d.attn == VISTA_ATTN_SILU;
+  const bool wide = a.G / d.B >= 8;
+  const int per = wide ? 64 : 256;
+  const int64_t blocks = int64_t(d.B) * d.H * ((int64_t(d.S) * (d.d / d.H) + per - 1) / per);
+  if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
+  void (*kernel)(const float*, const int64_t*, int, int, int, int, int, int64_t, int64_t, T*, int*, int, const T*, int64_t,
+                 const float*, const float*, float) =
+      silu ? (wide ? merge_kernel<T, true, 4> : merge_kernel<T, true, 1>)
+           : (wide ? merge_kernel<T, false, 4> : merge_kernel<T, false, 1>);
+  return launch(kernel, dim3(unsigned(blocks)), dim3(256), 0, a.stream, partials, a.offsets, d.B, d.S, d.d, d.H, a.seg,
+                d.total_items, a.G, static_cast<T*>(a.out), status, a.offsets_checked ? 0 : 1, static_cast<const T*>(a.Q),
+                d.q_user_stride, Ks, Vs, silu ? a.scale_plain : a.scale_log2);
 }
 
 // ---------------------------------------------- quasi-linear attention (plain path)
@@ -830,13 +903,32 @@ static vista_status generic_summarize_t(const SummarizeArgs& a) {
     VISTA_LAUNCH((qla_finish_kernel<T, 0>), dim3(d.B, d.H), dim3(1024), 0, a.stream, partials, a.offsets, d.S, d.d,
                  d.H, a.seg, a.G, out, Q, d.q_user_stride, Ks, Vs,
                  a.seg_user ? nullptr : reinterpret_cast<int*>(a.workspace));
-  else if (silu)
-    VISTA_LAUNCH((merge_kernel<T, true>), dim3(d.B, d.H), dim3(256), 0, a.stream, partials, a.offsets, d.S, d.d,
-                 d.H, a.seg, a.G, out, Q, d.q_user_stride, Ks, Vs, score_scale);
-  else
-    VISTA_LAUNCH((merge_kernel<T, false>), dim3(d.B, d.H), dim3(256), 0, a.stream, partials, a.offsets, d.S, d.d,
-                 d.H, a.seg, a.G, out, Q, d.q_user_stride, Ks, Vs, score_scale);
+  else if (launch_merge<T>(a, partials, Ks, Vs, nullptr) != hipSuccess)
+    return VISTA_ERR_HIP;
   return VISTA_OK;
+}
+
+// [header][seg_user][partial records][K' of the seeds][V' of the seeds]
+size_t f32_summarize_workspace(const vista_summarize_desc& d, int seg) {
+  const int64_t G = (d.total_items + seg - 1) / seg;
+  return kHeaderBytes + plan_bytes(G) + align256(generic_partials_bytes(d, seg)) + 2 * self_kv_bytes(d);
+}
+
+vista_status f32_summarize(const SummarizeArgs& a) {
+  const vista_summarize_desc& d = a.desc;
+  float* partials = reinterpret_cast<float*>(a.workspace + kHeaderBytes + plan_bytes(a.G));
+  float* Ks = nullptr;
+  float* Vs = nullptr;
+  if (d.flags & VISTA_FLAG_SELF_TERM) {
+    Ks = partials + align256(generic_partials_bytes(d, a.seg)) / sizeof(float);
+    Vs = Ks + self_kv_bytes(d) / sizeof(float);
+    if (launch_self_kv(d, a.Q, a.Wk, a.Wv, Ks, Vs, a.stream) != hipSuccess) return VISTA_ERR_HIP;
+  }
+  if (a.G > 0 && f32_history(a, partials) != hipSuccess) return VISTA_ERR_HIP;
+  int* status = reinterpret_cast<int*>(a.workspace);
+  const hipError_t e = d.dtype == VISTA_BF16 ? launch_merge<bf16_t>(a, partials, Ks, Vs, status)
+                                             : launch_merge<float>(a, partials, Ks, Vs, status);
+  return e == hipSuccess ? VISTA_OK : VISTA_ERR_HIP;
 }
 
 vista_status generic_summarize(const SummarizeArgs& a) {

@@ -219,7 +219,7 @@ struct SummarizeLds {
 // denominator, no norm test; the key weights then carry -scale*log2(e), so a score leaves the
 // MFMA as t = -s log2(e) and SiLU(s) = -ln(2) t / (1 + 2^t); the weight handed to the second
 // product is t / (1 + 2^t) and the constant joins the 1/L_b of the merge.
-template <int D, int NQB, int HPW, int FW, bool WREG, bool SPLIT, int ROLE, int ATTN>
+template <int D, int NQB, int HPW, int FW, bool WREG, bool SPLIT, bool ALLF, int ROLE, int ATTN>
 __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, SummarizeLds<D, HPW, WREG, SPLIT>& sm,
                                                int64_t g, int h, int hl, int qslot, int64_t seg_begin,
                                                int64_t seg_end) {
@@ -396,7 +396,7 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
   // load has two tile periods.  Rows past the piece are clamped to its last row.
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   auto fetch = [&](const Cursor& c, int xb) __attribute__((always_inline)) {
-    if (SPLIT && wave >= FW) return;                       // (elsewhere every wave fetches)
+    if (!ALLF && wave >= FW) return;
     const int last = (c.tiles_left == 1 ? c.tail : kTile) - 1;   // last valid row of the tile
     const char* base = reinterpret_cast<const char*>(p.X) + c.row * (D * 2);
 #pragma unroll
@@ -707,7 +707,8 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
   }
 }
 
-// MAXT: largest workgroup of the instantiation (it bounds the registers of a wave).  FW waves fetch X.
+// MAXT: largest workgroup of the instantiation (it bounds the registers of a wave).  The first FW waves
+// fetch X (ALLF: that is every wave).
 template <int D, int NQB, int HPW, int FW, bool WREG, bool SPLIT, int MAXT, int ATTN>
 __global__ __launch_bounds__(MAXT) void summarize_mfma_kernel(MfmaSummarizeParams p) {
   __shared__ SummarizeLds<D, HPW, WREG, SPLIT> sm;
@@ -732,11 +733,11 @@ __global__ __launch_bounds__(MAXT) void summarize_mfma_kernel(MfmaSummarizeParam
   const int64_t seg_end = (seg_begin + p.seg < p.N) ? seg_begin + p.seg : p.N;
   // All roles run the same sequence of barriers; only the MFMA operand order differs.
   if (slot == 0)
-    summarize_wave<D, NQB, HPW, FW, WREG, SPLIT, 0, ATTN>(p, sm, g, h, hl, 0, seg_begin, seg_end);
+    summarize_wave<D, NQB, HPW, FW, WREG, SPLIT, (!SPLIT && MAXT == 64 * FW), 0, ATTN>(p, sm, g, h, hl, 0, seg_begin, seg_end);
   else if (slot == 1)
-    summarize_wave<D, NQB, HPW, FW, WREG, SPLIT, 1, ATTN>(p, sm, g, h, hl, 1, seg_begin, seg_end);
+    summarize_wave<D, NQB, HPW, FW, WREG, SPLIT, (!SPLIT && MAXT == 64 * FW), 1, ATTN>(p, sm, g, h, hl, 1, seg_begin, seg_end);
   else if constexpr (MAXT != HPW * 128)      // (two waves per head: there is no third slot)
-    summarize_wave<D, NQB, HPW, FW, WREG, SPLIT, 2, ATTN>(p, sm, g, h, hl, slot, seg_begin, seg_end);
+    summarize_wave<D, NQB, HPW, FW, WREG, SPLIT, (!SPLIT && MAXT == 64 * FW), 2, ATTN>(p, sm, g, h, hl, slot, seg_begin, seg_end);
 }
 
 // Merge of a user's partial records in a fixed order, so the result is bitwise reproducible.
@@ -1061,6 +1062,9 @@ static hipError_t launch_main(MfmaSummarizeParams& p, int wph, int64_t G, hipStr
 template <int ATTN>
 static hipError_t launch_for_shape(MfmaSummarizeParams& p, int d, int64_t G, hipStream_t s) {
   if (d == 128) {
+    // SiLU at S = 128: its two transcendentals a score leave the vector unit the bound, and sixteen waves of
+    // one block each feed it better than eight of two (115 -> 108 us; softmax the other way, 87 -> 92)
+    if (ATTN == VISTA_ATTN_SILU && p.nqb == 4) return launch_main<128, 1, 4, 8, true, false, 1024, ATTN>(p, 4, G, s);
     if (p.nqb <= 2) return launch_main<128, 1, 4, 8, true, false, 512, ATTN>(p, 2, G, s);
     if (p.nqb <= 4) return launch_main<128, 2, 4, 8, true, false, 512, ATTN>(p, 2, G, s);
     if (p.nqb <= 8) return launch_main<128, 4, 4, 8, true, false, 512, ATTN>(p, 2, G, s);

@@ -47,15 +47,15 @@ int32_t resolve_segment(const vista_summarize_desc* d) {
 }
 
 // How a call is carried out: the kernel family, its segment size and the workspace it needs.
-enum class Route { kMfma, kSplit, kGeneric };
+enum class Route { kMfma, kSplit, kF32, kGeneric };
 struct Work {
   Route route;
   int32_t seg;
   size_t need;
 };
 
-// The plain path at the default segment size: what a bf16 softmax shape outside the fixed seed counts
-// falls back to when the workspace or a pointer's alignment does not suit the matrix-core kernel.
+// The schedule of vista_summarize_segment_items, outside the fixed seed counts on the plain path: what a
+// call falls back to when the workspace or a pointer's alignment does not suit the preferred way.
 Work base_work(const vista_summarize_desc& d) {
   const int32_t seg = resolve_segment(&d);
   if (mfma_summarize_supported(d)) return {Route::kMfma, seg, mfma_summarize_workspace(d, seg)};
@@ -68,16 +68,19 @@ Work base_work(const vista_summarize_desc& d) {
 // that the static entry point and the one with a workspace always do the same.
 Work best_work(const vista_summarize_desc& d) {
   const Work base = base_work(d);
-  const bool split = mfma_split_supported(d);
-  if (base.route == Route::kGeneric && !split) return base;
-  const Route route = split ? Route::kSplit : Route::kMfma;
+  const Route route = base.route == Route::kMfma  ? Route::kMfma
+                      : mfma_split_supported(d)   ? Route::kSplit
+                      : f32_history_supported(d)  ? Route::kF32
+                                                  : Route::kGeneric;
+  if (route == Route::kGeneric) return base;
+  const bool f32 = route == Route::kF32;
   const size_t limit = base.need > size_t(VISTA_STATIC_SCRATCH_BYTES) ? base.need : size_t(VISTA_STATIC_SCRATCH_BYTES);
   if (d.segment_items == 0) {
-    const int32_t seg = mfma_summarize_segment(d);
-    const size_t need = mfma_summarize_workspace(d, seg);
+    const int32_t seg = f32 ? f32_history_segment(d) : mfma_summarize_segment(d);
+    const size_t need = f32 ? f32_summarize_workspace(d, seg) : mfma_summarize_workspace(d, seg);
     if (need <= limit) return {route, seg, need};
   }
-  const Work w = {route, base.seg, mfma_summarize_workspace(d, base.seg)};
+  const Work w = {route, base.seg, f32 ? f32_summarize_workspace(d, base.seg) : mfma_summarize_workspace(d, base.seg)};
   return w.need <= limit ? w : base;
 }
 
@@ -181,11 +184,12 @@ static vista_status summarize_impl(const vista_summarize_desc* desc, const void*
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0 || workspace_bytes < base.need)
     return VISTA_ERR_WORKSPACE;
   if (workspace_bytes < w.need) w = base;
-  // the split kernels load 16 bytes of history, 8 of the seeds and store 8 of the output at a time;
-  // the plain kernels of these shapes take any element-aligned pointer
+  // the split kernels load 16 bytes of history, 8 of the seeds and store 8 of the output at a time, the
+  // fp32 matrix kernels load four elements; the plain kernels take any element-aligned pointer
   if (w.route == Route::kSplit &&
       ((reinterpret_cast<uintptr_t>(history_emb) & 15) || ((reinterpret_cast<uintptr_t>(virtual_queries) | reinterpret_cast<uintptr_t>(out)) & 7)))
     w = base;
+  if (w.route == Route::kF32 && !f32_history_aligned(*desc, history_emb, virtual_queries, W_k, W_v)) w = base;
 
   SummarizeArgs a;
   a.desc = *desc;
@@ -212,6 +216,7 @@ static vista_status summarize_impl(const vista_summarize_desc* desc, const void*
   a.seg_user = nullptr;
   // the matrix-core kernels find each segment's first user themselves and their merge kernel checks
   // the offsets (unless that was done above) and writes the status word: no plan kernel
+  if (w.route == Route::kF32) return f32_summarize(a);
   if (w.route != Route::kGeneric) return mfma_summarize(a);
   // likewise; the finishing kernel clears the status word
   if (offsets_host && mfma_qla_supported(*desc)) return generic_summarize(a);
@@ -336,6 +341,8 @@ static vista_status target_attend_impl(const vista_attend_desc* desc, const void
   const bool aligned = !codes || (desc->d % 16 == 0 && (reinterpret_cast<uintptr_t>(codes) & 15) == 0);
   if (mfma_target_attend_supported(*desc) && aligned)
     return mfma_target_attend(*desc, scale * kLog2e, candidates, summaries, codes, scales, out, s);
+  if (!codes && f32_candidates_supported(*desc, candidates, summaries, out))
+    return f32_candidates(*desc, scale * kLog2e, candidates, summaries, out, s) == hipSuccess ? VISTA_OK : VISTA_ERR_HIP;
   return generic_target_attend(*desc, scale * kLog2e, candidates, summaries, codes, scales, out, s);
 }
 
