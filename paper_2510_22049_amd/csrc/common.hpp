@@ -148,6 +148,16 @@ struct TileCursor {
         valid = false;               // stays on its last tile
     }
   }
+  // Full tiles this cursor can still pass, its current one included, before the last tile of its piece:
+  // while `behind` (a cursor some tiles earlier in the stream) is in the same piece, both walk them
+  // by adding to `row`, with no look at the pieces (skip).
+  __host__ __device__ __forceinline__ int straight(const TileCursor& behind) const {
+    return valid && wpos == behind.wpos && user == behind.user ? tiles_left - 1 : 0;
+  }
+  __host__ __device__ __forceinline__ void skip(int n) {
+    tiles_left -= n;
+    row += int64_t(n) * kTileItems;
+  }
   // valid rows of the current tile
   __host__ __device__ __forceinline__ int rows() const { return tiles_left == 1 ? tail : kTileItems; }
 };
@@ -218,6 +228,7 @@ size_t mfma_summarize_workspace(const vista_summarize_desc& d, int seg);
 vista_status mfma_summarize(const SummarizeArgs& a);
 
 bool mfma_qla_supported(const vista_summarize_desc& d);
+int mfma_qla_segment(const vista_summarize_desc& d);
 vista_status mfma_qla_state(const SummarizeArgs& a, float* partials);
 // dz: dZs [B][H][32][32] fp32 (device); writes dK and dV rows of every item
 vista_status mfma_qla_backward_items(const SummarizeArgs& a, const float* dz, void* d_keys, void* d_values);

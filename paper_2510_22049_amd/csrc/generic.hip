@@ -49,6 +49,19 @@ hipError_t launch_plan(const int64_t* offsets, int B, int64_t N, int seg, int64_
   return launch(plan_kernel, dim3(blocks), dim3(256), 0, s, offsets, B, N, seg, G, status, seg_user);
 }
 
+// The status word, published by a launch's first block: without a plan kernel in front the offsets are
+// checked here, unless the host has done that (N < 0).
+__device__ __forceinline__ void publish_status(const int64_t* __restrict__ offsets, int B, int64_t N, int* status) {
+  int bad = 0;
+  if (N >= 0)
+    for (int u = threadIdx.x; u <= B; u += blockDim.x) {
+      const int64_t v = offsets[u];
+      bad |= (u == 0 && v != 0) || (u == B && v != N) || (u < B && offsets[u + 1] < v);
+    }
+  bad = __syncthreads_or(bad);
+  if (threadIdx.x == 0) *status = bad ? int(VISTA_ERR_OFFSETS) : int(VISTA_OK);
+}
+
 // -------------------------------------------------- stage 1: K/V projection
 // K = X W_k, V = X W_v in fp32 (Sec. 3.2.1: K and V of shape (L, d)).
 // Block = 256 threads = (256/d') rows x d' columns; each thread one (row, col).
@@ -172,27 +185,17 @@ hipError_t launch_self_kv(const vista_summarize_desc& d, const void* Q, const vo
 // element, each taking a run of the user's records, ascending, eight loads in flight; the runs are
 // combined in ascending order.  Four runs where users hold eight records or more: one user's 16
 // records of a 1024-item history took 10.5 us in one block of dependent loads.
-// With `status` the first block publishes the status word, after a check of the offsets where
-// check_offsets says that nobody has.  scale: as in the main kernel.
+// With `status` the first block publishes the status word (publish_status).  scale: as in the main kernel.
 template <typename T, bool SILU, int RG>
 __global__ __launch_bounds__(256) void merge_kernel(const float* __restrict__ partials,
                                                     const int64_t* __restrict__ offsets, int B, int S, int d, int H,
                                                     int seg, int64_t N, int64_t G, T* __restrict__ out, int* status,
-                                                    int check_offsets, const T* __restrict__ Q, int64_t q_user_stride,
+                                                    const T* __restrict__ Q, int64_t q_user_stride,
                                                     const float* __restrict__ Ks, const float* __restrict__ Vs,
                                                     float scale) {
   constexpr int kPer = 256 / RG, kBatch = 8;
   __shared__ float group[RG][3][kPer];
-  if (status && blockIdx.x == 0) {
-    int bad = 0;
-    if (check_offsets)
-      for (int u = threadIdx.x; u <= B; u += blockDim.x) {
-        const int64_t v = offsets[u];
-        bad |= (u == 0 && v != 0) || (u == B && v != N) || (u < B && offsets[u + 1] < v);
-      }
-    bad = __syncthreads_or(bad);
-    if (threadIdx.x == 0) *status = bad ? int(VISTA_ERR_OFFSETS) : int(VISTA_OK);
-  }
+  if (status && blockIdx.x == 0) publish_status(offsets, B, N, status);
   const int dh = d / H;
   const int ne = (S * dh + kPer - 1) / kPer;
   const int eb = blockIdx.x % ne, h = blockIdx.x / ne % H, b = blockIdx.x / ne / H;
@@ -288,12 +291,12 @@ static hipError_t launch_merge(const SummarizeArgs& a, const float* partials, co
   const int per = wide ? 64 : 256;
   const int64_t blocks = int64_t(d.B) * d.H * ((int64_t(d.S) * (d.d / d.H) + per - 1) / per);
   if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
-  void (*kernel)(const float*, const int64_t*, int, int, int, int, int, int64_t, int64_t, T*, int*, int, const T*, int64_t,
+  void (*kernel)(const float*, const int64_t*, int, int, int, int, int, int64_t, int64_t, T*, int*, const T*, int64_t,
                  const float*, const float*, float) =
       silu ? (wide ? merge_kernel<T, true, 4> : merge_kernel<T, true, 1>)
            : (wide ? merge_kernel<T, false, 4> : merge_kernel<T, false, 1>);
   return launch(kernel, dim3(unsigned(blocks)), dim3(256), 0, a.stream, partials, a.offsets, d.B, d.S, d.d, d.H, a.seg,
-                d.total_items, a.G, static_cast<T*>(a.out), status, a.offsets_checked ? 0 : 1, static_cast<const T*>(a.Q),
+                a.offsets_checked ? -1 : d.total_items, a.G, static_cast<T*>(a.out), status, static_cast<const T*>(a.Q),
                 d.q_user_stride, Ks, Vs, silu ? a.scale_plain : a.scale_log2);
 }
 
@@ -333,12 +336,11 @@ __global__ __launch_bounds__(1024) void qla_finish_kernel(const float* __restric
                                                          int seg, int64_t G, T* __restrict__ out,
                                                          const T* __restrict__ Q, int64_t q_user_stride,
                                                          const float* __restrict__ Ks,
-                                                         const float* __restrict__ Vs, int* status) {
+                                                         const float* __restrict__ Vs, int B, int64_t N, int* status) {
   constexpr int kW = DH ? DH : kMaxDh;          // register rows are sized for it
   constexpr int kRun = 256;                     // queries per pass: four threads each at 1024 threads
   constexpr int kDeep = 8;                      // record loads a thread keeps in flight
-  // without a plan kernel in front (offsets checked on the host) the status word is cleared here
-  if (status && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *status = VISTA_OK;
+  if (status && blockIdx.x == 0 && blockIdx.y == 0) publish_status(offsets, B, N, status);
   __shared__ float z[kW * kW];
   const int dh = DH ? DH : d / H;
   const int b = blockIdx.x, h = blockIdx.y;
@@ -482,9 +484,8 @@ __global__ __launch_bounds__(1024) void qla_bwd_state_kernel(const float* __rest
                                                             const int64_t* __restrict__ offsets, int S, int d, int H,
                                                             int seg, int64_t G, const T* __restrict__ Q,
                                                             int64_t q_user_stride, const T* __restrict__ dO,
-                                                            T* __restrict__ dQ, float* __restrict__ dz, int* status) {
-  // without a plan kernel in front (offsets checked on the host) the status word is cleared here
-  if (status && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *status = VISTA_OK;
+                                                            T* __restrict__ dQ, float* __restrict__ dz, int B, int64_t N, int* status) {
+  if (status && blockIdx.x == 0 && blockIdx.y == 0) publish_status(offsets, B, N, status);
   __shared__ float zs[kMaxDh * kMaxDh];        // Zs, then SiLU'(Zs)
   __shared__ float gt[kMaxDh * (kMaxDh + 1)];  // G transposed: gt[c][a]
   __shared__ float qa[64][kMaxDh + 1];         // SiLU(q) of the run
@@ -625,9 +626,9 @@ __global__ __launch_bounds__(1024) void qla_bwd_state32_kernel(const float* __re
                                                                const int64_t* __restrict__ offsets, int S, int d, int H,
                                                                int seg, int64_t G, const T* __restrict__ Q,
                                                                int64_t q_user_stride, const T* __restrict__ dO,
-                                                               T* __restrict__ dQ, float* __restrict__ dz, int* status) {
+                                                               T* __restrict__ dQ, float* __restrict__ dz, int B, int64_t N, int* status) {
   constexpr int dh = 32, zz = dh * dh, kRun = 256, kRow = 36;
-  if (status && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *status = VISTA_OK;
+  if (status && blockIdx.x == 0 && blockIdx.y == 0) publish_status(offsets, B, N, status);
   __shared__ __align__(16) float zs[zz];                 // Zs, then SiLU'(Zs)
   __shared__ __align__(16) float gt[dh * kRow];          // G transposed: gt[c][a]
   __shared__ __align__(16) float qa[kRun * kRow];        // SiLU(q) of the run; at the end the partial dG of the four quarters
@@ -897,11 +898,11 @@ static vista_status generic_summarize_t(const SummarizeArgs& a) {
   T* out = static_cast<T*>(a.out);
   if (qla && d.d / d.H == 32)
     VISTA_LAUNCH((qla_finish_kernel<T, 32>), dim3(d.B, d.H), dim3(1024), 0, a.stream, partials, a.offsets, d.S, d.d,
-                 d.H, a.seg, a.G, out, Q, d.q_user_stride, Ks, Vs,
+                 d.H, a.seg, a.G, out, Q, d.q_user_stride, Ks, Vs, d.B, a.offsets_checked ? -1 : d.total_items,
                  a.seg_user ? nullptr : reinterpret_cast<int*>(a.workspace));
   else if (qla)
     VISTA_LAUNCH((qla_finish_kernel<T, 0>), dim3(d.B, d.H), dim3(1024), 0, a.stream, partials, a.offsets, d.S, d.d,
-                 d.H, a.seg, a.G, out, Q, d.q_user_stride, Ks, Vs,
+                 d.H, a.seg, a.G, out, Q, d.q_user_stride, Ks, Vs, d.B, a.offsets_checked ? -1 : d.total_items,
                  a.seg_user ? nullptr : reinterpret_cast<int*>(a.workspace));
   else if (launch_merge<T>(a, partials, Ks, Vs, nullptr) != hipSuccess)
     return VISTA_ERR_HIP;
@@ -973,11 +974,11 @@ static vista_status qla_backward_t(const SummarizeArgs& a, const void* d_out, vo
   if (dh == 32)
     VISTA_LAUNCH(qla_bwd_state32_kernel<T>, dim3(d.B, d.H), dim3(1024), 0, a.stream, partials, a.offsets, d.S, d.d, d.H,
                  a.seg, a.G, static_cast<const T*>(a.Q), d.q_user_stride, static_cast<const T*>(d_out),
-                 static_cast<T*>(d_queries), dz, status);
+                 static_cast<T*>(d_queries), dz, d.B, a.offsets_checked ? -1 : d.total_items, status);
   else
     VISTA_LAUNCH(qla_bwd_state_kernel<T>, dim3(d.B, d.H), dim3(1024), 0, a.stream, partials, a.offsets, d.S, d.d, d.H,
                  a.seg, a.G, static_cast<const T*>(a.Q), d.q_user_stride, static_cast<const T*>(d_out),
-                 static_cast<T*>(d_queries), dz, status);
+                 static_cast<T*>(d_queries), dz, d.B, a.offsets_checked ? -1 : d.total_items, status);
   if (d.flags & VISTA_FLAG_SELF_TERM) {
     // the seeds' own keys and values, then the diagonal term's gradients (dQ is added to)
     float* Ks = V + kv_each / sizeof(float);

@@ -30,7 +30,6 @@ constexpr int kRing = 3;
 struct QlaParams {
   const uint16_t* X;
   const int64_t* offsets;
-  const int* seg_user;
   const uint16_t* Wk;
   const uint16_t* Wv;
   float* partials;    // [slot][head][32][32] fp32
@@ -64,6 +63,64 @@ __device__ __forceinline__ constexpr int acc_row0(int i) { return 8 * (i / 4) + 
 template <int V>
 struct Int { static constexpr int value = V; };
 
+// The projection weights of head h as MFMA operands, key weights times c: element j of slice ks is
+// W[16 ks + 8 hf + j][32 h + l32].  16-byte aligned weights are read as rows, 16 bytes a lane, and turned
+// by the matrix core (a 32 x 32 block times a 0/1 selector lands in accumulator layout; the lane picks
+// its row so that registers 0..7 and 8..15 are two operands): all loads in flight at once, where
+// 2-byte loads, a slice at a time, held the first tile up by several microseconds.
+template <int D>
+__device__ __forceinline__ void load_weights(const uint16_t* Wk, const uint16_t* Wv, int h, float c,
+                                             bf16x8 (&wk)[D / 16], bf16x8 (&wv)[D / 16]) {
+  constexpr int KS = D / 16;
+  const int lane = threadIdx.x & 63, hf = lane >> 5, l32 = lane & 31;
+  if (((reinterpret_cast<uintptr_t>(Wk) | reinterpret_cast<uintptr_t>(Wv)) & 15) == 0) {
+    const int row = (l32 & 16) | ((l32 & 4) << 1) | ((l32 & 8) >> 1) | (l32 & 3);
+    const int at = row * D + 32 * h + 8 * hf;
+    Pack8 sel[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) sel[q].h[j] = (l32 == 16 * q + 8 * hf + j) ? 0x3F80 : 0;
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {                  // the keys' matrix, then the values'
+      Pack8 raw[KS / 2][2];
+#pragma unroll
+      for (int b = 0; b < KS / 2; ++b)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) raw[b][q].u = *reinterpret_cast<const uint4*>((m ? Wv : Wk) + at + 32 * b * D + 16 * q);
+      const float f = m ? 1.f : c;
+#pragma unroll
+      for (int b = 0; b < KS / 2; ++b) {
+        f32x16 t = {0};
+        t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(raw[b][0].v, sel[0].v, t, 0, 0, 0);
+        t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(raw[b][1].v, sel[1].v, t, 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          Pack8 w;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) w.w[j] = cvt_pk_bf16(t[8 * q + 2 * j] * f, t[8 * q + 2 * j + 1] * f);
+          if (m) wv[2 * b + q] = w.v; else wk[2 * b + q] = w.v;
+        }
+      }
+      if (D > 128) __builtin_amdgcn_sched_barrier(0);      // one matrix in flight at a time: registers
+    }
+  } else {
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      Pack8 a, b;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int64_t at = int64_t(16 * ks + 8 * hf + j) * D + 32 * h + l32;
+        a.h[j] = f32_to_bf16_bits(__uint_as_float(uint32_t(Wk[at]) << 16) * c);
+        b.h[j] = Wv[at];
+      }
+      wk[ks] = a.v;
+      wv[ks] = b.v;
+      __builtin_amdgcn_sched_barrier(0);     // one slice's loads at a time: they all land in registers of their own
+    }
+  }
+}
+
 // D = model width, one wave per head (D / 32 waves).
 template <int D>
 __global__ __launch_bounds__(D * 2, 2) void qla_state_mfma_kernel(QlaParams p) {
@@ -90,19 +147,7 @@ __global__ __launch_bounds__(D * 2, 2) void qla_state_mfma_kernel(QlaParams p) {
   // The key weights carry -log2(e): the projection then yields t = -k log2(e) and
   // SiLU(k) = -ln(2) t / (1 + 2^t); the constant is applied once, to the record.
   bf16x8 wk[KS], wv[KS];
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    Pack8 a, b;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int64_t at = int64_t(16 * ks + 8 * hf + j) * D + 32 * h + l32;
-      a.h[j] = f32_to_bf16_bits(__uint_as_float(uint32_t(p.Wk[at]) << 16) * -kLog2e);
-      b.h[j] = p.Wv[at];
-    }
-    wk[ks] = a.v;
-    wv[ks] = b.v;
-    __builtin_amdgcn_sched_barrier(0);     // one slice's loads at a time: they all land in registers of their own
-  }
+  load_weights<D>(p.Wk, p.Wv, h, -kLog2e, wk, wv);
 
   // A workgroup keeps its weights and takes segments blockIdx.x, blockIdx.x + gridDim.x, ...
   // (records are indexed by segment, so the result does not depend on the grid).
@@ -110,15 +155,13 @@ __global__ __launch_bounds__(D * 2, 2) void qla_state_mfma_kernel(QlaParams p) {
   const int64_t seg_begin = g * p.seg;
   const int64_t seg_end = (seg_begin + p.seg < p.N) ? seg_begin + p.seg : p.N;
   TileCursor ca, cf;
-  ca.init(p.offsets, p.B, p.seg_user ? __builtin_amdgcn_readfirstlane(p.seg_user[g]) : find_user(p.offsets, p.B, seg_begin),
+  ca.init(p.offsets, p.B, find_user_wave(p.offsets, p.B, seg_begin),
           seg_begin, seg_end);
   if (!ca.valid) continue;               // only with invalid offsets (whole workgroup)
   cf = ca;
 
   const int wave = h;
-  auto fetch = [&](const TileCursor& c, int xb) __attribute__((always_inline)) {
-    const int last = c.rows() - 1;                        // last valid row of the tile
-    const char* base = reinterpret_cast<const char*>(p.X) + c.row * (D * 2);
+  auto fetch_rows = [&](const char* base, int last, int xb) __attribute__((always_inline)) {     // last: last valid row
 #pragma unroll
     for (int k = 0; k < CPT; ++k) {
       const int slot = k * NT + tid;                      // LDS slot = item * CH + position
@@ -138,6 +181,9 @@ __global__ __launch_bounds__(D * 2, 2) void qla_state_mfma_kernel(QlaParams p) {
     __builtin_amdgcn_s_waitcnt((n & 0xF) | ((n >> 4) << 14) | 0x0F70);
   };
   static_assert(2 * CPT < 64, "vmcnt holds six bits");
+  auto fetch = [&](const TileCursor& c, int xb) __attribute__((always_inline)) {
+    fetch_rows(reinterpret_cast<const char*>(p.X) + c.row * (D * 2), c.rows() - 1, xb);
+  };
 
   f32x16 z = {0};
   auto write_record = [&](int user) __attribute__((always_inline)) {
@@ -160,9 +206,8 @@ __global__ __launch_bounds__(D * 2, 2) void qla_state_mfma_kernel(QlaParams p) {
 
   int xb = 0;
   bool drain = false;
-  for (;;) {
-    const bool last_in_piece = ca.tiles_left == 1;
-    const int nvl = (last_in_piece ? ca.tail : kTile) - 4 * hf;   // register i is valid iff acc_row0(i) < nvl
+  // Z += SiLU(K)^T V of the tile in slot xb
+  auto tile = [&](bool masked) __attribute__((always_inline)) {
     // K first, turned into the A operand right away, then V: one projection accumulator is
     // live at a time (at D = 256 the weights alone take half of the register file).
     Pack8 a0, a1, b0, b1;
@@ -199,9 +244,9 @@ __global__ __launch_bounds__(D * 2, 2) void qla_state_mfma_kernel(QlaParams p) {
         if (i < 8) b0.w[i / 2] = pb; else b1.w[(i - 8) / 2] = pb;
       }
     }
-    if (last_in_piece) {
-      // Rows past the piece's end count for nothing: their SiLU(k) is cleared.  One wave-uniform
-      // branch per tile, taken once per piece, instead of a select per value on every tile.
+    if (masked) {
+      // Rows past the piece's end count for nothing: their SiLU(k) is cleared.
+      const int nvl = ca.tail - 4 * hf;             // register i is valid iff acc_row0(i) < nvl
 #pragma unroll
       for (int i = 0; i < 16; i += 2) {
         const uint32_t keep = (acc_row0(i) < nvl ? 0x0000FFFFu : 0u) | (acc_row0(i + 1) < nvl ? 0xFFFF0000u : 0u);
@@ -210,6 +255,27 @@ __global__ __launch_bounds__(D * 2, 2) void qla_state_mfma_kernel(QlaParams p) {
     }
     z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0.v, b0.v, z, 0, 0, 0);
     z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1.v, b1.v, z, 0, 0, 0);
+  };
+
+  for (;;) {
+    // Tiles while the tile being requested is a full one of the same piece: no cursor in the loop (its
+    // branches and state moves took 490 clocks of a wave's 2330 per tile; with three waves on a SIMD most of
+    // that was hidden, 72.4 -> 71.5 us over the jagged batch).
+    const int run = cf.straight(ca);
+    const char* base = reinterpret_cast<const char*>(p.X) + cf.row * (D * 2);
+    for (int n = 0; n < run; ++n) {
+      tile(false);
+      if (drain) wait_vm(Int<0>{}); else wait_vm(Int<CPT>{});
+      drain = false;
+      lds_barrier();
+      fetch_rows(base, kTile - 1, xb);
+      base += kTile * D * 2;
+      xb = xb == kRing - 1 ? 0 : xb + 1;
+    }
+    ca.skip(run);
+    cf.skip(run);
+    const bool last_in_piece = ca.tiles_left == 1;
+    tile(last_in_piece);
 
     // tile t+1 has landed (this wave's part); everyone is done with tile t's rows
     if (drain) wait_vm(Int<0>{}); else wait_vm(Int<CPT>{});
@@ -261,19 +327,7 @@ __global__ __launch_bounds__(D * 2, 2) void qla_bwd_items_mfma_kernel(QlaParams 
   const int h = __builtin_amdgcn_readfirstlane(tid >> 6);
 
   bf16x8 wk[KS], wv[KS];
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    Pack8 a, b;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int64_t at = int64_t(16 * ks + 8 * hf + j) * D + 32 * h + l32;
-      a.h[j] = f32_to_bf16_bits(__uint_as_float(uint32_t(p.Wk[at]) << 16) * -kLog2e);   // t = -k log2(e)
-      b.h[j] = p.Wv[at];
-    }
-    wk[ks] = a.v;
-    wv[ks] = b.v;
-    __builtin_amdgcn_sched_barrier(0);
-  }
+  load_weights<D>(p.Wk, p.Wv, h, -kLog2e, wk, wv);      // t = -k log2(e)
 
   const int wave = h;
   auto fetch = [&](const TileCursor& c, int xb) __attribute__((always_inline)) {
@@ -321,7 +375,7 @@ __global__ __launch_bounds__(D * 2, 2) void qla_bwd_items_mfma_kernel(QlaParams 
     const int64_t seg_begin = g * p.seg;
     const int64_t seg_end = (seg_begin + p.seg < p.N) ? seg_begin + p.seg : p.N;
     TileCursor ca, cf;
-    ca.init(p.offsets, p.B, p.seg_user ? __builtin_amdgcn_readfirstlane(p.seg_user[g]) : find_user(p.offsets, p.B, seg_begin),
+    ca.init(p.offsets, p.B, find_user_wave(p.offsets, p.B, seg_begin),
             seg_begin, seg_end);
     if (!ca.valid) continue;
     cf = ca;
@@ -441,13 +495,32 @@ bool mfma_qla_supported(const vista_summarize_desc& d) {
   return d.dtype == VISTA_BF16 && d.attn == VISTA_ATTN_QLA && ((d.d == 128 && d.H == 4) || (d.d == 256 && d.H == 8));
 }
 
+// Resident workgroups of the two streaming kernels: three a compute unit (state) and two (items) at
+// D = 128, one at D = 256.
+static int64_t state_workgroups(int d) { return d == 128 ? 768 : 256; }
+static int64_t items_workgroups(int d) { return d == 128 ? 512 : 256; }
+
+// The history in equal segments, one for each of `workgroups` or a small multiple of them: a multiple of 32,
+// 128 to `most` items.  At D = 256 a workgroup's set-up is long enough that four segments apiece, or
+// one more than others, showed: 300 000 items 107.8 us with 1024 segments, 91.2 with 256, their
+// gradients (200 000 items) 230 and 179 us; at D = 128 (1024 against 768) within 2 %.
+static int even_segment(int64_t N, int64_t workgroups, int64_t most) {
+  int64_t k = (N + workgroups * most - 1) / (workgroups * most);
+  if (k < 1) k = 1;
+  int64_t s = (N + workgroups * k - 1) / (workgroups * k);
+  s = (s + 31) / 32 * 32;
+  return int(s < 128 ? 128 : s);
+}
+
+// Segment size of the state pass where the caller leaves it open.
+int mfma_qla_segment(const vista_summarize_desc& d) { return even_segment(d.total_items, state_workgroups(d.d), 8192); }
+
 // Streams the history into the state records (slot = segment + user, row-major 32 x 32 fp32).
 vista_status mfma_qla_state(const SummarizeArgs& a, float* partials) {
   const vista_summarize_desc& d = a.desc;
   QlaParams p;
   p.X = static_cast<const uint16_t*>(a.X);
   p.offsets = a.offsets;
-  p.seg_user = a.seg_user;
   p.Wk = static_cast<const uint16_t*>(a.Wk);
   p.Wv = static_cast<const uint16_t*>(a.Wv);
   p.partials = partials;
@@ -455,8 +528,8 @@ vista_status mfma_qla_state(const SummarizeArgs& a, float* partials) {
   p.H = d.H;
   p.N = d.total_items;
   p.seg = a.seg;
-  // three resident workgroups per compute unit at D = 128 (one at D = 256), each walking its share of the segments
-  const int64_t resident = d.d == 128 ? 768 : 256;
+  // persistent workgroups, each walking its share of the segments
+  const int64_t resident = state_workgroups(d.d);
   const unsigned blocks = unsigned(a.G < resident ? a.G : resident);
   if (d.d == 128)
     VISTA_LAUNCH(qla_state_mfma_kernel<128>, dim3(blocks), dim3(256), 0, a.stream, p);
@@ -470,16 +543,17 @@ vista_status mfma_qla_backward_items(const SummarizeArgs& a, const float* dz, vo
   QlaParams p;
   p.X = static_cast<const uint16_t*>(a.X);
   p.offsets = a.offsets;
-  p.seg_user = a.seg_user;
   p.Wk = static_cast<const uint16_t*>(a.Wk);
   p.Wv = static_cast<const uint16_t*>(a.Wv);
   p.partials = nullptr;
   p.B = d.B;
   p.H = d.H;
   p.N = d.total_items;
-  p.seg = a.seg;
-  const int64_t resident = d.d == 128 ? 512 : 256;
-  const unsigned blocks = unsigned(a.G < resident ? a.G : resident);
+  // nothing is recorded per segment here: they are this kernel's own
+  const int64_t resident = items_workgroups(d.d);
+  p.seg = even_segment(d.total_items, resident, 1 << 20);
+  const int64_t G = (d.total_items + p.seg - 1) / p.seg;
+  const unsigned blocks = unsigned(G < resident ? G : resident);
   if (d.d == 128)
     VISTA_LAUNCH(qla_bwd_items_mfma_kernel<128>, dim3(blocks), dim3(256), 0, a.stream, p, dz,
                  static_cast<uint16_t*>(d_keys), static_cast<uint16_t*>(d_values));

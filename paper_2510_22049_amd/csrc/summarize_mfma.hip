@@ -395,10 +395,8 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
   // buffer tile t has vacated and must have landed by the end of tile t+1, so a
   // load has two tile periods.  Rows past the piece are clamped to its last row.
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  auto fetch = [&](const Cursor& c, int xb) __attribute__((always_inline)) {
+  auto fetch_rows = [&](const char* base, int last, int xb) __attribute__((always_inline)) {   // last: last valid row
     if (!ALLF && wave >= FW) return;
-    const int last = (c.tiles_left == 1 ? c.tail : kTile) - 1;   // last valid row of the tile
-    const char* base = reinterpret_cast<const char*>(p.X) + c.row * (D * 2);
 #pragma unroll
     for (int k = 0; k < CPT; ++k) {
       const int slot = k * NT + tid;                         // LDS slot = chunk * 32 + item
@@ -414,6 +412,9 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
                    : "s"(lds_base), "v"(voff), "s"(base)
                    : "memory", "m0");
     }
+  };
+  auto fetch = [&](const Cursor& c, int xb) __attribute__((always_inline)) {
+    fetch_rows(reinterpret_cast<const char*>(p.X) + c.row * (D * 2), c.rows() - 1, xb);
   };
   // k-slices [ks0, ks1) of this wave's projection of the X tile in xbuf[buf]
   auto project = [&](int buf, int ks0, int ks1, f32x16& acc) __attribute__((always_inline)) {
@@ -673,6 +674,30 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
   };
   bool plain = is_plain();
   for (;;) {
+    // Plain tiles while the tile being requested is a full one of the same piece: no cursor in the loop.  Its
+    // branches and state moves, on every wave between two barriers, were 2 to 4 % of the time: 8 users of
+    // a million items 1616 -> 1551 us, two layers at d = 256 23.9 -> 22.8 ms, jagged batch 175 -> 172.
+    if (plain) {
+      const int run = cf.straight(ca);
+      const char* base = reinterpret_cast<const char*>(p.X) + cf.row * (D * 2);
+      int n = 0;
+      while (n < run && plain) {
+        lds_barrier();
+        fetch_rows(base, kTile - 1, r == kXBuf - 1 ? 0 : r + 1);
+        base += kTile * D * 2;
+        mode = 1;
+        fast_tile(r);
+        if (drain) wait_vm(Int<0>{}); else wait_vm(Int<CPT>{});
+        drain = false;
+        ++n;
+        r = r == kXBuf - 1 ? 0 : r + 1;
+        unsafe = unsafe_tile(kn2);
+        plain = !unsafe;
+      }
+      ca.skip(n);
+      cf.skip(n);
+      plain = is_plain();
+    }
     while (__builtin_expect(plain, 1)) {
       begin_tile();
       mode = 1;

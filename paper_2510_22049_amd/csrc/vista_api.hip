@@ -68,6 +68,13 @@ Work base_work(const vista_summarize_desc& d) {
 // that the static entry point and the one with a workspace always do the same.
 Work best_work(const vista_summarize_desc& d) {
   const Work base = base_work(d);
+  if (mfma_qla_supported(d) && d.segment_items == 0) {     // the plain family's layout, the state pass's own segments
+    const int32_t seg = mfma_qla_segment(d);
+    const size_t need = generic_summarize_workspace(d, seg);
+    if (need <= (base.need > size_t(VISTA_STATIC_SCRATCH_BYTES) ? base.need : size_t(VISTA_STATIC_SCRATCH_BYTES)))
+      return {Route::kGeneric, seg, need};
+    return base;
+  }
   const Route route = base.route == Route::kMfma  ? Route::kMfma
                       : mfma_split_supported(d)   ? Route::kSplit
                       : f32_history_supported(d)  ? Route::kF32
@@ -218,8 +225,7 @@ static vista_status summarize_impl(const vista_summarize_desc* desc, const void*
   // the offsets (unless that was done above) and writes the status word: no plan kernel
   if (w.route == Route::kF32) return f32_summarize(a);
   if (w.route != Route::kGeneric) return mfma_summarize(a);
-  // likewise; the finishing kernel clears the status word
-  if (offsets_host && mfma_qla_supported(*desc)) return generic_summarize(a);
+  if (mfma_qla_supported(*desc)) return generic_summarize(a);      // likewise; the finishing kernel checks them
   int* seg_user = reinterpret_cast<int*>(a.workspace + kHeaderBytes);
   a.seg_user = seg_user;
   if (launch_plan(offsets, desc->B, desc->total_items, a.seg, a.G, reinterpret_cast<int*>(workspace), seg_user,
@@ -256,7 +262,9 @@ vista_status vista_quantize_summaries(const vista_codec_desc* desc, const void* 
 
 size_t vista_qla_backward_workspace_bytes(const vista_summarize_desc* desc) {
   if (check_summarize_desc(desc) != VISTA_OK || desc->attn != VISTA_ATTN_QLA) return 0;
-  return qla_backward_workspace(*desc, resolve_segment(desc));
+  const size_t base = qla_backward_workspace(*desc, resolve_segment(desc));
+  const size_t best = qla_backward_workspace(*desc, best_work(*desc).seg);
+  return best > base ? best : base;
 }
 
 vista_status vista_qla_backward(const vista_summarize_desc* desc, const void* history_emb, const int64_t* offsets,
@@ -275,12 +283,16 @@ vista_status vista_qla_backward(const vista_summarize_desc* desc, const void* hi
     for (int b = 0; b < desc->B; ++b)
       if (offsets_host[b + 1] < offsets_host[b]) return VISTA_ERR_OFFSETS;
   }
-  const size_t need = vista_qla_backward_workspace_bytes(desc);
-  if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0 || workspace_bytes < need)
+  // a workspace that holds the base schedule only gets the base schedule
+  int32_t seg = best_work(*desc).seg;
+  const int32_t base_seg = resolve_segment(desc);
+  if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0 ||
+      workspace_bytes < qla_backward_workspace(*desc, base_seg))
     return VISTA_ERR_WORKSPACE;
+  if (workspace_bytes < qla_backward_workspace(*desc, seg)) seg = base_seg;
   SummarizeArgs a;
   a.desc = *desc;
-  a.seg = resolve_segment(desc);
+  a.seg = seg;
   a.G = (desc->total_items + a.seg - 1) / a.seg;
   if (a.G + desc->B > 0x7FFFFFFF) return VISTA_ERR_UNSUPPORTED;
   a.offsets_checked = offsets_host != nullptr;
@@ -295,9 +307,9 @@ vista_status vista_qla_backward(const vista_summarize_desc* desc, const void* hi
   a.out_scales = nullptr;
   a.workspace = static_cast<char*>(workspace);
   a.stream = static_cast<hipStream_t>(hip_stream);
-  if (offsets_host && mfma_qla_supported(*desc)) {
-    // offsets already checked on the host: the streaming kernels find each segment's first user
-    // themselves and the state-gradient kernel clears the status word
+  if (mfma_qla_supported(*desc)) {
+    // the streaming kernels find each segment's first user themselves and the state-gradient kernel
+    // checks the offsets (unless the host has) and writes the status word
     a.seg_user = nullptr;
     return qla_backward(a, d_out, d_queries, d_keys, d_values, d_self_keys, d_self_values);
   }
