@@ -475,6 +475,67 @@ __device__ __forceinline__ float silu_prime_f(float x) {
   return sg * (1.f + x * (1.f - sg));
 }
 
+__device__ __forceinline__ void load4(const float* p, float v[4]) {
+  const float4 t = *reinterpret_cast<const float4*>(p);
+  v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+}
+__device__ __forceinline__ void load4(const bf16_t* p, float v[4]) {
+  const uint2 t = *reinterpret_cast<const uint2*>(p);
+  v[0] = __uint_as_float(t.x << 16); v[1] = __uint_as_float(t.x & 0xFFFF0000u);
+  v[2] = __uint_as_float(t.y << 16); v[3] = __uint_as_float(t.y & 0xFFFF0000u);
+}
+__device__ __forceinline__ void store4(float* p, const float v[4]) {
+  *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+}
+__device__ __forceinline__ void store4(bf16_t* p, const float v[4]) {
+  uint2 t;
+  t.x = uint32_t(f32_to_bf16_bits(v[0])) | (uint32_t(f32_to_bf16_bits(v[1])) << 16);
+  t.y = uint32_t(f32_to_bf16_bits(v[2])) | (uint32_t(f32_to_bf16_bits(v[3])) << 16);
+  *reinterpret_cast<uint2*>(p) = t;
+}
+
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+constexpr int kRow32 = 36;       // floats between rows of a 32 x 32 array in LDS: 16-byte aligned, four rows are 16 banks apart
+
+// Sum of a user's 32 x 32 records into z (rows kRow32 apart), 1024 threads, in the order of
+// qla_finish_kernel: four groups of 256 threads take every fourth record each, ascending, eight 16-byte
+// loads in flight, and the sub-sums are added as ((s0 + s1) + s2) + s3.  Ends with a barrier.
+__device__ __forceinline__ void sum_records32(const float* __restrict__ partials, int64_t begin, int64_t end, int seg,
+                                              int64_t G, int b, int h, int H, float* z) {
+  constexpr int kDeep = 8;
+  int64_t g0 = begin / seg, g1 = (end - 1) / seg;
+  if (g0 < 0) g0 = 0;
+  if (g1 > G - 1) g1 = G - 1;
+  const int grp = threadIdx.x >> 8, e = 4 * (threadIdx.x & 255);
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int64_t g = g0 + grp; g <= g1; g += 4 * kDeep) {
+    float4 v[kDeep];
+#pragma unroll
+    for (int u = 0; u < kDeep; ++u)
+      v[u] = g + 4 * u <= g1 ? *reinterpret_cast<const float4*>(partials + ((g + 4 * u + b) * H + h) * 1024 + e)
+                             : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int u = 0; u < kDeep; ++u) {
+      acc.x += v[u].x;
+      acc.y += v[u].y;
+      acc.z += v[u].z;
+      acc.w += v[u].w;
+    }
+  }
+  float4* dst = reinterpret_cast<float4*>(z + e / 32 * kRow32 + e % 32);
+  for (int turn = 0; turn < 4; ++turn) {
+    if (grp == turn) {
+      if (turn > 0) {
+        const float4 t = *dst;
+        acc = make_float4(t.x + acc.x, t.y + acc.y, t.z + acc.z, t.w + acc.w);
+      }
+      *dst = acc;
+    }
+    __syncthreads();
+  }
+}
+
+
 // Per (user, head): the state Zs (fixed-order sum of the user's records), G = SiLU(Zs),
 //   dQ = (dO G^T) * SiLU'(Q)         written to d_queries,
 //   dZs = (SiLU(Q)^T dO) * SiLU'(Zs) written to dz [B][H][dh][dh] fp32 for the item pass.
@@ -595,154 +656,111 @@ __global__ __launch_bounds__(1024) void qla_bwd_state_kernel(const float* __rest
   }
 }
 
-// The same for heads of width 32 (the matrix-core shapes), with the LDS traffic cut by register
-// blocking: a thread owns four neighbouring key channels, so one 16-byte and one 4-byte LDS
-// read feed four multiply-adds.  1024 threads; queries pass through LDS in runs of 256 (rows
-// 36 floats apart: 16-byte aligned, spread over the banks).
-//   dG:  thread (quarter g, key channels 4 ab .. 4 ab + 3, value channel c) sums over the
-//        run's rows 64 g .. 64 g + 63; the four quarters are added at the end as ((s0+s1)+s2)+s3;
-//   dQ:  thread (row, key channels 4 ab .. 4 ab + 3), two rows per thread and run.
-__device__ __forceinline__ void load4(const float* p, float v[4]) {
-  const float4 t = *reinterpret_cast<const float4*>(p);
-  v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
-}
-__device__ __forceinline__ void load4(const bf16_t* p, float v[4]) {
-  const uint2 t = *reinterpret_cast<const uint2*>(p);
-  v[0] = __uint_as_float(t.x << 16); v[1] = __uint_as_float(t.x & 0xFFFF0000u);
-  v[2] = __uint_as_float(t.y << 16); v[3] = __uint_as_float(t.y & 0xFFFF0000u);
-}
-__device__ __forceinline__ void store4(float* p, const float v[4]) {
-  *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
-}
-__device__ __forceinline__ void store4(bf16_t* p, const float v[4]) {
-  uint2 t;
-  t.x = uint32_t(f32_to_bf16_bits(v[0])) | (uint32_t(f32_to_bf16_bits(v[1])) << 16);
-  t.y = uint32_t(f32_to_bf16_bits(v[2])) | (uint32_t(f32_to_bf16_bits(v[3])) << 16);
-  *reinterpret_cast<uint2*>(p) = t;
-}
-
+// The same for heads of width 32 (the matrix-core shapes) on the fp32 matrix instructions
+// (v_mfma_f32_16x16x4_f32, layout as in plain_mfma.hip); 1024 threads, S <= 512.  A wave owns 16 queries,
+// requested before the records are waited for: dQ^T = G dO^T straight from registers (a lane's four steps
+// are four neighbouring channels, and four neighbouring channels of a query come out in a lane); for
+// dG = SiLU(Q)^T dO the queries are the contraction, so the wave's rows pass through its own LDS patch,
+// and the sixteen waves' sums are added in ascending order at the end.  (From LDS, one 16-byte and one
+// 4-byte read to four multiply-adds, this took 21.8 us of the jagged batch's gradients; now 14.8.)
 template <typename T>
 __global__ __launch_bounds__(1024) void qla_bwd_state32_kernel(const float* __restrict__ partials,
                                                                const int64_t* __restrict__ offsets, int S, int d, int H,
                                                                int seg, int64_t G, const T* __restrict__ Q,
                                                                int64_t q_user_stride, const T* __restrict__ dO,
-                                                               T* __restrict__ dQ, float* __restrict__ dz, int B, int64_t N, int* status) {
-  constexpr int dh = 32, zz = dh * dh, kRun = 256, kRow = 36;
+                                                               T* __restrict__ dQ, float* __restrict__ dz, int B, int64_t N,
+                                                               int* status) {
   if (status && blockIdx.x == 0 && blockIdx.y == 0) publish_status(offsets, B, N, status);
-  __shared__ __align__(16) float zs[zz];                 // Zs, then SiLU'(Zs)
-  __shared__ __align__(16) float gt[dh * kRow];          // G transposed: gt[c][a]
-  __shared__ __align__(16) float qa[kRun * kRow];        // SiLU(q) of the run; at the end the partial dG of the four quarters
-  __shared__ __align__(16) float dy[kRun * kRow];        // dO of the run
-  const int b = blockIdx.x, h = blockIdx.y;
-  const int tid = threadIdx.x;
+  __shared__ __align__(16) float zs[32 * kRow32];        // Zs, then G = SiLU(Zs)
+  __shared__ __align__(16) float patch[16][2 * 16 * kRow32];   // per wave: SiLU(q), dO of its 16 queries; at the end its dG
+  const int b = blockIdx.x, h = blockIdx.y, tid = threadIdx.x;
+  const int lane = tid & 63, w = tid >> 6, g = lane >> 4, c = lane & 15;
   const int64_t begin = offsets[b], end = offsets[b + 1];
-  float* dzb = dz + (int64_t(b) * H + h) * zz;
-  T* dq = dQ + int64_t(b) * S * d + h * dh;
+  float* dzb = dz + (int64_t(b) * H + h) * 1024;
+  T* dq = dQ + int64_t(b) * S * d + h * 32;
   if (end <= begin) {       // no history: the forward output is zero whatever Q is
-    for (int e = tid; e < S * dh; e += 1024) store_as(dq + int64_t(e / dh) * d + (e % dh), 0.f);
+    for (int e = tid; e < S * 32; e += 1024) store_as(dq + int64_t(e / 32) * d + (e % 32), 0.f);
     dzb[tid] = 0.f;
     return;
   }
-  int64_t g0 = begin / seg, g1 = (end - 1) / seg;
-  if (g0 < 0) g0 = 0;
-  if (g1 > G - 1) g1 = G - 1;
-  const int grp = tid >> 8, t256 = tid & 255;
-  {   // the user's records in the finishing kernel's order
-    const int e = 4 * t256;
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int64_t g = g0 + grp; g <= g1; g += 32) {
-      float4 v[8];
+  // this wave's queries and their output gradients, requested before the records are waited for
+  const T* Qb = Q + q_user_stride * b + h * 32 + 4 * g;
+  const T* Db = dO + int64_t(b) * S * d + h * 32 + 4 * g;
+  float q[2][2][4], y[2][2][4];
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
-        v[u] = g + 4 * u <= g1 ? *reinterpret_cast<const float4*>(partials + ((g + 4 * u + b) * H + h) * zz + e)
-                               : make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int u = 0; u < 2; ++u)
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        acc.x += v[u].x;
-        acc.y += v[u].y;
-        acc.z += v[u].z;
-        acc.w += v[u].w;
+    for (int a = 0; a < 2; ++a) {
+      const int i = 16 * (w + 16 * u) + c;
+      if (i < S) {
+        load4(Qb + int64_t(i) * d + 16 * a, q[u][a]);
+        load4(Db + int64_t(i) * d + 16 * a, y[u][a]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) q[u][a][e] = y[u][a][e] = 0.f;
       }
     }
-    for (int turn = 0; turn < 4; ++turn) {
-      if (grp == turn) {
-        if (turn == 0) {
-          zs[e] = acc.x; zs[e + 1] = acc.y; zs[e + 2] = acc.z; zs[e + 3] = acc.w;
-        } else {
-          zs[e] += acc.x; zs[e + 1] += acc.y; zs[e + 2] += acc.z; zs[e + 3] += acc.w;
-        }
-      }
-      __syncthreads();
-    }
-  }
-  {
-    const float acc = zs[tid];             // entry (a, c) = (tid / 32, tid % 32)
-    zs[tid] = silu_prime_f(acc);
-    gt[(tid & 31) * kRow + (tid >> 5)] = silu_f(acc);
-  }
-  const int ab = t256 >> 5, c = t256 & 31;          // dG: key channels 4 ab .., value channel c
-  float dg[4] = {0.f, 0.f, 0.f, 0.f};
-  const T* Qb = Q + q_user_stride * b + h * dh;
-  const T* Db = dO + int64_t(b) * S * d + h * dh;
-  for (int i0 = 0; i0 < S; i0 += kRun) {
-    __syncthreads();
-    // eight elements of either array per thread, all loads issued before the first is used
-    {
-      float qv[8], yv[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int e = tid + 1024 * j, r = e >> 5, a = e & 31;
-        const bool on = i0 + r < S;
-        qv[j] = on ? to_f32(Qb[int64_t(i0 + r) * d + a]) : 0.f;
-        yv[j] = on ? to_f32(Db[int64_t(i0 + r) * d + a]) : 0.f;
-      }
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int e = tid + 1024 * j, r = e >> 5, a = e & 31;
-        qa[r * kRow + a] = silu_f(qv[j]);
-        dy[r * kRow + a] = yv[j];
-      }
-    }
-    __syncthreads();
-    // dG += SiLU(Q)^T dO over this quarter's 64 rows
-#pragma unroll 4
-    for (int r = 64 * grp; r < 64 * grp + 64; ++r) {
-      const float4 q4 = *reinterpret_cast<const float4*>(&qa[r * kRow + 4 * ab]);
-      const float y = dy[r * kRow + c];
-      dg[0] = fmaf(q4.x, y, dg[0]);
-      dg[1] = fmaf(q4.y, y, dg[1]);
-      dg[2] = fmaf(q4.z, y, dg[2]);
-      dg[3] = fmaf(q4.w, y, dg[3]);
-    }
-    // dQ = (dO G^T) * SiLU'(Q): rows tid / 8 and tid / 8 + 128, key channels 4 (tid % 8) ..
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int r = (tid >> 3) + 128 * j, a4 = 4 * (tid & 7);
-      if (i0 + r < S) {
-        float o[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-        for (int cc = 0; cc < dh; ++cc) {
-          const float y = dy[r * kRow + cc];
-          const float4 g4 = *reinterpret_cast<const float4*>(&gt[cc * kRow + a4]);
-          o[0] = fmaf(y, g4.x, o[0]);
-          o[1] = fmaf(y, g4.y, o[1]);
-          o[2] = fmaf(y, g4.z, o[2]);
-          o[3] = fmaf(y, g4.w, o[3]);
-        }
-        float q[4];
-        load4(Qb + int64_t(i0 + r) * d + a4, q);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) o[k] *= silu_prime_f(q[k]);
-        store4(dq + int64_t(i0 + r) * d + a4, o);
-      }
-    }
-  }
-  // the four quarters' partial dG, added in a fixed order, times SiLU'(Zs)
+  sum_records32(partials, begin, end, seg, G, b, h, H, zs);
+  const float zraw = zs[tid / 32 * kRow32 + tid % 32];
   __syncthreads();
-#pragma unroll
-  for (int k = 0; k < 4; ++k) qa[grp * zz + (4 * ab + k) * dh + c] = dg[k];
+  zs[tid / 32 * kRow32 + tid % 32] = silu_f(zraw);
   __syncthreads();
-  dzb[tid] = (((qa[tid] + qa[zz + tid]) + qa[2 * zz + tid]) + qa[3 * zz + tid]) * zs[tid];
+  f32x4 dg[2][2];
+#pragma unroll
+  for (int n = 0; n < 2; ++n)
+#pragma unroll
+    for (int m = 0; m < 2; ++m) dg[n][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float* qa = patch[w];
+  float* dy = patch[w] + 16 * kRow32;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    if (16 * (w + 16 * u) >= S) break;                   // (wave-uniform)
+    const int i = 16 * (w + 16 * u) + c;
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+      *reinterpret_cast<float4*>(qa + c * kRow32 + 16 * a + 4 * g) =
+          make_float4(silu_f(q[u][a][0]), silu_f(q[u][a][1]), silu_f(q[u][a][2]), silu_f(q[u][a][3]));
+      *reinterpret_cast<float4*>(dy + c * kRow32 + 16 * a + 4 * g) = make_float4(y[u][a][0], y[u][a][1], y[u][a][2], y[u][a][3]);
+    }
+    // (the patch is the wave's own: program order is enough)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {                        // step r takes queries 4 g + r
+      const float* qr = qa + (4 * g + r) * kRow32 + c;
+      const float* yr = dy + (4 * g + r) * kRow32 + c;
+#pragma unroll
+      for (int n = 0; n < 2; ++n)
+#pragma unroll
+        for (int m = 0; m < 2; ++m) dg[n][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(qr[16 * n], yr[16 * m], dg[n][m], 0, 0, 0);
+    }
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        const float4 gz = *reinterpret_cast<const float4*>(zs + (16 * n + c) * kRow32 + 16 * a + 4 * g);
+        const float ga[4] = {gz.x, gz.y, gz.z, gz.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o = __builtin_amdgcn_mfma_f32_16x16x4f32(ga[e], y[u][a][e], o, 0, 0, 0);
+      }
+      if (i < S) {
+        float v[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = o[r] * silu_prime_f(q[u][n][r]);
+        store4(dq + int64_t(i) * d + 16 * n + 4 * g, v);
+      }
+    }
+  }
+#pragma unroll
+  for (int n = 0; n < 2; ++n)
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) patch[w][(16 * n + 4 * g + r) * 32 + 16 * m + c] = dg[n][m][r];
+  __syncthreads();
+  float sum = 0.f;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) sum += patch[k][tid];
+  dzb[tid] = sum * silu_prime_f(zraw);
 }
 
 // Gradients of the target-side diagonal term (phi(q_i) . phi(k'_i)) v'_i (App. B.1: second term of
@@ -896,14 +914,14 @@ static vista_status generic_summarize_t(const SummarizeArgs& a) {
                    d.q_user_stride, a.offsets, d.B, d.S, d.d, d.H, score_scale, N, a.seg, a.seg_user, partials);
   }
   T* out = static_cast<T*>(a.out);
+  int* status = a.seg_user ? nullptr : reinterpret_cast<int*>(a.workspace);
+  const int64_t check = a.offsets_checked ? -1 : d.total_items;
   if (qla && d.d / d.H == 32)
     VISTA_LAUNCH((qla_finish_kernel<T, 32>), dim3(d.B, d.H), dim3(1024), 0, a.stream, partials, a.offsets, d.S, d.d,
-                 d.H, a.seg, a.G, out, Q, d.q_user_stride, Ks, Vs, d.B, a.offsets_checked ? -1 : d.total_items,
-                 a.seg_user ? nullptr : reinterpret_cast<int*>(a.workspace));
+                 d.H, a.seg, a.G, out, Q, d.q_user_stride, Ks, Vs, d.B, check, status);
   else if (qla)
     VISTA_LAUNCH((qla_finish_kernel<T, 0>), dim3(d.B, d.H), dim3(1024), 0, a.stream, partials, a.offsets, d.S, d.d,
-                 d.H, a.seg, a.G, out, Q, d.q_user_stride, Ks, Vs, d.B, a.offsets_checked ? -1 : d.total_items,
-                 a.seg_user ? nullptr : reinterpret_cast<int*>(a.workspace));
+                 d.H, a.seg, a.G, out, Q, d.q_user_stride, Ks, Vs, d.B, check, status);
   else if (launch_merge<T>(a, partials, Ks, Vs, nullptr) != hipSuccess)
     return VISTA_ERR_HIP;
   return VISTA_OK;
