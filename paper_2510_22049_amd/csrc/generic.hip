@@ -223,8 +223,8 @@ __global__ __launch_bounds__(256) void merge_kernel(const float* __restrict__ pa
       const bool on = g + u <= r1;
       const float* p = partials + (((on ? g + u : r1) + b) * H + h) * int64_t(S) * (dh + 2) + int64_t(i) * (dh + 2);
       v[u][0] = on ? p[dh + 1] : -INFINITY;
-      v[u][1] = p[dh];
-      v[u][2] = on || !SILU ? p[t] : 0.f;
+      v[u][1] = on ? p[dh] : 0.f;
+      v[u][2] = on ? p[t] : 0.f;
     }
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {

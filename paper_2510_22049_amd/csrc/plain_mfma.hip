@@ -255,9 +255,14 @@ __global__ __launch_bounds__(256) void history_f32_kernel(HistoryParams p) {
         for (int t = 0; t < 4; ++t) {
           if (16 * t + 16 <= lo || 16 * t >= hi) continue;
 #pragma unroll
-          for (int r = 0; r < 4; ++r)
+          for (int r = 0; r < 4; ++r) {
+            // rows of other users in the tile are left out of the product, not only given weight 0: theirs
+            // may be infinite
+            const int i = 16 * t + 4 * g + r;
+            const bool mine = i >= lo && i < hi;
 #pragma unroll
-            for (int n = 0; n < DT; ++n) o[u][n] = mfma4(vs[(16 * t + 4 * g + r) * kRow + 16 * n + c], s[t][r], o[u][n]);
+            for (int n = 0; n < DT; ++n) o[u][n] = mfma4(mine ? vs[i * kRow + 16 * n + c] : 0.f, s[t][r], o[u][n]);
+          }
         }
       }
     }

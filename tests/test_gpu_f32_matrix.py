@@ -76,3 +76,26 @@ def test_element_aligned_pointers_keep_the_plain_path():
     check(host64(out), want, "f32")
     V.vista_target_attend(shifted(T), dev(want.astype(np.float32), "f32"), scored, H=H)
     check(host64(scored), O.target_attend(T, want.astype(np.float32), H), "f32")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("form", [V.VISTA_ATTN_SOFTMAX, V.VISTA_ATTN_SILU])
+def test_users_are_isolated(dtype, form):
+    """Infinite rows of one user leave the bits of the users that share its tiles unchanged."""
+    d, H, S = 64, 1, 20
+    r = draw(9, dtype)
+    off = I.offsets_from_lengths([40, 7, 90, 3, 200])
+    X, Q, Wk, Wv = r((off[-1], d)), r((S, d)), r((d, d), d ** -0.5), r((d, d), d ** -0.5)
+
+    def run():
+        out = torch.empty((5, S, d), device="cuda", dtype=torch_dtype(dtype))
+        V.vista_summarize(dev(X, dtype), torch.from_numpy(off).cuda(), dev(Q, dtype), dev(Wk, dtype), dev(Wv, dtype), out, H=H,
+                          attn=form)
+        return host64(out)
+
+    before = run()
+    X[off[1]:off[2]] = np.inf
+    X[off[3]:off[4], 5] = -np.inf
+    after = run()
+    for b in (0, 2, 4):
+        assert np.array_equal(before[b], after[b])

@@ -104,3 +104,15 @@ def test_offsets_are_checked_on_the_device(bad):
     ws = V.vista_summarize(z(100, d), torch.tensor(bad, device="cuda"), z(S, d), z(d, d), z(d, d), out, H=4)
     torch.cuda.synchronize()
     assert int(ws[:4].view(torch.int32).item()) == V.VISTA_ERR_OFFSETS
+
+
+def test_split_users_are_isolated():
+    """Infinite rows of one user leave the other users' bits unchanged."""
+    lens = [40, 7, 90, 3, 200]
+    X, off, Q, Wk, Wv = problem(9, 64, 40, lens=lens)
+    before = run(X, off, Q, Wk, Wv, 2)
+    X[off[1]:off[2]] = np.inf
+    X[off[3]:off[4], 5] = -np.inf
+    after = run(X, off, Q, Wk, Wv, 2)
+    for b in (0, 2, 4):
+        assert np.array_equal(before[b], after[b])
