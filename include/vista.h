@@ -106,9 +106,9 @@ typedef struct {
  * smallest count that keeps a segment at or below 8192 items -- 1024 k segments
  * of at most 2048 items for VISTA_ATTN_QLA, whose workgroups are small; at
  * least 256 items); 0 if the descriptor is invalid.  Where the size is left open
- * (segment_items = 0) the matrix-core path of the softmax and SiLU forms fits its
- * segments to the launch instead (multiples of 32 from 128 to 32768 items, a
- * function of the descriptor alone); a size that is given is always kept.
+ * (segment_items = 0) the matrix-core paths fit their segments to the launch instead
+ * (multiples of 32 up to 32768 items, a function of the descriptor alone); a size
+ * that is given is always kept.
  */
 int32_t vista_summarize_segment_items(const vista_summarize_desc* desc);
 

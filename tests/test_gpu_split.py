@@ -116,3 +116,20 @@ def test_split_users_are_isolated():
     after = run(X, off, Q, Wk, Wv, 2)
     for b in (0, 2, 4):
         assert np.array_equal(before[b], after[b])
+
+
+@pytest.mark.parametrize("form,d,H,S,n", [(V.VISTA_ATTN_SOFTMAX, 128, 4, 256, 7001), (V.VISTA_ATTN_SILU, 256, 8, 128, 3000),
+                                          (V.VISTA_ATTN_QLA, 128, 4, 40, 5000)])
+def test_a_workspace_of_the_base_schedule_gets_the_base_schedule(form, d, H, S, n):
+    """Where the fitted segments need more, the smaller workspace is still taken, and the call is bit for bit
+    the one with the base segment size given."""
+    X, off, Q, Wk, Wv = problem(n, d, S, lens=[n - 90, 0, 90])
+    desc = V.summarize_desc(3, S, d, H, V.VISTA_BF16, n, attn=form)
+    seg = V.vista_summarize_segment_items(desc)
+    base = V.vista_summarize_workspace_bytes(V.summarize_desc(3, S, d, H, V.VISTA_BF16, n, attn=form, segment_items=seg))
+    assert base < V.vista_summarize_workspace_bytes(desc)
+    ws = torch.empty(base, dtype=torch.uint8, device="cuda")
+    got = run(X, off, Q, Wk, Wv, H, attn=form, workspace=ws)
+    assert np.array_equal(got, run(X, off, Q, Wk, Wv, H, attn=form, segment_items=seg))
+    with pytest.raises(V.VistaError):
+        run(X, off, Q, Wk, Wv, H, attn=form, workspace=ws[:base - 1])
