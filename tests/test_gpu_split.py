@@ -133,3 +133,19 @@ def test_a_workspace_of_the_base_schedule_gets_the_base_schedule(form, d, H, S, 
     assert np.array_equal(got, run(X, off, Q, Wk, Wv, H, attn=form, segment_items=seg))
     with pytest.raises(V.VistaError):
         run(X, off, Q, Wk, Wv, H, attn=form, workspace=ws[:base - 1])
+
+
+@pytest.mark.parametrize("form,d,H,S", [(V.VISTA_ATTN_SOFTMAX, 128, 4, 256), (V.VISTA_ATTN_SOFTMAX, 256, 8, 512), (V.VISTA_ATTN_SOFTMAX, 64, 2, 40),
+                                        (V.VISTA_ATTN_QLA, 128, 4, 40), (V.VISTA_ATTN_QLA, 256, 8, 64)])
+def test_element_aligned_weights_give_the_same_bits(form, d, H, S):
+    """Weights that are not 16-byte aligned are read two bytes at a time into the same operands."""
+    X, off, Q, Wk, Wv = problem(S, d, S)
+
+    def shifted(w):
+        flat = torch.empty(w.size + 1, device="cuda", dtype=torch.bfloat16)
+        flat[1:].copy_(dev(w, "bf16").flatten())
+        return flat[1:].view(w.shape)
+
+    out = torch.full((len(LENS), S, d), float("nan"), device="cuda", dtype=torch.bfloat16)
+    V.vista_summarize(dev(X, "bf16"), torch.from_numpy(off).cuda(), dev(Q, "bf16"), shifted(Wk), shifted(Wv), out, H=H, attn=form)
+    assert np.array_equal(host64(out), run(X, off, Q, Wk, Wv, H, attn=form))
