@@ -159,7 +159,7 @@ size_t vista_summarize_workspace_bytes(const vista_summarize_desc* desc);
  *
  * Supported: bf16 with (d, H) = (128, 4) or (256, 8), S in {64, 128, 256, 512} (MFMA path);
  * bf16 softmax with (d, H) = (64, 2), (128, 4) or (256, 8) and any other S (MFMA path whose K, V
- * and weights keep 16 significant bits; history 16-byte, queries and out 8-byte aligned, else the
+ * and weights keep the 24 bits of fp32; history 16-byte, queries and out 8-byte aligned, else the
  * plain path); any dtype with d/H <= 64, d <= 512, S <= 512 (plain fp32-ALU path).
  * The workspace grows with the user count as well as with the history: the MFMA
  * path keeps (G + B) partial records of H * S * 144 bytes (G = segments; S rounded

@@ -22,12 +22,15 @@
 // slower than eight of four: twice the operand reads from LDS and idle attend-only waves.)
 //
 // SPLIT.  The fixed seed counts keep K, V and the softmax weights as bf16 operands.  Any other seed
-// count (and d = 64) carries them as a bf16 value plus a bf16 remainder, 16 significant bits: scores
-// take two products (the seeds are bf16 already), P V three, the scale is applied to the fp32 keys,
-// and what is left against fp64 is the rounding of the bf16 output.  Twice the matrix work of the
-// plain operands and five more vector instructions per weight pair; against one thread per query on
-// the vector unit, which these shapes used to take: 48 users, 300 007 items, d = 64, S = 100 from
-// 9 800 to 51 us, 3 users, 20 000 items, d = 256, S = 100 from 2 717 to 34 us.
+// count (and d = 64) computes with them in fp32, as one thread per query on the vector unit did
+// before: each is three bf16 terms, 24 bits.  Scores take three products (the seeds are bf16
+// already), P V six, the scale is applied to the fp32 keys.  Error of the result before its bf16
+// rounding against fp64 (2-norm; d = 64 to 256, scores up to 6 / 25 / 100): 0.3-0.8 / 0.5-1.7 /
+// 0.7-1.2 e-6, one thread per query 0.4-1.6 / 0.6-7.5 / 0.8-1.5 e-6; two terms were 1.3-3.4 /
+// 6.1-8.2 / 9.5-15 e-6 and 20 to 30 % faster, and are not enough for that reason.  More than four
+// times the matrix work of the plain operands and ten more vector instructions per weight pair;
+// against one thread per query: 48 users, 300 007 items, d = 64, S = 100 from 10 500 to 68 us,
+// 3 users, 20 000 items, d = 256, S = 100 from 2 717 to 37 us.
 //
 // Softmax reference.  Scores are kept in base-2 units.  While every score of a
 // tile is provably inside [-60, 60] (Cauchy-Schwarz: |q| |k| <= 60) the
@@ -104,40 +107,50 @@ __device__ __forceinline__ void lds_barrier() {
 // Register i of a lane in half hf holds row 4 hf + acc_row0(i) of the 32x32 accumulator.
 __device__ __forceinline__ constexpr int acc_row0(int i) { return 8 * (i / 4) + (i % 4); }
 
-// One 32-wide operand of a tile: the two k-halves of its bf16 value and, where values are kept to 16
-// significant bits (SPLIT), of the bf16 remainder.
+// One 32-wide operand of a tile: the two k-halves of its bf16 value and, where values are kept whole
+// (SPLIT), of the two bf16 terms that make up the rest of their 24 bits.
 template <bool SPLIT>
 struct Operand {
   Pack8 hi[2];
+  Pack8 mid[SPLIT ? 2 : 1];
   Pack8 lo[SPLIT ? 2 : 1];
 };
 
-// bf16 pair of (a, b) and of what that pair leaves of them
-__device__ __forceinline__ void split_pk(float a, float b, uint32_t& hi, uint32_t& lo) {
+// fp32 pair (a, b) as three bf16 pairs: 8 + 8 + 8 bits, nothing is left of finite values below 2^127
+__device__ __forceinline__ void split_pk(float a, float b, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
   hi = cvt_pk_bf16(a, b);
-  lo = cvt_pk_bf16(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xFFFF0000u));
+  a -= __uint_as_float(hi << 16);
+  b -= __uint_as_float(hi & 0xFFFF0000u);
+  mid = cvt_pk_bf16(a, b);
+  lo = cvt_pk_bf16(a - __uint_as_float(mid << 16), b - __uint_as_float(mid & 0xFFFF0000u));
 }
 
-// acc += A B with A = hi (+ lo) and B exact (bf16)
+// acc += A B with A = hi (+ mid + lo) and B exact (bf16)
 template <bool SPLIT>
 __device__ __forceinline__ f32x16 mma_exact_b(const Operand<SPLIT>& a, const bf16x8 (&b)[2], f32x16 acc) {
   acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi[0].v, b[0], acc, 0, 0, 0);
   acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi[1].v, b[1], acc, 0, 0, 0);
   if constexpr (SPLIT) {
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.lo[0].v, b[0], acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.lo[1].v, b[1], acc, 0, 0, 0);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.mid[q].v, b[q], acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.lo[q].v, b[q], acc, 0, 0, 0);
+    }
   }
   return acc;
 }
 
-// acc += A B, both hi (+ lo); the product of the two remainders (2^-18 of the value) is left out
+// acc += A B, both hi (+ mid + lo); mid and lo are at most 2^-8 and 2^-16 of hi, so what is left out (mid lo, lo lo) is 2^-24
 template <bool SPLIT>
 __device__ __forceinline__ f32x16 mma(const Operand<SPLIT>& a, const Operand<SPLIT>& b, f32x16 acc) {
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi[q].v, b.hi[q].v, acc, 0, 0, 0);
     if constexpr (SPLIT) {
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.mid[q].v, b.hi[q].v, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi[q].v, b.mid[q].v, acc, 0, 0, 0);
       acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.lo[q].v, b.hi[q].v, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.mid[q].v, b.mid[q].v, acc, 0, 0, 0);
       acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi[q].v, b.lo[q].v, acc, 0, 0, 0);
     }
   }
@@ -182,7 +195,7 @@ __device__ __forceinline__ void attend_block(const Operand<SPLIT>& k, const Oper
 #pragma unroll
   for (int i = 0; i < 16; i += 2) {
     if constexpr (SPLIT) {
-      split_pk(s[i], s[i + 1], p.hi[i / 8].w[(i % 8) / 2], p.lo[i / 8].w[(i % 8) / 2]);
+      split_pk(s[i], s[i + 1], p.hi[i / 8].w[(i % 8) / 2], p.mid[i / 8].w[(i % 8) / 2], p.lo[i / 8].w[(i % 8) / 2]);
       l += s[i] + s[i + 1];
     } else {
       const uint32_t pk = cvt_pk_bf16(s[i], s[i + 1]);
@@ -197,14 +210,18 @@ template <int V>
 struct Int { static constexpr int value = V; };
 
 constexpr int kXBuf = 3;             // ring depth of the X tiles and of the projected tiles in LDS
+// The split operands are three times as large, and two slots are enough (two workgroups then still fit a
+// compute unit): a tile is published into the slot of the one whose operands every wave has read, one
+// tile ago, and the barrier in between orders the two.
+constexpr int kvbuf_slots(bool split) { return split ? 2 : kXBuf; }
 
 // Shared memory of one workgroup.  WREG: a projecting wave keeps its D x 32 weight operands in
 // registers (D / 4 of them; it saves half of the operand reads of a projection) instead of in LDS.
 template <int D, int HPW, bool WREG, bool SPLIT>
 struct SummarizeLds {
   uint4 xbuf[kXBuf][(D / 8) * 32];    // X tiles: [16-byte chunk][item], filled by direct global->LDS loads
-  uint4 kvbuf[kXBuf][HPW][2][SPLIT ? 4 : 2][64];   // projected tiles: [ring slot][head][K|V][half of the 16 registers (, of the remainders)][lane]
-  float knorm[kXBuf][HPW][64];        // squared norm of the scaled key rows (half per lane)
+  uint4 kvbuf[kvbuf_slots(SPLIT)][HPW][2][SPLIT ? 6 : 2][64];   // projected tiles: [ring slot][head][K|V][(term, )half of the 16 registers][lane]
+  float knorm[kvbuf_slots(SPLIT)][HPW][64];   // squared norm of the scaled key rows (half per lane)
   uint4 wop[WREG ? 1 : HPW * 2 * (D / 16) * 64];   // projection weights as MFMA operands: [head][K|V][k-slice][lane]
 };
 
@@ -369,6 +386,7 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
   // plain tiles keep their share of the denominators in lacc (register qb of either accumulator);
   // the general route folds it into l first
   static_assert(NQB <= 4, "one accumulator register per query block");
+  // (SPLIT adds its fp32 weights into l directly)
   f32x4 lacc[2];
   uint2 onesrow[NQB];
 #pragma unroll
@@ -439,7 +457,7 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
         uint32_t pk;
         if constexpr (SPLIT) {
           const float c = ROLE ? 1.f : p.c;      // the keys' scale, in fp32
-          split_pk(acc[i] * c, acc[i + 1] * c, pk, r.lo[i / 8].w[(i % 8) / 2]);
+          split_pk(acc[i] * c, acc[i + 1] * c, pk, r.mid[i / 8].w[(i % 8) / 2], r.lo[i / 8].w[(i % 8) / 2]);
         } else {
           pk = cvt_pk_bf16(acc[i], acc[i + 1]);
         }
@@ -449,7 +467,10 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
         sm.kvbuf[buf][hl][WR][q][lane] = r.hi[q].u;
-        if constexpr (SPLIT) sm.kvbuf[buf][hl][WR][2 + q][lane] = r.lo[q].u;
+        if constexpr (SPLIT) {
+          sm.kvbuf[buf][hl][WR][2 + q][lane] = r.mid[q].u;
+          sm.kvbuf[buf][hl][WR][4 + q][lane] = r.lo[q].u;
+        }
       }
       if (ROLE == 0 && !SILU) sm.knorm[buf][hl][lane] = n2;
     }
@@ -480,7 +501,10 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       r.hi[q].u = sm.kvbuf[i1][hl][which][q][lane];
-      if constexpr (SPLIT) r.lo[q].u = sm.kvbuf[i1][hl][which][2 + q][lane];
+      if constexpr (SPLIT) {
+        r.mid[q].u = sm.kvbuf[i1][hl][which][2 + q][lane];
+        r.lo[q].u = sm.kvbuf[i1][hl][which][4 + q][lane];
+      }
     }
   };
   auto read_k = [&](int i1) __attribute__((always_inline)) {
@@ -490,65 +514,76 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
   auto read_v = [&](int i1) __attribute__((always_inline)) {
     read_operand(vv, i1, 1);
   };
-  auto fast_tile = [&](int r) __attribute__((always_inline)) {   // r = tile index mod 3
-    const int i1 = r == kXBuf - 1 ? 0 : r + 1;
-    const int i2 = i1 == kXBuf - 1 ? 0 : i1 + 1;
+  int odd = 0;              // tile index mod 2
+  // slots of tiles t+1 and t+2 in a ring of the X tiles and of the operands, r = tile index mod 3
+  struct Slots { int x2, kv1, kv2; };
+  auto slots = [&](int r) __attribute__((always_inline)) {
+    const int i1 = r == kXBuf - 1 ? 0 : r + 1, i2 = i1 == kXBuf - 1 ? 0 : i1 + 1;
+    return SPLIT ? Slots{i2, odd ^ 1, odd} : Slots{i2, i1, i2};
+  };
+  auto fast_tile = [&](int r) __attribute__((always_inline)) {
+    const Slots at = slots(r);
     f32x16 acc = {0};
     // scores run one query block ahead of the exponentials that consume them
     f32x16 nx = {0};
     nx = mma_exact_b<SPLIT>(kk, qop[0], nx);
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb) {
-      if (qb == NQB - 1) read_k(i1);     // the last scores of this tile are already issued
+      if (qb == NQB - 1) read_k(at.kv1);     // the last scores of this tile are already issued
       const f32x16 sc = nx;
       if (qb + 1 < NQB) {
         const f32x16 z = {0};
         nx = mma_exact_b<SPLIT>(kk, qop[qb + 1], z);
       }
-      if (qb * KPB < KS) project(i2, qb * KPB, qb * KPB + KPB < KS ? qb * KPB + KPB : KS, acc);
+      if (qb * KPB < KS) project(at.x2, qb * KPB, qb * KPB + KPB < KS ? qb * KPB + KPB : KS, acc);
       Operand<SPLIT> pp;
+      float lsum[2] = {0.f, 0.f};
 #pragma unroll
       for (int i = 0; i < 16; i += 2) {
         float ea = __builtin_amdgcn_exp2f(sc[i]), eb = __builtin_amdgcn_exp2f(sc[i + 1]);
+        if constexpr (SPLIT) lsum[(i / 2) & 1] += ea + eb;
         if constexpr (SILU) {
           ea = sc[i] * __builtin_amdgcn_rcpf(1.f + ea);
           eb = sc[i + 1] * __builtin_amdgcn_rcpf(1.f + eb);
         }
         if constexpr (SPLIT)
-          split_pk(ea, eb, pp.hi[i / 8].w[(i % 8) / 2], pp.lo[i / 8].w[(i % 8) / 2]);
+          split_pk(ea, eb, pp.hi[i / 8].w[(i % 8) / 2], pp.mid[i / 8].w[(i % 8) / 2], pp.lo[i / 8].w[(i % 8) / 2]);
         else
           pp.hi[i / 8].w[(i % 8) / 2] = cvt_pk_bf16(ea, eb);
       }
       // The denominator on the matrix core: a 4x4x4 product (16 blocks, one per four lanes)
       // whose A block has ones in row qb adds a lane's own four packed weights into register
       // qb of that lane -- the lane-local partial sum a chain of adds would form, taken over
-      // the bf16 weights (and remainders) the numerator uses.  It issues like one plain vector
-      // instruction for four weights; two accumulators take turns so that consecutive products
-      // do not wait for each other.
-      if constexpr (!SILU) {
+      // the bf16 weights the numerator uses.  It issues like one plain vector instruction for four
+      // weights; two accumulators take turns so that consecutive products do not wait for each
+      // other.  (SPLIT: the fp32 weights are added as they are; three terms would be twelve products.)
+      if constexpr (SPLIT) {
+        l[qb] += lsum[0] + lsum[1];
+      } else if constexpr (!SILU) {
         const i16x4 sel = __builtin_bit_cast(i16x4, onesrow[qb]);
 #pragma unroll
-        for (int part = 0; part < (SPLIT ? 8 : 4); ++part) {
-          const Pack8& src = SPLIT && part >= 4 ? pp.lo[SPLIT ? part / 2 - 2 : 0] : pp.hi[(part / 2) & 1];
+        for (int part = 0; part < 4; ++part) {
+          const Pack8& src = pp.hi[part / 2];
           const uint2 pw = make_uint2(src.w[2 * (part & 1)], src.w[2 * (part & 1) + 1]);
           lacc[part & 1] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(sel, __builtin_bit_cast(i16x4, pw), lacc[part & 1], 0, 0, 0);
         }
       }
       o[qb] = mma<SPLIT>(vv, pp, o[qb]);
     }
-    read_v(i1);
-    publish(i2, acc);
+    read_v(at.kv1);
+    publish(at.kv2, acc);
   };
 
   // Any tile: ragged tail, scores beyond the bound, last tile of the segment.
   auto slow_tile = [&](int r, int nvalid, bool unsafe) __attribute__((always_inline)) {
-    const int i1 = r == kXBuf - 1 ? 0 : r + 1;
-    const int i2 = i1 == kXBuf - 1 ? 0 : i1 + 1;
+    const Slots at = slots(r);
     const int nvl = nvalid - 4 * hf;
+    if constexpr (!SPLIT) {
 #pragma unroll
-    for (int qb = 0; qb < NQB; ++qb) {
-      l[qb] += lacc[0][qb] + lacc[1][qb];
-      lacc[0][qb] = lacc[1][qb] = 0.f;
+      for (int qb = 0; qb < NQB; ++qb) {
+        l[qb] += lacc[0][qb] + lacc[1][qb];
+        lacc[0][qb] = lacc[1][qb] = 0.f;
+      }
     }
     if constexpr (SILU) {
       // pointwise form: scores, weights (rows past the piece's end get weight 0), second product
@@ -580,12 +615,12 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
     for (int qb = 0; qb < NQB; ++qb)
       attend_block<SPLIT>(kk, vv, qop[qb], o[qb], l[qb], m[qb], general, masked, nvl);
     }
-    read_k(i1);
-    read_v(i1);
+    read_k(at.kv1);
+    read_v(at.kv1);
     // the tile two ahead (past the end of the segment: a repeat of its last tile, never used)
     f32x16 acc = {0};
-    project(i2, 0, KS, acc);
-    publish(i2, acc);
+    project(at.x2, 0, KS, acc);
+    publish(at.kv2, acc);
   };
 
   // partial record of a finished piece: slot = segment + user
@@ -615,7 +650,7 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
   };
 
   // Tile t lives in ring slot t mod 3, as raw rows (xbuf) and, projected, as operands
-  // (kvbuf).  While tile t is attended over, tile t+2 is projected and published, the
+  // (kvbuf; SPLIT: slot t mod 2).  While tile t is attended over, tile t+2 is projected and published, the
   // operands of tile t+1 move into registers, the rows of tile t+3 land and those of tile
   // t+4 are requested into the slot whose rows (tile t+1) were projected one tile ago.
   // ---- prologue: tiles 0, 1, 2 requested; 0 and 1 landed, projected and published
@@ -691,6 +726,7 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
         drain = false;
         ++n;
         r = r == kXBuf - 1 ? 0 : r + 1;
+        odd ^= 1;
         unsafe = unsafe_tile(kn2);
         plain = !unsafe;
       }
@@ -706,6 +742,7 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
       --ca.tiles_left;
       ca.row += kTile;
       r = r == kXBuf - 1 ? 0 : r + 1;
+      odd ^= 1;
       unsafe = unsafe_tile(kn2);
       plain = is_plain();
     }
@@ -726,6 +763,7 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
       drain = true;
     }
     r = r == kXBuf - 1 ? 0 : r + 1;
+    odd ^= 1;
     if (!ca.valid) break;
     unsafe = unsafe_tile(kn2);
     plain = is_plain();
@@ -1028,7 +1066,7 @@ bool mfma_summarize_supported(const vista_summarize_desc& d) {
 }
 
 // The other bf16 softmax shapes of the same head width: any seed count, K, V and weights as split
-// operands (a bf16 value and a bf16 remainder, 16 significant bits).
+// operands (three bf16 terms, 24 bits).
 bool mfma_split_supported(const vista_summarize_desc& d) {
   if (d.dtype != VISTA_BF16 || d.attn != VISTA_ATTN_SOFTMAX || mfma_summarize_supported(d)) return false;
   return (d.d == 64 && d.H == 2) || (d.d == 128 && d.H == 4) || (d.d == 256 && d.H == 8);

@@ -1,6 +1,6 @@
 """GPU parity of the matrix-core path with split operands (bf16 softmax shapes outside the fixed seed
-counts): K, V and weights keep 16 significant bits, so what separates a result from the oracle is the
-rounding of the bf16 output."""
+counts): K, V and weights keep their 24 bits as three bf16 terms, so what separates a result from the
+oracle is the rounding of the bf16 output and of fp32 sums."""
 import numpy as np
 import pytest
 import torch
@@ -149,3 +149,26 @@ def test_element_aligned_weights_give_the_same_bits(form, d, H, S):
     out = torch.full((len(LENS), S, d), float("nan"), device="cuda", dtype=torch.bfloat16)
     V.vista_summarize(dev(X, "bf16"), torch.from_numpy(off).cuda(), dev(Q, "bf16"), shifted(Wk), shifted(Wv), out, H=H, attn=form)
     assert np.array_equal(host64(out), run(X, off, Q, Wk, Wv, H, attn=form))
+
+
+def test_split_keeps_the_precision_of_fp32_operands():
+    """Two items a user with nearly equal keys and opposite values: an output is a weight difference times
+    a value, so an error of a score shows undamped.  Keys and scores are fp32 sums of 64 and 32 rounded
+    terms: about sqrt(96) units of 2^-24 of the largest score, half of which reaches the weights' difference."""
+    g = np.random.default_rng(11)
+    d, H, S, B = 64, 2, 40, 24
+    half, r = d // 2, np.arange(B)
+    bf = lambda x: I.round_to(np.asarray(x, dtype=np.float32), "bf16")
+    a, c = bf(g.normal(size=(B, half)) * 12.5), bf(g.normal(size=(B, half)))
+    a2, j = a.copy(), g.integers(0, half, size=B)
+    a2[r, j] = (a[r, j].view(np.uint32) + 0x10000).view(np.float32)          # the next bf16 number
+    X = np.empty((2 * B, d), np.float32)
+    X[0::2], X[1::2] = np.concatenate([a, c], 1), np.concatenate([a2, -c], 1)
+    Wk, Wv = np.zeros((d, d), np.float32), np.zeros((d, d), np.float32)
+    Wk[:half], Wv[half:] = bf(g.normal(size=(half, d)) * half ** -0.5), bf(g.normal(size=(half, d)) * half ** -0.5)
+    Q, off = bf(g.normal(size=(S, d)) * 12.5), np.arange(0, 2 * B + 1, 2)
+    keys = (X.astype(np.float64) @ Wk).reshape(-1, H, d // H)
+    smax = np.abs(np.einsum("nhe,she->nsh", keys, Q.reshape(S, H, d // H))).max() * (d // H) ** -0.5
+    want, got = O.summarize(X, off, Q, Wk, Wv, H), run(X, off, Q, Wk, Wv, H)
+    top = np.abs(X.astype(np.float64) @ Wv).reshape(B, -1).max(axis=1)[:, None, None]
+    assert np.all(np.abs(got - want) <= 2.0 ** -8 * np.abs(want) + 0.5 * 96 ** 0.5 * 2.0 ** -24 * smax * top)
