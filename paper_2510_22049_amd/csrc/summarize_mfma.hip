@@ -54,6 +54,9 @@ typedef __attribute__((ext_vector_type(4))) short i16x4;
 
 constexpr int kTile = kTileItems;    // items per tile
 constexpr float kSafeBound2 = 3600.f;  // (60)^2: |q|^2 |k|^2 below this keeps 2^s in range
+// SPLIT: values up to 2^40 (squared, half a column of a tile) meet weights up to 2^60 with room for any history;
+// a tile beyond, or with an infinite or NaN value, takes the running maximum and an fp32 product.
+constexpr float kLarge2 = 1.2089258196146292e24f;
 constexpr int kRecRows = 18;         // 16 O registers + l + m per lane
 constexpr int kRecFloats = kRecRows * 64;
 
@@ -125,6 +128,15 @@ __device__ __forceinline__ void split_pk(float a, float b, uint32_t& hi, uint32_
   lo = cvt_pk_bf16(a - __uint_as_float(mid << 16), b - __uint_as_float(mid & 0xFFFF0000u));
 }
 
+// The same for any pair: the leading terms are cut off instead of rounded, so that a value beyond the largest
+// bf16 number stays finite, and an infinite or NaN value leaves no rest.
+__device__ __forceinline__ void split_pk_any(float a, float b, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
+  const uint32_t ha = __float_as_uint(a) & 0xFFFF0000u, hb = __float_as_uint(b) & 0xFFFF0000u;
+  uint32_t low;
+  split_pk(__builtin_isfinite(a) ? a - __uint_as_float(ha) : 0.f, __builtin_isfinite(b) ? b - __uint_as_float(hb) : 0.f, mid, lo, low);
+  hi = (ha >> 16) | hb;
+}
+
 // acc += A B with A = hi (+ mid + lo) and B exact (bf16)
 template <bool SPLIT>
 __device__ __forceinline__ f32x16 mma_exact_b(const Operand<SPLIT>& a, const bf16x8 (&b)[2], f32x16 acc) {
@@ -157,13 +169,15 @@ __device__ __forceinline__ f32x16 mma(const Operand<SPLIT>& a, const Operand<SPL
   return acc;
 }
 
-// One block of 32 queries against one tile of 32 items.  `general` and `masked`
+// One block of 32 queries against one tile of 32 items.  `general`, `masked` and `large`
 // are wave-uniform; the MFMAs sit on the common path so the accumulators keep
-// one register assignment whichever route a tile takes.
+// one register assignment whichever route a tile takes.  large (SPLIT): the tile has
+// values of any size, infinite ones included: the second product in fp32 (a term 0 of a
+// weight times an infinite value would be NaN), rows past the piece left out of it.
 template <bool SPLIT>
 __device__ __forceinline__ void attend_block(const Operand<SPLIT>& k, const Operand<SPLIT>& v,
                                              const bf16x8 (&q)[2], f32x16& o, float& l, float& m, bool general,
-                                             bool masked, int nvl) {
+                                             bool masked, int nvl, bool large) {
   // nvl = valid items of the tile minus 4 hf: register i is valid iff acc_row0(i) < nvl
   f32x16 s = {0};
   s = mma_exact_b<SPLIT>(k, q, s);
@@ -190,6 +204,18 @@ __device__ __forceinline__ void attend_block(const Operand<SPLIT>& k, const Oper
 #pragma unroll
     for (int i = 0; i < 16; ++i)
       if (acc_row0(i) >= nvl) s[i] = 0.f;
+  }
+  if constexpr (SPLIT) {
+    if (large) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        auto term = [&](const Pack8& w) __attribute__((always_inline)) { return __uint_as_float(uint32_t(w.h[i % 8]) << 16); };
+        const float vi = term(v.hi[i / 8]) + (term(v.mid[i / 8]) + term(v.lo[i / 8]));
+        o = __builtin_amdgcn_mfma_f32_32x32x2f32(acc_row0(i) < nvl ? vi : 0.f, s[i], o, 0, 0, 0);
+        l += s[i];
+      }
+      return;
+    }
   }
   Operand<SPLIT> p;
 #pragma unroll
@@ -222,6 +248,7 @@ struct SummarizeLds {
   uint4 xbuf[kXBuf][(D / 8) * 32];    // X tiles: [16-byte chunk][item], filled by direct global->LDS loads
   uint4 kvbuf[kvbuf_slots(SPLIT)][HPW][2][SPLIT ? 6 : 2][64];   // projected tiles: [ring slot][head][K|V][(term, )half of the 16 registers][lane]
   float knorm[kvbuf_slots(SPLIT)][HPW][64];   // squared norm of the scaled key rows (half per lane)
+  float vnorm[SPLIT ? 2 : 1][HPW][64];        // SPLIT: that of the value columns
   uint4 wop[WREG ? 1 : HPW * 2 * (D / 16) * 64];   // projection weights as MFMA operands: [head][K|V][k-slice][lane]
 };
 
@@ -461,8 +488,18 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
         } else {
           pk = cvt_pk_bf16(acc[i], acc[i + 1]);
         }
-        if (ROLE == 0 && !SILU) n2 = dot2_self(pk, n2);
+        if ((ROLE == 0 && !SILU) || SPLIT) n2 = dot2_self(pk, n2);
         r.hi[i / 8].w[(i % 8) / 2] = pk;
+      }
+      if constexpr (SPLIT) {
+        if (__builtin_amdgcn_ballot_w64(!(n2 <= kLarge2))) {
+#pragma unroll
+          for (int i = 0; i < 16; i += 2) {
+            const float c = ROLE ? 1.f : p.c;
+            split_pk_any(acc[i] * c, acc[i + 1] * c, r.hi[i / 8].w[(i % 8) / 2], r.mid[i / 8].w[(i % 8) / 2], r.lo[i / 8].w[(i % 8) / 2]);
+          }
+        }
+        if (ROLE == 1) sm.vnorm[buf][hl][lane] = n2;
       }
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
@@ -475,8 +512,10 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
       if (ROLE == 0 && !SILU) sm.knorm[buf][hl][lane] = n2;
     }
   };
+  float vn2 = 0.f;          // SPLIT: squared norm of half a value column of the tile being attended over
   auto unsafe_tile = [&](float kn2) __attribute__((always_inline)) {
     if constexpr (SILU) return false;
+    if constexpr (SPLIT) return __builtin_amdgcn_ballot_w64(!(kn2 * qmax2 <= kSafeBound2 && vn2 <= kLarge2)) != 0;
     return __builtin_amdgcn_ballot_w64(kn2 * qmax2 > kSafeBound2) != 0;
   };
 
@@ -510,6 +549,7 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
   auto read_k = [&](int i1) __attribute__((always_inline)) {
     read_operand(kk, i1, 0);
     if constexpr (!SILU) kn2 = sm.knorm[i1][hl][lane] + sm.knorm[i1][hl][lane ^ 32];
+    if constexpr (SPLIT) vn2 = sm.vnorm[i1][hl][lane];
   };
   auto read_v = [&](int i1) __attribute__((always_inline)) {
     read_operand(vv, i1, 1);
@@ -611,9 +651,10 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
     }
     mode = general ? 2 : 1;
     const bool masked = nvalid < kTile;
+    const bool large = SPLIT && __builtin_amdgcn_ballot_w64(!(vn2 <= kLarge2)) != 0;
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb)
-      attend_block<SPLIT>(kk, vv, qop[qb], o[qb], l[qb], m[qb], general, masked, nvl);
+      attend_block<SPLIT>(kk, vv, qop[qb], o[qb], l[qb], m[qb], general, masked, nvl, large);
     }
     read_k(at.kv1);
     read_v(at.kv1);
@@ -814,7 +855,9 @@ __global__ __launch_bounds__(MAXT) void summarize_mfma_kernel(MfmaSummarizeParam
 // RG = 4: each of the four is a block of four waves; wave r takes the r-th run of the records,
 // ascending, and the runs' sums are combined in ascending order.  (No codec: its scale spans the four.)
 // Columns past the last query are computed and not stored.
-template <bool SILU, int RG>
+// SPLIT: records of the split operands, whose values may be infinite.  (Clearing the padding entries for the
+// other records as well made one user of 7001 items 1 us slower.)
+template <bool SILU, int RG, bool SPLIT>
 __global__ __launch_bounds__(256) void merge_mfma_kernel(const float* __restrict__ partials,
                                                               const int64_t* __restrict__ offsets, int B, int S, int d,
                                                               int H, int seg, int64_t N, int64_t G,
@@ -896,6 +939,7 @@ __global__ __launch_bounds__(256) void merge_mfma_kernel(const float* __restrict
     }
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {     // ascending segment order
+      if (SPLIT && g + u > g1) v[u][2] = v[u][3] = v[u][4] = v[u][5] = 0.f;   // (they may be infinite: a weight of 0 is not enough)
       if (SILU) {
         const float on = g + u <= g1 ? 1.f : 0.f;
         o0 = fmaf(v[u][2], on, o0);
@@ -1156,11 +1200,11 @@ static hipError_t launch_split(MfmaSummarizeParams& p, int d, int64_t G, hipStre
   return launch_main<256, 2, 1, 4, false, true, 512, A>(p, w2, G, s);
 }
 
-template <bool SILU, int RG>
+template <bool SILU, int RG, bool SPLIT>
 static hipError_t launch_merge(const MfmaSummarizeParams& p, const SummarizeArgs& a, const float* Ks, const float* Vs,
                                int64_t blocks) {
   const vista_summarize_desc& d = a.desc;
-  return launch(merge_mfma_kernel<SILU, RG>, dim3(unsigned(RG > 1 ? 4 * blocks : blocks)), dim3(256), 0, a.stream, p.partials, a.offsets,
+  return launch(merge_mfma_kernel<SILU, RG, SPLIT>, dim3(unsigned(RG > 1 ? 4 * blocks : blocks)), dim3(256), 0, a.stream, p.partials, a.offsets,
                 d.B, d.S, d.d, d.H, a.seg, d.total_items, a.G, static_cast<uint16_t*>(a.out),
                 reinterpret_cast<int*>(a.workspace), a.offsets_checked ? 0 : 1, p.Q, d.q_user_stride, Ks, Vs,
                 SILU ? a.scale_plain : a.scale_log2, a.out_scales);
@@ -1202,8 +1246,13 @@ vista_status mfma_summarize(const SummarizeArgs& a) {
   // Few blocks: four times as many, and four waves to a user's records.  A merge is bound by what a
   // compute unit can read (about 20 GB/s each when all do), so it wants them all.
   const bool wide = merge_blocks <= 512 && !a.out_scales;
-  const hipError_t e = silu ? (wide ? launch_merge<true, 4>(p, a, Ks, Vs, merge_blocks) : launch_merge<true, 1>(p, a, Ks, Vs, merge_blocks))
-                            : (wide ? launch_merge<false, 4>(p, a, Ks, Vs, merge_blocks) : launch_merge<false, 1>(p, a, Ks, Vs, merge_blocks));
+  auto merge = [&](auto four) {
+    constexpr int RG = decltype(four)::value;
+    return silu                       ? launch_merge<true, RG, false>(p, a, Ks, Vs, merge_blocks)
+           : mfma_split_supported(d) ? launch_merge<false, RG, true>(p, a, Ks, Vs, merge_blocks)
+                                     : launch_merge<false, RG, false>(p, a, Ks, Vs, merge_blocks);
+  };
+  const hipError_t e = wide ? merge(Int<4>{}) : merge(Int<1>{});
   return e == hipSuccess ? VISTA_OK : VISTA_ERR_HIP;
 }
 

@@ -172,3 +172,34 @@ def test_split_keeps_the_precision_of_fp32_operands():
     want, got = O.summarize(X, off, Q, Wk, Wv, H), run(X, off, Q, Wk, Wv, H)
     top = np.abs(X.astype(np.float64) @ Wv).reshape(B, -1).max(axis=1)[:, None, None]
     assert np.all(np.abs(got - want) <= 2.0 ** -8 * np.abs(want) + 0.5 * 96 ** 0.5 * 2.0 ** -24 * smax * top)
+@pytest.mark.parametrize("d,H", [(64, 2), (128, 4), (256, 8)])
+@pytest.mark.parametrize("rows", [(5,), (33,), (69,), (3, 40, 69)])
+def test_split_values_and_keys_that_leave_the_bf16_range(d, H, rows):
+    """Values that overflow (or that only bf16 cannot hold) and keys at minus infinity behave as in fp32:
+    they reach their own channel, a key at minus infinity takes its item out."""
+    g = np.random.default_rng(13)
+    S, L = 40, 70                                                 # two full tiles and a ragged one
+    bf = lambda x: I.round_to(np.asarray(x, dtype=np.float32), "bf16")
+    X, Q = bf(g.normal(size=(2 * L, d))), bf(g.normal(size=(S, d)))
+    X[:, -3:] = 0.0
+    Wk, Wv = bf(g.normal(size=(d, d)) * d ** -0.5), bf(g.normal(size=(d, d)) * d ** -0.5)
+    Wk[-3:], Wv[-3:], Wk[:, -1], Q[:, -1] = 0.0, 0.0, 0.0, 1.0
+    Wk[-2, -1] = -2.0                                             # 2^127 in channel -2: the last key is minus infinity
+    Wv[-1, [0, 7, 31, d - 1]] = 2.0, -2.0, 1.9921875, 2.0 ** -20  # 2^127 in channel -1: inf, -inf, the largest bf16, 2^107
+    Wv[-3, 31] = 1.5 * 2.0 ** 119                                 # 1 in channel -3: beyond the largest bf16, within fp32
+    off = np.array([0, L, 2 * L])
+    clean = O.summarize(X, off, Q, Wk, Wv, H)
+    for r in rows:
+        X[r, -1], X[r, -3] = 2.0 ** 127, 1.0
+    want, dh = O.summarize(X, off, Q, Wk, Wv, H), d // H
+    X[17, -2] = 2.0 ** 127                                        # the item leaves the last head
+    want[:, :, -dh:] = O.summarize(np.delete(X, 17, axis=0), np.array([0, L - 1, 2 * L - 1]), Q, Wk, Wv, H)[:, :, -dh:]
+    out = torch.full((2, S, d), float("nan"), device="cuda", dtype=torch.bfloat16)
+    V.vista_summarize(dev(X, "bf16"), torch.from_numpy(off).cuda(), dev(Q, "bf16"), dev(Wk, "bf16"), dev(Wv, "bf16"), out, H=H)
+    got = host64(out)
+    assert np.all(np.isposinf(got[0, :, 0])) and np.all(np.isneginf(got[0, :, 7]))
+    top = np.abs(want).max(axis=1, keepdims=True)                 # per channel: their sizes differ by 2^100
+    near = lambda a, b, t: np.abs(a - b) <= 2.0 ** -8 * np.abs(b) + 1e-4 * t
+    rest = np.setdiff1d(np.arange(d), [0, 7] if len(rows) == 1 else [0, 7, 31])    # (several overflow the un-normalised sum)
+    assert np.all(near(got[0], want[0], top[0])[:, rest])
+    assert np.all(near(got[1], clean[1], np.abs(clean).max(axis=1, keepdims=True)[1]))
