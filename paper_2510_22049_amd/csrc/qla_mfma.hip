@@ -67,57 +67,96 @@ struct Int { static constexpr int value = V; };
 // W[16 ks + 8 hf + j][32 h + l32].  16-byte aligned weights are read as rows, 16 bytes a lane, and turned
 // by the matrix core (a 32 x 32 block times a 0/1 selector lands in accumulator layout; the lane picks
 // its row so that registers 0..7 and 8..15 are two operands): all loads in flight at once, where
-// 2-byte loads, a slice at a time, held the first tile up by several microseconds.
+// 2-byte loads, a slice at a time, held the first tile up by several microseconds.  Weights that are not all
+// finite go by 2-byte loads too: in the product with 0 an infinite or NaN entry would spoil its whole row.
+template <int D>
+struct RawMatrix { Pack8 u[D / 32][2]; };
+
+template <int D>
+__device__ __forceinline__ void request_matrix(const uint16_t* W, int h, RawMatrix<D>& raw) {
+  const int lane = threadIdx.x & 63, hf = lane >> 5, l32 = lane & 31;
+  const int row = (l32 & 16) | ((l32 & 4) << 1) | ((l32 & 8) >> 1) | (l32 & 3);
+  const uint16_t* src = W + row * D + 32 * h + 8 * hf;
+#pragma unroll
+  for (int b = 0; b < D / 32; ++b)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) raw.u[b][q].u = *reinterpret_cast<const uint4*>(src + 32 * b * D + 16 * q);
+}
+
+// Returns 0 over finite weights, NaN otherwise.
+template <int D>
+__device__ __forceinline__ float turn_matrix(float c, const RawMatrix<D>& raw, bf16x8 (&out)[D / 16]) {
+  const int lane = threadIdx.x & 63, hf = lane >> 5, l32 = lane & 31;
+  Pack8 sel[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) sel[q].h[j] = (l32 == 16 * q + 8 * hf + j) ? 0x3F80 : 0;
+  float rest = 0.f;
+#pragma unroll
+  for (int b = 0; b < D / 32; ++b) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      rest = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, raw.u[b][e / 4].w[e % 4]), bf16x2{}, rest, false);
+    f32x16 t = {0};
+    t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(raw.u[b][0].v, sel[0].v, t, 0, 0, 0);
+    t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(raw.u[b][1].v, sel[1].v, t, 0, 0, 0);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      Pack8 w;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) w.w[j] = cvt_pk_bf16(t[8 * q + 2 * j] * c, t[8 * q + 2 * j + 1] * c);
+      out[2 * b + q] = w.v;
+    }
+  }
+  return rest;
+}
+
+template <int D>
+__device__ __forceinline__ void gather_matrix(const uint16_t* W, int h, float c, bf16x8 (&out)[D / 16]) {
+  const int lane = threadIdx.x & 63, hf = lane >> 5, l32 = lane & 31;
+#pragma unroll
+  for (int ks = 0; ks < D / 16; ++ks) {
+    Pack8 a;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      a.h[j] = f32_to_bf16_bits(__uint_as_float(uint32_t(W[int64_t(16 * ks + 8 * hf + j) * D + 32 * h + l32]) << 16) * c);
+    out[ks] = a.v;
+    __builtin_amdgcn_sched_barrier(0);     // one slice's loads at a time: they all land in registers of their own
+  }
+}
+
 template <int D>
 __device__ __forceinline__ void load_weights(const uint16_t* Wk, const uint16_t* Wv, int h, float c,
                                              bf16x8 (&wk)[D / 16], bf16x8 (&wv)[D / 16]) {
-  constexpr int KS = D / 16;
-  const int lane = threadIdx.x & 63, hf = lane >> 5, l32 = lane & 31;
-  if (((reinterpret_cast<uintptr_t>(Wk) | reinterpret_cast<uintptr_t>(Wv)) & 15) == 0) {
-    const int row = (l32 & 16) | ((l32 & 4) << 1) | ((l32 & 8) >> 1) | (l32 & 3);
-    const int at = row * D + 32 * h + 8 * hf;
-    Pack8 sel[2];
-#pragma unroll
-    for (int q = 0; q < 2; ++q)
-#pragma unroll
-      for (int j = 0; j < 8; ++j) sel[q].h[j] = (l32 == 16 * q + 8 * hf + j) ? 0x3F80 : 0;
-#pragma unroll
-    for (int m = 0; m < 2; ++m) {                  // the keys' matrix, then the values'
-      Pack8 raw[KS / 2][2];
-#pragma unroll
-      for (int b = 0; b < KS / 2; ++b)
-#pragma unroll
-        for (int q = 0; q < 2; ++q) raw[b][q].u = *reinterpret_cast<const uint4*>((m ? Wv : Wk) + at + 32 * b * D + 16 * q);
-      const float f = m ? 1.f : c;
-#pragma unroll
-      for (int b = 0; b < KS / 2; ++b) {
-        f32x16 t = {0};
-        t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(raw[b][0].v, sel[0].v, t, 0, 0, 0);
-        t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(raw[b][1].v, sel[1].v, t, 0, 0, 0);
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          Pack8 w;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) w.w[j] = cvt_pk_bf16(t[8 * q + 2 * j] * f, t[8 * q + 2 * j + 1] * f);
-          if (m) wv[2 * b + q] = w.v; else wk[2 * b + q] = w.v;
-        }
-      }
-      if (D > 128) __builtin_amdgcn_sched_barrier(0);      // one matrix in flight at a time: registers
+  const bool whole = ((reinterpret_cast<uintptr_t>(Wk) | reinterpret_cast<uintptr_t>(Wv)) & 15) == 0;
+  auto finite = [](float rest) __attribute__((always_inline)) { return __builtin_amdgcn_ballot_w64(rest != 0.f) == 0; };
+  RawMatrix<D> raw[2];
+  bool turned = whole;
+  if (D <= 128) {
+    if (whole) {
+      request_matrix<D>(Wk, h, raw[0]);
+      request_matrix<D>(Wv, h, raw[1]);
+      const float rest = turn_matrix<D>(c, raw[0], wk);
+      turned = finite(rest + turn_matrix<D>(1.f, raw[1], wv));
     }
-  } else {
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      Pack8 a, b;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int64_t at = int64_t(16 * ks + 8 * hf + j) * D + 32 * h + l32;
-        a.h[j] = f32_to_bf16_bits(__uint_as_float(uint32_t(Wk[at]) << 16) * c);
-        b.h[j] = Wv[at];
-      }
-      wk[ks] = a.v;
-      wv[ks] = b.v;
-      __builtin_amdgcn_sched_barrier(0);     // one slice's loads at a time: they all land in registers of their own
+    if (!turned) {
+      gather_matrix<D>(Wk, h, c, wk);
+      gather_matrix<D>(Wv, h, 1.f, wv);
     }
+    return;
+  }
+  // one matrix in flight at a time: registers
+#pragma unroll
+  for (int m = 0; m < 2; ++m) {
+    const uint16_t* W = m ? Wv : Wk;
+    bf16x8 (&out)[D / 16] = m ? wv : wk;
+    if (whole) {
+      request_matrix<D>(W, h, raw[m]);
+      turned = finite(turn_matrix<D>(m ? 1.f : c, raw[m], out));
+    }
+    if (!turned) gather_matrix<D>(W, h, m ? 1.f : c, out);
+    __builtin_amdgcn_sched_barrier(0);
   }
 }
 

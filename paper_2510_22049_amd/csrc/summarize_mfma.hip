@@ -95,6 +95,11 @@ __device__ __forceinline__ float dot2_ones(uint32_t pk, float acc) {
   return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk), ones, acc, false);
 }
 
+// acc + 0: NaN if either number of the pair is infinite or NaN
+__device__ __forceinline__ float dot2_zero(uint32_t pk, float acc) {
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk), bf16x2{}, acc, false);
+}
+
 __device__ __forceinline__ float dot2_self(uint32_t pk, float acc) {
   const bf16x2 v = __builtin_bit_cast(bf16x2, pk);
   return __builtin_amdgcn_fdot2_f32_bf16(v, v, acc, false);
@@ -248,7 +253,7 @@ struct SummarizeLds {
   uint4 xbuf[kXBuf][(D / 8) * 32];    // X tiles: [16-byte chunk][item], filled by direct global->LDS loads
   uint4 kvbuf[kvbuf_slots(SPLIT)][HPW][2][SPLIT ? 6 : 2][64];   // projected tiles: [ring slot][head][K|V][(term, )half of the 16 registers][lane]
   float knorm[kvbuf_slots(SPLIT)][HPW][64];   // squared norm of the scaled key rows (half per lane)
-  float vnorm[SPLIT ? 2 : 1][HPW][64];        // SPLIT: that of the value columns
+  float vnorm[SPLIT ? 2 : 1][SPLIT ? HPW : 1][SPLIT ? 64 : 1];   // SPLIT: that of the value columns
   uint4 wop[WREG ? 1 : HPW * 2 * (D / 16) * 64];   // projection weights as MFMA operands: [head][K|V][k-slice][lane]
 };
 
@@ -296,7 +301,8 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
   // 0/1 selector lands in accumulator layout with the lane on the block's column.  The lane picks its
   // row so that registers 0..7 and 8..15 come out as two operands (row of register i, half hf:
   // 16 (i / 8) + 8 hf + i % 8).  Two loads a block instead of sixteen 2-byte ones; bit for bit the
-  // same operands (a product with 1.0 is exact).
+  // same operands (a product with 1.0 is exact) as long as the weights are finite: an infinite or NaN
+  // entry would spoil its whole row of the block (0 times it is NaN), so such weights go the other way.
   const uint16_t* W = ROLE ? p.Wv : p.Wk;
   const bool wide_rows = (reinterpret_cast<uintptr_t>(W) & 15) == 0;
   Pack8 wraw[PROJ ? KS / 2 : 1][2];
@@ -314,7 +320,16 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
   };
   auto settle_weights = [&]() __attribute__((always_inline)) {
     if constexpr (PROJ) {
+      bool turned = wide_rows;
       if (wide_rows) {
+        float rest[4] = {0.f, 0.f, 0.f, 0.f};      // stay 0 over finite weights, NaN otherwise
+#pragma unroll
+        for (int b = 0; b < KS / 2; ++b)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) rest[e % 4] = dot2_zero(wraw[b][e / 4].w[e % 4], rest[e % 4]);
+        turned = __builtin_amdgcn_ballot_w64((rest[0] + rest[1]) + (rest[2] + rest[3]) != 0.f) == 0;
+      }
+      if (turned) {
         Pack8 sel[2];
 #pragma unroll
         for (int q = 0; q < 2; ++q)
@@ -1055,6 +1070,7 @@ __global__ __launch_bounds__(256) void self_kv_mfma_kernel(const uint16_t* __res
   f32x16 acc[2] = {{0}, {0}};
 #pragma unroll 4
   for (int k = 0; k < d; k += 32) {
+    float rest = 0.f;
     Pack8 x[2], raw[2][2];
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
@@ -1068,10 +1084,18 @@ __global__ __launch_bounds__(256) void self_kv_mfma_kernel(const uint16_t* __res
       t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(raw[m][0].v, sel[0].v, t, 0, 0, 0);
       t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(raw[m][1].v, sel[1].v, t, 0, 0, 0);
 #pragma unroll
+      for (int e = 0; e < 8; ++e) rest = dot2_zero(raw[m][e / 4].w[e % 4], rest);
+      const bool finite = __builtin_amdgcn_ballot_w64(rest != 0.f) == 0;     // (else not turned: see summarize_wave)
+#pragma unroll
       for (int e = 0; e < 2; ++e) {
         Pack8 w;
 #pragma unroll
         for (int j = 0; j < 4; ++j) w.w[j] = cvt_pk_bf16(t[8 * e + 2 * j], t[8 * e + 2 * j + 1]);
+        if (!finite) {
+          const uint16_t* W = (m ? Wv : Wk) + int64_t(k + 16 * e + 8 * hf) * d + c0 + l32;
+#pragma unroll
+          for (int j = 0; j < 8; ++j) w.h[j] = W[j * d];
+        }
         acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[e].v, w.v, acc[m], 0, 0, 0);
       }
     }

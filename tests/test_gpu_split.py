@@ -203,3 +203,24 @@ def test_split_values_and_keys_that_leave_the_bf16_range(d, H, rows):
     rest = np.setdiff1d(np.arange(d), [0, 7] if len(rows) == 1 else [0, 7, 31])    # (several overflow the un-normalised sum)
     assert np.all(near(got[0], want[0], top[0])[:, rest])
     assert np.all(near(got[1], clean[1], np.abs(clean).max(axis=1, keepdims=True)[1]))
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("-inf"), float("nan")])
+@pytest.mark.parametrize("form,d,H,S,self_term", [
+    (V.VISTA_ATTN_SOFTMAX, 128, 4, 256, True), (V.VISTA_ATTN_SOFTMAX, 256, 8, 64, False), (V.VISTA_ATTN_SOFTMAX, 64, 2, 40, True),
+    (V.VISTA_ATTN_SILU, 128, 4, 64, True), (V.VISTA_ATTN_QLA, 128, 4, 40, True), (V.VISTA_ATTN_QLA, 256, 8, 64, False)])
+def test_a_weight_that_is_not_finite_stays_in_its_column(form, d, H, S, self_term, bad):
+    """One such entry of W_v reaches one channel; the others keep their bits.  (The split shapes take other
+    products for such tiles: fp32 sums in another order, at most the next bf16 number, 2^-7 of the value,
+    plus 1e-5 of the block.)"""
+    X, off, Q, Wk, Wv = problem(S + d, d, S, lens=[300, 0, 45])
+    before = run(X, off, Q, Wk, Wv, H, attn=form, self_term=self_term)
+    r, c = d // 2 + 3, d - 14
+    Wv[r, c] = bad
+    out = torch.zeros((3, S, d), device="cuda", dtype=torch.bfloat16)
+    V.vista_summarize(dev(X, "bf16"), torch.from_numpy(off).cuda(), dev(Q, "bf16"), dev(Wk, "bf16"), dev(Wv, "bf16"), out, H=H,
+                      attn=form, self_term=self_term)
+    got, rest = host64(out), np.delete(np.arange(d), c)
+    one_ulp = 2.0 ** -7 * np.abs(before) + 1e-5 * np.abs(before).max(axis=(1, 2), keepdims=True)
+    assert np.all(np.abs(got - before)[:, :, rest] <= (one_ulp[:, :, rest] if S == 40 and form == V.VISTA_ATTN_SOFTMAX else 0.0))
+    assert not np.any(np.isfinite(got[[0, 2]][:, :, c]))
