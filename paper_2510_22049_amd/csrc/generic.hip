@@ -684,6 +684,8 @@ __global__ __launch_bounds__(1024) void qla_bwd_state32_kernel(const float* __re
     return;
   }
   // this wave's queries and their output gradients, requested before the records are waited for
+  // (d_out may be aligned to its elements only)
+  const bool vec_dO = (reinterpret_cast<uintptr_t>(dO) & (4 * sizeof(T) - 1)) == 0;
   const T* Qb = Q + q_user_stride * b + h * 32 + 4 * g;
   const T* Db = dO + int64_t(b) * S * d + h * 32 + 4 * g;
   float q[2][2][4], y[2][2][4];
@@ -694,7 +696,13 @@ __global__ __launch_bounds__(1024) void qla_bwd_state32_kernel(const float* __re
       const int i = 16 * (w + 16 * u) + c;
       if (i < S) {
         load4(Qb + int64_t(i) * d + 16 * a, q[u][a]);
-        load4(Db + int64_t(i) * d + 16 * a, y[u][a]);
+        const T* src = Db + int64_t(i) * d + 16 * a;
+        if (vec_dO) {
+          load4(src, y[u][a]);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) y[u][a][e] = to_f32(src[e]);
+        }
       } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e) q[u][a][e] = y[u][a][e] = 0.f;

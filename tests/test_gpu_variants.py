@@ -433,3 +433,21 @@ def test_qla_backward_with_the_self_term(dtype, d, H, S, per_user):
             sl = slice(off[b], off[b + 1])
             for got_, want_ in ((host64(dK)[sl], wK[sl]), (host64(dV)[sl], wV[sl])):
                 assert block_errors(got_[None], want_[None])[0] <= tol
+
+
+@pytest.mark.parametrize("dtype,d,H,S", [("bf16", 128, 4, 40), ("bf16", 256, 8, 300), ("f32", 64, 2, 24)])
+def test_qla_backward_takes_an_element_aligned_d_out(dtype, d, H, S):
+    """The state-gradient kernel of head width 32 reads d_out four elements at a time where it may."""
+    X, off, Q, Wk, Wv = problem(91, [300, 0, 45], d, S, dtype)
+    dO = dev(I.round_to(np.random.default_rng(92).normal(size=(3, S, d)).astype(np.float32), dtype), dtype)
+    flat = torch.empty(dO.numel() + 1, device="cuda", dtype=dO.dtype)
+    flat[1:].copy_(dO.flatten())
+    args = (dev(X, dtype), torch.from_numpy(off).cuda(), dev(Q, dtype), dev(Wk, dtype), dev(Wv, dtype))
+
+    def grads(g):
+        out = [torch.full(s, float("nan"), device="cuda", dtype=dO.dtype) for s in (dO.shape, X.shape, X.shape)]
+        V.vista_qla_backward(*args, g, *out, H=H)
+        return out
+
+    for a, b in zip(grads(dO), grads(flat[1:].view(dO.shape))):
+        assert torch.equal(a, b) and bool(torch.isfinite(a.float()).all())
