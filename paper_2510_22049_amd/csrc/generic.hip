@@ -181,7 +181,8 @@ hipError_t launch_self_kv(const vista_summarize_desc& d, const void* Q, const vo
 //   softmax:  m = max m_c,  l = sum l_c 2^(m_c - m),  O = sum O_c 2^(m_c - m),  out = O / l;
 //             the self term is one more slot: m = own score, l = 1, O = own value;
 //   SiLU form: out = (sum O_c [+ SiLU(own score) own value]) / L_b.
-// One thread per (query, channel), 256 / RG of them a block, all of one (user, head); RG threads share an
+// grid (users, heads x element blocks): threads along x stay below the runtime's 2^32 for as many users as one
+// block a user did.  One thread per (query, channel), 256 / RG of them a block, all of one (user, head); RG threads share an
 // element, each taking a run of the user's records, ascending, eight loads in flight; the runs are
 // combined in ascending order.  Four runs where users hold eight records or more: one user's 16
 // records of a 1024-item history took 10.5 us in one block of dependent loads.
@@ -195,10 +196,10 @@ __global__ __launch_bounds__(256) void merge_kernel(const float* __restrict__ pa
                                                     float scale) {
   constexpr int kPer = 256 / RG, kBatch = 8;
   __shared__ float group[RG][3][kPer];
-  if (status && blockIdx.x == 0) publish_status(offsets, B, N, status);
+  if (status && blockIdx.x == 0 && blockIdx.y == 0) publish_status(offsets, B, N, status);
   const int dh = d / H;
   const int ne = (S * dh + kPer - 1) / kPer;
-  const int eb = blockIdx.x % ne, h = blockIdx.x / ne % H, b = blockIdx.x / ne / H;
+  const int eb = blockIdx.y % ne, h = blockIdx.y / ne, b = blockIdx.x;
   const int rg = threadIdx.x / kPer, el = threadIdx.x % kPer;
   const bool live = eb * kPer + el < S * dh;
   const int e = live ? eb * kPer + el : S * dh - 1;
@@ -289,13 +290,12 @@ static hipError_t launch_merge(const SummarizeArgs& a, const float* partials, co
   const bool silu = d.attn == VISTA_ATTN_SILU;
   const bool wide = a.G / d.B >= 8;
   const int per = wide ? 64 : 256;
-  const int64_t blocks = int64_t(d.B) * d.H * ((int64_t(d.S) * (d.d / d.H) + per - 1) / per);
-  if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
+  const int blocks = d.H * ((d.S * (d.d / d.H) + per - 1) / per);       // at most 512 x 512 / 64 + H
   void (*kernel)(const float*, const int64_t*, int, int, int, int, int, int64_t, int64_t, T*, int*, const T*, int64_t,
                  const float*, const float*, float) =
       silu ? (wide ? merge_kernel<T, true, 4> : merge_kernel<T, true, 1>)
            : (wide ? merge_kernel<T, false, 4> : merge_kernel<T, false, 1>);
-  return launch(kernel, dim3(unsigned(blocks)), dim3(256), 0, a.stream, partials, a.offsets, d.B, d.S, d.d, d.H, a.seg,
+  return launch(kernel, dim3(unsigned(d.B), unsigned(blocks)), dim3(256), 0, a.stream, partials, a.offsets, d.B, d.S, d.d, d.H, a.seg,
                 a.offsets_checked ? -1 : d.total_items, a.G, static_cast<T*>(a.out), status, static_cast<const T*>(a.Q),
                 d.q_user_stride, Ks, Vs, silu ? a.scale_plain : a.scale_log2);
 }
