@@ -447,9 +447,10 @@ hipError_t f32_history(const SummarizeArgs& a, float* partials) {
   return silu ? launch_history_dt<float, true>(p, a.G, a.stream) : launch_history_dt<float, false>(p, a.G, a.stream);
 }
 
+// (a wave per unit, and the runtime takes fewer than 2^32 threads: beyond, one thread per candidate and head)
 bool f32_candidates_supported(const vista_attend_desc& d, const void* cand, const void* summ, const void* out) {
   return d.d / d.H % 16 == 0 && aligned4(d.dtype, cand) && aligned4(d.dtype, summ) && aligned4(d.dtype, out) &&
-         int64_t(d.B) * d.H * ((d.C + 15) / 16) <= 0x7FFFFFFF;
+         int64_t(d.B) * d.H * ((int64_t(d.C) + 15) / 16) * 64 <= 0xFFFFFFFF;
 }
 
 hipError_t f32_candidates(const vista_attend_desc& d, float scale_log2, const void* cand, const void* summ, void* out,

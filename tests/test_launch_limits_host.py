@@ -60,3 +60,9 @@ def call(stub, entry, **kw):
 def test_merge_of_many_outputs(stub, kw):
     st, launches, refused = call(stub, "summarize", **kw)
     assert (st, refused) == (0, 0) and launches >= 2
+
+
+# stage 2 outside the bf16 shapes: a wave for 16 candidates of a head
+@pytest.mark.parametrize("kw", [dict(B=1 << 16, C=1 << 15, S=16, d=16, H=1, dtype=1), dict(B=1 << 12, C=1 << 17, S=16, d=64, H=4, dtype=0)])
+def test_many_candidates(stub, kw):
+    assert call(stub, "attend", **kw) == [0, 1, 0]
