@@ -1180,7 +1180,8 @@ vista_status generic_quantize(const vista_codec_desc& d, const void* y, int8_t* 
   const int64_t blocks = (groups + 127) / 128;
   if (blocks > 0x7FFFFFFF) return VISTA_ERR_UNSUPPORTED;
   const int dh = d.d / d.H;
-  if ((dh == 8 || dh == 16 || dh == 32 || dh == 64) && groups <= (int64_t(1) << 32) &&
+  // dh / 8 threads a group, of which the runtime takes fewer than 2^32: beyond, one thread a group
+  if ((dh == 8 || dh == 16 || dh == 32 || dh == 64) && (groups * (dh / 8) + 255) / 256 * 256 <= 0xFFFFFFFF &&
       (reinterpret_cast<uintptr_t>(y) & 15) == 0 && (reinterpret_cast<uintptr_t>(codes) & 7) == 0) {
     const hipError_t e = d.dtype == VISTA_BF16 ? launch_quantize8(d, static_cast<const bf16_t*>(y), codes, scales, s)
                                                : launch_quantize8(d, static_cast<const float*>(y), codes, scales, s);

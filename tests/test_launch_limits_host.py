@@ -66,3 +66,10 @@ def test_merge_of_many_outputs(stub, kw):
 @pytest.mark.parametrize("kw", [dict(B=1 << 16, C=1 << 15, S=16, d=16, H=1, dtype=1), dict(B=1 << 12, C=1 << 17, S=16, d=64, H=4, dtype=0)])
 def test_many_candidates(stub, kw):
     assert call(stub, "attend", **kw) == [0, 1, 0]
+
+
+# codec: one to eight threads for a (token, head)
+@pytest.mark.parametrize("kw", [dict(rows=1 << 28, d=128, H=4, dtype=1), dict(rows=1 << 26, d=512, H=8, dtype=0),
+                                dict(rows=(1 << 29) - 1, d=64, H=8, dtype=1)])
+def test_many_summary_rows(stub, kw):
+    assert call(stub, "quantize", **kw) == [0, 1, 0]
