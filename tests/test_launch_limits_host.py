@@ -70,6 +70,6 @@ def test_many_candidates(stub, kw):
 
 # codec: one to eight threads for a (token, head)
 @pytest.mark.parametrize("kw", [dict(rows=1 << 28, d=128, H=4, dtype=1), dict(rows=1 << 26, d=512, H=8, dtype=0),
-                                dict(rows=(1 << 29) - 1, d=64, H=8, dtype=1)])
+                                dict(rows=(1 << 29) - 32, d=64, H=8, dtype=1)])
 def test_many_summary_rows(stub, kw):
     assert call(stub, "quantize", **kw) == [0, 1, 0]
