@@ -314,7 +314,7 @@ def main() -> None:
         "vs_baseline": None, "dtype": "bf16", "data": "synthetic",
         "config": {"workload": "stage-1 jagged batch: 64 users, lognormal lengths (median 8k, [1k,100k]), "
                                "d=128, 4 heads, S=256, bf16", "total_items": N,
-                   "segment_items": V.vista_summarize_segment_items(desc1)},
+                   "segment_items": V.vista_summarize_call_segment_items(desc1)},
         "roofline": mfma_roofline(
             flop_item, items_per_s, cal, traffic=traffic.get("summarize_mfma"),
             traffic_source="profiles/hbm_traffic_pmc.txt (default segment size)" if traffic else None,
@@ -436,7 +436,7 @@ def main() -> None:
         ips3 = N3 / (ms3 * 1e-3)
         res["lifelong"] = {"value": ips3, "unit": "items/s", "ms_per_step": ms3, "ms_per_step_median": med3, "steps": few,
                            "config": {"workload": "stage-1 lifelong: 8 users x 1,000,000 items, d=128, 4 heads, S=256, bf16",
-                                      "total_items": N3, "segment_items": V.vista_summarize_segment_items(d3)},
+                                      "total_items": N3, "segment_items": V.vista_summarize_call_segment_items(d3)},
                            "roofline": mfma_roofline(flop_item, ips3, cal)}
         del X3, o3, w3
         torch.cuda.empty_cache()

@@ -95,28 +95,45 @@ typedef struct {
  * a segment is processed by one workgroup and is further cut at user
  * boundaries into pieces.  Piece (g, b) -- the rows of user b inside segment g
  * -- writes its running maximum, sum of exponentials and un-normalised output
- * to partial slot g + b; a merge pass combines a user's slots in an order fixed
- * by their count alone (ascending g; the quasi-linear form adds four interleaved
- * ascending sub-sums).  The schedule is a pure function of (offsets,
- * segment_items), never of the device, so results are bitwise reproducible.
+ * to partial slot g + b; a merge pass combines a user's slots in a fixed order:
+ * ascending g, or four ascending runs of them combined in ascending order where
+ * that keeps the device busier (the quasi-linear form adds four interleaved
+ * ascending sub-sums).  The schedule is a pure function of (offsets, segment
+ * size), never of the device, and the segment size one of the descriptor, of
+ * whether the workspace has the stated size and of whether the pointers are
+ * aligned as the path wants them: equal calls give equal bits.
  *
- * vista_summarize_segment_items: the segment size the call will use
- * (desc->segment_items, or the default derived from total_items and the
- * attention form alone: the history is cut into 256 k equal segments, k the
- * smallest count that keeps a segment at or below 8192 items -- 1024 k segments
- * of at most 2048 items for VISTA_ATTN_QLA, whose workgroups are small; at
- * least 256 items); 0 if the descriptor is invalid.  Where the size is left open
- * (segment_items = 0) the matrix-core paths fit their segments to the launch instead
- * (multiples of 32 up to 32768 items, a function of the descriptor alone); a size
- * that is given is always kept.
+ * vista_summarize_segment_items: the base segment size (desc->segment_items, or
+ * the default derived from total_items and the attention form alone: the history
+ * is cut into 256 k equal segments, k the smallest count that keeps a segment at
+ * or below 8192 items -- 1024 k segments of at most 2048 items for
+ * VISTA_ATTN_QLA, whose workgroups are small; at least 256 items); 0 if the
+ * descriptor is invalid.  A size that is given is always kept.
+ *
+ * vista_summarize_call_segment_items: the segment size the call uses.  Where the
+ * size is left open (segment_items = 0) the matrix-core paths fit their segments
+ * to the launch instead of taking the base size (multiples of 32 up to 32768
+ * items, a function of the descriptor alone); a workspace smaller than
+ * vista_summarize_workspace_bytes states, or a pointer the path's loads do not
+ * take (see "Supported" below), brings the base size back.  workspace_bytes: what
+ * the call is going to be given, 0 for the stated size.  Returns 0 if the
+ * descriptor is invalid or the workspace too small.  With a workspace of the
+ * stated size, a call with desc->segment_items set to the returned size is the
+ * same call bit for bit.
  */
 int32_t vista_summarize_segment_items(const vista_summarize_desc* desc);
+int32_t vista_summarize_call_segment_items(const vista_summarize_desc* desc, size_t workspace_bytes);
 
 /*
- * The schedule itself, computed on the host by the very code the kernels run
- * (App. B: blocks of the history are summed first, in any grouping; this is the
- * grouping).  Every segment is walked as a stream of tiles of at most 32 rows;
- * a tile never spans two users.  Writes up to max_tiles records
+ * The schedule at the base segment size, computed on the host by the very code
+ * the kernels run (App. B: blocks of the history are summed first, in any
+ * grouping; this is the grouping).  For the schedule of a call whose size is left
+ * open, set desc->segment_items to vista_summarize_call_segment_items.  Every
+ * segment is walked as a stream of tiles of at most 32 rows; a tile never spans
+ * two users.  (That is the walk of the bf16 matrix-core paths.  The other paths
+ * cut the same pieces at the same places and keep the same slots, but take a
+ * piece item by item, or 64 rows at a time counted from the segment's first,
+ * leaving other users' rows out.)  Writes up to max_tiles records
  *     tiles[4 i + 0..3] = { segment, user, first flat row, rows in the tile (1..32) }
  * in the order the kernels visit them and returns the total number of tiles
  * (which may exceed max_tiles; pass max_tiles = 0, tiles = NULL to count), or -1
@@ -164,7 +181,7 @@ size_t vista_summarize_workspace_bytes(const vista_summarize_desc* desc);
  * The workspace grows with the user count as well as with the history: the MFMA
  * path keeps (G + B) partial records of H * S * 144 bytes (G = segments; S rounded
  * up to 32), the plain path the same count of H * S * (d/H + 2) * 4 bytes plus fp32
- * K and V.  A workspace that holds what the segments of
+ * K and V.  A workspace that holds what the base segments of
  * vista_summarize_segment_items take (on the plain path, outside the MFMA seed
  * counts) is accepted even where the stated size is larger: the call then uses those.
  */

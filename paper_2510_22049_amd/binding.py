@@ -28,6 +28,7 @@ VISTA_FLAG_SELF_TERM = 1
 EXPORTS = (
     "vista_status_string",
     "vista_summarize_segment_items",
+    "vista_summarize_call_segment_items",
     "vista_summarize_workspace_bytes",
     "vista_summarize_schedule",
     "vista_summarize",
@@ -87,6 +88,8 @@ def lib() -> C.CDLL:
     L.vista_status_string.argtypes = [C.c_int]
     L.vista_summarize_segment_items.restype = C.c_int32
     L.vista_summarize_segment_items.argtypes = [C.POINTER(SummarizeDesc)]
+    L.vista_summarize_call_segment_items.restype = C.c_int32
+    L.vista_summarize_call_segment_items.argtypes = [C.POINTER(SummarizeDesc), C.c_size_t]
     L.vista_summarize_workspace_bytes.restype = C.c_size_t
     L.vista_summarize_workspace_bytes.argtypes = [C.POINTER(SummarizeDesc)]
     L.vista_summarize_schedule.restype = C.c_int64
@@ -143,6 +146,10 @@ def summarize_desc(B, S, d, H, dtype, total_items, per_user_q=False, scale=0.0, 
 
 def vista_summarize_segment_items(desc: SummarizeDesc) -> int:
     return lib().vista_summarize_segment_items(C.byref(desc))
+
+
+def vista_summarize_call_segment_items(desc: SummarizeDesc, workspace_bytes: int = 0) -> int:
+    return lib().vista_summarize_call_segment_items(C.byref(desc), workspace_bytes)
 
 
 def vista_summarize_workspace_bytes(desc: SummarizeDesc) -> int:

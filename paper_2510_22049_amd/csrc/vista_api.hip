@@ -137,6 +137,14 @@ int32_t vista_summarize_segment_items(const vista_summarize_desc* desc) {
   return resolve_segment(desc);
 }
 
+int32_t vista_summarize_call_segment_items(const vista_summarize_desc* desc, size_t workspace_bytes) {
+  if (check_summarize_desc(desc) != VISTA_OK) return 0;
+  const Work best = best_work(*desc), base = base_work(*desc);
+  if (workspace_bytes == 0 || workspace_bytes >= (best.need > base.need ? best.need : base.need)) return best.seg;
+  if (workspace_bytes < base.need) return 0;
+  return workspace_bytes >= best.need ? best.seg : base.seg;
+}
+
 int64_t vista_summarize_schedule(const vista_summarize_desc* desc, const int64_t* offsets_host, int64_t* tiles,
                                  int64_t max_tiles) {
   if (check_summarize_desc(desc) != VISTA_OK || !offsets_host || max_tiles < 0 || (max_tiles > 0 && !tiles))

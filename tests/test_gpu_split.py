@@ -224,3 +224,25 @@ def test_a_weight_that_is_not_finite_stays_in_its_column(form, d, H, S, self_ter
     one_ulp = 2.0 ** -7 * np.abs(before) + 1e-5 * np.abs(before).max(axis=(1, 2), keepdims=True)
     assert np.all(np.abs(got - before)[:, :, rest] <= (one_ulp[:, :, rest] if S == 40 and form == V.VISTA_ATTN_SOFTMAX else 0.0))
     assert not np.any(np.isfinite(got[[0, 2]][:, :, c]))
+
+
+@pytest.mark.parametrize("form,dtype,d,H,S,n", [
+    (V.VISTA_ATTN_SOFTMAX, "bf16", 128, 4, 256, 7001), (V.VISTA_ATTN_SILU, "bf16", 256, 8, 128, 3000), (V.VISTA_ATTN_SOFTMAX, "bf16", 64, 2, 40, 5000),
+    (V.VISTA_ATTN_QLA, "bf16", 128, 4, 40, 5000), (V.VISTA_ATTN_SOFTMAX, "f32", 64, 1, 16, 1024), (V.VISTA_ATTN_SILU, "f32", 40, 2, 16, 1024)])
+def test_the_reported_segment_size_is_the_one_used(form, dtype, d, H, S, n):
+    """With that size given the call writes the same workspace, records and all (another size puts them elsewhere)."""
+    X, off, Q, Wk, Wv = problem(n, d, S, lens=[n - 90, 0, 90])
+    desc = lambda seg: V.summarize_desc(3, S, d, H, V.VISTA_BF16 if dtype == "bf16" else V.VISTA_F32, n, attn=form, segment_items=seg)
+    used = V.vista_summarize_call_segment_items(desc(0))
+    bytes_ = max(V.vista_summarize_workspace_bytes(desc(0)), V.vista_summarize_workspace_bytes(desc(used)))
+
+    def call(seg):
+        ws = torch.zeros(bytes_, dtype=torch.uint8, device="cuda")
+        out = torch.empty((3, S, d), device="cuda", dtype=torch.bfloat16 if dtype == "bf16" else torch.float32)
+        V.vista_summarize(dev(X, dtype), torch.from_numpy(off).cuda(), dev(Q, dtype), dev(Wk, dtype), dev(Wv, dtype), out, H=H,
+                          segment_items=seg, workspace=ws, attn=form)
+        return ws, out
+
+    (ws0, out0), (ws1, out1) = call(0), call(used)
+    assert torch.equal(ws0, ws1) and torch.equal(out0, out1)
+    assert not torch.equal(ws0, call(used + 32)[0])

@@ -1,5 +1,6 @@
-"""Host-only checks of the split-L schedule (integer work, bit-exact): the tile walk the kernels
-run, reported by vista_summarize_schedule, against a brute-force statement of the same schedule."""
+"""Host-only checks of the split-L schedule (integer work, bit-exact): the tile walk of the streaming
+kernels, reported by vista_summarize_schedule, against a brute-force statement of the same schedule at
+the base segment size and at the one a call uses."""
 import numpy as np
 import pytest
 
@@ -98,3 +99,28 @@ def test_schedule_rejects_bad_arguments():
     assert L.vista_summarize_schedule(C.byref(d_), ptr, None, 5) == -1
     assert L.vista_summarize_schedule(C.byref(desc(0, 100)), ptr, None, 0) == -1
     assert L.vista_summarize_schedule(C.byref(d_), ptr, None, 0) == 4        # 50 rows = 2 tiles per user
+
+
+@pytest.mark.parametrize("kw,base,call", [
+    (dict(B=64, N=768597), 3008, 3008),
+    (dict(B=8, N=8_000_000), 7840, 31264),                       # 256 segments instead of 1024
+    (dict(B=1, N=7001), 256, 128),
+    (dict(B=256, N=14_026_438, S=512, d=256, H=8), 7840, 31328), # 448 segments of four head groups: seven turns of 256
+    (dict(B=8, N=8_000_000, seg=4096), 4096, 4096)])
+def test_the_segment_size_a_call_uses(kw, base, call):
+    d_ = desc(**kw)
+    assert V.vista_summarize_segment_items(d_) == base
+    assert V.vista_summarize_call_segment_items(d_) == call
+    stated = V.vista_summarize_workspace_bytes(d_)
+    assert V.vista_summarize_call_segment_items(d_, stated) == call
+    least = V.vista_summarize_workspace_bytes(desc(**{**kw, "seg": base}))
+    assert V.vista_summarize_call_segment_items(d_, least) == (base if least < stated else call)
+    assert V.vista_summarize_call_segment_items(d_, least - 1) == 0
+    off = np.linspace(0, kw["N"], kw["B"] + 1).astype(np.int64)
+    given = desc(**{**kw, "seg": call})
+    assert np.array_equal(V.vista_summarize_schedule(given, off), brute_force_tiles(off, call))
+
+
+def test_the_segment_size_of_an_invalid_call():
+    assert V.vista_summarize_call_segment_items(desc(0, 100)) == 0
+    assert V.vista_summarize_call_segment_items(desc(2, 100), 1) == 0
