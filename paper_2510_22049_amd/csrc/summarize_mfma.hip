@@ -1193,9 +1193,12 @@ static hipError_t launch_main(MfmaSummarizeParams& p, int wph, int64_t G, hipStr
 template <int ATTN>
 static hipError_t launch_for_shape(MfmaSummarizeParams& p, int d, int64_t G, hipStream_t s) {
   if (d == 128) {
-    // SiLU at S = 128: its two transcendentals a score leave the vector unit the bound, and sixteen waves of
-    // one block each feed it better than eight of two (115 -> 108 us; softmax the other way, 87 -> 92)
-    if (ATTN == VISTA_ATTN_SILU && p.nqb == 4) return launch_main<128, 1, 4, 8, true, false, 1024, ATTN>(p, 4, G, s);
+    // SiLU's two transcendentals a score leave the vector unit the bound: one block a wave feeds it better than
+    // two, sixteen waves of them at S = 128 (115 -> 108 us over 500 003 items; softmax the other way, 87 -> 92;
+    // at S = 64 eight waves hold one block each as it is).  Sixteen waves of two blocks lose to eight of four:
+    // 149 -> 182 us at S = 256, 251 -> 281 at 512; at d = 256 364 -> 361 and, S = 512, 337 -> 356.
+    if constexpr (ATTN == VISTA_ATTN_SILU)
+      if (p.nqb == 4) return launch_main<128, 1, 4, 8, true, false, 1024, ATTN>(p, 4, G, s);
     if (p.nqb <= 2) return launch_main<128, 1, 4, 8, true, false, 512, ATTN>(p, 2, G, s);
     if (p.nqb <= 4) return launch_main<128, 2, 4, 8, true, false, 512, ATTN>(p, 2, G, s);
     if (p.nqb <= 8) return launch_main<128, 4, 4, 8, true, false, 512, ATTN>(p, 2, G, s);
