@@ -1,4 +1,5 @@
-"""GPU parity of the plain fp32-ALU path against the CPU oracle, through the C ABI."""
+"""GPU parity of the shapes outside the fixed bf16 ones against the CPU oracle, through the C ABI: the fp32 matrix
+kernels, split operands for bf16 softmax of d = 64, H = 2, the plain gated block."""
 import numpy as np
 import pytest
 import torch

@@ -48,7 +48,8 @@ def run(form, X, off, Q, Wk, Wv, H, dtype, self_term=False, **kw):
                                             ("softmax", True)])
 @pytest.mark.parametrize("H,d,S,per_user", [(2, 64, 24, False), (4, 64, 40, True), (1, 48, 7, False)])
 def test_plain_path_forms(dtype, form, self_term, H, d, S, per_user):
-    """Empty, single-item, ragged and multi-segment users on the fp32-ALU kernels."""
+    """Empty, single-item, ragged and multi-segment users: SiLU and softmax on the fp32 matrix kernels (bf16 softmax of
+    d = 64, H = 2 on split operands), QLA on the plain ones."""
     X, off, Q, Wk, Wv = problem(H * 100 + S, LENS, d, S, dtype, per_user)
     got = run(form, X, off, Q, Wk, Wv, H, dtype, self_term, segment_items=64)
     want = oracle(form, X, off, Q, Wk, Wv, H, self_term)
@@ -451,3 +452,79 @@ def test_qla_backward_takes_an_element_aligned_d_out(dtype, d, H, S):
 
     for a, b in zip(grads(dO), grads(flat[1:].view(dO.shape))):
         assert torch.equal(a, b) and bool(torch.isfinite(a.float()).all())
+
+
+# sixteen waves of one query block each (the layout of this shape alone)
+@pytest.mark.parametrize("seg,per_user,self_term,qscale,scale", [
+    (0, False, False, 1.0, 0.0), (96, True, True, 1.0, 0.0), (32, False, True, 1.0, 0.2), (64, True, False, 12.0, 0.0)])
+def test_mfma_silu_form_on_sixteen_waves(seg, per_user, self_term, qscale, scale):
+    """Ragged tails, per-user seeds, the self term, scores of several hundred either way, a run of full tiles."""
+    X, off, Q, Wk, Wv = problem(35, LENS, 128, 128, "bf16", per_user, qscale)
+    got = run("silu", X, off, Q, Wk, Wv, 4, "bf16", self_term, segment_items=seg, scale=scale)
+    want = O.summarize_silu(X, off, Q, Wk, Wv, 4, scale=scale or None, self_term=self_term)
+    assert_blocks_close(got, want, "bf16", f"silu, sixteen waves, seg={seg} self={self_term} scale={scale}")
+    assert np.all(got[1] == 0) and np.all(got[8] == 0)
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_random_jagged_batches_on_sixteen_waves(seed):
+    g = np.random.default_rng(1100 + seed)
+    seg = int(g.choice([32, 64, 96, 256, 992]))
+    lens = random_lengths(g, seg)
+    per_user, self_term = bool(g.integers(0, 2)), bool(g.integers(0, 2))
+    X, off, Q, Wk, Wv = problem(2100 + seed, lens, 128, 128, "bf16", per_user=per_user)
+    got = run("silu", X, off, Q, Wk, Wv, 4, "bf16", self_term=self_term, segment_items=seg,
+              offsets_host=torch.from_numpy(off) if seed % 2 else None)
+    want = oracle("silu", X, off, Q, Wk, Wv, 4, self_term)
+    assert_blocks_close(got, want, "bf16", f"silu, sixteen waves, seed={seed} lens={lens} seg={seg}")
+
+
+# head widths that are no multiple of 16 (or 2-byte aligned pointers) are all that is left to one thread per query
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("form,self_term", [("softmax", False), ("softmax", True), ("silu", False), ("silu", True)])
+@pytest.mark.parametrize("H,d,S,per_user,seg", [(2, 40, 24, False, 64), (3, 72, 40, True, 32), (8, 64, 7, False, 0), (1, 20, 300, True, 0)])
+def test_one_thread_per_query(dtype, form, self_term, H, d, S, per_user, seg):
+    """Head widths 20, 24, 8: empty, single-item, ragged and multi-segment users, both merges."""
+    X, off, Q, Wk, Wv = problem(H * 100 + S, LENS, d, S, dtype, per_user)
+    got = run(form, X, off, Q, Wk, Wv, H, dtype, self_term, segment_items=seg)
+    want = oracle(form, X, off, Q, Wk, Wv, H, self_term)
+    assert_blocks_close(got, want, dtype, f"{form} self={self_term} {dtype}")
+    assert np.all(got[1] == 0) and np.all(got[8] == 0)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("form,self_term", [("softmax", False), ("softmax", True), ("silu", False), ("silu", True)])
+@pytest.mark.parametrize("H,d,S", [(2, 64, 24), (1, 48, 65), (2, 40, 24)])
+@pytest.mark.parametrize("lens", [[32 * 9 + 5], [32 * 40, 3, 700], [1, 32 * 33 - 1]])
+def test_merge_in_four_runs(dtype, form, self_term, H, d, S, lens):
+    """Eight or more segments a user on average: four threads share an element; runs of unequal length and,
+    for short users, empty ones."""
+    if form == "softmax" and dtype == "bf16" and (d, H) == (64, 2):
+        H = 4                                        # (64, 2) has a path of its own
+    X, off, Q, Wk, Wv = problem(len(lens) + S, lens, d, S, dtype)
+    got = run(form, X, off, Q, Wk, Wv, H, dtype, self_term, segment_items=32)
+    assert_blocks_close(got, oracle(form, X, off, Q, Wk, Wv, H, self_term), dtype, f"{form} self={self_term} {dtype} {lens}")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("H,d", [(4, 32), (8, 128), (2, 64), (8, 512), (3, 72), (2, 192)])     # heads of 8, 16, 32, 64; 24 and 96 (refused)
+@pytest.mark.parametrize("rows,shift", [(1, 0), (37, 0), (600, 0), (37, 1)])
+def test_codec_at_every_head_width(dtype, H, d, rows, shift):
+    """Codes and scales equal the oracle's bit for bit; groups of zeros, of one entry, and ties; aligned and not."""
+    g = np.random.default_rng(rows + d)
+    y = I.round_to((g.normal(size=(rows, d)) * np.exp(g.normal(size=(rows, 1)) * 3)).astype(np.float32), dtype)
+    y[0, : d // H] = 0.0
+    y[-1, d // H:] = 0.0
+    y[-1, -1] = -3.0
+    flat = torch.zeros(y.size + shift, device="cuda", dtype=torch_dtype(dtype))
+    flat[shift:].copy_(dev(y, dtype).flatten())
+    codes = torch.full((rows * d + shift,), 99, device="cuda", dtype=torch.int8)
+    scales = torch.full((rows, H), float("nan"), device="cuda")
+    if d // H > 64:
+        with pytest.raises(V.VistaError):
+            V.vista_quantize_summaries(flat[shift:].view(rows, d), codes[shift:].view(rows, d), scales, H=H)
+        return
+    V.vista_quantize_summaries(flat[shift:].view(rows, d), codes[shift:].view(rows, d), scales, H=H)
+    wc, ws = O.quantize_summaries(y, H)
+    assert np.array_equal(codes[shift:].view(rows, d).cpu().numpy(), wc) and np.array_equal(scales.cpu().numpy(), ws)
+    assert shift == 0 or int(codes[0]) == 99
