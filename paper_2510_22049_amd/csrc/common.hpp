@@ -28,6 +28,9 @@ __device__ __forceinline__ void store_as(float* p, float v) { *p = v; }
 __device__ __forceinline__ void store_as(bf16_t* p, float v) { p->bits = f32_to_bf16_bits(v); }
 
 constexpr float kLog2e = 1.4426950408889634f;
+// A running maximum starts here and not at minus infinity: a tile or segment whose scores are all minus
+// infinity then weighs nothing (2^(-inf - lowest) = 0), where -inf - (-inf) would be NaN.
+constexpr float kLowest = -3.402823466e38f;
 constexpr int kHeaderBytes = 256;  // workspace header: int32 device status at byte 0
 // Workspace layout of vista_summarize: [header 256 B][seg_user int32[G], padded to 256 B][path-specific data]
 __host__ __device__ inline size_t plan_bytes(int64_t G) { return (size_t(G) * sizeof(int) + 255) & ~size_t(255); }

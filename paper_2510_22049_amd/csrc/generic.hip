@@ -216,7 +216,7 @@ __global__ __launch_bounds__(256) void merge_kernel(const float* __restrict__ pa
   const int64_t run = (g1 - g0 + RG) / RG;
   const int64_t r0 = g0 + rg * run;
   const int64_t r1 = g1 < r0 + run - 1 ? g1 : r0 + run - 1;
-  float m = -INFINITY, l = 0.f, o = 0.f;
+  float m = kLowest, l = 0.f, o = 0.f;
   for (int64_t g = r0; g <= r1; g += kBatch) {
     float v[kBatch][3];
 #pragma unroll
@@ -253,7 +253,7 @@ __global__ __launch_bounds__(256) void merge_kernel(const float* __restrict__ pa
         o += o2;
         continue;
       }
-      const float mn = fmaxf(m, m2);                                // run 0 is never empty: finite
+      const float mn = fmaxf(m, m2);
       const float keep = exp2f(m - mn), w = exp2f(m2 - mn);
       l = fmaf(l2, w, l * keep);
       o = fmaf(o2, w, o * keep);

@@ -97,7 +97,7 @@ __global__ __launch_bounds__(256) void history_f32_kernel(HistoryParams p) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       l[u] = 0.f;
-      m[u] = SILU ? 0.f : -INFINITY;
+      m[u] = SILU ? 0.f : kLowest;
 #pragma unroll
       for (int n = 0; n < DT; ++n) o[u][n] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
@@ -236,7 +236,7 @@ __global__ __launch_bounds__(256) void history_f32_kernel(HistoryParams p) {
             }
           top = fmaxf(top, __shfl_xor(top, 16, 64));
           top = fmaxf(top, __shfl_xor(top, 32, 64));
-          const float mn = fmaxf(m[u], top), alpha = exp2f(m[u] - mn);   // 0 on the first tile (m = -inf)
+          const float mn = fmaxf(m[u], top), alpha = exp2f(m[u] - mn);   // 0 on the first tile (m lowest)
           m[u] = mn;
           l[u] *= alpha;
 #pragma unroll
@@ -295,7 +295,7 @@ __global__ __launch_bounds__(64) void candidates_f32_kernel(const T* __restrict_
   f32x4 o[DT];
 #pragma unroll
   for (int n = 0; n < DT; ++n) o[n] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m = -INFINITY, l = 0.f;
+  float m = kLowest, l = 0.f;
   for (int j0 = 0; j0 < S; j0 += 64) {
     f32x4 s[4];
 #pragma unroll

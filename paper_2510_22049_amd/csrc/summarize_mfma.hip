@@ -662,7 +662,7 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
     const bool general = mode == 2 || unsafe;
     if (mode != 2) {   // the reference so far: nothing (fresh piece) or the constant 0
 #pragma unroll
-      for (int qb = 0; qb < NQB; ++qb) m[qb] = (general && mode == 0) ? -INFINITY : 0.f;
+      for (int qb = 0; qb < NQB; ++qb) m[qb] = (general && mode == 0) ? kLowest : 0.f;
     }
     mode = general ? 2 : 1;
     const bool masked = nvalid < kTile;
@@ -935,7 +935,7 @@ __global__ __launch_bounds__(256) void merge_mfma_kernel(const float* __restrict
   // One pass with a running maximum (rescale when it moves); loads are issued kBatch
   // records at a time so a long user is not a chain of dependent round trips.
   constexpr int kBatch = RG > 1 ? 4 : 8;
-  float m = -INFINITY, l = 0.f, o0 = 0.f, o1 = 0.f, o2 = 0.f, o3 = 0.f;
+  float m = kLowest, l = 0.f, o0 = 0.f, o1 = 0.f, o2 = 0.f, o3 = 0.f;
   const int64_t run = (g1 - g0 + RG) / RG;                  // records per group
   const int64_t r0 = g0 + rg * run;
   if (g1 > r0 + run - 1) g1 = r0 + run - 1;
@@ -964,7 +964,7 @@ __global__ __launch_bounds__(256) void merge_mfma_kernel(const float* __restrict
         continue;
       }
       const float mn = fmaxf(m, v[u][0]);
-      const float keep = exp2f(m - mn);       // 0 on the first record (m = -inf), 1 while the maximum stands
+      const float keep = exp2f(m - mn);       // 0 on the first record (m lowest), 1 while the maximum stands
       const float wgt = exp2f(v[u][0] - mn);  // 0 for the padding entries
       l = fmaf(v[u][1], wgt, l * keep);
       o0 = fmaf(v[u][2], wgt, o0 * keep);
@@ -987,8 +987,8 @@ __global__ __launch_bounds__(256) void merge_mfma_kernel(const float* __restrict
       float keep = 1.f, wgt = 1.f;
       if (!SILU) {
         const float mn = fmaxf(m, x[0]);
-        keep = exp2f(m - mn);               // group 0 is never empty: mn is finite
-        wgt = exp2f(x[0] - mn);             // 0 for an empty group (m = -inf)
+        keep = exp2f(m - mn);
+        wgt = exp2f(x[0] - mn);             // 0 for an empty group (m lowest)
         m = mn;
       }
       l = fmaf(x[64], wgt, l * keep);

@@ -246,3 +246,24 @@ def test_the_reported_segment_size_is_the_one_used(form, dtype, d, H, S, n):
     (ws0, out0), (ws1, out1) = call(0), call(used)
     assert torch.equal(ws0, ws1) and torch.equal(out0, out1)
     assert not torch.equal(ws0, call(used + 32)[0])
+
+
+@pytest.mark.parametrize("dtype,d,H,S", [("f32", 64, 1, 16), ("f32", 96, 2, 200), ("bf16", 48, 1, 40), ("bf16", 64, 2, 40), ("bf16", 128, 4, 256),
+                                         ("bf16", 256, 8, 128)])
+@pytest.mark.parametrize("rows", [(64, 128), (128, 160), (0, 64), (128, 700)])
+@pytest.mark.parametrize("seg", [0, 64])
+def test_items_at_minus_infinity_leave_the_softmax(dtype, d, H, S, rows, seg):
+    """Whole tiles and whole segments of them, wherever the segment edges lie."""
+    g = np.random.default_rng(17)
+    L, dh = 700 + 97, d // H
+    r = lambda shape, s=1.0: I.round_to((g.normal(size=shape) * s).astype(np.float32), dtype)
+    X, Q, Wk, Wv = r((L + 50, d)), r((S, d)), r((d, d), d ** -0.5), r((d, d), d ** -0.5)
+    X[:, -1] = Wk[-1] = Wv[-1] = 0.0
+    Q[:, ::dh], Wk[-1, ::dh] = 1.0, -16.0                       # 2^127 in the last channel: every head's first key channel is -inf
+    X[rows[0]:rows[1], -1] = 2.0 ** 127
+    off, gone = np.array([0, L, L + 50]), rows[1] - rows[0]
+    out = torch.full((2, S, d), float("nan"), device="cuda", dtype=torch.float32 if dtype == "f32" else torch.bfloat16)
+    V.vista_summarize(dev(X, dtype), torch.from_numpy(off).cuda(), dev(Q, dtype), dev(Wk, dtype), dev(Wv, dtype), out, H=H, segment_items=seg)
+    want = O.summarize(np.delete(X, slice(*rows), axis=0), np.array([0, L - gone, L + 50 - gone]), Q, Wk, Wv, H)
+    # at fixed bf16 operands (S of 64, 128, 256, 512) the path's own tolerance, else that of fp32 sums
+    check(host64(out), want, (2e-2 if dtype == "bf16" and S in (128, 256) else 1e-4))
