@@ -177,11 +177,13 @@ size_t vista_summarize_workspace_bytes(const vista_summarize_desc* desc);
  * Supported: bf16 with (d, H) = (128, 4) or (256, 8), S in {64, 128, 256, 512} (MFMA path);
  * bf16 softmax with (d, H) = (64, 2), (128, 4) or (256, 8) and any other S (MFMA path whose K, V
  * and weights keep the 24 bits of fp32; history 16-byte, queries and out 8-byte aligned, else the
- * plain path); any dtype with d/H <= 64, d <= 512, S <= 512 (plain fp32-ALU path).
+ * plain path); any dtype with d/H <= 64, d <= 512, S <= 512 (softmax and SiLU at a head width that is
+ * a multiple of 16 on the fp32 matrix instructions, tensors aligned to four elements; else the plain
+ * path, one thread per query).
  * The workspace grows with the user count as well as with the history: the MFMA
  * path keeps (G + B) partial records of H * S * 144 bytes (G = segments; S rounded
- * up to 32), the plain path the same count of H * S * (d/H + 2) * 4 bytes plus fp32
- * K and V.  A workspace that holds what the base segments of
+ * up to 32), the other paths the same count of H * S * (d/H + 2) * 4 bytes, the plain
+ * one fp32 K and V as well.  A workspace that holds what the base segments of
  * vista_summarize_segment_items take (on the plain path, outside the MFMA seed
  * counts) is accepted even where the stated size is larger: the call then uses those.
  */
@@ -251,7 +253,9 @@ typedef struct {
  *   out         device [B, C, d]  dtype
  *
  * Supported: bf16 with d/H = 32, H even, S a multiple of 32 up to 256 or a multiple
- * of 64 up to 512 (MFMA path); any dtype with d/H <= 64, S <= 512 (plain path).
+ * of 64 up to 512 (MFMA path); any dtype with d/H <= 64, S <= 512 (at a head width that is a
+ * multiple of 16 on the fp32 matrix instructions, tensors aligned to four elements; else, and
+ * for int8 summaries, the plain path).
  * No workspace.
  */
 vista_status vista_target_attend(const vista_attend_desc* desc,

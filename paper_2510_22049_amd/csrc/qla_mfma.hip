@@ -298,8 +298,9 @@ __global__ __launch_bounds__(D * 2, 2) void qla_state_mfma_kernel(QlaParams p) {
 
   for (;;) {
     // Tiles while the tile being requested is a full one of the same piece: no cursor in the loop (its
-    // branches and state moves took 490 clocks of a wave's 2330 per tile; with three waves on a SIMD most of
-    // that was hidden, 72.4 -> 71.5 us over the jagged batch).
+    // branches and state moves took 490 clocks of a wave's 2330 per tile; the other waves of the SIMD hide
+    // most of that at d = 128: 74.3 -> 73.2 us over the jagged batch, 240 -> 236 over 3 M items; at d = 256
+    // 518 -> 497 over 2 M).
     const int run = cf.straight(ca);
     const char* base = reinterpret_cast<const char*>(p.X) + cf.row * (D * 2);
     for (int n = 0; n < run; ++n) {
@@ -541,8 +542,8 @@ static int64_t items_workgroups(int d) { return d == 128 ? 512 : 256; }
 
 // The history in equal segments, one for each of `workgroups` or a small multiple of them: a multiple of 32,
 // 128 to `most` items.  At D = 256 a workgroup's set-up is long enough that four segments apiece, or
-// one more than others, showed: 300 000 items 107.8 us with 1024 segments, 91.2 with 256, their
-// gradients (200 000 items) 230 and 179 us; at D = 128 (1024 against 768) within 2 %.
+// one more than others, showed: 300 000 items 120 us in 938 segments, 101 in 256, their gradients
+// (200 000 items) 204 and 180 us; at D = 128 (1024 against 768) within 2 %.
 static int even_segment(int64_t N, int64_t workgroups, int64_t most) {
   int64_t k = (N + workgroups * most - 1) / (workgroups * most);
   if (k < 1) k = 1;

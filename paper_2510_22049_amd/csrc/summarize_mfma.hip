@@ -766,8 +766,8 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
   bool plain = is_plain();
   for (;;) {
     // Plain tiles while the tile being requested is a full one of the same piece: no cursor in the loop.  Its
-    // branches and state moves, on every wave between two barriers, were 2 to 4 % of the time: 8 users of
-    // a million items 1616 -> 1551 us, two layers at d = 256 23.9 -> 22.8 ms, jagged batch 175 -> 172.
+    // branches and state moves are on every wave between two barriers; without this loop 8 users of a
+    // million items take 1720 us instead of 1652, two layers at d = 256 27.4 ms instead of 24.0.
     if (plain) {
       const int run = cf.straight(ca);
       const char* base = reinterpret_cast<const char*>(p.X) + cf.row * (D * 2);
@@ -1047,7 +1047,7 @@ __global__ __launch_bounds__(256) void merge_mfma_kernel(const float* __restrict
 // One wave forms 32 seeds x 32 channels of both, the seeds' rows read once as the A operand, the
 // weights 16 bytes a lane and turned by the matrix core as in the main kernel.  The whole of it is a
 // few launches' worth of latency: one thread per output walking 2-byte loads took 33 us for 128 seeds
-// of width 128, this takes 4.
+// of width 128, this takes 6.
 __global__ __launch_bounds__(256) void self_kv_mfma_kernel(const uint16_t* __restrict__ Q,
                                                            const uint16_t* __restrict__ Wk,
                                                            const uint16_t* __restrict__ Wv, float* __restrict__ Ks,
@@ -1154,10 +1154,10 @@ static int resident_workgroups(const vista_summarize_desc& d) {
 // Segment size of the matrix-core kernels where the caller leaves it open: the history is cut so that
 // the workgroups fill the chip k times, k the smallest count that keeps a segment at or below 32768
 // items, a multiple of 32, at least 128.  Longer segments mean fewer records to write and merge: 8
-// users of a million items (d = 128, S = 256) take 1641 us at this limit, 1655 at 16384 and 1683 at
-// 8192; two layers at d = 256, S = 512 over 14 M items 24.4, 24.8 and 25.0 ms.  Below 128 items a
-// workgroup's set-up and record outweigh its tiles: one user of 7001 items takes 35.1 us at 64, 30.5
-// at 96 and 29.0 at 128.
+// users of a million items (d = 128, S = 256) take 1650 us at this limit, 1669 at 16384 and 1704 or more
+// at 8192; one layer at d = 256, S = 512 over 14 M items 11.9, 12.0 and 12.25 ms.  Below 128 items a
+// workgroup's set-up and record outweigh its tiles: one user of 7001 items takes 29.0 us at 64, 27.1
+// at 96 and 26.6 at 128.
 int mfma_summarize_segment(const vista_summarize_desc& d) {
   const int64_t N = d.total_items;
   const int64_t units = 256 * resident_workgroups(d) / head_groups(d);

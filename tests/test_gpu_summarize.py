@@ -160,7 +160,7 @@ def test_mfma_is_bitwise_reproducible_and_isolated():
 
 
 def test_mfma_agrees_with_plain_path_on_gpu():
-    """Cross-check (not the oracle): the fp32-ALU kernels on the same bf16-representable inputs."""
+    """Cross-check (not the oracle): the fp32 matrix kernels on the same bf16-representable inputs."""
     X, off, Q, Wk, Wv = problem(7, [400, 90, 0, 800], 128, 256)
     got = run(X, off, Q, Wk, Wv, 4)
     out32 = torch.empty((4, 256, 128), device="cuda")
