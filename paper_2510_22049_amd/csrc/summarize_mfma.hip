@@ -5,8 +5,8 @@
 //   1. the X tile (32 x D bf16) goes from HBM straight into LDS (direct
 //      global->LDS loads, three tiles deep, no stop in registers);
 //   2. wave "K" of a pair forms K_h^T = (scale*log2e W_k,h)^T X^T, wave "V" forms
-//      V_h = X W_v,h -- eight 32x32x16 MFMAs each for D = 128, weights held in registers
-//      (as LDS operands at D = 256) -- and both hand the bf16 result to their partner through LDS;
+//      V_h = X W_v,h -- D / 16 32x32x16 MFMAs each, weights held in registers (as LDS operands
+//      only in the widest SPLIT shape) -- and both hand the bf16 result to their partner through LDS;
 //   3. each wave owns half of the S queries: for every block of 32 queries
 //      S^T = K_h Q_h^T (items x queries), p = 2^(s - m), O^T += V_h^T P^T.
 // With items on the MFMA row index and queries on the column index, every lane
@@ -17,7 +17,9 @@
 // the tiles of all pieces (user x segment) of the segment form one stream.
 // Where a pair would leave a wave with more than four query blocks (S = 512) or
 // with too few waves per compute unit (D = 256), a head gets more waves instead:
-// the K and V waves plus others that only attend, the queries shared by all.
+// the K and V waves plus others that only attend, the queries shared by all (at D = 256, S = 512
+// unevenly: two blocks to a projecting wave, whose weights take 64 registers, six to the others,
+// which comes to 24 MFMAs a tile for each of the four).
 // (Sixteen waves of two query blocks and 128 registers each, four to a SIMD, were 7 to 10 %
 // slower than eight of four: twice the operand reads from LDS and idle attend-only waves.)
 //
@@ -247,7 +249,10 @@ constexpr int kXBuf = 3;             // ring depth of the X tiles and of the pro
 constexpr int kvbuf_slots(bool split) { return split ? 2 : kXBuf; }
 
 // Shared memory of one workgroup.  WREG: a projecting wave keeps its D x 32 weight operands in
-// registers (D / 4 of them; it saves half of the operand reads of a projection) instead of in LDS.
+// registers (D / 4 of them) instead of in LDS, which halves the operand reads of a projection.  These
+// kernels run at the power the chip allows (MFMAs on random operands alone sustain 1724 of 2470
+// TFLOP/s), so LDS traffic saved is time: with the weights in LDS at D = 256, 32 users and 500 000
+// items took 242 us instead of 222 at S = 128 and 308 instead of 296 at S = 256.
 template <int D, int HPW, bool WREG, bool SPLIT>
 struct SummarizeLds {
   uint4 xbuf[kXBuf][(D / 8) * 32];    // X tiles: [16-byte chunk][item], filled by direct global->LDS loads
@@ -270,7 +275,7 @@ struct SummarizeLds {
 // product is t / (1 + 2^t) and the constant joins the 1/L_b of the merge.
 template <int D, int NQB, int HPW, int FW, bool WREG, bool SPLIT, bool ALLF, int ROLE, int ATTN>
 __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, SummarizeLds<D, HPW, WREG, SPLIT>& sm,
-                                               int64_t g, int h, int hl, int qslot, int64_t seg_begin,
+                                               int64_t g, int h, int hl, int qblock, int64_t seg_begin,
                                                int64_t seg_end) {
   constexpr bool PROJ = ROLE < 2;        // this wave projects
   constexpr bool SILU = ATTN == VISTA_ATTN_SILU;
@@ -368,7 +373,7 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
     }
   };
 
-  const int qbase = qslot * (NQB * 32);  // first query of this wave (qslot = ROLE when a head has two waves)
+  const int qbase = qblock * 32;         // first query of this wave
   bf16x8 qop[NQB][2];
   float qmax2 = 0.f;
   auto request_queries = [&](int user) __attribute__((always_inline)) {
@@ -425,14 +430,15 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
 
   f32x16 o[NQB];
   float l[NQB], m[NQB];
-  // plain tiles keep their share of the denominators in lacc (register qb of either accumulator);
+  // plain tiles keep their share of the denominators in lacc (register qb % 4 of either accumulator);
   // the general route folds it into l first
-  static_assert(NQB <= 4, "one accumulator register per query block");
   // (SPLIT adds its fp32 weights into l directly)
-  f32x4 lacc[2];
-  uint2 onesrow[NQB];
+  constexpr int NLA = (NQB + 3) / 4;     // pairs of accumulators: one register of each per query block
+  constexpr int NLR = NQB < 4 ? NQB : 4;
+  f32x4 lacc[NLA][2];
+  uint2 onesrow[NLR];
 #pragma unroll
-  for (int r = 0; r < NQB; ++r) {
+  for (int r = 0; r < NLR; ++r) {
     const uint32_t w = (lane & 3) == r ? 0x3F803F80u : 0u;
     onesrow[r] = make_uint2(w, w);
   }
@@ -445,7 +451,8 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
       l[qb] = 0.f;
       m[qb] = 0.f;
     }
-    lacc[0] = lacc[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int a = 0; a < NLA; ++a) lacc[a][0] = lacc[a][1] = f32x4{0.f, 0.f, 0.f, 0.f};
     mode = 0;
   };
 
@@ -607,20 +614,21 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
           pp.hi[i / 8].w[(i % 8) / 2] = cvt_pk_bf16(ea, eb);
       }
       // The denominator on the matrix core: a 4x4x4 product (16 blocks, one per four lanes)
-      // whose A block has ones in row qb adds a lane's own four packed weights into register
-      // qb of that lane -- the lane-local partial sum a chain of adds would form, taken over
+      // whose A block has ones in row qb % 4 adds a lane's own four packed weights into register
+      // qb % 4 of that lane -- the lane-local partial sum a chain of adds would form, taken over
       // the bf16 weights the numerator uses.  It issues like one plain vector instruction for four
       // weights; two accumulators take turns so that consecutive products do not wait for each
       // other.  (SPLIT: the fp32 weights are added as they are; three terms would be twelve products.)
       if constexpr (SPLIT) {
         l[qb] += lsum[0] + lsum[1];
       } else if constexpr (!SILU) {
-        const i16x4 sel = __builtin_bit_cast(i16x4, onesrow[qb]);
+        const i16x4 sel = __builtin_bit_cast(i16x4, onesrow[qb % 4]);
 #pragma unroll
         for (int part = 0; part < 4; ++part) {
           const Pack8& src = pp.hi[part / 2];
           const uint2 pw = make_uint2(src.w[2 * (part & 1)], src.w[2 * (part & 1) + 1]);
-          lacc[part & 1] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(sel, __builtin_bit_cast(i16x4, pw), lacc[part & 1], 0, 0, 0);
+          f32x4& a = lacc[qb / 4][part & 1];
+          a = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(sel, __builtin_bit_cast(i16x4, pw), a, 0, 0, 0);
         }
       }
       o[qb] = mma<SPLIT>(vv, pp, o[qb]);
@@ -636,8 +644,8 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
     if constexpr (!SPLIT) {
 #pragma unroll
       for (int qb = 0; qb < NQB; ++qb) {
-        l[qb] += lacc[0][qb] + lacc[1][qb];
-        lacc[0][qb] = lacc[1][qb] = 0.f;
+        l[qb] += lacc[qb / 4][0][qb % 4] + lacc[qb / 4][1][qb % 4];
+        lacc[qb / 4][0][qb % 4] = lacc[qb / 4][1][qb % 4] = 0.f;
       }
     }
     if constexpr (SILU) {
@@ -828,8 +836,9 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
 
 // MAXT: largest workgroup of the instantiation (it bounds the registers of a wave).  The first FW waves
 // fetch X (ALLF: that is every wave).
-template <int D, int NQB, int HPW, int FW, bool WREG, bool SPLIT, int MAXT, int ATTN>
-__global__ __launch_bounds__(MAXT) void summarize_mfma_kernel(MfmaSummarizeParams p) {
+// NQB query blocks to a projecting wave, NQA to one that only attends; OCC: waves of the kernel on a SIMD, at least.
+template <int D, int NQB, int NQA, int HPW, int FW, bool WREG, bool SPLIT, int MAXT, int ATTN, int OCC>
+__global__ __launch_bounds__(MAXT, OCC) void summarize_mfma_kernel(MfmaSummarizeParams p) {
   __shared__ SummarizeLds<D, HPW, WREG, SPLIT> sm;
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform, kept scalar
@@ -854,9 +863,9 @@ __global__ __launch_bounds__(MAXT) void summarize_mfma_kernel(MfmaSummarizeParam
   if (slot == 0)
     summarize_wave<D, NQB, HPW, FW, WREG, SPLIT, (!SPLIT && MAXT == 64 * FW), 0, ATTN>(p, sm, g, h, hl, 0, seg_begin, seg_end);
   else if (slot == 1)
-    summarize_wave<D, NQB, HPW, FW, WREG, SPLIT, (!SPLIT && MAXT == 64 * FW), 1, ATTN>(p, sm, g, h, hl, 1, seg_begin, seg_end);
+    summarize_wave<D, NQB, HPW, FW, WREG, SPLIT, (!SPLIT && MAXT == 64 * FW), 1, ATTN>(p, sm, g, h, hl, NQB, seg_begin, seg_end);
   else if constexpr (MAXT != HPW * 128)      // (two waves per head: there is no third slot)
-    summarize_wave<D, NQB, HPW, FW, WREG, SPLIT, (!SPLIT && MAXT == 64 * FW), 2, ATTN>(p, sm, g, h, hl, slot, seg_begin, seg_end);
+    summarize_wave<D, NQA, HPW, FW, WREG, SPLIT, (!SPLIT && MAXT == 64 * FW), 2, ATTN>(p, sm, g, h, hl, 2 * NQB + (slot - 2) * NQA, seg_begin, seg_end);
 }
 
 // Merge of a user's partial records in a fixed order, so the result is bitwise reproducible.
@@ -1148,7 +1157,8 @@ static int head_groups(const vista_summarize_desc& d) {
   return nqb > 8 ? d.H : d.H / 2;
 }
 static int resident_workgroups(const vista_summarize_desc& d) {
-  return mfma_split_supported(d) && d.d != 256 && d.S <= 128 ? 2 : 1;
+  if (mfma_split_supported(d)) return d.d != 256 && d.S <= 128 ? 2 : 1;
+  return d.d == 256 && d.S == 64 && d.total_items > 131072 ? 2 : 1;   // (two cold starts on a compute unit: 2048 items pay for them)
 }
 
 // Segment size of the matrix-core kernels where the caller leaves it open: the history is cut so that
@@ -1180,13 +1190,13 @@ size_t mfma_summarize_workspace(const vista_summarize_desc& d, int seg) {
   return kHeaderBytes + plan_bytes(G) + ((partial_bytes(d, seg) + 255) & ~size_t(255)) + 2 * self_kv_bytes(d);
 }
 
-template <int D, int NQB, int HPW, int FW, bool WREG, bool SPLIT, int MAXT, int ATTN>
+template <int D, int NQB, int HPW, int FW, bool WREG, bool SPLIT, int MAXT, int ATTN, int NQA = NQB, int OCC = MAXT / 256>
 static hipError_t launch_main(MfmaSummarizeParams& p, int wph, int64_t G, hipStream_t s) {
   p.wph = wph;
   p.nhg = p.H / HPW;
   const int64_t groups = (G + 7) / 8;
   const int64_t blocks = groups * 8 * p.nhg;
-  return launch(summarize_mfma_kernel<D, NQB, HPW, FW, WREG, SPLIT, MAXT, ATTN>, dim3(unsigned(blocks)),
+  return launch(summarize_mfma_kernel<D, NQB, NQA, HPW, FW, WREG, SPLIT, MAXT, ATTN, OCC>, dim3(unsigned(blocks)),
                 dim3(HPW * wph * 64), 0, s, p);
 }
 
@@ -1204,10 +1214,14 @@ static hipError_t launch_for_shape(MfmaSummarizeParams& p, int d, int64_t G, hip
     if (p.nqb <= 8) return launch_main<128, 4, 4, 8, true, false, 512, ATTN>(p, 2, G, s);
     return launch_main<128, 4, 2, 8, true, false, 512, ATTN>(p, 4, G, s);
   }
-  if (p.nqb <= 2) return launch_main<256, 1, 2, 4, false, false, 256, ATTN>(p, 2, G, s);
-  if (p.nqb <= 4) return launch_main<256, 1, 2, 8, false, false, 512, ATTN>(p, 4, G, s);
-  if (p.nqb <= 8) return launch_main<256, 2, 2, 8, false, false, 512, ATTN>(p, 4, G, s);
-  return launch_main<256, 4, 2, 8, false, false, 512, ATTN>(p, 4, G, s);
+  // Two workgroups of four waves on a compute unit: their barriers are not in step (209 -> 167 us over 500 000 items,
+  // SiLU form 143 -> 112 over 300 000; with the weights in LDS there was room for one).
+  if (p.nqb <= 2) return launch_main<256, 1, 2, 4, true, false, 256, ATTN, 1, 2>(p, 2, G, s);
+  if (p.nqb <= 4) return launch_main<256, 1, 2, 8, true, false, 512, ATTN>(p, 4, G, s);
+  if (p.nqb <= 8) return launch_main<256, 2, 2, 8, true, false, 512, ATTN>(p, 4, G, s);
+  // 2 + 2 + 6 + 6 blocks instead of four each, which leaves no registers for the weights: 421 -> 413 us over
+  // 500 000 items, two layers over 14 M items with the rest of the path 22.8 -> 22.35 ms.
+  return launch_main<256, 2, 2, 8, true, false, 512, ATTN, 6>(p, 4, G, s);
 }
 
 static hipError_t launch_split(MfmaSummarizeParams& p, int d, int64_t G, hipStream_t s) {
@@ -1223,7 +1237,7 @@ static hipError_t launch_split(MfmaSummarizeParams& p, int d, int64_t G, hipStre
     if (p.nqb <= 8) return launch_main<128, 2, 2, 4, true, true, 512, A>(p, w2, G, s);
     return launch_main<128, 2, 1, 4, true, true, 512, A>(p, w2, G, s);
   }
-  if (p.nqb <= 8) return launch_main<256, 1, 1, 4, false, true, 512, A>(p, w1, G, s);
+  if (p.nqb <= 8) return launch_main<256, 1, 1, 4, true, true, 512, A>(p, w1, G, s);
   return launch_main<256, 2, 1, 4, false, true, 512, A>(p, w2, G, s);
 }
 

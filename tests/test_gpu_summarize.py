@@ -211,3 +211,14 @@ def test_nothing_is_written_outside_out_and_the_stated_workspace():
         assert bool((raw[:pad] == 0xA5).all()) and bool((raw[pad + n_out:] == 0xA5).all()), "write outside out"
         assert bool((wraw[need:] == 0x5A).all()), "write beyond the stated workspace size"
         assert_blocks_close(host64(out), O.summarize(X, off, Q, Wk, Wv, H), dtype, "canary case")
+
+
+@pytest.mark.parametrize("S,block", [(512, 0), (512, 1), (512, 2), (512, 3), (512, 4), (512, 9), (512, 10), (512, 15), (256, 2), (128, 3), (64, 1)])
+def test_queries_of_one_block_beyond_the_bound(S, block):
+    """d = 256: the waves of a head hold unequal shares of the queries; the wave whose block leaves the score bound
+    takes the running maximum, the others do not, and every query gets its own result."""
+    X, off, Q, Wk, Wv = problem(40 + block, [900, 1, 33, 2047], 256, S)
+    Q[32 * block:32 * block + 32] *= 5.0          # exact in bf16 up to its rounding; |q| |k| passes 60, scores stay near 20
+    Q = bf(Q)
+    got = run(X, off, Q, Wk, Wv, 8, segment_items=960)
+    assert_blocks_close(got, O.summarize(X, off, Q, Wk, Wv, 8), "bf16", f"S={S} block={block}")
