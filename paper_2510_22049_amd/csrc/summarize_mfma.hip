@@ -43,6 +43,8 @@
 //
 // Each piece ends with one partial record (O, l, m) per head; merge_mfma_kernel
 // combines a user's records in ascending segment order.
+#include <math.h>
+
 #include "common.hpp"
 
 namespace vista {
@@ -1149,25 +1151,49 @@ bool mfma_split_supported(const vista_summarize_desc& d) {
   return (d.d == 64 && d.H == 2) || (d.d == 128 && d.H == 4) || (d.d == 256 && d.H == 8);
 }
 
+// Short histories go to workgroups of half the heads, so of half the waves.  A tile then takes one wave's time a
+// SIMD instead of two, and twice the workgroups find compute units idle; once they are all busy the rows are
+// merely fetched twice.  us a call, whole / half workgroups, few users: d = 128, S = 256, 7001 items 26.5 / 20.8,
+// 60 000 42.7 / 35.4, 200 000 65.8 / 61.8, 400 000 104 / 106; S = 64, 60 000 23.7 / 21.3, 140 000 30.0 / 29.6, 200 000 35.3 /
+// 36.2; S = 128, 100 000 33.9 / 31.4, 200 000 45.5 / 45.5; S = 512, 80 000 52.5 / 50.7, 200 000 92.2 / 95.4.  The SiLU form at
+// S = 128 has sixteen waves beyond: 60 000 29.4 / 28.4, 80 000 32.2 / 33.2.  At d = 256 a tile is twice the bytes and four groups of
+// heads share the chip as it is: S = 64, 7001 18.2 / 17.9, 15 000 21.4 / 23.1; S = 128, 15 000 24.6 / 22.8, 20 000 25.8 / 26.0; S = 256,
+// 15 000 31.4 / 28.8, 25 000 35.4 / 36.0; S = 512, 30 000 53.7 / 51.1, 45 000 62.1 / 62.2; SiLU, S = 128, 13 845 24.1 / 25.5.
+// A user costs its record and a ragged tile, about 128 items: 128 users of 15 000 items, d = 256, S = 256 54.1 / 61.1; of 225 000, d = 128,
+// S = 256 75.7 / 78.0.
+static bool short_history(const vista_summarize_desc& d) {
+  const bool silu = d.attn == VISTA_ATTN_SILU;
+  int64_t most;
+  if (d.d == 256)
+    most = d.S == 64 ? 8192 : d.S == 512 ? 32768 : silu ? 12288 : 16384;
+  else if (silu && d.S == 128)
+    most = 65536;
+  else
+    most = d.S == 256 ? 229376 : d.S == 512 ? 98304 : 131072;
+  return d.total_items + 128 * int64_t(d.B) <= most;
+}
+
 // Head groups (workgroups per segment) and workgroups resident on a compute unit, as launched below.
 static int head_groups(const vista_summarize_desc& d) {
   const int nqb = (d.S + 31) / 32;
-  if (mfma_summarize_supported(d)) return d.d == 256 ? 4 : nqb > 8 ? 2 : 1;
+  if (mfma_summarize_supported(d)) return (d.d == 256 ? 4 : nqb > 8 ? 2 : 1) * (short_history(d) ? 2 : 1);
   if (d.d == 256) return 8;
   return nqb > 8 ? d.H : d.H / 2;
 }
 static int resident_workgroups(const vista_summarize_desc& d) {
-  if (mfma_split_supported(d)) return d.d != 256 && d.S <= 128 ? 2 : 1;
-  return d.d == 256 && d.S == 64 && d.total_items > 131072 ? 2 : 1;   // (two cold starts on a compute unit: 2048 items pay for them)
+  // Two fit, but two cold starts on a compute unit have to pay: a segment of 768 items for one does it with the split
+  // operands (d = 64, S = 100: 60 000 items in 29.7 us with one, 33.7 with two, 200 000 in 52.5 and 51.9), 2048 at d = 256.
+  if (mfma_split_supported(d)) return d.d != 256 && d.S <= 128 && d.total_items > 768 * 256 / head_groups(d) ? 2 : 1;
+  return d.d == 256 && d.S == 64 && d.total_items > 131072 ? 2 : 1;
 }
 
 // Segment size of the matrix-core kernels where the caller leaves it open: the history is cut so that
 // the workgroups fill the chip k times, k the smallest count that keeps a segment at or below 32768
-// items, a multiple of 32, at least 128.  Longer segments mean fewer records to write and merge: 8
+// items, a multiple of 32, at least 128 (short histories: see below).  Longer segments mean fewer records to write and merge: 8
 // users of a million items (d = 128, S = 256) take 1650 us at this limit, 1669 at 16384 and 1704 or more
 // at 8192; one layer at d = 256, S = 512 over 14 M items 11.9, 12.0 and 12.25 ms.  Below 128 items a
-// workgroup's set-up and record outweigh its tiles: one user of 7001 items takes 29.0 us at 64, 27.1
-// at 96 and 26.6 at 128.
+// workgroup's set-up and record outweigh its tiles: one user of 7001 items takes 24.8 us at 64, 21.9
+// at 96 and 20.8 at 128.
 int mfma_summarize_segment(const vista_summarize_desc& d) {
   const int64_t N = d.total_items;
   const int64_t units = 256 * resident_workgroups(d) / head_groups(d);
@@ -1176,6 +1202,13 @@ int mfma_summarize_segment(const vista_summarize_desc& d) {
   if (k < 1) k = 1;
   int64_t s = (N + units * k - 1) / (units * k);
   s = (s + 31) / 32 * 32;
+  if (mfma_summarize_supported(d) && short_history(d)) {
+    // Few workgroups: a longer segment is more tiles for each, a shorter one more records to write and merge, so the
+    // best length goes with the square root: 1.5 sqrt(N).  (15 000 items, d = 128, S = 256: 27.7 us at 128, 24.8 at 192,
+    // 24.3 at 256; 30 000: 34.4 at 128, 28.6 at 256, 31.4 at 512.)
+    const int64_t r = (int64_t(1.5 * sqrt(double(N))) + 16) / 32 * 32;
+    if (s < r) s = r;
+  }
   return int(s < kLeast ? kLeast : s);
 }
 
@@ -1201,7 +1234,20 @@ static hipError_t launch_main(MfmaSummarizeParams& p, int wph, int64_t G, hipStr
 }
 
 template <int ATTN>
-static hipError_t launch_for_shape(MfmaSummarizeParams& p, int d, int64_t G, hipStream_t s) {
+static hipError_t launch_for_shape(MfmaSummarizeParams& p, const vista_summarize_desc& desc, int64_t G, hipStream_t s) {
+  const int d = desc.d;
+  if (short_history(desc)) {
+    if (d == 128) {
+      if (p.nqb <= 2) return launch_main<128, 1, 2, 4, true, false, 256, ATTN, 1, 2>(p, 2, G, s);
+      if (p.nqb <= 4) return launch_main<128, 2, 2, 4, true, false, 256, ATTN, 2, 2>(p, 2, G, s);
+      if (p.nqb <= 8) return launch_main<128, 4, 2, 4, true, false, 256, ATTN, 4, 2>(p, 2, G, s);
+      return launch_main<128, 4, 1, 4, true, false, 256, ATTN, 4, 2>(p, 4, G, s);
+    }
+    if (p.nqb <= 2) return launch_main<256, 1, 1, 2, true, false, 128, ATTN, 1, 2>(p, 2, G, s);
+    if (p.nqb <= 4) return launch_main<256, 1, 1, 4, true, false, 256, ATTN, 1, 2>(p, 4, G, s);
+    if (p.nqb <= 8) return launch_main<256, 2, 1, 4, true, false, 256, ATTN, 2, 2>(p, 4, G, s);
+    return launch_main<256, 2, 1, 4, true, false, 256, ATTN, 6, 2>(p, 4, G, s);
+  }
   if (d == 128) {
     // SiLU's two transcendentals a score leave the vector unit the bound: one block a wave feeds it better than
     // two, sixteen waves of them at S = 128 (115 -> 108 us over 500 003 items; softmax the other way, 87 -> 92;
@@ -1280,8 +1326,8 @@ vista_status mfma_summarize(const SummarizeArgs& a) {
   if ((a.G + 7) / 8 * 8 * 8 > 0x7FFFFFFF || merge_blocks > 0x7FFFFFFF) return VISTA_ERR_UNSUPPORTED;
   if (a.G > 0) {
     const hipError_t e = mfma_split_supported(d) ? launch_split(p, d.d, a.G, a.stream)
-                         : silu          ? launch_for_shape<VISTA_ATTN_SILU>(p, d.d, a.G, a.stream)
-                                         : launch_for_shape<VISTA_ATTN_SOFTMAX>(p, d.d, a.G, a.stream);
+                         : silu          ? launch_for_shape<VISTA_ATTN_SILU>(p, d, a.G, a.stream)
+                                         : launch_for_shape<VISTA_ATTN_SOFTMAX>(p, d, a.G, a.stream);
     if (e != hipSuccess) return VISTA_ERR_HIP;
   }
   // Few blocks: four times as many, and four waves to a user's records.  A merge is bound by what a

@@ -222,3 +222,25 @@ def test_queries_of_one_block_beyond_the_bound(S, block):
     Q = bf(Q)
     got = run(X, off, Q, Wk, Wv, 8, segment_items=960)
     assert_blocks_close(got, O.summarize(X, off, Q, Wk, Wv, 8), "bf16", f"S={S} block={block}")
+
+
+LIMITS = [("softmax", 128, 4, 64, 131072), ("softmax", 128, 4, 128, 131072), ("softmax", 128, 4, 512, 98304), ("silu", 128, 4, 128, 65536),
+          ("silu", 128, 4, 64, 131072), ("silu", 128, 4, 512, 98304), ("softmax", 256, 8, 64, 8192), ("softmax", 256, 8, 128, 16384),
+          ("softmax", 256, 8, 256, 16384), ("softmax", 256, 8, 512, 32768), ("silu", 256, 8, 256, 12288), ("silu", 256, 8, 512, 32768)]
+
+
+@pytest.mark.parametrize("form,d,H,S,most", LIMITS)
+@pytest.mark.parametrize("beyond", [0, 1])
+def test_both_sides_of_the_short_history_limit(form, d, H, S, most, beyond):
+    """A history of `most` items, a user counted as 128, goes to workgroups of half the heads, one item more to whole ones:
+    ragged users, one without items, tiles and segments that end inside them, default and short segments."""
+    lens = [1, 0, 33, 2011]
+    items = most - 128 * 5 + beyond
+    lens.insert(2, items - sum(lens))
+    X, off, Q, Wk, Wv = problem(50, lens, d, S)
+    silu = form == "silu"
+    want = (O.summarize_silu if silu else O.summarize)(X, off, Q, Wk, Wv, H)
+    for seg in (0, 480):
+        got = run(X, off, Q, Wk, Wv, H, segment_items=seg, attn=V.VISTA_ATTN_SILU if silu else V.VISTA_ATTN_SOFTMAX)
+        assert_blocks_close(got, want, "bf16", f"{form} d={d} S={S} N={items} seg={seg}")
+        assert np.all(got[1] == 0)
