@@ -247,41 +247,31 @@ __global__ __launch_bounds__(D * 2, 2) void qla_state_mfma_kernel(QlaParams p) {
   bool drain = false;
   // Z += SiLU(K)^T V of the tile in slot xb
   auto tile = [&](bool masked) __attribute__((always_inline)) {
-    // K first, turned into the A operand right away, then V: one projection accumulator is
-    // live at a time (at D = 256 the weights alone take half of the register file).
+    // K and V side by side: each operand of the X tile is read once for the two products.  (One after the other, with
+    // one accumulator live at a time, the tile was read twice at D = 256: 500 000 items 136 us instead of 132,
+    // their gradients 370 instead of 352.  At D = 128 the compiler had merged the reads already.)
     Pack8 a0, a1, b0, b1;
-    {
-      f32x16 ak = {0};
+    f32x16 ak = {0}, av = {0};
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        Pack8 x;
-        x.u = xbuf[xb][l32 * CH + ((2 * ks + hf) ^ (l32 & 15))];
-        ak = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.v, wk[ks], ak, 0, 0, 0);
-        if (kFence && ks % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // keeps later operand reads from being hoisted and held
-      }
+    for (int ks = 0; ks < KS; ++ks) {
+      Pack8 x;
+      x.u = xbuf[xb][l32 * CH + ((2 * ks + hf) ^ (l32 & 15))];
+      ak = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.v, wk[ks], ak, 0, 0, 0);
+      av = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.v, wv[ks], av, 0, 0, 0);
+      if (kFence && ks % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // keeps later operand reads from being hoisted and held
+    }
 #pragma unroll
-      for (int i = 0; i < 16; i += 2) {
-        const float fa = ak[i] * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(ak[i]));
-        const float fb = ak[i + 1] * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(ak[i + 1]));
-        const uint32_t pa = cvt_pk_bf16(fa, fb);
-        if (i < 8) a0.w[i / 2] = pa; else a1.w[(i - 8) / 2] = pa;
-      }
+    for (int i = 0; i < 16; i += 2) {
+      const float fa = ak[i] * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(ak[i]));
+      const float fb = ak[i + 1] * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(ak[i + 1]));
+      const uint32_t pa = cvt_pk_bf16(fa, fb);
+      if (i < 8) a0.w[i / 2] = pa; else a1.w[(i - 8) / 2] = pa;
     }
     if (kFence) __builtin_amdgcn_sched_barrier(0);
-    {
-      f32x16 av = {0};
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        Pack8 x;
-        x.u = xbuf[xb][l32 * CH + ((2 * ks + hf) ^ (l32 & 15))];
-        av = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.v, wv[ks], av, 0, 0, 0);
-        if (kFence && ks % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-      }
-#pragma unroll
-      for (int i = 0; i < 16; i += 2) {
-        const uint32_t pb = cvt_pk_bf16(av[i], av[i + 1]);
-        if (i < 8) b0.w[i / 2] = pb; else b1.w[(i - 8) / 2] = pb;
-      }
+    for (int i = 0; i < 16; i += 2) {
+      const uint32_t pb = cvt_pk_bf16(av[i], av[i + 1]);
+      if (i < 8) b0.w[i / 2] = pb; else b1.w[(i - 8) / 2] = pb;
     }
     if (masked) {
       // Rows past the piece's end count for nothing: their SiLU(k) is cleared.
@@ -435,45 +425,34 @@ __global__ __launch_bounds__(D * 2, 2) void qla_bwd_items_mfma_kernel(QlaParams 
       const int nvalid = ca.rows();
       Pack8 pk0, pk1, pv0, pv1;       // SiLU(K)^T and V^T as B operands (two halves of the 16 registers)
       float dsilu[16];                // SiLU'(k) of this lane's item, channels in register order
-      {
-        f32x16 ak = {0};
+      f32x16 ak = {0}, av = {0};
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          Pack8 x;
-          x.u = xbuf[xb][l32 * CH + ((2 * ks + hf) ^ (l32 & 15))];
-          ak = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wk[ks], x.v, ak, 0, 0, 0);
-          if (kFence && ks % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+      for (int ks = 0; ks < KS; ++ks) {
+        Pack8 x;
+        x.u = xbuf[xb][l32 * CH + ((2 * ks + hf) ^ (l32 & 15))];
+        ak = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wk[ks], x.v, ak, 0, 0, 0);
+        av = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv[ks], x.v, av, 0, 0, 0);
+        if (kFence && ks % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int i = 0; i < 16; i += 2) {
+        float f[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const float t = ak[i + u];                                  // -k log2(e)
+          const float sg = __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(t));
+          const float k = t * -0.69314718056f;
+          f[u] = k * sg;
+          dsilu[i + u] = sg * fmaf(k, 1.f - sg, 1.f);
         }
-#pragma unroll
-        for (int i = 0; i < 16; i += 2) {
-          float f[2];
-#pragma unroll
-          for (int u = 0; u < 2; ++u) {
-            const float t = ak[i + u];                                  // -k log2(e)
-            const float sg = __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(t));
-            const float k = t * -0.69314718056f;
-            f[u] = k * sg;
-            dsilu[i + u] = sg * fmaf(k, 1.f - sg, 1.f);
-          }
-          const uint32_t w = cvt_pk_bf16(f[0], f[1]);
-          if (i < 8) pk0.w[i / 2] = w; else pk1.w[(i - 8) / 2] = w;
-        }
+        const uint32_t w = cvt_pk_bf16(f[0], f[1]);
+        if (i < 8) pk0.w[i / 2] = w; else pk1.w[(i - 8) / 2] = w;
       }
       if (kFence) __builtin_amdgcn_sched_barrier(0);
-      {
-        f32x16 av = {0};
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          Pack8 x;
-          x.u = xbuf[xb][l32 * CH + ((2 * ks + hf) ^ (l32 & 15))];
-          av = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv[ks], x.v, av, 0, 0, 0);
-          if (kFence && ks % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-        for (int i = 0; i < 16; i += 2) {
-          const uint32_t w = cvt_pk_bf16(av[i], av[i + 1]);
-          if (i < 8) pv0.w[i / 2] = w; else pv1.w[(i - 8) / 2] = w;
-        }
+      for (int i = 0; i < 16; i += 2) {
+        const uint32_t w = cvt_pk_bf16(av[i], av[i + 1]);
+        if (i < 8) pv0.w[i / 2] = w; else pv1.w[(i - 8) / 2] = w;
       }
       // Both projections have read the tile's rows.  Everything this wave has in flight -- the
       // stores of the previous tile, issued a projection ago, and the requests for the next two
