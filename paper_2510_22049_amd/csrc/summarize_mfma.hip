@@ -79,6 +79,9 @@ struct MfmaSummarizeParams {
   int seg;
   int nhg;        // head groups = H / HPW
   float c;        // scale * log2(e)
+  float* Ks;      // self term: K', V' of the seeds, formed beside the history, or null
+  float* Vs;
+  int64_t self_rows;
 };
 
 union Pack8 {
@@ -836,6 +839,69 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
   }
 }
 
+// Self term: K' = Q W_k and V' = Q W_v of the seeds in fp32 (bf16 inputs, products exact, fp32 sums).
+// A unit is 32 seeds x 32 channels of both, formed by one wave: the seeds' rows read once as the A operand, the
+// weights 16 bytes a lane and turned by the matrix core as in the main kernel.
+__device__ __forceinline__ void self_kv_unit(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Wk,
+                                             const uint16_t* __restrict__ Wv, float* __restrict__ Ks,
+                                             float* __restrict__ Vs, int64_t rows, int d, int64_t unit) {
+  const int nc = d / 32;
+  const int64_t r0 = unit / nc * 32;
+  const int c0 = int(unit % nc) * 32;
+  if (r0 >= rows) return;
+  const int lane = threadIdx.x & 63, hf = lane >> 5, l32 = lane & 31;
+  const int64_t qrow = r0 + l32 < rows ? r0 + l32 : rows - 1;   // rows past the end repeat the last; not stored
+  const uint16_t* q = Q + qrow * d + 8 * hf;
+  const int wrow = (l32 & 16) | ((l32 & 4) << 1) | ((l32 & 8) >> 1) | (l32 & 3);
+  const uint16_t* src[2] = {Wk + wrow * d + c0 + 8 * hf, Wv + wrow * d + c0 + 8 * hf};
+  Pack8 sel[2];
+#pragma unroll
+  for (int e = 0; e < 2; ++e)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) sel[e].h[j] = (l32 == 16 * e + 8 * hf + j) ? 0x3F80 : 0;
+  f32x16 acc[2] = {{0}, {0}};
+#pragma unroll 2
+  for (int k = 0; k < d; k += 32) {
+    float rest = 0.f;
+    Pack8 x[2], raw[2][2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      x[e].u = *reinterpret_cast<const uint4*>(q + k + 16 * e);
+#pragma unroll
+      for (int m = 0; m < 2; ++m) raw[m][e].u = *reinterpret_cast<const uint4*>(src[m] + k * d + 16 * e);
+    }
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      f32x16 t = {0};
+      t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(raw[m][0].v, sel[0].v, t, 0, 0, 0);
+      t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(raw[m][1].v, sel[1].v, t, 0, 0, 0);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) rest = dot2_zero(raw[m][e / 4].w[e % 4], rest);
+      const bool finite = __builtin_amdgcn_ballot_w64(rest != 0.f) == 0;     // (else not turned: see summarize_wave)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        Pack8 w;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) w.w[j] = cvt_pk_bf16(t[8 * e + 2 * j], t[8 * e + 2 * j + 1]);
+        if (!finite) {
+          const uint16_t* W = (m ? Wv : Wk) + int64_t(k + 16 * e + 8 * hf) * d + c0 + l32;
+#pragma unroll
+          for (int j = 0; j < 8; ++j) w.h[j] = W[j * d];
+        }
+        acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[e].v, w.v, acc[m], 0, 0, 0);
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int64_t r = r0 + acc_row0(i) + 4 * hf;
+    if (r < rows) {
+      Ks[r * d + c0 + l32] = acc[0][i];
+      Vs[r * d + c0 + l32] = acc[1][i];
+    }
+  }
+}
+
 // MAXT: largest workgroup of the instantiation (it bounds the registers of a wave).  The first FW waves
 // fetch X (ALLF: that is every wave).
 // NQB query blocks to a projecting wave, NQA to one that only attends; OCC: waves of the kernel on a SIMD, at least.
@@ -868,6 +934,15 @@ __global__ __launch_bounds__(MAXT, OCC) void summarize_mfma_kernel(MfmaSummarize
     summarize_wave<D, NQB, HPW, FW, WREG, SPLIT, (!SPLIT && MAXT == 64 * FW), 1, ATTN>(p, sm, g, h, hl, NQB, seg_begin, seg_end);
   else if constexpr (MAXT != HPW * 128)      // (two waves per head: there is no third slot)
     summarize_wave<D, NQA, HPW, FW, WREG, SPLIT, (!SPLIT && MAXT == 64 * FW), 2, ATTN>(p, sm, g, h, hl, 2 * NQB + (slot - 2) * NQA, seg_begin, seg_end);
+  // The seeds' own keys and values, which the merge needs: units of them go round the workgroups' first waves, then their
+  // second and so on.  A kernel in front of this one was a launch and 6 us of latency: 500 003 items, SiLU, S = 128 107.0 ->
+  // 100.5 us a call without it; 7000 items, d = 128, S = 256 29.1 -> 25.0; 100 users with queries of their own, 60 000 items,
+  // d = 256, S = 512 280 -> 265.
+  if (p.Ks) {
+    const int64_t groups = (p.N + p.seg - 1) / p.seg * p.nhg, units = (p.self_rows + 31) / 32 * (D / 32);
+    for (int64_t u = int64_t(wave) * groups + g * p.nhg + hg; u < units; u += groups * (blockDim.x >> 6))
+      self_kv_unit(p.Q, p.Wk, p.Wv, p.Ks, p.Vs, p.self_rows, D, u);
+  }
 }
 
 // Merge of a user's partial records in a fixed order, so the result is bitwise reproducible.
@@ -1054,71 +1129,13 @@ __global__ __launch_bounds__(256) void merge_mfma_kernel(const float* __restrict
   *reinterpret_cast<uint2*>(dst) = pk;
 }
 
-// Self term: K' = Q W_k and V' = Q W_v of the seeds in fp32 (bf16 inputs, products exact, fp32 sums).
-// One wave forms 32 seeds x 32 channels of both, the seeds' rows read once as the A operand, the
-// weights 16 bytes a lane and turned by the matrix core as in the main kernel.  The whole of it is a
-// few launches' worth of latency: one thread per output walking 2-byte loads took 33 us for 128 seeds
-// of width 128, this takes 6.
+// The same as a kernel of its own, for the paths whose main kernel does not form them.  It is a few launches' worth of
+// latency: one thread per output walking 2-byte loads took 33 us for 128 seeds of width 128, this takes 6.
 __global__ __launch_bounds__(256) void self_kv_mfma_kernel(const uint16_t* __restrict__ Q,
                                                            const uint16_t* __restrict__ Wk,
                                                            const uint16_t* __restrict__ Wv, float* __restrict__ Ks,
                                                            float* __restrict__ Vs, int64_t rows, int d) {
-  const int64_t unit = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
-  const int nc = d / 32;
-  const int64_t r0 = unit / nc * 32;
-  const int c0 = int(unit % nc) * 32;
-  if (r0 >= rows) return;
-  const int lane = threadIdx.x & 63, hf = lane >> 5, l32 = lane & 31;
-  const int64_t qrow = r0 + l32 < rows ? r0 + l32 : rows - 1;   // rows past the end repeat the last; not stored
-  const uint16_t* q = Q + qrow * d + 8 * hf;
-  const int wrow = (l32 & 16) | ((l32 & 4) << 1) | ((l32 & 8) >> 1) | (l32 & 3);
-  const uint16_t* src[2] = {Wk + wrow * d + c0 + 8 * hf, Wv + wrow * d + c0 + 8 * hf};
-  Pack8 sel[2];
-#pragma unroll
-  for (int e = 0; e < 2; ++e)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) sel[e].h[j] = (l32 == 16 * e + 8 * hf + j) ? 0x3F80 : 0;
-  f32x16 acc[2] = {{0}, {0}};
-#pragma unroll 4
-  for (int k = 0; k < d; k += 32) {
-    float rest = 0.f;
-    Pack8 x[2], raw[2][2];
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      x[e].u = *reinterpret_cast<const uint4*>(q + k + 16 * e);
-#pragma unroll
-      for (int m = 0; m < 2; ++m) raw[m][e].u = *reinterpret_cast<const uint4*>(src[m] + k * d + 16 * e);
-    }
-#pragma unroll
-    for (int m = 0; m < 2; ++m) {
-      f32x16 t = {0};
-      t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(raw[m][0].v, sel[0].v, t, 0, 0, 0);
-      t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(raw[m][1].v, sel[1].v, t, 0, 0, 0);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) rest = dot2_zero(raw[m][e / 4].w[e % 4], rest);
-      const bool finite = __builtin_amdgcn_ballot_w64(rest != 0.f) == 0;     // (else not turned: see summarize_wave)
-#pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        Pack8 w;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) w.w[j] = cvt_pk_bf16(t[8 * e + 2 * j], t[8 * e + 2 * j + 1]);
-        if (!finite) {
-          const uint16_t* W = (m ? Wv : Wk) + int64_t(k + 16 * e + 8 * hf) * d + c0 + l32;
-#pragma unroll
-          for (int j = 0; j < 8; ++j) w.h[j] = W[j * d];
-        }
-        acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[e].v, w.v, acc[m], 0, 0, 0);
-      }
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int64_t r = r0 + acc_row0(i) + 4 * hf;
-    if (r < rows) {
-      Ks[r * d + c0 + l32] = acc[0][i];
-      Vs[r * d + c0 + l32] = acc[1][i];
-    }
-  }
+  self_kv_unit(Q, Wk, Wv, Ks, Vs, rows, d, int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6));
 }
 
 // ------------------------------------------------------------------ host side
@@ -1315,12 +1332,20 @@ vista_status mfma_summarize(const SummarizeArgs& a) {
   p.N = d.total_items;
   p.seg = a.seg;
   p.c = silu ? -a.scale_log2 : a.scale_log2;
+  p.Ks = p.Vs = nullptr;
+  p.self_rows = 0;
   float* Ks = nullptr;
   float* Vs = nullptr;
   if (d.flags & VISTA_FLAG_SELF_TERM) {
     Ks = reinterpret_cast<float*>(reinterpret_cast<char*>(p.partials) + ((partial_bytes(d, a.seg) + 255) & ~size_t(255)));
     Vs = Ks + self_kv_bytes(d) / sizeof(float);
-    if (launch_self_kv(d, a.Q, a.Wk, a.Wv, Ks, Vs, a.stream) != hipSuccess) return VISTA_ERR_HIP;
+    if (a.G > 0 && mfma_self_kv_supported(d, a.Q, a.Wk, a.Wv)) {
+      p.Ks = Ks;
+      p.Vs = Vs;
+      p.self_rows = d.q_user_stride ? int64_t(d.B) * d.S : d.S;
+    } else if (launch_self_kv(d, a.Q, a.Wk, a.Wv, Ks, Vs, a.stream) != hipSuccess) {
+      return VISTA_ERR_HIP;
+    }
   }
   const int64_t merge_blocks = int64_t(d.B) * d.H * p.nqb;
   if ((a.G + 7) / 8 * 8 * 8 > 0x7FFFFFFF || merge_blocks > 0x7FFFFFFF) return VISTA_ERR_UNSUPPORTED;

@@ -528,3 +528,14 @@ def test_codec_at_every_head_width(dtype, H, d, rows, shift):
     wc, ws = O.quantize_summaries(y, H)
     assert np.array_equal(codes[shift:].view(rows, d).cpu().numpy(), wc) and np.array_equal(scales.cpu().numpy(), ws)
     assert shift == 0 or int(codes[0]) == 99
+
+
+@pytest.mark.parametrize("form,d,H,S,lens", [("softmax", 128, 4, 256, [3] * 40), ("silu", 128, 4, 128, [1, 0, 50] * 9), ("softmax", 256, 8, 64, [700, 33]),
+                                             ("softmax", 128, 4, 100, [5] * 30), ("softmax", 64, 2, 33, [4000])])
+@pytest.mark.parametrize("per_user", [False, True])
+def test_own_keys_formed_beside_the_history(form, d, H, S, lens, per_user):
+    """Few workgroups with many seeds' own keys and values to form (several units a wave), and more than there are units."""
+    X, off, Q, Wk, Wv = problem(77, lens, d, S, "bf16", per_user=per_user)
+    got = run(form, X, off, Q, Wk, Wv, H, "bf16", True)
+    want = (O.summarize_silu if form == "silu" else O.summarize)(X, off, Q, Wk, Wv, H, self_term=True)
+    assert_blocks_close(got, want, "bf16", f"{form} d={d} S={S} per_user={per_user}")
