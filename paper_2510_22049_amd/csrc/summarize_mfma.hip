@@ -1204,6 +1204,18 @@ static int resident_workgroups(const vista_summarize_desc& d) {
   return d.d == 256 && d.S == 64 && d.total_items > 131072 ? 2 : 1;
 }
 
+// Whether the seeds' own keys and values are formed beside the history.  With workgroups on nearly every compute unit the
+// main kernel's waves do it as fast as a kernel of its own, without its launch and cold start; with fewer, only a few units
+// for each are worth it, and queries of their own for many users over few items go to the kernel that fills the chip.  us a
+// call, in front / beside, queries of their own: 250 workgroups or more, d = 128, S = 256, 40 000 items, 32 users (4 units a
+// workgroup) 47.1 / 44.9, 128 users (16) 85.1 / 82.5; d = 256, S = 512, 128 users, 8000 items (64) 293 / 285.  126 workgroups, d = 128,
+// S = 256, 8000 items: 8 users (2) 38.8 / 34.6, 32 users (8) 41.2 / 41.9, 128 users (32) 84.9 / 94.8.  32 workgroups, 2000 items: 2
+// users (2) 29.6 / 26.6, 8 users (8) 35.9 / 36.6, 32 users (32) 43.3 / 64.4.
+static bool self_beside_history(const vista_summarize_desc& d, int64_t G, int64_t rows) {
+  const int64_t units = (rows + 31) / 32 * (d.d / 32), groups = G * head_groups(d);
+  return units <= (groups >= 240 ? 64 : 4) * groups;
+}
+
 // Segment size of the matrix-core kernels where the caller leaves it open: the history is cut so that
 // the workgroups fill the chip k times, k the smallest count that keeps a segment at or below 32768
 // items, a multiple of 32, at least 128 (short histories: see below).  Longer segments mean fewer records to write and merge: 8
@@ -1343,10 +1355,11 @@ vista_status mfma_summarize(const SummarizeArgs& a) {
   if (d.flags & VISTA_FLAG_SELF_TERM) {
     Ks = reinterpret_cast<float*>(reinterpret_cast<char*>(p.partials) + ((partial_bytes(d, a.seg) + 255) & ~size_t(255)));
     Vs = Ks + self_kv_bytes(d) / sizeof(float);
-    if (a.G > 0 && mfma_self_kv_supported(d, a.Q, a.Wk, a.Wv)) {
+    const int64_t rows = d.q_user_stride ? int64_t(d.B) * d.S : d.S;
+    if (mfma_self_kv_supported(d, a.Q, a.Wk, a.Wv) && self_beside_history(d, a.G, rows)) {
       p.Ks = Ks;
       p.Vs = Vs;
-      p.self_rows = d.q_user_stride ? int64_t(d.B) * d.S : d.S;
+      p.self_rows = rows;
     } else if (launch_self_kv(d, a.Q, a.Wk, a.Wv, Ks, Vs, a.stream) != hipSuccess) {
       return VISTA_ERR_HIP;
     }

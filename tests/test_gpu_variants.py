@@ -531,10 +531,12 @@ def test_codec_at_every_head_width(dtype, H, d, rows, shift):
 
 
 @pytest.mark.parametrize("form,d,H,S,lens", [("softmax", 128, 4, 256, [3] * 40), ("silu", 128, 4, 128, [1, 0, 50] * 9), ("softmax", 256, 8, 64, [700, 33]),
-                                             ("softmax", 128, 4, 100, [5] * 30), ("softmax", 64, 2, 33, [4000])])
+                                             ("softmax", 128, 4, 100, [5] * 30), ("softmax", 64, 2, 33, [4000]),
+                                             ("softmax", 128, 4, 64, [128, 128]), ("softmax", 128, 4, 64, [85, 85, 86])])
 @pytest.mark.parametrize("per_user", [False, True])
 def test_own_keys_formed_beside_the_history(form, d, H, S, lens, per_user):
-    """Few workgroups with many seeds' own keys and values to form (several units a wave), and more than there are units."""
+    """Seeds' own keys and values by the kernel in front (many of them, few workgroups) and beside the history (several units a
+    wave, or fewer units than workgroups), and on both sides of the limit between the two."""
     X, off, Q, Wk, Wv = problem(77, lens, d, S, "bf16", per_user=per_user)
     got = run(form, X, off, Q, Wk, Wv, H, "bf16", True)
     want = (O.summarize_silu if form == "silu" else O.summarize)(X, off, Q, Wk, Wv, H, self_term=True)
