@@ -1294,13 +1294,19 @@ static hipError_t launch_for_shape(MfmaSummarizeParams& p, const vista_summarize
   if (p.nqb <= 2) return launch_main<256, 1, 2, 4, true, false, 256, ATTN, 1, 2>(p, 2, G, s);
   if (p.nqb <= 4) return launch_main<256, 1, 2, 8, true, false, 512, ATTN>(p, 4, G, s);
   if (p.nqb <= 8) return launch_main<256, 2, 2, 8, true, false, 512, ATTN>(p, 4, G, s);
-  // Queries of their own are loaded anew for each user, and the waves of six blocks are late at every change: many short
-  // users keep four blocks each, the weights in LDS (100 users of 600 items 128 us, 133 in the other split; of
-  // 2500 269 and 271; of 5000 459 and 453).
-  if (p.q_user_stride != 0 && p.N < 4096 * int64_t(p.B)) return launch_main<256, 4, 2, 8, false, false, 512, ATTN>(p, 4, G, s);
-  // 2 + 2 + 6 + 6 blocks instead of four each, which leaves no registers for the weights: 421 -> 413 us over
-  // 500 000 items, two layers over 14 M items with the rest of the path 22.8 -> 22.35 ms.
-  return launch_main<256, 2, 2, 8, true, false, 512, ATTN, 6>(p, 4, G, s);
+  // At S = 512 either four blocks a wave, the weights in LDS, or 2 + 2 + 6 + 6, which leaves the projecting waves registers for
+  // the weights.  Softmax: 421 -> 413 us over 500 000 items, two layers over 14 M items with the rest of the path 22.8 -> 22.35
+  // ms.  SiLU keeps four each: its vector work is three times as long in a wave of six blocks as beside it (100 000 items in segments
+  // of 4096 250 us against 261, 300 000 of 8192 481 against 505, 262 144 at the default 278 against 284).
+  if constexpr (ATTN == VISTA_ATTN_SILU) {
+    return launch_main<256, 4, 2, 8, false, false, 512, ATTN>(p, 4, G, s);
+  } else {
+    // Queries of their own are loaded anew for each user, and the waves of six blocks are late at every change: many short
+    // users keep four blocks each (100 users of 600 items 128 us, 133 in the other split; of 2500 269 and 271; of 5000 459
+    // and 453).
+    if (p.q_user_stride != 0 && p.N < 4096 * int64_t(p.B)) return launch_main<256, 4, 2, 8, false, false, 512, ATTN>(p, 4, G, s);
+    return launch_main<256, 2, 2, 8, true, false, 512, ATTN, 6>(p, 4, G, s);
+  }
 }
 
 static hipError_t launch_split(MfmaSummarizeParams& p, int d, int64_t G, hipStream_t s) {

@@ -541,3 +541,22 @@ def test_own_keys_formed_beside_the_history(form, d, H, S, lens, per_user):
     got = run(form, X, off, Q, Wk, Wv, H, "bf16", True)
     want = (O.summarize_silu if form == "silu" else O.summarize)(X, off, Q, Wk, Wv, H, self_term=True)
     assert_blocks_close(got, want, "bf16", f"{form} d={d} S={S} per_user={per_user}")
+
+
+# so many users that workgroups hold two heads and not one, most of them with a handful of items
+CROWD = LENS + [4000] + [1, 5, 0, 33] * 46
+
+
+@pytest.mark.parametrize("form,per_user,self_term,block", [("softmax", True, False, 3), ("softmax", True, True, 15), ("silu", False, True, 0),
+                                                           ("silu", True, False, 9)])
+@pytest.mark.parametrize("seg", [0, 160])
+def test_four_query_blocks_a_wave_at_512_seeds(form, per_user, self_term, block, seg):
+    """d = 256, S = 512 with the queries shared evenly and the weights in LDS (SiLU, and many short users with queries of
+    their own): one block of queries beyond the score bound, users that change every few items, the self term."""
+    X, off, Q, Wk, Wv = problem(83 + block, CROWD, 256, 512, "bf16", per_user=per_user)
+    Q[..., 32 * block:32 * block + 32, :] *= 5.0
+    Q = I.round_to(Q, "bf16")
+    got = run(form, X, off, Q, Wk, Wv, 8, "bf16", self_term, segment_items=seg)
+    want = oracle(form, X, off, Q, Wk, Wv, 8, self_term)
+    assert_blocks_close(got, want, "bf16", f"{form} per_user={per_user} self={self_term} block={block} seg={seg}")
+    assert np.all(got[1] == 0) and np.all(got[8] == 0)
