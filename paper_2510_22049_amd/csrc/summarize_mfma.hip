@@ -1176,18 +1176,24 @@ bool mfma_split_supported(const vista_summarize_desc& d) {
 // S = 128 has sixteen waves beyond: 60 000 29.4 / 28.4, 80 000 32.2 / 33.2.  At d = 256 a tile is twice the bytes and four groups of
 // heads share the chip as it is: S = 64, 7001 18.2 / 17.9, 15 000 21.4 / 23.1; S = 128, 15 000 24.6 / 22.8, 20 000 25.8 / 26.0; S = 256,
 // 15 000 31.4 / 28.8, 25 000 35.4 / 36.0; S = 512, 30 000 53.7 / 51.1, 45 000 62.1 / 62.2; SiLU, S = 128, 13 845 24.1 / 25.5.
-// A user costs its record and a ragged tile, about 128 items: 128 users of 15 000 items, d = 256, S = 256 54.1 / 61.1; of 225 000, d = 128,
-// S = 256 75.7 / 78.0.
+// Users count too: a workgroup of half the heads walks twice the items, so twice the users, and at every change of user its one
+// wave a SIMD goes through a ragged tile, a record and, with queries of their own, their load with nobody beside it.  Lognormal
+// users, d = 256, S = 512: 64 of 24 576 items 74.0 / 84.2, queries of their own 84.1 / 99.7; 8 of 31 744 52.3 / 48.2; d = 128, S = 512,
+// 96 of 43 008 with queries of their own 69 / 78; S = 64, 200 of 65 536 30.8 / 33.5.  So a user counts as 1024 items, twice that with
+// queries of its own and at d = 256, S = 512.  Up to `few` items both kinds have segments of the least length, a workgroup of either
+// the same tiles, and any number of users is faster in halves (200 of 2048 items, d = 256, S = 512 205 / 182; own 287 / 260).
 static bool short_history(const vista_summarize_desc& d) {
   const bool silu = d.attn == VISTA_ATTN_SILU;
+  const int64_t few = d.d == 256 ? 4096 : 8192;
+  const int64_t user = (d.d == 256 && d.S == 512 ? 2048 : 1024) * (d.q_user_stride ? 2 : 1);
   int64_t most;
   if (d.d == 256)
-    most = d.S == 64 ? 8192 : d.S == 512 ? 32768 : silu ? 12288 : 16384;
+    most = d.S == 64 ? 8192 : d.S == 512 ? (silu ? 20480 : 32768) : silu ? 12288 : 16384;
   else if (silu && d.S == 128)
     most = 65536;
   else
     most = d.S == 256 ? 229376 : d.S == 512 ? 98304 : 131072;
-  return d.total_items + 128 * int64_t(d.B) <= most;
+  return d.total_items <= few || d.total_items + user * int64_t(d.B) <= most;
 }
 
 // Head groups (workgroups per segment) and workgroups resident on a compute unit, as launched below.

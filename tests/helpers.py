@@ -56,3 +56,21 @@ def assert_in_value_hull(out: torch.Tensor, values: torch.Tensor, what="", slack
     tol = slack * torch.maximum(lo.abs(), hi.abs())
     o = out.float()
     assert bool(((o >= lo - tol) & (o <= hi + tol)).all()), f"{what}: output outside the hull of its values"
+
+
+def short_history_limit(form, d, S):
+    """Largest history, users counted as items, that the bf16 matrix-core kernels of S = 64, 128, 256, 512 give to
+    workgroups of half the heads (tests/test_schedule_host.py pins it against the library)."""
+    if d == 256:
+        return 8192 if S == 64 else {"softmax": 32768, "silu": 20480}[form] if S == 512 else {"softmax": 16384, "silu": 12288}[form]
+    if form == "silu" and S == 128:
+        return 65536
+    return {64: 131072, 128: 131072, 256: 229376, 512: 98304}[S]
+
+
+def user_as_items(d, S, own_queries=False):
+    return (2048 if (d, S) == (256, 512) else 1024) * (2 if own_queries else 1)
+
+
+def is_short_history(form, d, S, N, B, own_queries=False):
+    return N <= (4096 if d == 256 else 8192) or N + user_as_items(d, S, own_queries) * B <= short_history_limit(form, d, S)

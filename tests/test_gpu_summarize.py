@@ -6,7 +6,7 @@ import torch
 from oracle import vista_oracle as O
 from paper_2510_22049_amd import binding as V
 from paper_2510_22049_amd import inputs as I
-from tests.helpers import assert_blocks_close, block_errors, dev, host64
+from tests.helpers import assert_blocks_close, block_errors, dev, host64, is_short_history, short_history_limit, user_as_items
 
 pytestmark = pytest.mark.gpu
 
@@ -224,19 +224,21 @@ def test_queries_of_one_block_beyond_the_bound(S, block):
     assert_blocks_close(got, O.summarize(X, off, Q, Wk, Wv, 8), "bf16", f"S={S} block={block}")
 
 
-LIMITS = [("softmax", 128, 4, 64, 131072), ("softmax", 128, 4, 128, 131072), ("softmax", 128, 4, 512, 98304), ("silu", 128, 4, 128, 65536),
-          ("silu", 128, 4, 64, 131072), ("silu", 128, 4, 512, 98304), ("softmax", 256, 8, 64, 8192), ("softmax", 256, 8, 128, 16384),
-          ("softmax", 256, 8, 256, 16384), ("softmax", 256, 8, 512, 32768), ("silu", 256, 8, 256, 12288), ("silu", 256, 8, 512, 32768)]
+LIMITS = [("softmax", 128, 4, 64, 92), ("softmax", 128, 4, 128, 92), ("softmax", 128, 4, 256, 188), ("softmax", 128, 4, 512, 60),
+          ("silu", 128, 4, 64, 92), ("silu", 128, 4, 128, 28), ("silu", 128, 4, 256, 188), ("silu", 128, 4, 512, 60),
+          ("softmax", 256, 8, 64, 3), ("softmax", 256, 8, 128, 5), ("softmax", 256, 8, 256, 5), ("softmax", 256, 8, 512, 5),
+          ("silu", 256, 8, 64, 3), ("silu", 256, 8, 128, 5), ("silu", 256, 8, 256, 5), ("silu", 256, 8, 512, 5)]
 
 
-@pytest.mark.parametrize("form,d,H,S,most", LIMITS)
+@pytest.mark.parametrize("form,d,H,S,users", LIMITS)
 @pytest.mark.parametrize("beyond", [0, 1])
-def test_both_sides_of_the_short_history_limit(form, d, H, S, most, beyond):
-    """A history of `most` items, a user counted as 128, goes to workgroups of half the heads, one item more to whole ones:
+def test_both_sides_of_the_short_history_limit(form, d, H, S, users, beyond):
+    """A history at the limit, users counted as items, goes to workgroups of half the heads, one item more to whole ones:
     ragged users, one without items, tiles and segments that end inside them, default and short segments."""
-    lens = [1, 0, 33, 2011]
-    items = most - 128 * 5 + beyond
+    lens = ([1, 0, 33, 2011] + [40] * users)[:users - 1]
+    items = short_history_limit(form, d, S) - user_as_items(d, S) * users + beyond
     lens.insert(2, items - sum(lens))
+    assert is_short_history(form, d, S, items, users) == (not beyond)
     X, off, Q, Wk, Wv = problem(50, lens, d, S)
     silu = form == "silu"
     want = (O.summarize_silu if silu else O.summarize)(X, off, Q, Wk, Wv, H)
