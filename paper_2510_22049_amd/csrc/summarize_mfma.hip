@@ -927,6 +927,17 @@ __global__ __launch_bounds__(MAXT, OCC) void summarize_mfma_kernel(MfmaSummarize
   const int64_t seg_begin = g * p.seg;
   if (seg_begin >= p.N) return;          // padding blocks of the last group (whole workgroup)
   const int64_t seg_end = (seg_begin + p.seg < p.N) ? seg_begin + p.seg : p.N;
+  // The seeds' own keys and values, which the merge needs: units of them go round the workgroups' first waves, then their
+  // second and so on.  A kernel in front of this one was a launch and 6 us of latency: 500 003 items, SiLU, S = 128 106.3 ->
+  // 100.5 us a call without it; 7000 items, d = 128, S = 256 33.8 -> 24.9; 100 users with queries of their own, 60 000 items,
+  // d = 256, S = 512 255 -> 243.  They come before the history because what they need would have to be kept through it
+  // otherwise, and every call would pay (behind it, calls without the self term: SiLU, d = 128, S = 256, 300 users, 9557
+  // items 103.4 us instead of 97.9; S = 64, 110 users, 117 964 items 36.3 instead of 35.7).
+  if (p.Ks) {
+    const int64_t groups = (p.N + p.seg - 1) / p.seg * p.nhg, units = (p.self_rows + 31) / 32 * (D / 32);
+    for (int64_t u = int64_t(wave) * groups + g * p.nhg + hg; u < units; u += groups * (blockDim.x >> 6))
+      self_kv_unit(p.Q, p.Wk, p.Wv, p.Ks, p.Vs, p.self_rows, D, u);
+  }
   // All roles run the same sequence of barriers; only the MFMA operand order differs.
   if (slot == 0)
     summarize_wave<D, NQB, HPW, FW, WREG, SPLIT, (!SPLIT && MAXT == 64 * FW), 0, ATTN>(p, sm, g, h, hl, 0, seg_begin, seg_end);
@@ -934,15 +945,6 @@ __global__ __launch_bounds__(MAXT, OCC) void summarize_mfma_kernel(MfmaSummarize
     summarize_wave<D, NQB, HPW, FW, WREG, SPLIT, (!SPLIT && MAXT == 64 * FW), 1, ATTN>(p, sm, g, h, hl, NQB, seg_begin, seg_end);
   else if constexpr (MAXT != HPW * 128)      // (two waves per head: there is no third slot)
     summarize_wave<D, NQA, HPW, FW, WREG, SPLIT, (!SPLIT && MAXT == 64 * FW), 2, ATTN>(p, sm, g, h, hl, 2 * NQB + (slot - 2) * NQA, seg_begin, seg_end);
-  // The seeds' own keys and values, which the merge needs: units of them go round the workgroups' first waves, then their
-  // second and so on.  A kernel in front of this one was a launch and 6 us of latency: 500 003 items, SiLU, S = 128 107.0 ->
-  // 100.5 us a call without it; 7000 items, d = 128, S = 256 29.1 -> 25.0; 100 users with queries of their own, 60 000 items,
-  // d = 256, S = 512 280 -> 265.
-  if (p.Ks) {
-    const int64_t groups = (p.N + p.seg - 1) / p.seg * p.nhg, units = (p.self_rows + 31) / 32 * (D / 32);
-    for (int64_t u = int64_t(wave) * groups + g * p.nhg + hg; u < units; u += groups * (blockDim.x >> 6))
-      self_kv_unit(p.Q, p.Wk, p.Wv, p.Ks, p.Vs, p.self_rows, D, u);
-  }
 }
 
 // Merge of a user's partial records in a fixed order, so the result is bitwise reproducible.

@@ -535,8 +535,8 @@ def test_codec_at_every_head_width(dtype, H, d, rows, shift):
                                              ("softmax", 128, 4, 64, [128, 128]), ("softmax", 128, 4, 64, [85, 85, 86])])
 @pytest.mark.parametrize("per_user", [False, True])
 def test_own_keys_formed_beside_the_history(form, d, H, S, lens, per_user):
-    """Seeds' own keys and values by the kernel in front (many of them, few workgroups) and beside the history (several units a
-    wave, or fewer units than workgroups), and on both sides of the limit between the two."""
+    """Seeds' own keys and values by the kernel in front (many of them, few workgroups) and beside the history (at most one
+    unit a wave), and on both sides of the limit between the two."""
     X, off, Q, Wk, Wv = problem(77, lens, d, S, "bf16", per_user=per_user)
     got = run(form, X, off, Q, Wk, Wv, H, "bf16", True)
     want = (O.summarize_silu if form == "silu" else O.summarize)(X, off, Q, Wk, Wv, H, self_term=True)
@@ -560,3 +560,13 @@ def test_four_query_blocks_a_wave_at_512_seeds(form, per_user, self_term, block,
     want = oracle(form, X, off, Q, Wk, Wv, 8, self_term)
     assert_blocks_close(got, want, "bf16", f"{form} per_user={per_user} self={self_term} block={block} seg={seg}")
     assert np.all(got[1] == 0) and np.all(got[8] == 0)
+
+
+@pytest.mark.parametrize("lens", [[38] * 199 + [182], [4] * 1936, [4] * 1936 + [0]])
+def test_several_units_of_own_keys_a_wave(lens):
+    """242 workgroups of four waves: 1600 units of 32 seeds by 32 channels are two for most waves; 15 488 are 64 a workgroup, the
+    most that are formed beside the history; one user more goes to the kernel in front."""
+    assert sum(lens) == 121 * 64
+    X, off, Q, Wk, Wv = problem(78, lens, 128, 64, "bf16", per_user=True)
+    got = run("silu", X, off, Q, Wk, Wv, 4, "bf16", True, segment_items=64)
+    assert_blocks_close(got, O.summarize_silu(X, off, Q, Wk, Wv, 4, self_term=True), "bf16", f"{len(lens)} users")
