@@ -1309,10 +1309,14 @@ static hipError_t launch_for_shape(MfmaSummarizeParams& p, const vista_summarize
   if constexpr (ATTN == VISTA_ATTN_SILU) {
     return launch_main<256, 4, 2, 8, false, false, 512, ATTN>(p, 4, G, s);
   } else {
-    // Queries of their own are loaded anew for each user, and the waves of six blocks are late at every change: many short
-    // users keep four blocks each (100 users of 600 items 128 us, 133 in the other split; of 2500 269 and 271; of 5000 459
-    // and 453).
-    if (p.q_user_stride != 0 && p.N < 4096 * int64_t(p.B)) return launch_main<256, 4, 2, 8, false, false, 512, ATTN>(p, 4, G, s);
+    // The waves of six blocks are late at every change of user, more so where they load the queries anew: 0.5 to 1 us a change
+    // with shared queries, 1.5 to 3 with queries of their own, against 2 % of the call.  So short histories and short users
+    // keep four blocks each.  us a call, four each / uneven, lognormal users: shared queries, 32 of 16 000 items 51.7 / 52.5, of
+    // 40 000 69.5 / 68.9, of 80 000 101.3 / 99.3; 300 of 40 000 214 / 218, of 320 000 420 / 417; own, 4 of 24 000 53.4 / 55.5, of 80 000
+    // 96.0 / 96.2; 32 of 40 000 76.0 / 78.5, of 160 000 168 / 167; 200 of 160 000 269 / 274, of 1 280 000 1164 / 1139.
+    const bool own = p.q_user_stride != 0;
+    if (p.N < (own ? 65536 : 24576) || p.N < (own ? 4096 : 1024) * int64_t(p.B))
+      return launch_main<256, 4, 2, 8, false, false, 512, ATTN>(p, 4, G, s);
     return launch_main<256, 2, 2, 8, true, false, 512, ATTN, 6>(p, 4, G, s);
   }
 }

@@ -213,15 +213,40 @@ def test_nothing_is_written_outside_out_and_the_stated_workspace():
         assert_blocks_close(host64(out), O.summarize(X, off, Q, Wk, Wv, H), dtype, "canary case")
 
 
-@pytest.mark.parametrize("S,block", [(512, 0), (512, 1), (512, 2), (512, 3), (512, 4), (512, 9), (512, 10), (512, 15), (256, 2), (128, 3), (64, 1)])
-def test_queries_of_one_block_beyond_the_bound(S, block):
-    """d = 256: the waves of a head hold unequal shares of the queries; the wave whose block leaves the score bound
-    takes the running maximum, the others do not, and every query gets its own result."""
-    X, off, Q, Wk, Wv = problem(40 + block, [900, 1, 33, 2047], 256, S)
+BLOCKS = [(512, 0), (512, 1), (512, 2), (512, 3), (512, 4), (512, 9), (512, 10), (512, 15), (256, 2), (128, 3), (64, 1)]
+
+
+@pytest.mark.parametrize("S,block,longest", [(S, b, 2047) for S, b in BLOCKS] +
+                         [(S, b, 24000 if S == 512 else 13000) for S, b in BLOCKS if (S, b) not in ((512, 0), (512, 2))])
+def test_queries_of_one_block_beyond_the_bound(S, block, longest):
+    """d = 256: the waves of a head hold unequal shares of the queries (at S = 512 in workgroups of half the heads, and from
+    24 576 items with a thousand or more a user in whole ones); the wave whose block leaves the score bound takes the
+    running maximum, the others do not, and every query gets its own result."""
+    lens = [900, 1, 33, longest]
+    assert is_short_history("softmax", 256, S, sum(lens), 4) == (longest == 2047) and (S != 512 or longest == 2047 or sum(lens) >= 24576)
+    X, off, Q, Wk, Wv = problem(40 + block, lens, 256, S)
     Q[32 * block:32 * block + 32] *= 5.0          # exact in bf16 up to its rounding; |q| |k| passes 60, scores stay near 20
     Q = bf(Q)
-    got = run(X, off, Q, Wk, Wv, 8, segment_items=960)
-    assert_blocks_close(got, O.summarize(X, off, Q, Wk, Wv, 8), "bf16", f"S={S} block={block}")
+    want = O.summarize(X, off, Q, Wk, Wv, 8)
+    for seg in (960,) if longest == 2047 else (960, 0):
+        assert_blocks_close(run(X, off, Q, Wk, Wv, 8, segment_items=seg), want, "bf16", f"S={S} block={block} seg={seg}")
+
+
+@pytest.mark.parametrize("per_user,users", [(False, 24), (False, 25), (True, 16), (True, 17)])
+def test_both_sides_of_the_uneven_query_split(per_user, users):
+    """d = 256, S = 512, whole workgroups: 24 576 items (65 536 with queries of their own) of 1024 (4096) a user take the
+    uneven split, a user more the even one."""
+    items = 65536 if per_user else 24576
+    lens = [700, 0, 33] + [items // users] * (users - 3)
+    lens[0] += items - sum(lens)
+    assert not is_short_history("softmax", 256, 512, items, users, per_user)
+    X, off, Q, Wk, Wv = problem(61, lens, 256, 512, per_user=per_user)
+    got = run(X, off, Q, Wk, Wv, 8)
+    for b in (0, 1, 2, 3, users - 1):              # the longest, the one without items, the shortest and two ordinary ones
+        s = slice(off[b], off[b + 1])
+        want = O.summarize(X[s], [0, off[b + 1] - off[b]], Q[b] if per_user else Q, Wk, Wv, 8)
+        assert_blocks_close(got[b:b + 1], want, "bf16", f"user {b}")
+    assert np.all(np.isfinite(got)) and np.all(got[1] == 0)
 
 
 LIMITS = [("softmax", 128, 4, 64, 92), ("softmax", 128, 4, 128, 92), ("softmax", 128, 4, 256, 188), ("softmax", 128, 4, 512, 60),
