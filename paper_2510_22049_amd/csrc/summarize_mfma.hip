@@ -932,8 +932,9 @@ __global__ __launch_bounds__(MAXT, OCC) void summarize_mfma_kernel(MfmaSummarize
   // 100.5 us a call without it; 7000 items, d = 128, S = 256 33.8 -> 24.9; 100 users with queries of their own, 60 000 items,
   // d = 256, S = 512 255 -> 243.  They come before the history because what they need would have to be kept through it
   // otherwise, and every call would pay (behind it, calls without the self term: SiLU, d = 128, S = 256, 300 users, 9557
-  // items 103.4 us instead of 97.9; S = 64, 110 users, 117 964 items 36.3 instead of 35.7).
-  if (p.Ks) {
+  // items 103.4 us instead of 97.9; S = 64, 110 users, 117 964 items 36.3 instead of 35.7).  Marked as unlikely, they stand behind
+  // the streaming code instead of in front of it (softmax, S = 128, 64 users, 1 000 000 items 157.2 -> 155.3 us, others the same).
+  if (__builtin_expect(p.Ks != nullptr, 0)) {
     const int64_t groups = (p.N + p.seg - 1) / p.seg * p.nhg, units = (p.self_rows + 31) / 32 * (D / 32);
     for (int64_t u = int64_t(wave) * groups + g * p.nhg + hg; u < units; u += groups * (blockDim.x >> 6))
       self_kv_unit(p.Q, p.Wk, p.Wv, p.Ks, p.Vs, p.self_rows, D, u);
