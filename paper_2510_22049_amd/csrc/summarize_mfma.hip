@@ -1185,44 +1185,30 @@ bool mfma_split_supported(const vista_summarize_desc& d) {
 // 96 of 43 008 with queries of their own 69 / 78; S = 64, 200 of 65 536 30.8 / 33.5.  So a user counts as 1024 items, twice that with
 // queries of its own and at d = 256, S = 512.  Up to `few` items both kinds have segments of the least length, a workgroup of either
 // the same tiles, and any number of users is faster in halves (200 of 2048 items, d = 256, S = 512 205 / 182; own 287 / 260).
-static bool short_history(const vista_summarize_desc& d) {
+static int64_t short_limit(const vista_summarize_desc& d) {
   const bool silu = d.attn == VISTA_ATTN_SILU;
+  if (d.d == 256) return d.S == 64 ? 8192 : d.S == 512 ? (silu ? 20480 : 32768) : silu ? 12288 : 16384;
+  if (silu && d.S == 128) return 65536;
+  return d.S == 256 ? 229376 : d.S == 512 ? 98304 : 131072;
+}
+static bool short_history(const vista_summarize_desc& d) {
   const int64_t few = d.d == 256 ? 4096 : 8192;
   const int64_t user = (d.d == 256 && d.S == 512 ? 2048 : 1024) * (d.q_user_stride ? 2 : 1);
-  int64_t most;
-  if (d.d == 256)
-    most = d.S == 64 ? 8192 : d.S == 512 ? (silu ? 20480 : 32768) : silu ? 12288 : 16384;
-  else if (silu && d.S == 128)
-    most = 65536;
-  else
-    most = d.S == 256 ? 229376 : d.S == 512 ? 98304 : 131072;
-  return d.total_items <= few || d.total_items + user * int64_t(d.B) <= most;
+  return d.total_items <= few || d.total_items + user * int64_t(d.B) <= short_limit(d);
 }
 
-// Head groups (workgroups per segment) and workgroups resident on a compute unit, as launched below.
-static int head_groups(const vista_summarize_desc& d) {
+// Head groups (workgroups per segment; half: of half the heads each) and workgroups resident on a compute unit, as launched below.
+static int head_groups(const vista_summarize_desc& d, bool half) {
   const int nqb = (d.S + 31) / 32;
-  if (mfma_summarize_supported(d)) return (d.d == 256 ? 4 : nqb > 8 ? 2 : 1) * (short_history(d) ? 2 : 1);
+  if (mfma_summarize_supported(d)) return (d.d == 256 ? 4 : nqb > 8 ? 2 : 1) * (half ? 2 : 1);
   if (d.d == 256) return 8;
   return nqb > 8 ? d.H : d.H / 2;
 }
 static int resident_workgroups(const vista_summarize_desc& d) {
   // Two fit, but two cold starts on a compute unit have to pay: a segment of 768 items for one does it with the split
   // operands (d = 64, S = 100: 60 000 items in 29.7 us with one, 33.7 with two, 200 000 in 52.5 and 51.9), 2048 at d = 256.
-  if (mfma_split_supported(d)) return d.d != 256 && d.S <= 128 && d.total_items > 768 * 256 / head_groups(d) ? 2 : 1;
+  if (mfma_split_supported(d)) return d.d != 256 && d.S <= 128 && d.total_items > 768 * 256 / head_groups(d, false) ? 2 : 1;
   return d.d == 256 && d.S == 64 && d.total_items > 131072 ? 2 : 1;
-}
-
-// Whether the seeds' own keys and values are formed beside the history.  With workgroups on nearly every compute unit the
-// main kernel's waves do it as fast as a kernel of its own, without its launch and cold start; with fewer, only a few units
-// for each are worth it, and queries of their own for many users over few items go to the kernel that fills the chip.  us a
-// call, in front / beside, queries of their own: 250 workgroups or more, d = 128, S = 256, 40 000 items, 32 users (4 units a
-// workgroup) 47.1 / 44.9, 128 users (16) 85.1 / 82.5; d = 256, S = 512, 128 users, 8000 items (64) 293 / 285.  126 workgroups, d = 128,
-// S = 256, 8000 items: 8 users (2) 38.8 / 34.6, 32 users (8) 41.2 / 41.9, 128 users (32) 84.9 / 94.8.  32 workgroups, 2000 items: 2
-// users (2) 29.6 / 26.6, 8 users (8) 35.9 / 36.6, 32 users (32) 43.3 / 64.4.
-static bool self_beside_history(const vista_summarize_desc& d, int64_t G, int64_t rows) {
-  const int64_t units = (rows + 31) / 32 * (d.d / 32), groups = G * head_groups(d);
-  return units <= (groups >= 240 ? 64 : 4) * groups;
 }
 
 // Segment size of the matrix-core kernels where the caller leaves it open: the history is cut so that
@@ -1234,13 +1220,14 @@ static bool self_beside_history(const vista_summarize_desc& d, int64_t G, int64_
 // at 96 and 20.8 at 128.
 int mfma_summarize_segment(const vista_summarize_desc& d) {
   const int64_t N = d.total_items;
-  const int64_t units = 256 * resident_workgroups(d) / head_groups(d);
+  const bool half = mfma_summarize_supported(d) && short_history(d);
+  const int64_t units = 256 * resident_workgroups(d) / head_groups(d, half);
   constexpr int64_t kMost = 32768, kLeast = 128;
   int64_t k = (N + units * kMost - 1) / (units * kMost);
   if (k < 1) k = 1;
   int64_t s = (N + units * k - 1) / (units * k);
   s = (s + 31) / 32 * 32;
-  if (mfma_summarize_supported(d) && short_history(d)) {
+  if (half) {
     // Few workgroups: a longer segment is more tiles for each, a shorter one more records to write and merge, so the
     // best length goes with the square root: 1.5 sqrt(N).  (15 000 items, d = 128, S = 256: 27.7 us at 128, 24.8 at 192,
     // 24.3 at 256; 30 000: 34.4 at 128, 28.6 at 256, 31.4 at 512.)
@@ -1248,6 +1235,34 @@ int mfma_summarize_segment(const vista_summarize_desc& d) {
     if (s < r) s = r;
   }
   return int(s < kLeast ? kLeast : s);
+}
+
+// Whether G segments go to workgroups of half the heads.  Segments fitted here follow short_history.  Where the caller names their
+// size, or the workspace leaves the base schedule, both kinds walk the same tiles of the same users, and halves win while each has
+// a compute unit.  At d = 128 two of them share one, and in a short history nothing is lost beyond (a user is a record and a ragged tile
+// of it, 128 items).  Half / whole, mean over 1 to 200 users and segments of 64 to 4096 items: softmax, d = 128, S = 256, 60 halves 0.73, 240
+// 0.75, 500 0.95; S = 512, 120 0.77, 240 0.80; S = 128 in segments of 8192, 260 1.06; d = 256, S = 256, 64 halves 0.83, 240 0.86, 480 1.05; S = 512
+// 0.82, 0.86, 1.02.  At d = 256 up to 288 are well in segments of up to 256 (0.84 to 0.99), 1.1 to 1.2 in longer ones; S = 64 is 0.99 for 240,
+// 1.04 in long segments.
+static bool half_workgroups(const vista_summarize_desc& d, int seg, int64_t G) {
+  if (!mfma_summarize_supported(d)) return false;
+  if (seg == mfma_summarize_segment(d)) return short_history(d);
+  const bool few = d.total_items + 128 * int64_t(d.B) <= short_limit(d);
+  const int64_t halves = G * head_groups(d, true);
+  if (d.d == 128) return few || halves <= 256;
+  return few ? halves <= 288 : halves <= 256 && d.S != 64;
+}
+
+// Whether the seeds' own keys and values are formed beside the history.  With workgroups on nearly every compute unit the
+// main kernel's waves do it as fast as a kernel of its own, without its launch and cold start; with fewer, only a few units
+// for each are worth it, and queries of their own for many users over few items go to the kernel that fills the chip.  us a
+// call, in front / beside, queries of their own: 250 workgroups or more, d = 128, S = 256, 40 000 items, 32 users (4 units a
+// workgroup) 47.1 / 44.9, 128 users (16) 85.1 / 82.5; d = 256, S = 512, 128 users, 8000 items (64) 293 / 285.  126 workgroups, d = 128,
+// S = 256, 8000 items: 8 users (2) 38.8 / 34.6, 32 users (8) 41.2 / 41.9, 128 users (32) 84.9 / 94.8.  32 workgroups, 2000 items: 2
+// users (2) 29.6 / 26.6, 8 users (8) 35.9 / 36.6, 32 users (32) 43.3 / 64.4.
+static bool self_beside_history(const vista_summarize_desc& d, int seg, int64_t G, int64_t rows) {
+  const int64_t units = (rows + 31) / 32 * (d.d / 32), groups = G * head_groups(d, half_workgroups(d, seg, G));
+  return units <= (groups >= 240 ? 64 : 4) * groups;
 }
 
 static size_t partial_bytes(const vista_summarize_desc& d, int seg) {
@@ -1274,7 +1289,7 @@ static hipError_t launch_main(MfmaSummarizeParams& p, int wph, int64_t G, hipStr
 template <int ATTN>
 static hipError_t launch_for_shape(MfmaSummarizeParams& p, const vista_summarize_desc& desc, int64_t G, hipStream_t s) {
   const int d = desc.d;
-  if (short_history(desc)) {
+  if (half_workgroups(desc, p.seg, G)) {
     if (d == 128) {
       if (p.nqb <= 2) return launch_main<128, 1, 2, 4, true, false, 256, ATTN, 1, 2>(p, 2, G, s);
       if (p.nqb <= 4) return launch_main<128, 2, 2, 4, true, false, 256, ATTN, 2, 2>(p, 2, G, s);
@@ -1375,7 +1390,7 @@ vista_status mfma_summarize(const SummarizeArgs& a) {
     Ks = reinterpret_cast<float*>(reinterpret_cast<char*>(p.partials) + ((partial_bytes(d, a.seg) + 255) & ~size_t(255)));
     Vs = Ks + self_kv_bytes(d) / sizeof(float);
     const int64_t rows = d.q_user_stride ? int64_t(d.B) * d.S : d.S;
-    if (mfma_self_kv_supported(d, a.Q, a.Wk, a.Wv) && self_beside_history(d, a.G, rows)) {
+    if (mfma_self_kv_supported(d, a.Q, a.Wk, a.Wv) && self_beside_history(d, a.seg, a.G, rows)) {
       p.Ks = Ks;
       p.Vs = Vs;
       p.self_rows = rows;
