@@ -132,10 +132,17 @@ def _dev(t: torch.Tensor, name: str) -> int:
     return t.data_ptr()
 
 
-def _stream() -> int:
-    """The current stream of the current device as a hipStream_t.  (torch.cuda.current_stream() builds a Stream object
-    for it: 2.8 us, more than half of a small call's host time; this takes 0.2.)"""
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+def _stream_getter():
+    """A function that gives the current stream of the current device as a hipStream_t.  torch.cuda.current_stream() builds a
+    Stream object for it (2.8 us, more than half of a small call's host time), the two private functions take 0.2; a torch
+    that does not have them goes the public way."""
+    raw, device = (getattr(torch._C, n, None) for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+    if raw is None or device is None:
+        return lambda: torch.cuda.current_stream().cuda_stream
+    return lambda: raw(device())
+
+
+_stream = _stream_getter()
 
 
 def summarize_desc(B, S, d, H, dtype, total_items, per_user_q=False, scale=0.0, segment_items=0,

@@ -6,6 +6,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 from paper_2510_22049_amd import binding as V
 
@@ -178,3 +179,20 @@ def test_static_entry_point_rejects_what_does_not_fit_its_array():
     assert V.vista_summarize_workspace_bytes(d) > V.VISTA_STATIC_SCRATCH_BYTES
     assert L.vista_summarize_static(C.byref(d), one, one, None, one, one, one, one, None) == V.VISTA_ERR_SCRATCH
     assert L.vista_summarize_static(C.byref(desc(B=0)), one, one, None, one, one, one, one, None) == V.VISTA_ERR_SHAPE
+
+
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_stream_handle_without_the_private_functions(monkeypatch, missing):
+    """A torch without them is asked for the current stream the public way."""
+    monkeypatch.delattr(torch._C, missing, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("Stream", (), {"cuda_stream": 0x5EED})())
+    assert V._stream_getter()() == 0x5EED
+
+
+@pytest.mark.gpu
+def test_stream_handle_is_the_current_stream():
+    side = torch.cuda.Stream()
+    assert V._stream() == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert V._stream() == side.cuda_stream == torch.cuda.current_stream().cuda_stream
+    assert V._stream() == torch.cuda.current_stream().cuda_stream
