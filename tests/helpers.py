@@ -2,6 +2,8 @@
 import numpy as np
 import torch
 
+from paper_2510_22049_amd import binding as V
+
 TOL = {"f32": 1e-4, "bf16": 2e-2}     # max error per output block relative to the block's max |value|
 
 
@@ -74,3 +76,26 @@ def user_as_items(d, S, own_queries=False):
 
 def is_short_history(form, d, S, N, B, own_queries=False):
     return N <= (4096 if d == 256 else 8192) or N + user_as_items(d, S, own_queries) * B <= short_history_limit(form, d, S)
+
+
+def fitted_segment(form, d, S, N, B, own_queries=False):
+    """Segment size of those kernels before any limit of the workspace (histories of up to 131 072 items)."""
+    units = 256 // (4 if d == 256 else 2 if S == 512 else 1)
+    if not is_short_history(form, d, S, N, B, own_queries):
+        return max(128, -(-(-(-N // units)) // 32) * 32)
+    by_root = (int(1.5 * N ** 0.5) + 16) // 32 * 32 if d == 128 and S < 512 else 0
+    return max(128, -(-(-(-N // (units // 2))) // 32) * 32, by_root)
+
+
+def takes_half_workgroups(form, off, d, H, S, own_queries=False, segment_items=0):
+    """Which kind of workgroup a call of those kernels takes, as the library's rules put it: at the fitted segment size as
+    above, at another one (named, or the base schedule's where the workspace has a limit) by the number of workgroups."""
+    B, N = len(off) - 1, int(off[-1])
+    desc = V.summarize_desc(B, S, d, H, V.VISTA_BF16, N, own_queries, segment_items=segment_items,
+                            attn=V.VISTA_ATTN_SILU if form == "silu" else V.VISTA_ATTN_SOFTMAX)
+    seg = V.vista_summarize_call_segment_items(desc)
+    if seg == fitted_segment(form, d, S, N, B, own_queries):
+        return is_short_history(form, d, S, N, B, own_queries)
+    few = N + 128 * B <= short_history_limit(form, d, S)
+    halves = -(-N // seg) * (8 if d == 256 else 4 if S == 512 else 2)
+    return few or halves <= 256 if d == 128 else halves <= 288 if few else halves <= 256 and S != 64

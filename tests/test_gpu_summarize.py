@@ -6,7 +6,7 @@ import torch
 from oracle import vista_oracle as O
 from paper_2510_22049_amd import binding as V
 from paper_2510_22049_amd import inputs as I
-from tests.helpers import assert_blocks_close, block_errors, dev, host64, is_short_history, short_history_limit, user_as_items
+from tests.helpers import assert_blocks_close, block_errors, dev, host64, is_short_history, short_history_limit, takes_half_workgroups, user_as_items
 
 pytestmark = pytest.mark.gpu
 
@@ -271,3 +271,72 @@ def test_both_sides_of_the_short_history_limit(form, d, H, S, users, beyond):
         got = run(X, off, Q, Wk, Wv, H, segment_items=seg, attn=V.VISTA_ATTN_SILU if silu else V.VISTA_ATTN_SOFTMAX)
         assert_blocks_close(got, want, "bf16", f"{form} d={d} S={S} N={items} seg={seg}")
         assert np.all(got[1] == 0)
+
+
+EDGES = ["self", "own", "mixed", "negative", "infinite weight", "aligned to an element", "codec"]
+
+
+@pytest.mark.parametrize("form,edge", [("softmax", e) for e in EDGES] + [("silu", e) for e in EDGES if e != "negative"])
+@pytest.mark.parametrize("d,H,S", [(128, 4, 64), (128, 4, 128), (128, 4, 256), (128, 4, 512), (256, 8, 64), (256, 8, 128), (256, 8, 256), (256, 8, 512)])
+def test_whole_workgroups_on_the_edges(form, d, H, S, edge):
+    """The same users alone (workgroups of half the heads) and in front of a crowd that makes whole ones of them: same
+    segments, so the same records in the same order.  Bits are equal, but at d = 256, S = 512, where a wave holds other
+    queries and the running maximum starts at other tiles; and right by the oracle.  The edges: the self term and a
+    scale, queries of their own, scores on both sides of the bound (SiLU: several hundred either way), all of them near
+    -260, a weight that is not finite, weights at element alignment, the fused codec."""
+    lens = [700, 0, 1, 31, 32, 33, 1100, 64, 0, 95, 1029] + [9, 0, 4] * (20 if d == 128 else 14)
+    crowd = [2000] if d == 256 else [5000] + [1, 5, 0, 33] * (8 if S == 512 else 50)
+    silu, B = form == "silu", len(lens)
+    X, off, Q, Wk, Wv = problem(90 + S, lens + crowd, d, S, per_user=edge == "own")
+    if edge == "mixed" and silu:
+        Q = bf(Q * 12)
+    elif edge == "mixed":
+        X = bf(X * 6)
+        X[40:60] = bf(X[40:60] / 6)
+    elif edge == "negative":
+        Wk = np.eye(d, dtype=np.float32)
+        X[:, ::32], Q[..., ::32] = 32.0, -32.0
+    elif edge == "infinite weight":
+        Wv[d // 2 + 3, d - 14] = np.inf
+
+    def call(users):
+        o = off[:users + 1]
+        assert takes_half_workgroups(form, o, d, H, S, edge == "own") == (users == B)
+        q = dev(Q[:users] if edge == "own" else Q, "bf16")
+        w = [dev(m, "bf16") for m in (Wk, Wv)]
+        if edge == "aligned to an element":
+            flat = [torch.empty(d * d + 1, device="cuda", dtype=torch.bfloat16) for _ in w]
+            for f, m in zip(flat, w):
+                f[1:].copy_(m.flatten())
+            w = [f[1:].view(d, d) for f in flat]
+        args = (dev(X[:o[-1]], "bf16"), torch.from_numpy(o).cuda(), q, *w)
+        kw = dict(H=H, attn=V.VISTA_ATTN_SILU if silu else V.VISTA_ATTN_SOFTMAX, self_term=edge == "self", scale=0.2 if edge == "self" else 0.0)
+        if edge == "codec":
+            codes, scales = torch.full((users, S, d), 99, device="cuda", dtype=torch.int8), torch.zeros((users, S, H), device="cuda")
+            V.vista_summarize_q8(*args, codes, scales, **kw)
+            return O.dequantize_summaries(codes.cpu().numpy()[:B], scales.cpu().numpy()[:B])
+        out = torch.full((users, S, d), float("nan"), device="cuda", dtype=torch.bfloat16)
+        V.vista_summarize(*args, out, **kw)
+        return host64(out)[:B]
+
+    desc = lambda users: V.summarize_desc(users, S, d, H, V.VISTA_BF16, int(off[users]), edge == "own",
+                                          attn=V.VISTA_ATTN_SILU if silu else V.VISTA_ATTN_SOFTMAX)
+    assert V.vista_summarize_call_segment_items(desc(B)) == V.vista_summarize_call_segment_items(desc(len(off) - 1)) == 128
+    assert B * H * (S // 32) > 512                 # both calls merge a user's records in one run
+    alone, among = call(B), call(len(off) - 1)
+    if (d, S) != (256, 512):
+        assert np.array_equal(alone, among, equal_nan=True)
+    if edge == "infinite weight":
+        rest = np.delete(np.arange(d), d - 14)
+        assert np.all(np.isfinite(among[:, :, rest])) and not np.any(np.isfinite(among[[0, 6]][:, :, d - 14]))
+        Wv[d // 2 + 3, d - 14], among = 0.0, among[:, :, rest]
+    want = (O.summarize_silu if silu else O.summarize)(X[:off[B]], off[:B + 1], Q[:B] if edge == "own" else Q, Wk, Wv, H,
+                                                       **(dict(self_term=True, scale=0.2) if edge == "self" else {}))
+    if edge == "infinite weight":
+        want = want[:, :, rest]
+    if edge == "codec":     # half a step of the codec, 1/254 of a group's largest magnitude, on top of the path's 2e-2
+        assert np.all(np.abs(among - want) <= (2e-2 + 1 / 254) * np.abs(want).max(axis=(1, 2), keepdims=True) * 1.02)
+    else:
+        # a user of a few items takes the rounding of single scores, 2^-9 of up to 20 where keys are six times as long, into its output
+        users = [b for b in range(B) if edge != "mixed" or silu or lens[b] == 0 or lens[b] > 30]
+        assert_blocks_close(among[users], want[users], "bf16", f"{form} d={d} S={S} {edge}")

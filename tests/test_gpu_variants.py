@@ -7,7 +7,7 @@ import torch
 from oracle import vista_oracle as O
 from paper_2510_22049_amd import binding as V
 from paper_2510_22049_amd import inputs as I
-from tests.helpers import TOL, assert_blocks_close, block_errors, dev, host64, torch_dtype
+from tests.helpers import TOL, assert_blocks_close, block_errors, dev, host64, takes_half_workgroups, torch_dtype
 
 pytestmark = pytest.mark.gpu
 
@@ -454,12 +454,16 @@ def test_qla_backward_takes_an_element_aligned_d_out(dtype, d, H, S):
         assert torch.equal(a, b) and bool(torch.isfinite(a.float()).all())
 
 
-# sixteen waves of one query block each (the layout of this shape alone)
+# sixteen waves of one query block each (the layout of this shape alone): so many users, or items, that workgroups hold all heads
+MANY = [9000] + [1, 5, 0, 33] * 115
+
+
 @pytest.mark.parametrize("seg,per_user,self_term,qscale,scale", [
     (0, False, False, 1.0, 0.0), (96, True, True, 1.0, 0.0), (32, False, True, 1.0, 0.2), (64, True, False, 12.0, 0.0)])
 def test_mfma_silu_form_on_sixteen_waves(seg, per_user, self_term, qscale, scale):
     """Ragged tails, per-user seeds, the self term, scores of several hundred either way, a run of full tiles."""
-    X, off, Q, Wk, Wv = problem(35, LENS, 128, 128, "bf16", per_user, qscale)
+    X, off, Q, Wk, Wv = problem(35, LENS + MANY, 128, 128, "bf16", per_user, qscale)
+    assert not takes_half_workgroups("silu", off, 128, 4, 128, per_user, seg)
     got = run("silu", X, off, Q, Wk, Wv, 4, "bf16", self_term, segment_items=seg, scale=scale)
     want = O.summarize_silu(X, off, Q, Wk, Wv, 4, scale=scale or None, self_term=self_term)
     assert_blocks_close(got, want, "bf16", f"silu, sixteen waves, seg={seg} self={self_term} scale={scale}")
@@ -469,10 +473,11 @@ def test_mfma_silu_form_on_sixteen_waves(seg, per_user, self_term, qscale, scale
 @pytest.mark.parametrize("seed", range(4))
 def test_random_jagged_batches_on_sixteen_waves(seed):
     g = np.random.default_rng(1100 + seed)
-    seg = int(g.choice([32, 64, 96, 256, 992]))
-    lens = random_lengths(g, seg)
+    seg = int(g.choice([0, 32, 64, 96]))
+    lens = random_lengths(g, seg or 128) + MANY
     per_user, self_term = bool(g.integers(0, 2)), bool(g.integers(0, 2))
     X, off, Q, Wk, Wv = problem(2100 + seed, lens, 128, 128, "bf16", per_user=per_user)
+    assert not takes_half_workgroups("silu", off, 128, 4, 128, per_user, seg)
     got = run("silu", X, off, Q, Wk, Wv, 4, "bf16", self_term=self_term, segment_items=seg,
               offsets_host=torch.from_numpy(off) if seed % 2 else None)
     want = oracle("silu", X, off, Q, Wk, Wv, 4, self_term)
@@ -554,6 +559,7 @@ def test_four_query_blocks_a_wave_at_512_seeds(form, per_user, self_term, block,
     """d = 256, S = 512 with the queries shared evenly and the weights in LDS (SiLU, and many short users with queries of
     their own): one block of queries beyond the score bound, users that change every few items, the self term."""
     X, off, Q, Wk, Wv = problem(83 + block, CROWD, 256, 512, "bf16", per_user=per_user)
+    assert not takes_half_workgroups(form, off, 256, 8, 512, per_user, seg)
     Q[..., 32 * block:32 * block + 32, :] *= 5.0
     Q = I.round_to(Q, "bf16")
     got = run(form, X, off, Q, Wk, Wv, 8, "bf16", self_term, segment_items=seg)

@@ -6,7 +6,7 @@ import pytest
 
 from paper_2510_22049_amd import binding as V
 from paper_2510_22049_amd import inputs as I
-from tests.helpers import is_short_history, short_history_limit, user_as_items
+from tests.helpers import fitted_segment, is_short_history, short_history_limit, user_as_items
 
 
 def desc(B, N, seg=0, S=256, d=128, H=4):
@@ -134,17 +134,16 @@ def test_the_segment_size_of_an_invalid_call():
 def test_where_a_history_is_short(form, d, H, S, own):
     """Workgroups of half the heads are twice as many, so the segments that fill the chip with them are twice as long: the
     segment size tells which kind a call takes.  Many users make a history long, queries of their own twice as fast."""
-    units = 256 // (4 if d == 256 else 2 if S == 512 else 1)     # segments a turn, workgroups of all heads
-    size = lambda N, u: max(128, -(-(-(-N // u)) // 32) * 32)
     told = 0
     for B in (1, 2, 3, 5, 8, 13, 30, 60, 100, 200):
         edge = short_history_limit(form, d, S) - user_as_items(d, S, own) * B
         for N in (edge - 999, edge, edge + 1, edge + 999):
-            if N < max(128 * units // 2 + 32, 30000 if d == 128 else 0):
-                continue                                         # segments of the least length, or fitted to few workgroups
-            short = is_short_history(form, d, S, N, B, own)
-            assert short == (N <= edge)
+            if N < (4096 if d == 256 else 8192) + 1:
+                continue
+            assert is_short_history(form, d, S, N, B, own) == (N <= edge)
             q = V.summarize_desc(B, S, d, H, V.VISTA_BF16, N, own, attn=V.VISTA_ATTN_SILU if form == "silu" else V.VISTA_ATTN_SOFTMAX)
-            assert V.vista_summarize_call_segment_items(q) == size(N, units // 2 if short else units), (B, N)
-            told += size(N, units) != size(N, units // 2)
+            seg = fitted_segment(form, d, S, N, B, own)
+            fits = (-(-N // seg) + B) * H * -(-S // 32) * 18 * 256 < 63 << 20         # (the base schedule otherwise)
+            assert V.vista_summarize_call_segment_items(q) == (seg if fits else 256), (B, N)
+            told += fits and seg != fitted_segment(form, d, S, N, 10 ** 6 if N <= edge else 0, own)
     assert told >= 4
