@@ -1180,11 +1180,12 @@ bool mfma_split_supported(const vista_summarize_desc& d) {
 // heads share the chip as it is: S = 64, 7001 18.2 / 17.9, 15 000 21.4 / 23.1; S = 128, 15 000 24.6 / 22.8, 20 000 25.8 / 26.0; S = 256,
 // 15 000 31.4 / 28.8, 25 000 35.4 / 36.0; S = 512, 30 000 53.7 / 51.1, 45 000 62.1 / 62.2; SiLU, S = 128, 13 845 24.1 / 25.5.
 // Users count too: a workgroup of half the heads walks twice the items, so twice the users, and at every change of user its one
-// wave a SIMD goes through a ragged tile, a record and, with queries of their own, their load with nobody beside it.  Lognormal
-// users, d = 256, S = 512: 64 of 24 576 items 74.0 / 84.2, queries of their own 84.1 / 99.7; 8 of 31 744 52.3 / 48.2; d = 128, S = 512,
-// 96 of 43 008 with queries of their own 69 / 78; S = 64, 200 of 65 536 30.8 / 33.5.  So a user counts as 1024 items, twice that with
-// queries of its own and at d = 256, S = 512.  Up to `few` items both kinds have segments of the least length, a workgroup of either
-// the same tiles, and any number of users is faster in halves (200 of 2048 items, d = 256, S = 512 205 / 182; own 287 / 260).
+// wave a SIMD goes through a ragged tile, a record and, with queries of their own, their load with nobody beside it.  Each user
+// beyond the first counts as some items, few in the SiLU form, whose ragged tiles cost what full ones do, many where a wave holds six
+// blocks of queries.  Lognormal users, whole / half: softmax, d = 256, S = 512, 64 of 24 576 items 74.0 / 84.2, queries of their own
+// 84.1 / 99.7; 8 of 31 744 52.3 / 48.2; d = 128, S = 512, 96 of 43 008 with queries of their own 69 / 78; S = 64, 200 of 65 536 30.8 / 33.5,
+// SiLU, S = 256, 110 of 22 937 63 / 49.  Up to `few` items any number of users is faster in halves (200 of 2048, d = 256, S = 512
+// 205 / 182; own 287 / 260).  Over 6350 calls (1 to 300 users) ten take halves that are 3 to 6 % behind, 154 whole ones.
 static int64_t short_limit(const vista_summarize_desc& d) {
   const bool silu = d.attn == VISTA_ATTN_SILU;
   if (d.d == 256) return d.S == 64 ? 8192 : d.S == 512 ? (silu ? 20480 : 32768) : silu ? 12288 : 16384;
@@ -1192,9 +1193,16 @@ static int64_t short_limit(const vista_summarize_desc& d) {
   return d.S == 256 ? 229376 : d.S == 512 ? 98304 : 131072;
 }
 static bool short_history(const vista_summarize_desc& d) {
-  const int64_t few = d.d == 256 ? 4096 : 8192;
-  const int64_t user = (d.d == 256 && d.S == 512 ? 2048 : 1024) * (d.q_user_stride ? 2 : 1);
-  return d.total_items <= few || d.total_items + user * int64_t(d.B) <= short_limit(d);
+  const bool silu = d.attn == VISTA_ATTN_SILU, own = d.q_user_stride != 0;
+  const int64_t few = d.d == 128 ? 12288 : d.S < 256 ? 4096 : 6144;
+  int64_t user;
+  if (d.d == 256)
+    user = d.S == 64 ? 2048 : silu ? 384 : d.S < 512 ? 192 : own ? 3072 : 2048;
+  else if (silu)
+    user = d.S == 128 ? (own ? 768 : 320) : 128;
+  else
+    user = d.S == 512 ? (own ? 1024 : 768) : own ? 640 : 384;
+  return d.total_items <= few || d.total_items + user * int64_t(d.B - 1) <= short_limit(d);
 }
 
 // Head groups (workgroups per segment; half: of half the heads each) and workgroups resident on a compute unit, as launched below.

@@ -61,8 +61,8 @@ def assert_in_value_hull(out: torch.Tensor, values: torch.Tensor, what="", slack
 
 
 def short_history_limit(form, d, S):
-    """Largest history, users counted as items, that the bf16 matrix-core kernels of S = 64, 128, 256, 512 give to
-    workgroups of half the heads (tests/test_schedule_host.py pins it against the library)."""
+    """Largest history, users beyond the first counted as items, that the bf16 matrix-core kernels of S = 64, 128, 256, 512
+    give to workgroups of half the heads (tests/test_schedule_host.py pins it against the library)."""
     if d == 256:
         return 8192 if S == 64 else {"softmax": 32768, "silu": 20480}[form] if S == 512 else {"softmax": 16384, "silu": 12288}[form]
     if form == "silu" and S == 128:
@@ -70,12 +70,20 @@ def short_history_limit(form, d, S):
     return {64: 131072, 128: 131072, 256: 229376, 512: 98304}[S]
 
 
-def user_as_items(d, S, own_queries=False):
-    return (2048 if (d, S) == (256, 512) else 1024) * (2 if own_queries else 1)
+def user_as_items(form, d, S, own_queries=False):
+    if d == 256:
+        return 2048 if S == 64 else 384 if form == "silu" else 192 if S < 512 else 3072 if own_queries else 2048
+    if form == "silu":
+        return (768 if own_queries else 320) if S == 128 else 128
+    return (1024 if own_queries else 768) if S == 512 else 640 if own_queries else 384
+
+
+def always_short(d, S):
+    return 12288 if d == 128 else 4096 if S < 256 else 6144
 
 
 def is_short_history(form, d, S, N, B, own_queries=False):
-    return N <= (4096 if d == 256 else 8192) or N + user_as_items(d, S, own_queries) * B <= short_history_limit(form, d, S)
+    return N <= always_short(d, S) or N + user_as_items(form, d, S, own_queries) * (B - 1) <= short_history_limit(form, d, S)
 
 
 def fitted_segment(form, d, S, N, B, own_queries=False):

@@ -217,7 +217,7 @@ BLOCKS = [(512, 0), (512, 1), (512, 2), (512, 3), (512, 4), (512, 9), (512, 10),
 
 
 @pytest.mark.parametrize("S,block,longest", [(S, b, 2047) for S, b in BLOCKS] +
-                         [(S, b, 24000 if S == 512 else 13000) for S, b in BLOCKS if (S, b) not in ((512, 0), (512, 2))])
+                         [(S, b, 27000 if S == 512 else 17000) for S, b in BLOCKS if (S, b) not in ((512, 0), (512, 2))])
 def test_queries_of_one_block_beyond_the_bound(S, block, longest):
     """d = 256: the waves of a head hold unequal shares of the queries (at S = 512 in workgroups of half the heads, and from
     24 576 items with a thousand or more a user in whole ones); the wave whose block leaves the score bound takes the
@@ -249,10 +249,10 @@ def test_both_sides_of_the_uneven_query_split(per_user, users):
     assert np.all(np.isfinite(got)) and np.all(got[1] == 0)
 
 
-LIMITS = [("softmax", 128, 4, 64, 92), ("softmax", 128, 4, 128, 92), ("softmax", 128, 4, 256, 188), ("softmax", 128, 4, 512, 60),
-          ("silu", 128, 4, 64, 92), ("silu", 128, 4, 128, 28), ("silu", 128, 4, 256, 188), ("silu", 128, 4, 512, 60),
-          ("softmax", 256, 8, 64, 3), ("softmax", 256, 8, 128, 5), ("softmax", 256, 8, 256, 5), ("softmax", 256, 8, 512, 5),
-          ("silu", 256, 8, 64, 3), ("silu", 256, 8, 128, 5), ("silu", 256, 8, 256, 5), ("silu", 256, 8, 512, 5)]
+LIMITS = [("softmax", 128, 4, 64, 240), ("softmax", 128, 4, 128, 240), ("softmax", 128, 4, 256, 200), ("softmax", 128, 4, 512, 80),
+          ("silu", 128, 4, 64, 300), ("silu", 128, 4, 128, 80), ("silu", 128, 4, 256, 200), ("silu", 128, 4, 512, 100),
+          ("softmax", 256, 8, 64, 2), ("softmax", 256, 8, 128, 20), ("softmax", 256, 8, 256, 20), ("softmax", 256, 8, 512, 5),
+          ("silu", 256, 8, 64, 2), ("silu", 256, 8, 128, 10), ("silu", 256, 8, 256, 10), ("silu", 256, 8, 512, 10)]
 
 
 @pytest.mark.parametrize("form,d,H,S,users", LIMITS)
@@ -261,16 +261,16 @@ def test_both_sides_of_the_short_history_limit(form, d, H, S, users, beyond):
     """A history at the limit, users counted as items, goes to workgroups of half the heads, one item more to whole ones:
     ragged users, one without items, tiles and segments that end inside them, default and short segments."""
     lens = ([1, 0, 33, 2011] + [40] * users)[:users - 1]
-    items = short_history_limit(form, d, S) - user_as_items(d, S) * users + beyond
+    items = short_history_limit(form, d, S) - user_as_items(form, d, S) * (users - 1) + beyond
     lens.insert(2, items - sum(lens))
-    assert is_short_history(form, d, S, items, users) == (not beyond)
     X, off, Q, Wk, Wv = problem(50, lens, d, S)
+    assert takes_half_workgroups(form, off, d, H, S) == (not beyond)
     silu = form == "silu"
     want = (O.summarize_silu if silu else O.summarize)(X, off, Q, Wk, Wv, H)
     for seg in (0, 480):
         got = run(X, off, Q, Wk, Wv, H, segment_items=seg, attn=V.VISTA_ATTN_SILU if silu else V.VISTA_ATTN_SOFTMAX)
         assert_blocks_close(got, want, "bf16", f"{form} d={d} S={S} N={items} seg={seg}")
-        assert np.all(got[1] == 0)
+        assert all(np.all(got[b] == 0) for b in range(users) if lens[b] == 0)
 
 
 EDGES = ["self", "own", "mixed", "negative", "infinite weight", "aligned to an element", "codec"]
@@ -279,15 +279,17 @@ EDGES = ["self", "own", "mixed", "negative", "infinite weight", "aligned to an e
 @pytest.mark.parametrize("form,edge", [("softmax", e) for e in EDGES] + [("silu", e) for e in EDGES if e != "negative"])
 @pytest.mark.parametrize("d,H,S", [(128, 4, 64), (128, 4, 128), (128, 4, 256), (128, 4, 512), (256, 8, 64), (256, 8, 128), (256, 8, 256), (256, 8, 512)])
 def test_whole_workgroups_on_the_edges(form, d, H, S, edge):
-    """The same users alone (workgroups of half the heads) and in front of a crowd that makes whole ones of them: same
+    """The same users alone (workgroups of half the heads) and in front of one so long that workgroups are whole: same
     segments, so the same records in the same order.  Bits are equal, but at d = 256, S = 512, where a wave holds other
     queries and the running maximum starts at other tiles; and right by the oracle.  The edges: the self term and a
     scale, queries of their own, scores on both sides of the bound (SiLU: several hundred either way), all of them near
     -260, a weight that is not finite, weights at element alignment, the fused codec."""
     lens = [700, 0, 1, 31, 32, 33, 1100, 64, 0, 95, 1029] + [9, 0, 4] * (20 if d == 128 else 14)
-    crowd = [2000] if d == 256 else [5000] + [1, 5, 0, 33] * (8 if S == 512 else 50)
     silu, B = form == "silu", len(lens)
-    X, off, Q, Wk, Wv = problem(90 + S, lens + crowd, d, S, per_user=edge == "own")
+    X, off, Q, Wk, Wv = problem(90 + S, lens, d, S, per_user=edge == "own")
+    long = short_history_limit(form, d, S)
+    X, off = np.concatenate([X, np.resize(X, (long, d))]), np.append(off, off[-1] + long)
+    Q = np.concatenate([Q, Q[:1]]) if edge == "own" else Q
     if edge == "mixed" and silu:
         Q = bf(Q * 12)
     elif edge == "mixed":
@@ -301,7 +303,7 @@ def test_whole_workgroups_on_the_edges(form, d, H, S, edge):
 
     def call(users):
         o = off[:users + 1]
-        assert takes_half_workgroups(form, o, d, H, S, edge == "own") == (users == B)
+        assert takes_half_workgroups(form, o, d, H, S, edge == "own", 128) == (users == B)
         q = dev(Q[:users] if edge == "own" else Q, "bf16")
         w = [dev(m, "bf16") for m in (Wk, Wv)]
         if edge == "aligned to an element":
@@ -310,7 +312,8 @@ def test_whole_workgroups_on_the_edges(form, d, H, S, edge):
                 f[1:].copy_(m.flatten())
             w = [f[1:].view(d, d) for f in flat]
         args = (dev(X[:o[-1]], "bf16"), torch.from_numpy(o).cuda(), q, *w)
-        kw = dict(H=H, attn=V.VISTA_ATTN_SILU if silu else V.VISTA_ATTN_SOFTMAX, self_term=edge == "self", scale=0.2 if edge == "self" else 0.0)
+        kw = dict(H=H, attn=V.VISTA_ATTN_SILU if silu else V.VISTA_ATTN_SOFTMAX, self_term=edge == "self", scale=0.2 if edge == "self" else 0.0,
+                  segment_items=128)
         if edge == "codec":
             codes, scales = torch.full((users, S, d), 99, device="cuda", dtype=torch.int8), torch.zeros((users, S, H), device="cuda")
             V.vista_summarize_q8(*args, codes, scales, **kw)
@@ -319,11 +322,8 @@ def test_whole_workgroups_on_the_edges(form, d, H, S, edge):
         V.vista_summarize(*args, out, **kw)
         return host64(out)[:B]
 
-    desc = lambda users: V.summarize_desc(users, S, d, H, V.VISTA_BF16, int(off[users]), edge == "own",
-                                          attn=V.VISTA_ATTN_SILU if silu else V.VISTA_ATTN_SOFTMAX)
-    assert V.vista_summarize_call_segment_items(desc(B)) == V.vista_summarize_call_segment_items(desc(len(off) - 1)) == 128
     assert B * H * (S // 32) > 512                 # both calls merge a user's records in one run
-    alone, among = call(B), call(len(off) - 1)
+    alone, among = call(B), call(B + 1)
     if (d, S) != (256, 512):
         assert np.array_equal(alone, among, equal_nan=True)
     if edge == "infinite weight":
@@ -334,9 +334,10 @@ def test_whole_workgroups_on_the_edges(form, d, H, S, edge):
                                                        **(dict(self_term=True, scale=0.2) if edge == "self" else {}))
     if edge == "infinite weight":
         want = want[:, :, rest]
-    if edge == "codec":     # half a step of the codec, 1/254 of a group's largest magnitude, on top of the path's 2e-2
+    if edge == "codec":     # on top of the path's 2e-2 half a step of the codec, 1/254 of a group's largest computed magnitude
         assert np.all(np.abs(among - want) <= (2e-2 + 1 / 254) * np.abs(want).max(axis=(1, 2), keepdims=True) * 1.02)
     else:
-        # a user of a few items takes the rounding of single scores, 2^-9 of up to 20 where keys are six times as long, into its output
-        users = [b for b in range(B) if edge != "mixed" or silu or lens[b] == 0 or lens[b] > 30]
-        assert_blocks_close(among[users], want[users], "bf16", f"{form} d={d} S={S} {edge}")
+        # mixed: keys six times as long.  Their bf16 rounding moves a score by 2^-9 / sqrt(3) x 6 = 0.007 (one sigma), 0.03 at the worst of
+        # the 10^6 there are; between two items of equal weight and opposite value that is 0.25 x 0.03 x 2 of the largest value
+        slack = 0.015 if edge == "mixed" and not silu else 0.0
+        assert np.all(np.isfinite(among)) and block_errors(among, want).max() <= 2e-2 + slack, f"{form} d={d} S={S} {edge}"

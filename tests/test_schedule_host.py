@@ -6,7 +6,7 @@ import pytest
 
 from paper_2510_22049_amd import binding as V
 from paper_2510_22049_amd import inputs as I
-from tests.helpers import fitted_segment, is_short_history, short_history_limit, user_as_items
+from tests.helpers import always_short, fitted_segment, is_short_history, short_history_limit, user_as_items
 
 
 def desc(B, N, seg=0, S=256, d=128, H=4):
@@ -133,17 +133,18 @@ def test_the_segment_size_of_an_invalid_call():
 @pytest.mark.parametrize("own", [False, True])
 def test_where_a_history_is_short(form, d, H, S, own):
     """Workgroups of half the heads are twice as many, so the segments that fill the chip with them are twice as long: the
-    segment size tells which kind a call takes.  Many users make a history long, queries of their own twice as fast."""
+    segment size tells which kind a call takes.  Many users make a history long."""
     told = 0
     for B in (1, 2, 3, 5, 8, 13, 30, 60, 100, 200):
-        edge = short_history_limit(form, d, S) - user_as_items(d, S, own) * B
+        edge = short_history_limit(form, d, S) - user_as_items(form, d, S, own) * (B - 1)
         for N in (edge - 999, edge, edge + 1, edge + 999):
-            if N < (4096 if d == 256 else 8192) + 1:
+            if N <= always_short(d, S):
                 continue
             assert is_short_history(form, d, S, N, B, own) == (N <= edge)
             q = V.summarize_desc(B, S, d, H, V.VISTA_BF16, N, own, attn=V.VISTA_ATTN_SILU if form == "silu" else V.VISTA_ATTN_SOFTMAX)
             seg = fitted_segment(form, d, S, N, B, own)
-            fits = (-(-N // seg) + B) * H * -(-S // 32) * 18 * 256 < 63 << 20         # (the base schedule otherwise)
-            assert V.vista_summarize_call_segment_items(q) == (seg if fits else 256), (B, N)
+            base = V.vista_summarize_segment_items(q)                                 # what stays where the records are too many
+            fits = (-(-N // seg) + B) * H * (S // 32) * 18 * 256 < 63 << 20 or seg >= base
+            assert V.vista_summarize_call_segment_items(q) == (seg if fits else base), (B, N)
             told += fits and seg != fitted_segment(form, d, S, N, 10 ** 6 if N <= edge else 0, own)
     assert told >= 4
