@@ -5,8 +5,9 @@
 //   1. the X tile (32 x D bf16) goes from HBM straight into LDS (direct
 //      global->LDS loads, three tiles deep, no stop in registers);
 //   2. wave "K" of a pair forms K_h^T = (scale*log2e W_k,h)^T X^T, wave "V" forms
-//      V_h = X W_v,h -- D / 16 32x32x16 MFMAs each, weights held in registers (as LDS operands
-//      only in the widest SPLIT shape) -- and both hand the bf16 result to their partner through LDS;
+//      V_h = X W_v,h -- D / 16 32x32x16 MFMAs each, weights held in registers (as LDS operands only in
+//      the widest SPLIT shape and with four query blocks a wave at d = 256) -- and both hand the bf16
+//      result to their partner through LDS;
 //   3. each wave owns half of the S queries: for every block of 32 queries
 //      S^T = K_h Q_h^T (items x queries), p = 2^(s - m), O^T += V_h^T P^T.
 // With items on the MFMA row index and queries on the column index, every lane
@@ -17,9 +18,9 @@
 // the tiles of all pieces (user x segment) of the segment form one stream.
 // Where a pair would leave a wave with more than four query blocks (S = 512) or
 // with too few waves per compute unit (D = 256), a head gets more waves instead:
-// the K and V waves plus others that only attend, the queries shared by all (at D = 256, S = 512
-// unevenly: two blocks to a projecting wave, whose weights take 64 registers, six to the others,
-// which comes to 24 MFMAs a tile for each of the four).
+// the K and V waves plus others that only attend, the queries shared by all.  At D = 256, S = 512 they are shared
+// unevenly in long softmax histories and in workgroups of half the heads: two blocks to a projecting wave, whose weights take
+// 64 registers, six to the others, which comes to 24 MFMAs a tile for each of the four.
 // (Sixteen waves of two query blocks and 128 registers each, four to a SIMD, were 7 to 10 %
 // slower than eight of four: twice the operand reads from LDS and idle attend-only waves.)
 //
@@ -254,10 +255,9 @@ constexpr int kXBuf = 3;             // ring depth of the X tiles and of the pro
 constexpr int kvbuf_slots(bool split) { return split ? 2 : kXBuf; }
 
 // Shared memory of one workgroup.  WREG: a projecting wave keeps its D x 32 weight operands in
-// registers (D / 4 of them) instead of in LDS, which halves the operand reads of a projection.  These
-// kernels run at the power the chip allows (MFMAs on random operands alone sustain 1724 of 2470
-// TFLOP/s), so LDS traffic saved is time: with the weights in LDS at D = 256, 32 users and 500 000
-// items took 242 us instead of 222 at S = 128 and 308 instead of 296 at S = 256.
+// registers (D / 4 of them) instead of in LDS, which halves the operand reads of a projection: with the
+// weights in LDS at D = 256, 32 users and 500 000 items took 242 us instead of 222 at S = 128 and 308
+// instead of 296 at S = 256.
 template <int D, int HPW, bool WREG, bool SPLIT>
 struct SummarizeLds {
   uint4 xbuf[kXBuf][(D / 8) * 32];    // X tiles: [16-byte chunk][item], filled by direct global->LDS loads
@@ -904,7 +904,9 @@ __device__ __forceinline__ void self_kv_unit(const uint16_t* __restrict__ Q, con
 
 // MAXT: largest workgroup of the instantiation (it bounds the registers of a wave).  The first FW waves
 // fetch X (ALLF: that is every wave).
-// NQB query blocks to a projecting wave, NQA to one that only attends; OCC: waves of the kernel on a SIMD, at least.
+// NQB query blocks to a projecting wave, NQA to one that only attends.  OCC: waves on a SIMD that the registers have to leave
+// room for, as far as the workgroups that fit the LDS can fill them (the two-wave workgroups of D = 256, S = 64 cannot, and take
+// 295 registers).
 template <int D, int NQB, int NQA, int HPW, int FW, bool WREG, bool SPLIT, int MAXT, int ATTN, int OCC>
 __global__ __launch_bounds__(MAXT, OCC) void summarize_mfma_kernel(MfmaSummarizeParams p) {
   __shared__ SummarizeLds<D, HPW, WREG, SPLIT> sm;
@@ -1235,10 +1237,11 @@ int mfma_summarize_segment(const vista_summarize_desc& d) {
   if (k < 1) k = 1;
   int64_t s = (N + units * k - 1) / (units * k);
   s = (s + 31) / 32 * 32;
-  if (half) {
+  if (half && d.d == 128 && d.S < 512) {
     // Few workgroups: a longer segment is more tiles for each, a shorter one more records to write and merge, so the
-    // best length goes with the square root: 1.5 sqrt(N).  (15 000 items, d = 128, S = 256: 27.7 us at 128, 24.8 at 192,
-    // 24.3 at 256; 30 000: 34.4 at 128, 28.6 at 256, 31.4 at 512.)
+    // best length goes with the square root: 1.5 sqrt(N), which is beyond both the least length and an even share of the
+    // chip from 9200 to 28 700 items.  (15 000 items, d = 128, S = 256: 27.7 us at 128, 24.8 at 192, 24.3 at 256; 30 000: 34.4 at
+    // 128, 28.6 at 256, 31.4 at 512.  The other shapes have no such range.)
     const int64_t r = (int64_t(1.5 * sqrt(double(N))) + 16) / 32 * 32;
     if (s < r) s = r;
   }
@@ -1264,10 +1267,11 @@ static bool half_workgroups(const vista_summarize_desc& d, int seg, int64_t G) {
 // Whether the seeds' own keys and values are formed beside the history.  With workgroups on nearly every compute unit the
 // main kernel's waves do it as fast as a kernel of its own, without its launch and cold start; with fewer, only a few units
 // for each are worth it, and queries of their own for many users over few items go to the kernel that fills the chip.  us a
-// call, in front / beside, queries of their own: 250 workgroups or more, d = 128, S = 256, 40 000 items, 32 users (4 units a
-// workgroup) 47.1 / 44.9, 128 users (16) 85.1 / 82.5; d = 256, S = 512, 128 users, 8000 items (64) 293 / 285.  126 workgroups, d = 128,
-// S = 256, 8000 items: 8 users (2) 38.8 / 34.6, 32 users (8) 41.2 / 41.9, 128 users (32) 84.9 / 94.8.  32 workgroups, 2000 items: 2
-// users (2) 29.6 / 26.6, 8 users (8) 35.9 / 36.6, 32 users (32) 43.3 / 64.4.
+// call, in front / beside, queries of their own: 250 workgroups, d = 128, S = 256, 40 000 items, 32 users (4 units a workgroup) 46.6 /
+// 43.4, 128 users (16) 90.6 / 86.2; 256, d = 256, S = 512, 8000 items, 128 users (64) 302 / 296.  126, d = 128, S = 256, 8000 items: 8 users
+// (2) 39.3 / 34.6, 32 users (8) 44.7 / 44.0, 128 users (32) 86.5 / 96.6.  32, 2000 items: 2 users (2) 29.3 / 25.5, 8 users (8) 36.0 / 36.5, 32
+// users (32) 47.5 / 67.9.  Split operands: d = 64, S = 100, 63 workgroups, 32 users (3) 35.4 / 31.8; 250, 128 users (3) 43.6 / 38.7;
+// d = 256, S = 200, 256, 32 users (6) 103.2 / 95.5.  Of 1152 calls five take the kernel in front where beside is 5 to 13 % faster.
 static bool self_beside_history(const vista_summarize_desc& d, int seg, int64_t G, int64_t rows) {
   const int64_t units = (rows + 31) / 32 * (d.d / 32), groups = G * head_groups(d, half_workgroups(d, seg, G));
   return units <= (groups >= 240 ? 64 : 4) * groups;
