@@ -210,7 +210,7 @@ __global__ __launch_bounds__(256) void merge_kernel(const float* __restrict__ pa
     if (live && rg == 0) store_as(dst, 0.f);
     return;
   }
-  int64_t g0 = begin / seg, g1 = (end - 1) / seg;
+  int64_t g0 = segment_of(begin, seg), g1 = segment_of(end - 1, seg);
   if (g0 < 0) g0 = 0;
   if (g1 > G - 1) g1 = G - 1;
   const int64_t run = (g1 - g0 + RG) / RG;
@@ -329,20 +329,20 @@ __global__ void qla_state_kernel(const float* __restrict__ K, const float* __res
 
 // out_h = SiLU(Q_h) SiLU(Z_h) with Z_h the fixed-order sum of the user's states;
 // the self term adds (SiLU(q) . SiLU(k')) v'.  grid (B, H), 1024 threads, Z staged in LDS.
-// DH = the head width when it is known at compile time (32: the matrix-core shapes), else 0.
-template <typename T, int DH>
+// (Heads of width 32 have qla_finish32_kernel.)
+template <typename T>
 __global__ __launch_bounds__(1024) void qla_finish_kernel(const float* __restrict__ partials,
                                                          const int64_t* __restrict__ offsets, int S, int d, int H,
                                                          int seg, int64_t G, T* __restrict__ out,
                                                          const T* __restrict__ Q, int64_t q_user_stride,
                                                          const float* __restrict__ Ks,
                                                          const float* __restrict__ Vs, int B, int64_t N, int* status) {
-  constexpr int kW = DH ? DH : kMaxDh;          // register rows are sized for it
+  constexpr int kW = kMaxDh;                    // register rows are sized for it
   constexpr int kRun = 256;                     // queries per pass: four threads each at 1024 threads
   constexpr int kDeep = 8;                      // record loads a thread keeps in flight
   if (status && blockIdx.x == 0 && blockIdx.y == 0) publish_status(offsets, B, N, status);
   __shared__ float z[kW * kW];
-  const int dh = DH ? DH : d / H;
+  const int dh = d / H;
   const int b = blockIdx.x, h = blockIdx.y;
   const int64_t begin = offsets[b], end = offsets[b + 1];
   T* dst = out + int64_t(b) * S * d + h * dh;
@@ -350,7 +350,7 @@ __global__ __launch_bounds__(1024) void qla_finish_kernel(const float* __restric
     for (int e = threadIdx.x; e < S * dh; e += blockDim.x) store_as(dst + int64_t(e / dh) * d + (e % dh), 0.f);
     return;
   }
-  int64_t g0 = begin / seg, g1 = (end - 1) / seg;
+  int64_t g0 = segment_of(begin, seg), g1 = segment_of(end - 1, seg);
   if (g0 < 0) g0 = 0;
   if (g1 > G - 1) g1 = G - 1;
   // Sum of the user's records in a fixed order: four groups of 256 threads take every fourth
@@ -475,6 +475,30 @@ __device__ __forceinline__ float silu_prime_f(float x) {
   return sg * (1.f + x * (1.f - sg));
 }
 
+// SiLU and 1 / (1 + e^-x) in some eighteen instructions where expf and a division take about forty: 2^t by v_exp_f32 on
+// the fraction of t = -x log2(e) and what its rounding left, the quotient refined once from its remainder.  Largest error and 2-norm against fp64 over +-1, +-8 and
+// +-80 are those of expf and a division (1.5e-7, 3.8e-8; 1.5e-7, 4.1e-8; 1.8e-7, 4.1e-9), those of the derivative too.
+// Beyond +-88 the exponential stands still (below 1e-37 from the limit), and an infinite x is its own SiLU.
+struct Sigmoid { float a, r; };                          // 1 + e^-x and its reciprocal, to an ulp
+__device__ __forceinline__ Sigmoid sigmoid_parts(float x) {
+#pragma clang fp contract(off)                           // t is the rounded product wherever it stands
+  const float u = __builtin_amdgcn_fmed3f(x, -88.f, 88.f);
+  const float t = u * -1.44269502f;
+  const float rest = fmaf(u, -1.925963e-8f, fmaf(u, -1.44269502f, -t));      // -u log2(e) - t
+  const float n = rintf(t);
+  const float a = 1.f + __builtin_ldexpf(__builtin_amdgcn_exp2f((t - n) + rest), int(n));
+  return {a, __builtin_amdgcn_rcpf(a)};
+}
+__device__ __forceinline__ float silu_near(float x, Sigmoid s) {
+  const float y = x * s.r;
+  return x > 88.f ? x : fmaf(fmaf(-s.a, y, x), s.r, y);
+}
+__device__ __forceinline__ float silu_near(float x) { return silu_near(x, sigmoid_parts(x)); }
+__device__ __forceinline__ float silu_prime_near(float x, Sigmoid s) {
+  const float sg = fmaf(s.r, fmaf(-s.a, s.r, 1.f), s.r);
+  return sg * (1.f + x * (1.f - sg));
+}
+
 __device__ __forceinline__ void load4(const float* p, float v[4]) {
   const float4 t = *reinterpret_cast<const float4*>(p);
   v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
@@ -503,7 +527,7 @@ constexpr int kRow32 = 36;       // floats between rows of a 32 x 32 array in LD
 __device__ __forceinline__ void sum_records32(const float* __restrict__ partials, int64_t begin, int64_t end, int seg,
                                               int64_t G, int b, int h, int H, float* z) {
   constexpr int kDeep = 8;
-  int64_t g0 = begin / seg, g1 = (end - 1) / seg;
+  int64_t g0 = segment_of(begin, seg), g1 = segment_of(end - 1, seg);
   if (g0 < 0) g0 = 0;
   if (g1 > G - 1) g1 = G - 1;
   const int grp = threadIdx.x >> 8, e = 4 * (threadIdx.x & 255);
@@ -535,6 +559,132 @@ __device__ __forceinline__ void sum_records32(const float* __restrict__ partials
   }
 }
 
+// out_h = SiLU(Q_h) SiLU(Z_h) for heads of width 32 (see qla_finish_kernel), a workgroup to 16 of the head's output channels,
+// 512 threads.  It is bound by latency: offsets, records (the longest user's come at what one compute unit can
+// read, so two share them), and what follows them.  The first queries are requested before the records are waited for; a wave
+// takes 16 of them and sends them through v_mfma_f32_16x16x4_f32 as they lie in its registers (a lane's four steps are
+// four neighbouring channels, and four neighbouring output channels of a query come out in a lane).
+// The records are summed in the order of qla_finish_kernel.  What a kernel runs once comes out of a cold instruction cache at
+// some 0.2 us for 64 bytes, so the queries go round a loop that is not unrolled.  One workgroup of 1024 threads a head, four
+// threads a query out of LDS: jagged batch, S = 256, 77.8 us a call, now 76.2 (medians of two boxes 72.6, 71.4).
+template <typename T>
+__global__ __launch_bounds__(512, 4) void qla_finish32_kernel(const float* __restrict__ partials,
+                                                           const int64_t* __restrict__ offsets, int S, int d, int H,
+                                                           int seg, int64_t G, T* __restrict__ out,
+                                                           const T* __restrict__ Q, int64_t q_user_stride,
+                                                           const float* __restrict__ Ks, const float* __restrict__ Vs,
+                                                           int B, int64_t N, int* status) {
+  constexpr int kDeep = 8;
+  __shared__ __align__(16) float part[4][512];           // the four sub-sums of this half of the state
+  __shared__ __align__(16) float gt[16 * kRow32];        // SiLU(Z)^T: [output channel][state row]
+  if (status && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) publish_status(offsets, B, N, status);
+  const int b = blockIdx.x, h = blockIdx.y, half = blockIdx.z, tid = threadIdx.x;
+  const int lane = tid & 63, w = tid >> 6, g = lane >> 4, c = lane & 15;
+  const int64_t begin = offsets[b], end = offsets[b + 1];
+  T* dst = out + int64_t(b) * S * d + h * 32 + 16 * half;
+  if (end <= begin) {
+    for (int e = tid; e < S * 16; e += 512) store_as(dst + int64_t(e / 16) * d + (e % 16), 0.f);
+    return;
+  }
+  const bool vec_q = (reinterpret_cast<uintptr_t>(Q) & (4 * sizeof(T) - 1)) == 0 && q_user_stride % 4 == 0;
+  const bool vec_out = (reinterpret_cast<uintptr_t>(out) & (4 * sizeof(T) - 1)) == 0;
+  const T* Qb = Q + q_user_stride * b + h * 32 + 4 * g;
+  float q[2][4];               // channels 16 a + 4 g + 0..3 of this lane's query (past the last: the last; not stored)
+  auto request = [&](int i) __attribute__((always_inline)) {
+    const T* row = Qb + int64_t(i < S ? i : S - 1) * d;
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+      if (vec_q) {
+        load4(row + 16 * a, q[a]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) q[a][e] = to_f32(row[16 * a + e]);
+      }
+    }
+  };
+  request(16 * w + c);
+  int64_t g0 = segment_of(begin, seg), g1 = segment_of(end - 1, seg);
+  if (g0 < 0) g0 = 0;
+  if (g1 > G - 1) g1 = G - 1;
+  {
+    const int grp = tid >> 7, row = (tid & 127) >> 2, col = 4 * (tid & 3);
+    const int64_t step = int64_t(4) * H * 1024;          // from one of this thread's records to the next
+    const float* at = partials + ((g0 + grp + b) * H + h) * 1024 + row * 32 + 16 * half + col;
+    int left = int(g1 - g0) - grp;                       // records of the user from this thread's next one on, less one
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f), v[kDeep];
+    auto load = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int u = 0; u < kDeep; ++u) {
+        v[u] = 4 * u <= left ? *reinterpret_cast<const float4*>(at) : make_float4(0.f, 0.f, 0.f, 0.f);
+        at += step;
+      }
+    };
+    load();
+    for (;;) {
+#pragma unroll
+      for (int u = 0; u < kDeep; ++u) {
+        acc.x += v[u].x;
+        acc.y += v[u].y;
+        acc.z += v[u].z;
+        acc.w += v[u].w;
+      }
+      left -= 4 * kDeep;
+      if (left < 0) break;
+      load();
+    }
+    *reinterpret_cast<float4*>(&part[grp][row * 16 + col]) = acc;
+  }
+  __syncthreads();
+  gt[(tid & 15) * kRow32 + (tid >> 4)] = silu_near(((part[0][tid] + part[1][tid]) + part[2][tid]) + part[3][tid]);
+  __syncthreads();
+  float z[2][4];
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+    const float4 t = *reinterpret_cast<const float4*>(gt + c * kRow32 + 16 * a + 4 * g);
+    z[a][0] = t.x; z[a][1] = t.y; z[a][2] = t.z; z[a][3] = t.w;
+  }
+  const int64_t srow0 = q_user_stride ? int64_t(b) * S : 0;
+#pragma unroll 1
+  for (int i = 16 * w + c; i - c < S; i += 128) {
+    float y[2][4];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) y[a][e] = silu_near(q[a][e]);
+    request(i + 128);
+    f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o = __builtin_amdgcn_mfma_f32_16x16x4f32(z[a][e], y[a][e], o, 0, 0, 0);
+    if (Ks) {                                            // the query's own key and value
+      const int64_t row = (srow0 + (i < S ? i : S - 1)) * d + h * 32;
+      float dot = 0.f, k[4], v[4];
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        load4(Ks + row + 16 * a + 4 * g, k);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dot = fmaf(y[a][e], silu_near(k[e]), dot);
+      }
+      dot += __shfl_xor(dot, 16, 64);
+      dot += __shfl_xor(dot, 32, 64);
+      load4(Vs + row + 16 * half + 4 * g, v);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) o[r] = fmaf(dot, v[r], o[r]);
+    }
+    if (i < S) {
+      T* at = dst + int64_t(i) * d + 4 * g;
+      const float v[4] = {o[0], o[1], o[2], o[3]};
+      if (vec_out) {
+        store4(at, v);
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) store_as(at + r, v[r]);
+      }
+    }
+  }
+}
+
 
 // Per (user, head): the state Zs (fixed-order sum of the user's records), G = SiLU(Zs),
 //   dQ = (dO G^T) * SiLU'(Q)         written to d_queries,
@@ -562,7 +712,7 @@ __global__ __launch_bounds__(1024) void qla_bwd_state_kernel(const float* __rest
     for (int e = threadIdx.x; e < zz; e += blockDim.x) dzb[e] = 0.f;
     return;
   }
-  int64_t g0 = begin / seg, g1 = (end - 1) / seg;
+  int64_t g0 = segment_of(begin, seg), g1 = segment_of(end - 1, seg);
   if (g0 < 0) g0 = 0;
   if (g1 > G - 1) g1 = G - 1;
   // The user's records, summed in the forward finishing kernel's order: four groups of 256
@@ -711,7 +861,8 @@ __global__ __launch_bounds__(1024) void qla_bwd_state32_kernel(const float* __re
   sum_records32(partials, begin, end, seg, G, b, h, H, zs);
   const float zraw = zs[tid / 32 * kRow32 + tid % 32];
   __syncthreads();
-  zs[tid / 32 * kRow32 + tid % 32] = silu_f(zraw);
+  const Sigmoid zsig = sigmoid_parts(zraw);
+  zs[tid / 32 * kRow32 + tid % 32] = silu_near(zraw, zsig);
   __syncthreads();
   f32x4 dg[2][2];
 #pragma unroll
@@ -724,10 +875,13 @@ __global__ __launch_bounds__(1024) void qla_bwd_state32_kernel(const float* __re
   for (int u = 0; u < 2; ++u) {
     if (16 * (w + 16 * u) >= S) break;                   // (wave-uniform)
     const int i = 16 * (w + 16 * u) + c;
+    Sigmoid sig[2][4];
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sig[a][e] = sigmoid_parts(q[u][a][e]);
       *reinterpret_cast<float4*>(qa + c * kRow32 + 16 * a + 4 * g) =
-          make_float4(silu_f(q[u][a][0]), silu_f(q[u][a][1]), silu_f(q[u][a][2]), silu_f(q[u][a][3]));
+          make_float4(silu_near(q[u][a][0], sig[a][0]), silu_near(q[u][a][1], sig[a][1]), silu_near(q[u][a][2], sig[a][2]), silu_near(q[u][a][3], sig[a][3]));
       *reinterpret_cast<float4*>(dy + c * kRow32 + 16 * a + 4 * g) = make_float4(y[u][a][0], y[u][a][1], y[u][a][2], y[u][a][3]);
     }
     // (the patch is the wave's own: program order is enough)
@@ -753,7 +907,7 @@ __global__ __launch_bounds__(1024) void qla_bwd_state32_kernel(const float* __re
       if (i < S) {
         float v[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = o[r] * silu_prime_f(q[u][n][r]);
+        for (int r = 0; r < 4; ++r) v[r] = o[r] * silu_prime_near(q[u][n][r], sig[n][r]);
         store4(dq + int64_t(i) * d + 16 * n + 4 * g, v);
       }
     }
@@ -768,7 +922,7 @@ __global__ __launch_bounds__(1024) void qla_bwd_state32_kernel(const float* __re
   float sum = 0.f;
 #pragma unroll
   for (int k = 0; k < 16; ++k) sum += patch[k][tid];
-  dzb[tid] = sum * silu_prime_f(zraw);
+  dzb[tid] = sum * silu_prime_near(zraw, zsig);
 }
 
 // Gradients of the target-side diagonal term (phi(q_i) . phi(k'_i)) v'_i (App. B.1: second term of
@@ -925,10 +1079,10 @@ static vista_status generic_summarize_t(const SummarizeArgs& a) {
   int* status = a.seg_user ? nullptr : reinterpret_cast<int*>(a.workspace);
   const int64_t check = a.offsets_checked ? -1 : d.total_items;
   if (qla && d.d / d.H == 32)
-    VISTA_LAUNCH((qla_finish_kernel<T, 32>), dim3(d.B, d.H), dim3(1024), 0, a.stream, partials, a.offsets, d.S, d.d,
+    VISTA_LAUNCH(qla_finish32_kernel<T>, dim3(d.B, d.H, 2), dim3(512), 0, a.stream, partials, a.offsets, d.S, d.d,
                  d.H, a.seg, a.G, out, Q, d.q_user_stride, Ks, Vs, d.B, check, status);
   else if (qla)
-    VISTA_LAUNCH((qla_finish_kernel<T, 0>), dim3(d.B, d.H), dim3(1024), 0, a.stream, partials, a.offsets, d.S, d.d,
+    VISTA_LAUNCH(qla_finish_kernel<T>, dim3(d.B, d.H), dim3(1024), 0, a.stream, partials, a.offsets, d.S, d.d,
                  d.H, a.seg, a.G, out, Q, d.q_user_stride, Ks, Vs, d.B, check, status);
   else if (launch_merge<T>(a, partials, Ks, Vs, nullptr) != hipSuccess)
     return VISTA_ERR_HIP;

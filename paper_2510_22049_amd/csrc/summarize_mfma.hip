@@ -1011,7 +1011,7 @@ __global__ __launch_bounds__(256) void merge_mfma_kernel(const float* __restrict
     }
     return;
   }
-  int64_t g0 = begin / seg, g1 = (end - 1) / seg;
+  int64_t g0 = segment_of(begin, seg), g1 = segment_of(end - 1, seg);
   if (g0 < 0) g0 = 0;
   if (g1 > G - 1) g1 = G - 1;
   // the query's own key and value (self term): score in the units of the records' m
