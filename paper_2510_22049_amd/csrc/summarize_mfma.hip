@@ -117,6 +117,10 @@ __device__ __forceinline__ float dot2_self(uint32_t pk, float acc) {
   return __builtin_amdgcn_fdot2_f32_bf16(v, v, acc, false);
 }
 
+// An instruction whose result is pinned comes before whatever is pinned later in the program.
+template <typename T>
+__device__ __forceinline__ void pin(T& v) { asm volatile("" : "+v"(v)); }
+
 // LDS-only workgroup barrier: global loads in flight (the X prefetch) stay in flight.
 __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
@@ -282,7 +286,7 @@ struct SummarizeLds {
 // denominator, no norm test; the key weights then carry -scale*log2(e), so a score leaves the
 // MFMA as t = -s log2(e) and SiLU(s) = -ln(2) t / (1 + 2^t); the weight handed to the second
 // product is t / (1 + 2^t) and the constant joins the 1/L_b of the merge.
-template <int D, int NQB, int HPW, int FW, bool WREG, bool SPLIT, bool ALLF, int ROLE, int ATTN>
+template <int D, int NQB, int HPW, int FW, bool WREG, bool SPLIT, bool ALLF, int ROLE, int ATTN, bool ORDERED>
 __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, SummarizeLds<D, HPW, WREG, SPLIT>& sm,
                                                int64_t g, int h, int hl, int qblock, int64_t seg_begin,
                                                int64_t seg_end) {
@@ -592,7 +596,7 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
     const int i1 = r == kXBuf - 1 ? 0 : r + 1, i2 = i1 == kXBuf - 1 ? 0 : i1 + 1;
     return SPLIT ? Slots{i2, odd ^ 1, odd} : Slots{i2, i1, i2};
   };
-  auto fast_tile = [&](int r) __attribute__((always_inline)) {
+  auto free_tile = [&](int r) __attribute__((always_inline)) {
     const Slots at = slots(r);
     f32x16 acc = {0};
     // scores run one query block ahead of the exponentials that consume them
@@ -644,6 +648,98 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
     }
     read_v(at.kv1);
     publish(at.kv2, acc);
+  };
+  // The same in an order of its own (pin).  A product keeps the matrix pipe for 32 clocks and the issue port for 8; three
+  // v_exp_f32 fit behind it for nothing, but products in a row hold up the vector instructions of both waves of the
+  // SIMD (18 products, then 72 v_exp_f32: 888 clocks a wave at two waves; one to four in turn: 722).  Left to itself the compiler
+  // ends a tile in runs of ten and more products.  So the second product of a block and its denominators wait for the
+  // exponentials of the next block, and a pair is packed a few instructions behind its exponentials.
+  auto ordered_tile = [&](int r) __attribute__((always_inline)) {
+    const Slots at = slots(r);
+    f32x16 acc = {0};
+    int ks = 0;
+    Pack8 xr;
+    if constexpr (PROJ) xr.u = sm.xbuf[at.x2][hf * 32 + l32];
+    auto proj = [&](int n) __attribute__((always_inline)) {      // n slices of the projection
+      if constexpr (PROJ) {
+#pragma unroll
+        for (int i = 0; i < n; ++i) {
+          if (ks >= KS) break;
+          Pack8 w;
+          if constexpr (WREG) w.v = wreg[ks]; else w.u = sm.wop[((hl * 2 + WR) * KS + ks) * 64 + lane];
+          acc = ROLE ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(xr.v, w.v, acc, 0, 0, 0)
+                     : __builtin_amdgcn_mfma_f32_32x32x16_bf16(w.v, xr.v, acc, 0, 0, 0);
+          pin(acc);
+          ++ks;
+          if (ks < KS) xr.u = sm.xbuf[at.x2][(2 * ks + hf) * 32 + l32];
+        }
+      }
+    };
+    Pack8 before[2];          // packed weights of the block before
+    auto small = [&](int qb, int part) __attribute__((always_inline)) {
+      const i16x4 sel = __builtin_bit_cast(i16x4, onesrow[qb % 4]);
+      const Pack8& src = before[part / 2];
+      const uint2 pw = make_uint2(src.w[2 * (part & 1)], src.w[2 * (part & 1) + 1]);
+      f32x4& a = lacc[qb / 4][part & 1];
+      a = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(sel, __builtin_bit_cast(i16x4, pw), a, 0, 0, 0);
+      pin(a);
+    };
+    auto second = [&](int qb, int half) __attribute__((always_inline)) {
+      o[qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vv.hi[half].v, before[half].v, o[qb], 0, 0, 0);
+      pin(o[qb]);
+    };
+    const f32x16 zero = {0};
+    f32x16 nx = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kk.hi[0].v, qop[0][0], zero, 0, 0, 0);
+    nx = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kk.hi[1].v, qop[0][1], nx, 0, 0, 0);
+    pin(nx);
+#pragma unroll
+    for (int qb = 0; qb < NQB; ++qb) {
+      const f32x16 sc = nx;
+      float ev[16];
+      Pack8 cur[2];
+      auto E = [&](int i) __attribute__((always_inline)) { ev[i] = __builtin_amdgcn_exp2f(sc[i]); pin(ev[i]); };
+      auto P = [&](int i) __attribute__((always_inline)) {
+        uint32_t t = cvt_pk_bf16(ev[i], ev[i + 1]);
+        pin(t);
+        cur[i / 8].w[(i % 8) / 2] = t;
+      };
+      const bool more = qb + 1 < NQB;
+      auto next = [&](int half) __attribute__((always_inline)) {
+        if (!more) return;
+        nx = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kk.hi[half].v, qop[(qb + 1) % NQB][half], half ? nx : zero, 0, 0, 0);
+        pin(nx);
+      };
+      auto share = [&](int i) __attribute__((always_inline)) { proj((i + 1) * KPB / 4 - i * KPB / 4); };
+      next(0);
+      E(0); E(1); E(2);
+      if (qb > 0) { small(qb - 1, 0); second(qb - 1, 0); }
+      P(0); E(3); E(4); E(5);
+      if (qb > 0) small(qb - 1, 1);
+      share(0);
+      P(2); E(6); E(7); P(4);
+      share(1);
+      next(1);
+      if (!more) read_k(at.kv1);
+      E(8); P(6); E(9); E(10);
+      if (qb > 0) { small(qb - 1, 2); second(qb - 1, 1); }
+      P(8); E(11); E(12);
+      if (qb > 0) small(qb - 1, 3);
+      share(2);
+      P(10); E(13); E(14); P(12); E(15);
+      share(3);
+      P(14);
+      before[0] = cur[0];
+      before[1] = cur[1];
+    }
+    second(NQB - 1, 0);
+    small(NQB - 1, 0); small(NQB - 1, 1);
+    second(NQB - 1, 1);
+    small(NQB - 1, 2); small(NQB - 1, 3);
+    read_v(at.kv1);
+    publish(at.kv2, acc);
+  };
+  auto fast_tile = [&](int r) __attribute__((always_inline)) {
+    if constexpr (ORDERED) ordered_tile(r); else free_tile(r);
   };
 
   // Any tile: ragged tail, scores beyond the bound, last tile of the segment.
@@ -912,7 +1008,7 @@ __device__ __forceinline__ void self_kv_unit(const uint16_t* __restrict__ Q, con
 // NQB query blocks to a projecting wave, NQA to one that only attends.  OCC: waves on a SIMD that the registers have to leave
 // room for, as far as the workgroups that fit the LDS can fill them (the two-wave workgroups of D = 256, S = 64 cannot, and take
 // 295 registers).
-template <int D, int NQB, int NQA, int HPW, int FW, bool WREG, bool SPLIT, int MAXT, int ATTN, int OCC>
+template <int D, int NQB, int NQA, int HPW, int FW, bool WREG, bool SPLIT, int MAXT, int ATTN, int OCC, bool ORDERED>
 __global__ __launch_bounds__(MAXT, OCC) void summarize_mfma_kernel(MfmaSummarizeParams p) {
   __shared__ SummarizeLds<D, HPW, WREG, SPLIT> sm;
 
@@ -948,11 +1044,11 @@ __global__ __launch_bounds__(MAXT, OCC) void summarize_mfma_kernel(MfmaSummarize
   }
   // All roles run the same sequence of barriers; only the MFMA operand order differs.
   if (slot == 0)
-    summarize_wave<D, NQB, HPW, FW, WREG, SPLIT, (!SPLIT && MAXT == 64 * FW), 0, ATTN>(p, sm, g, h, hl, 0, seg_begin, seg_end);
+    summarize_wave<D, NQB, HPW, FW, WREG, SPLIT, (!SPLIT && MAXT == 64 * FW), 0, ATTN, ORDERED>(p, sm, g, h, hl, 0, seg_begin, seg_end);
   else if (slot == 1)
-    summarize_wave<D, NQB, HPW, FW, WREG, SPLIT, (!SPLIT && MAXT == 64 * FW), 1, ATTN>(p, sm, g, h, hl, NQB, seg_begin, seg_end);
+    summarize_wave<D, NQB, HPW, FW, WREG, SPLIT, (!SPLIT && MAXT == 64 * FW), 1, ATTN, ORDERED>(p, sm, g, h, hl, NQB, seg_begin, seg_end);
   else if constexpr (MAXT != HPW * 128)      // (two waves per head: there is no third slot)
-    summarize_wave<D, NQA, HPW, FW, WREG, SPLIT, (!SPLIT && MAXT == 64 * FW), 2, ATTN>(p, sm, g, h, hl, 2 * NQB + (slot - 2) * NQA, seg_begin, seg_end);
+    summarize_wave<D, NQA, HPW, FW, WREG, SPLIT, (!SPLIT && MAXT == 64 * FW), 2, ATTN, ORDERED>(p, sm, g, h, hl, 2 * NQB + (slot - 2) * NQA, seg_begin, seg_end);
 }
 
 // Merge of a user's partial records in a fixed order, so the result is bitwise reproducible.
@@ -1294,25 +1390,34 @@ size_t mfma_summarize_workspace(const vista_summarize_desc& d, int seg) {
   return kHeaderBytes + plan_bytes(G) + ((partial_bytes(d, seg) + 255) & ~size_t(255)) + 2 * self_kv_bytes(d);
 }
 
-template <int D, int NQB, int HPW, int FW, bool WREG, bool SPLIT, int MAXT, int ATTN, int NQA = NQB, int OCC = MAXT / 256>
+template <int D, int NQB, int HPW, int FW, bool WREG, bool SPLIT, int MAXT, int ATTN, int NQA = NQB, int OCC = MAXT / 256, bool ORDERED = false>
 static hipError_t launch_main(MfmaSummarizeParams& p, int wph, int64_t G, hipStream_t s) {
   p.wph = wph;
   p.nhg = p.H / HPW;
   const int64_t groups = (G + 7) / 8;
   const int64_t blocks = groups * 8 * p.nhg;
-  return launch(summarize_mfma_kernel<D, NQB, NQA, HPW, FW, WREG, SPLIT, MAXT, ATTN, OCC>, dim3(unsigned(blocks)),
+  return launch(summarize_mfma_kernel<D, NQB, NQA, HPW, FW, WREG, SPLIT, MAXT, ATTN, OCC, ORDERED>, dim3(unsigned(blocks)),
                 dim3(HPW * wph * 64), 0, s, p);
 }
 
 template <int ATTN>
 static hipError_t launch_for_shape(MfmaSummarizeParams& p, const vista_summarize_desc& desc, int64_t G, hipStream_t s) {
   const int d = desc.d;
+  // Four query blocks a wave at d = 128, softmax: the tile in its own order (ordered_tile).  us a call, free / ordered: S = 256, jagged batch 169.6 /
+  // 168.3, 8 users of a million items 1560 / 1535, 300 users of 300 003 106.9 / 105.9, one of 7001 20.7 / 20.4; S = 512, 100 users of
+  // 300 003 134.6 / 133.4, with queries of their own 145.9 / 145.1.  With queries of their own at S = 256 the registers of
+  // their load are spilled in the loop (8 users 84.4 / 84.7, 300 users 120.7 / 122.4): those stay free.  So do one and two blocks a
+  // wave (S = 64 66.9 / 67.8, S = 128 equal) and d = 256 (S = 128 225 / 230, S = 512 435 / 450), where a wave has less to put between its
+  // products or attends without projecting.
+  constexpr bool softmax = ATTN == VISTA_ATTN_SOFTMAX;
+  const bool shared = p.q_user_stride == 0;
   if (half_workgroups(desc, p.seg, G)) {
     if (d == 128) {
       if (p.nqb <= 2) return launch_main<128, 1, 2, 4, true, false, 256, ATTN, 1, 2>(p, 2, G, s);
       if (p.nqb <= 4) return launch_main<128, 2, 2, 4, true, false, 256, ATTN, 2, 2>(p, 2, G, s);
+      if (p.nqb <= 8 && shared) return launch_main<128, 4, 2, 4, true, false, 256, ATTN, 4, 2, softmax>(p, 2, G, s);
       if (p.nqb <= 8) return launch_main<128, 4, 2, 4, true, false, 256, ATTN, 4, 2>(p, 2, G, s);
-      return launch_main<128, 4, 1, 4, true, false, 256, ATTN, 4, 2>(p, 4, G, s);
+      return launch_main<128, 4, 1, 4, true, false, 256, ATTN, 4, 2, softmax>(p, 4, G, s);
     }
     if (p.nqb <= 2) return launch_main<256, 1, 1, 2, true, false, 128, ATTN, 1, 2>(p, 2, G, s);
     if (p.nqb <= 4) return launch_main<256, 1, 1, 4, true, false, 256, ATTN, 1, 2>(p, 4, G, s);
@@ -1328,8 +1433,9 @@ static hipError_t launch_for_shape(MfmaSummarizeParams& p, const vista_summarize
       if (p.nqb == 4) return launch_main<128, 1, 4, 8, true, false, 1024, ATTN>(p, 4, G, s);
     if (p.nqb <= 2) return launch_main<128, 1, 4, 8, true, false, 512, ATTN>(p, 2, G, s);
     if (p.nqb <= 4) return launch_main<128, 2, 4, 8, true, false, 512, ATTN>(p, 2, G, s);
+    if (p.nqb <= 8 && shared) return launch_main<128, 4, 4, 8, true, false, 512, ATTN, 4, 2, softmax>(p, 2, G, s);
     if (p.nqb <= 8) return launch_main<128, 4, 4, 8, true, false, 512, ATTN>(p, 2, G, s);
-    return launch_main<128, 4, 2, 8, true, false, 512, ATTN>(p, 4, G, s);
+    return launch_main<128, 4, 2, 8, true, false, 512, ATTN, 4, 2, softmax>(p, 4, G, s);
   }
   // Two workgroups of four waves on a compute unit: their barriers are not in step (209 -> 167 us over 500 000 items,
   // SiLU form 143 -> 112 over 300 000; with the weights in LDS there was room for one).

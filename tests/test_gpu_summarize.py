@@ -50,6 +50,21 @@ def test_mfma_jagged_matches_oracle(d, H, S, seg):
     assert np.all(got[1] == 0) and np.all(got[8] == 0)
 
 
+@pytest.mark.parametrize("lens,seg,half", [(LENS, 64, True), ([5000], 0, True), ([9000, 33, 0, 120000, 1, 64, 20031, 150000], 2048, False)])
+def test_both_orders_of_a_tile_agree(lens, seg, half):
+    """S = 256 at d = 128 takes a tile in one order of instructions for shared queries and in another for queries of the
+    users' own: the same sums, so the same bits where every user's own are the shared ones."""
+    X, off, Q, Wk, Wv = problem(9, lens, 128, 256)
+    own = np.repeat(Q[None], len(lens), axis=0)
+    for per_user in (False, True):
+        assert takes_half_workgroups("softmax", off, 128, 4, 256, per_user, seg) == half
+    shared = run(X, off, Q, Wk, Wv, 4, segment_items=seg)
+    assert np.array_equal(shared, run(X, off, own, Wk, Wv, 4, segment_items=seg))
+    few = [b for b in range(len(lens)) if lens[b] <= 9000]
+    want = O.summarize(np.concatenate([X[off[b]:off[b + 1]] for b in few]), I.offsets_from_lengths([lens[b] for b in few]), Q, Wk, Wv, 4)
+    assert_blocks_close(shared[few], want, "bf16", f"ordered tile, seg={seg}")
+
+
 @pytest.mark.parametrize("d,H,S", [(128, 4, 256), (256, 8, 512)])
 def test_mfma_per_user_queries(d, H, S):
     X, off, Q, Wk, Wv = problem(2, LENS, d, S, per_user=True)
