@@ -2,6 +2,8 @@
 // They carry the fp32 configuration and every shape the MFMA kernels do not
 // take.  One thread owns one query (stage 1) or one (candidate, head) pair
 // (stage 2) and streams the keys with an online softmax in base 2.
+#include <float.h>
+
 #include "common.hpp"
 
 namespace vista {
@@ -475,27 +477,29 @@ __device__ __forceinline__ float silu_prime_f(float x) {
   return sg * (1.f + x * (1.f - sg));
 }
 
-// SiLU and 1 / (1 + e^-x) in some eighteen instructions where expf and a division take about forty: 2^t by v_exp_f32 on
-// the fraction of t = -x log2(e) and what its rounding left, the quotient refined once from its remainder.  Largest error and 2-norm against fp64 over +-1, +-8 and
-// +-80 are those of expf and a division (1.5e-7, 3.8e-8; 1.5e-7, 4.1e-8; 1.8e-7, 4.1e-9), those of the derivative too.
-// Beyond +-88 the exponential stands still (below 1e-37 from the limit), and an infinite x is its own SiLU.
-struct Sigmoid { float a, r; };                          // 1 + e^-x and its reciprocal, to an ulp
+// SiLU and 1 / (1 + e^-x) in some twenty instructions where expf and a division take about forty: 2^t by v_exp_f32 on
+// the fraction of t = -x log2(e) and what its rounding left (Cody and Waite's reduction, log2(e) in two fp32 parts), the quotient
+// refined once from its remainder.  Within 1.8e-7 of fp64, as expf and a division are, wherever e^-x is an fp32 number (x > -88.72);
+// below, SiLU and its derivative are the zeros that a division by infinity gives.  v_rcp_f32 flushes results below
+// 2^-126, which 1 / (1 + e^-x) is from x = -87.33 down, so a quarter of the denominator is kept.  -inf gives NaN as x / (1 + expf(-x)) does, +inf is
+// its own SiLU.
+struct Sigmoid { float a, r; };                          // (1 + e^-x) / 4, at most the largest fp32, and its reciprocal, to an ulp
 __device__ __forceinline__ Sigmoid sigmoid_parts(float x) {
 #pragma clang fp contract(off)                           // t is the rounded product wherever it stands
-  const float u = __builtin_amdgcn_fmed3f(x, -88.f, 88.f);
+  const float u = __builtin_amdgcn_fmed3f(x, -100.f, 100.f);
   const float t = u * -1.44269502f;
   const float rest = fmaf(u, -1.925963e-8f, fmaf(u, -1.44269502f, -t));      // -u log2(e) - t
   const float n = rintf(t);
-  const float a = 1.f + __builtin_ldexpf(__builtin_amdgcn_exp2f((t - n) + rest), int(n));
-  return {a, __builtin_amdgcn_rcpf(a)};
+  const float a = fmaf(__builtin_ldexpf(__builtin_amdgcn_exp2f((t - n) + rest), int(n)), 0.25f, 0.25f);
+  return {fminf(a, FLT_MAX), __builtin_amdgcn_rcpf(a)};
 }
 __device__ __forceinline__ float silu_near(float x, Sigmoid s) {
   const float y = x * s.r;
-  return x > 88.f ? x : fmaf(fmaf(-s.a, y, x), s.r, y);
+  return x > 88.f ? x : 0.25f * fmaf(fmaf(-s.a, y, x), s.r, y);
 }
 __device__ __forceinline__ float silu_near(float x) { return silu_near(x, sigmoid_parts(x)); }
 __device__ __forceinline__ float silu_prime_near(float x, Sigmoid s) {
-  const float sg = fmaf(s.r, fmaf(-s.a, s.r, 1.f), s.r);
+  const float sg = 0.25f * fmaf(s.r, fmaf(-s.a, s.r, 1.f), s.r);
   return sg * (1.f + x * (1.f - sg));
 }
 

@@ -170,6 +170,114 @@ def test_qla_outputs_of_heads_of_width_32(dtype, S, per_user, self_term):
     assert self_term or np.array_equal(got[0], got[1])
 
 
+EDGES = [-87.0, -87.5, -88.0, -88.5, -88.72, -89.0, -100.0, -1e4, -1e30, float(np.finfo(np.float32).min), 87.5, 88.5, 100.0, 1e4, 0.0, -0.5]
+
+
+def saturating(dtype, d, S):
+    """A history whose states lie on both sides of +-88 and far beyond, and a query for each of EDGES among ordinary ones."""
+    X, off, Q, Wk, Wv = problem(83, [400, 0, 37], d, S, dtype)
+    Wv = Wv * 16.0
+    for i, x in enumerate(EDGES):
+        Q[i] = I.round_to(np.full(d, x, dtype=np.float32), dtype) if x != EDGES[9] or dtype == "f32" else -3.3895314e38
+    return X, off, Q, Wk, Wv
+
+
+def states(X, Wk, Wv, h):
+    """(activated keys, values, state) of head h, width 32, in fp64."""
+    c = slice(32 * h, 32 * h + 32)
+    P, V_ = O.silu(X.astype(np.float64) @ Wk.astype(np.float64)[:, c]), X.astype(np.float64) @ Wv.astype(np.float64)[:, c]
+    return c, P, V_, P.T @ V_
+
+
+@pytest.mark.parametrize("dtype,d,H", [("f32", 64, 2), ("bf16", 128, 4)])
+def test_qla_activation_over_its_whole_range(dtype, d, H):
+    """Element by element: 1e-5 (bf16 2^-6) of the sum of magnitudes behind an output, the error of the state among them.
+    Where e^-x leaves fp32 the activation is the 0 that it is but for 3e-37."""
+    X, off, Q, Wk, Wv = saturating(dtype, d, 40)
+    got = run("qla", X, off, Q, Wk, Wv, H, dtype)
+    want = O.summarize_qla(X, off, Q, Wk, Wv, H)
+    tol = 1e-5 if dtype == "f32" else 2.0 ** -6
+    A = np.abs(O.silu(Q.astype(np.float64)))
+    for b in (0, 2):
+        for h in range(H):
+            c, P, V_, Z = states(X[off[b]:off[b + 1]], Wk, Wv, h)
+            assert b or (np.abs(Z) > 300).any() and (np.abs(np.abs(Z) - 88) < 8).any() and (Z < -88).any()
+            bound = tol * A[:, c] @ (np.abs(O.silu(Z)) + np.abs(P).T @ np.abs(V_)) + 3e-37 * (Q[:, c] < -88.7) @ np.abs(Z)
+            assert np.all(np.abs(got[b][:, c] - want[b][:, c]) <= bound), f"user {b}, head {h}"
+    assert np.all(got[1] == 0)
+
+
+def test_qla_state_gradients_over_their_whole_range():
+    """As above for the gradients in fp32: 1e-5 of the magnitudes behind a value; SiLU' moves by at most half of what a state does."""
+    d, H, S = 64, 2, 40
+    X, off, Q, Wk, Wv = saturating("f32", d, S)
+    Q[8] = -200.0                                               # (A^T dO stays in range)
+    dO = np.random.default_rng(84).normal(size=(3, S, d)).astype(np.float32)
+    got = [torch.full(s, float("nan"), device="cuda") for s in ((3, S, d), X.shape, X.shape)]
+    V.vista_qla_backward(dev(X, "f32"), torch.from_numpy(off).cuda(), dev(Q, "f32"), dev(Wk, "f32"), dev(Wv, "f32"), dev(dO, "f32"), *got, H=H)
+    dQ, dK, dV = (host64(t) for t in got)
+    with np.errstate(over="ignore"):
+        wQ, wK, wV = qla_backward_oracle(X, off, Q, Wk, Wv, dO, H)
+        slope, A = np.abs(O.silu_prime(Q.astype(np.float64))), np.abs(O.silu(Q.astype(np.float64)))
+    for b in (0, 2):
+        rows = slice(off[b], off[b + 1])
+        for h in range(H):
+            c, P, V_, Z = states(X[rows], Wk, Wv, h)
+            P, V_, G, y = np.abs(P), np.abs(V_), np.abs(O.silu(Z)), np.abs(dO[b][:, c]).astype(np.float64)
+            W = A[:, c].T @ y
+            M = W * np.abs(O.silu_prime(Z))                       # behind dZs; E its error
+            E = 1e-5 * (M + W * (P.T @ V_))
+            dk = 1e-6 * np.abs(X[rows]).sum(axis=1, keepdims=True).astype(np.float64)   # of a key; a value's is 16 times that
+            assert np.all(np.abs(dQ[b] - wQ[b])[:, c] <= 1e-5 * slope[:, c] * (y @ (G + P.T @ V_).T) + 3e-37 * (Q[:, c] < -88.7) * (y @ G.T))
+            assert np.all(np.abs(dV - wV)[rows, c] <= P @ (E + 1e-5 * M) + dk * M.sum(axis=0))
+            assert np.all(np.abs(dK - wK)[rows, c] <= 1.1 * (V_ @ (E + 1e-5 * M).T + 16 * dk * M.sum(axis=1)) + dk * (V_ @ M.T))
+    assert np.all(dQ[1] == 0)
+
+
+def test_qla_activation_keeps_the_error_of_a_rounded_quotient():
+    """Queries of one channel that is not 0: an output is SiLU(q) times a number that the query 100 of that channel, its own SiLU,
+    shows, and a gradient SiLU'(q) times one.  1.8e-7 of the activation and half an ulp for each of the two products: 3e-7, and
+    2e-7 more where the sigmoid is subnormal."""
+    d, H, S = 64, 2, 512
+    X, off, _, Wk, Wv = saturating("f32", d, S)
+    t = np.concatenate([-np.geomspace(88.7, 1e-4, 300), np.geomspace(1e-4, 100.0, 180)]).astype(np.float32)
+    Q = np.zeros((S, d), dtype=np.float32)
+    for i in range(S):
+        Q[i, i % 32::32] = t[i] if i < 480 else 100.0
+    dO = np.broadcast_to(np.random.default_rng(85).normal(size=d).astype(np.float32), (3, S, d))
+    out = run("qla", X, off, Q, Wk, Wv, H, "f32")
+    got = [torch.empty(s, device="cuda") for s in ((3, S, d), X.shape, X.shape)]
+    V.vista_qla_backward(dev(X, "f32"), torch.from_numpy(off).cuda(), dev(Q, "f32"), dev(Wk, "f32"), dev(Wv, "f32"), dev(dO, "f32"), *got, H=H)
+    x = t.astype(np.float64)
+    sg = 1.0 / (1.0 + np.exp(-x))
+    ch, ref = np.arange(480) % 32, 480 + np.arange(480) % 32
+    G = out[0][ref]                                             # 100 times SiLU of the state's row
+    use = np.abs(G) > 1.0
+    assert use.mean() > 0.3
+    y = np.where(use, out[0][:480] * 100.0 / np.where(use, G, 1.0), (x * sg)[:, None])
+    assert np.all(np.abs(y - (x * sg)[:, None]) <= (3e-7 * np.abs(x * sg))[:, None])
+    dQ = host64(got[0])[0]
+    for h in range(H):
+        slope = dQ[np.arange(480), ch + 32 * h] / dQ[ref, ch + 32 * h]
+        tol = np.where(x < -87.0, 5e-7, 3e-7) * sg * (1.0 + np.abs(x))
+        assert np.all(np.abs(slope - sg * (1.0 + x * (1.0 - sg))) <= tol)
+
+
+@pytest.mark.parametrize("dtype,d,H", [("f32", 64, 2), ("bf16", 128, 4)])
+def test_qla_queries_that_are_not_finite_keep_to_their_row(dtype, d, H):
+    X, off, Q, Wk, Wv = saturating(dtype, d, 40)
+    clean = run("qla", X, off, Q, Wk, Wv, H, dtype)
+    Q[20, 5], Q[21, 5], Q[22, 5] = float("nan"), -float("inf"), float("inf")
+    got = run("qla", X, off, Q, Wk, Wv, H, dtype)
+    Z = states(X[400:], Wk, Wv, 0)[3]
+    assert np.all(np.isnan(got[[0, 2], 20:22, :32]))            # (x / (1 + e^-x) at -inf)
+    sure = (np.abs(Z[5]) > 5) & (np.abs(Z[5]) < 60)           # (a state's sign is known, and its SiLU is not 0)
+    assert sure.any() and np.array_equal(got[2, 22, :32][sure], np.sign(Z[5][sure]) * np.inf)
+    rest = np.ones(got.shape, dtype=bool)
+    rest[:, 20:23, :32] = False
+    assert np.array_equal(got[rest], clean[rest])
+
+
 def test_qla_at_the_jagged_workload_shape_and_bitwise_repeatable():
     c = I.CONFIGS[2]
     lens = I.lengths(c)
