@@ -171,7 +171,10 @@ size_t vista_summarize_workspace_bytes(const vista_summarize_desc* desc);
  *                                         bad offsets give wrong numbers, never a fault.
  *   virtual_queries  device [S, d] or [B, S, d]   dtype
  *   W_k, W_v         device [d, d]        dtype; K = X @ W_k (input rows, output columns)
- *   out              device [B, S, d]     dtype (bf16: one round-to-nearest-even at the store)
+ *   out              device [B, S, d]     dtype (bf16: one round-to-nearest-even at the store).  It overlaps
+ *                                         no input, but where q_user_stride = S*d it may be the
+ *                                         virtual_queries buffer itself: in the quasi-linear form, and in
+ *                                         the other two without VISTA_FLAG_SELF_TERM.
  *   workspace        device, >= vista_summarize_workspace_bytes(desc), 256-byte aligned
  *
  * Supported: bf16 with (d, H) = (128, 4) or (256, 8), S in {64, 128, 256, 512} (MFMA path);

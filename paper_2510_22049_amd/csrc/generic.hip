@@ -331,12 +331,13 @@ __global__ void qla_state_kernel(const float* __restrict__ K, const float* __res
 
 // out_h = SiLU(Q_h) SiLU(Z_h) with Z_h the fixed-order sum of the user's states;
 // the self term adds (SiLU(q) . SiLU(k')) v'.  grid (B, H), 1024 threads, Z staged in LDS.
-// (Heads of width 32 have qla_finish32_kernel.)
+// (Heads of width 32 have qla_finish32_kernel, unless out lies over the queries: here a head's queries are read by the
+// workgroup that stores its outputs, a run at a time and before them, so out may be their own buffer.)
 template <typename T>
 __global__ __launch_bounds__(1024) void qla_finish_kernel(const float* __restrict__ partials,
                                                          const int64_t* __restrict__ offsets, int S, int d, int H,
-                                                         int seg, int64_t G, T* __restrict__ out,
-                                                         const T* __restrict__ Q, int64_t q_user_stride,
+                                                         int seg, int64_t G, T* out,
+                                                         const T* Q, int64_t q_user_stride,
                                                          const float* __restrict__ Ks,
                                                          const float* __restrict__ Vs, int B, int64_t N, int* status) {
   constexpr int kW = kMaxDh;                    // register rows are sized for it
@@ -568,6 +569,7 @@ __device__ __forceinline__ void sum_records32(const float* __restrict__ partials
 // read, so two share them), and what follows them.  The first queries are requested before the records are waited for; a wave
 // takes 16 of them and sends them through v_mfma_f32_16x16x4_f32 as they lie in its registers (a lane's four steps are
 // four neighbouring channels, and four neighbouring output channels of a query come out in a lane).
+// The two workgroups of a head read the same queries, so out must not lie over them.
 // The records are summed in the order of qla_finish_kernel.  What a kernel runs once comes out of a cold instruction cache at
 // some 0.2 us for 64 bytes, so the queries go round a loop that is not unrolled.  One workgroup of 1024 threads a head, four
 // threads a query out of LDS: jagged batch, S = 256, 77.8 us a call, now 76.2 (medians of two boxes 72.6, 71.4).
@@ -1082,7 +1084,11 @@ static vista_status generic_summarize_t(const SummarizeArgs& a) {
   T* out = static_cast<T*>(a.out);
   int* status = a.seg_user ? nullptr : reinterpret_cast<int*>(a.workspace);
   const int64_t check = a.offsets_checked ? -1 : d.total_items;
-  if (qla && d.d / d.H == 32)
+  // Heads of width 32 have a kernel of their own, whose two workgroups a head must not write what the other one still reads.
+  const size_t out_bytes = size_t(d.B) * d.S * d.d * sizeof(T), q_bytes = d.q_user_stride ? out_bytes : size_t(d.S) * d.d * sizeof(T);
+  const uintptr_t q0 = reinterpret_cast<uintptr_t>(Q), out0 = reinterpret_cast<uintptr_t>(out);
+  const bool apart = q0 + q_bytes <= out0 || out0 + out_bytes <= q0;
+  if (qla && d.d / d.H == 32 && apart)
     VISTA_LAUNCH(qla_finish32_kernel<T>, dim3(d.B, d.H, 2), dim3(512), 0, a.stream, partials, a.offsets, d.S, d.d,
                  d.H, a.seg, a.G, out, Q, d.q_user_stride, Ks, Vs, d.B, check, status);
   else if (qla)

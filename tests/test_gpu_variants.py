@@ -278,6 +278,17 @@ def test_qla_queries_that_are_not_finite_keep_to_their_row(dtype, d, H):
     assert np.array_equal(got[rest], clean[rest])
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("form,d,H,S,self_term", [("qla", 128, 4, 300, False), ("qla", 128, 4, 300, True), ("qla", 64, 1, 40, True), ("softmax", 128, 4, 256, False),
+                                                  ("softmax", 64, 2, 40, False), ("silu", 128, 4, 128, False)])
+def test_outputs_in_place_of_queries_of_their_own(dtype, form, d, H, S, self_term):
+    """Two runs of 256 queries with a remainder, and the other widths and forms."""
+    X, off, Q, Wk, Wv = problem(79, [700, 0, 1, 2100], d, S, dtype, True)
+    buf, offd = dev(Q, dtype), torch.from_numpy(off).cuda()
+    V.vista_summarize(dev(X, dtype), offd, buf, dev(Wk, dtype), dev(Wv, dtype), buf, H=H, attn=FORMS[form], self_term=self_term)
+    assert_blocks_close(host64(buf), oracle(form, X, off, Q, Wk, Wv, H, self_term), dtype, f"in place, {form}")
+
+
 def test_qla_at_the_jagged_workload_shape_and_bitwise_repeatable():
     c = I.CONFIGS[2]
     lens = I.lengths(c)
