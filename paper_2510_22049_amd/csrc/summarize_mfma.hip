@@ -1062,9 +1062,7 @@ __global__ __launch_bounds__(MAXT, OCC) void summarize_mfma_kernel(MfmaSummarize
 // RG = 4: each of the four is a block of four waves; wave r takes the r-th run of the records,
 // ascending, and the runs' sums are combined in ascending order.  (No codec: its scale spans the four.)
 // Columns past the last query are computed and not stored.
-// SPLIT: records of the split operands, whose values may be infinite.  (Clearing the padding entries for the
-// other records as well made one user of 7001 items 1 us slower.)
-template <bool SILU, int RG, bool SPLIT>
+template <bool SILU, int RG>
 __global__ __launch_bounds__(256) void merge_mfma_kernel(const float* __restrict__ partials,
                                                               const int64_t* __restrict__ offsets, int B, int S, int d,
                                                               int H, int seg, int64_t N, int64_t G,
@@ -1159,7 +1157,7 @@ __global__ __launch_bounds__(256) void merge_mfma_kernel(const float* __restrict
     }
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {     // ascending segment order
-      if (SPLIT && u > left) o[u] = make_float4(0.f, 0.f, 0.f, 0.f);   // (they may be infinite: a weight of 0 is not enough)
+      if (u > left) o[u] = make_float4(0.f, 0.f, 0.f, 0.f);   // (they may be infinite: a weight of 0 is not enough)
       if (!SILU) l = fmaf(lm[u].x, wgt[u], l);
       o0 = fmaf(o[u].x, wgt[u], o0);
       o1 = fmaf(o[u].y, wgt[u], o1);
@@ -1478,11 +1476,11 @@ static hipError_t launch_split(MfmaSummarizeParams& p, int d, int64_t G, hipStre
   return launch_main<256, 2, 1, 4, false, true, 512, A>(p, w2, G, s);
 }
 
-template <bool SILU, int RG, bool SPLIT>
+template <bool SILU, int RG>
 static hipError_t launch_merge(const MfmaSummarizeParams& p, const SummarizeArgs& a, const float* Ks, const float* Vs,
                                int64_t blocks) {
   const vista_summarize_desc& d = a.desc;
-  return launch(merge_mfma_kernel<SILU, RG, SPLIT>, dim3(unsigned(RG > 1 ? 4 * blocks : blocks)), dim3(256), 0, a.stream, p.partials, a.offsets,
+  return launch(merge_mfma_kernel<SILU, RG>, dim3(unsigned(RG > 1 ? 4 * blocks : blocks)), dim3(256), 0, a.stream, p.partials, a.offsets,
                 d.B, d.S, d.d, d.H, a.seg, d.total_items, a.G, static_cast<uint16_t*>(a.out),
                 reinterpret_cast<int*>(a.workspace), a.offsets_checked ? 0 : 1, p.Q, d.q_user_stride, Ks, Vs,
                 SILU ? a.scale_plain : a.scale_log2, a.out_scales);
@@ -1535,9 +1533,7 @@ vista_status mfma_summarize(const SummarizeArgs& a) {
   const bool wide = merge_blocks <= 512 && !a.out_scales;
   auto merge = [&](auto four) {
     constexpr int RG = decltype(four)::value;
-    return silu                       ? launch_merge<true, RG, false>(p, a, Ks, Vs, merge_blocks)
-           : mfma_split_supported(d) ? launch_merge<false, RG, true>(p, a, Ks, Vs, merge_blocks)
-                                     : launch_merge<false, RG, false>(p, a, Ks, Vs, merge_blocks);
+    return silu ? launch_merge<true, RG>(p, a, Ks, Vs, merge_blocks) : launch_merge<false, RG>(p, a, Ks, Vs, merge_blocks);
   };
   const hipError_t e = wide ? merge(Int<4>{}) : merge(Int<1>{});
   return e == hipSuccess ? VISTA_OK : VISTA_ERR_HIP;

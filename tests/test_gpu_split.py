@@ -226,6 +226,30 @@ def test_a_weight_that_is_not_finite_stays_in_its_column(form, d, H, S, self_ter
     assert not np.any(np.isfinite(got[[0, 2]][:, :, c]))
 
 
+@pytest.mark.parametrize("form", [V.VISTA_ATTN_SOFTMAX, V.VISTA_ATTN_SILU])
+@pytest.mark.parametrize("users", [4, 70])
+@pytest.mark.parametrize("records", [1, 3, 8, 9, 16, 20, 32, 33])
+def test_an_infinite_record_keeps_to_its_channel(form, users, records):
+    """A value beyond fp32 makes one channel of its user infinite in every record count a batch of the merge can end with (in
+    four runs of records for few users, in one for many), and leaves the other channels their bits."""
+    d, H, S, seg = 128, 4, 64, 64
+    X, off, Q, Wk, Wv = problem(records, d, S, lens=[seg * records] + [65] * (users - 1))
+    X[:, -1], Wk[-1], Wv[-1] = 0.0, 0.0, 0.0
+    Wv[-1, 40] = 2.0
+    clean = run(X, off, Q, Wk, Wv, H, attn=form, segment_items=seg)
+    run_of = -(-records // 4) if users == 4 else records
+    for last in {run_of, records}:                                # the last record of the first run, of the last
+        Y = X.copy()
+        Y[seg * last - 7, -1] = 2.0 ** 127
+        out = torch.zeros((users, S, d), device="cuda", dtype=torch.bfloat16)
+        V.vista_summarize(dev(Y, "bf16"), torch.from_numpy(off).cuda(), dev(Q, "bf16"), dev(Wk, "bf16"), dev(Wv, "bf16"), out, H=H,
+                          attn=form, segment_items=seg)
+        got = host64(out)
+        assert np.all(np.isinf(got[0, :, 40])), f"record {last} of {records}"
+        got[0, :, 40] = clean[0, :, 40]
+        assert np.array_equal(got, clean)
+
+
 @pytest.mark.parametrize("form,dtype,d,H,S,n", [
     (V.VISTA_ATTN_SOFTMAX, "bf16", 128, 4, 256, 7001), (V.VISTA_ATTN_SILU, "bf16", 256, 8, 128, 3000), (V.VISTA_ATTN_SOFTMAX, "bf16", 64, 2, 40, 5000),
     (V.VISTA_ATTN_QLA, "bf16", 128, 4, 40, 5000), (V.VISTA_ATTN_SOFTMAX, "f32", 64, 1, 16, 1024), (V.VISTA_ATTN_SILU, "f32", 40, 2, 16, 1024)])
