@@ -80,7 +80,8 @@ __device__ __forceinline__ int find_user_wave(const int64_t* __restrict__ offset
   return __builtin_amdgcn_readfirstlane(lo);
 }
 
-// row / seg, the segment of a row: 32-bit division (a tenth of the instructions of the 64-bit one) where the row allows.
+// row / seg, the segment of a row: 32-bit division where the row allows, a tenth of the instructions of the 64-bit one.  (No call
+// was measurably faster by it: jagged batch 169.7 us both ways, one user of 7001 items 20.4, quasi-linear form 71.5.)
 __device__ __forceinline__ int64_t segment_of(int64_t row, int seg) {
   return (uint64_t(row) >> 32) == 0 ? int64_t(uint32_t(row) / uint32_t(seg)) : row / seg;
 }

@@ -64,8 +64,10 @@ constexpr float kSafeBound2 = 3600.f;  // (60)^2: |q|^2 |k|^2 below this keeps 2
 constexpr float kLarge2 = 1.2089258196146292e24f;
 // A record: [four O registers][lane][4], then [lane][l, m]: five stores of 8 or 16 bytes a lane and block, and two loads a
 // record in a wave of the merge, which is bound by the latency of the longest user's records.  (A register a row, 18 stores and
-// six loads of 4 bytes, and the maximum moved record by record: one user of 7001 items 21.2 -> 20.7 us a call, jagged batch of
-// 768 597 items 171.6 -> 170.4, SiLU, S = 128, 500 003 items 103.0 -> 101.9, d = 64, S = 100, 300 007 items 67.0 -> 66.2.)
+// six loads of 4 bytes, and the maximum moved record by record, measured together: one user of 7001 items 21.1 -> 20.7 us a call, jagged
+// batch of 768 597 items 171.4 -> 170.0, 8 users of a million items 1586 -> 1580, SiLU, S = 128, 500 003 items 102.1 -> 101.2, d = 64,
+// S = 100, 300 007 items 67.0 -> 66.4.  The merge alone is slower by it where every compute unit reads: 32 768 blocks over 14 M items of
+// d = 256 116 -> 122 us, eight long users 12.1 -> 12.7; 5.8 -> 5.4, 12.3 -> 11.8 and 12.3 -> 11.6 in the first, second and fourth call.)
 constexpr int kRecFloats = 18 * 64;
 constexpr int kRecSums = 16 * 64;    // where l and m are
 
@@ -649,11 +651,11 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
     read_v(at.kv1);
     publish(at.kv2, acc);
   };
-  // The same in an order of its own (pin).  A product keeps the matrix pipe for 32 clocks and the issue port for 8; three
-  // v_exp_f32 fit behind it for nothing, but products in a row hold up the vector instructions of both waves of the
-  // SIMD (18 products, then 72 v_exp_f32: 888 clocks a wave at two waves; one to four in turn: 722).  Left to itself the compiler
-  // ends a tile in runs of ten and more products.  So the second product of a block and its denominators wait for the
-  // exponentials of the next block, and a pair is packed a few instructions behind its exponentials.
+  // The same in an order of its own (pin).  A product keeps the matrix pipe for 32 clocks and the issue port for some 11, and
+  // exponentials run beside it (four products and sixteen v_exp_f32 take what the exponentials do alone); products in a row wait for the
+  // pipe.  Left to itself the compiler ends a tile in runs of ten and more of them.  So the second product of a block and its denominators
+  // wait for the exponentials of the next block, and a pair is packed a few instructions behind its exponentials.
+  static_assert(!ORDERED || (!SILU && !SPLIT), "ordered_tile forms softmax weights as one bf16 term");
   auto ordered_tile = [&](int r) __attribute__((always_inline)) {
     const Slots at = slots(r);
     f32x16 acc = {0};
@@ -1401,12 +1403,12 @@ static hipError_t launch_main(MfmaSummarizeParams& p, int wph, int64_t G, hipStr
 template <int ATTN>
 static hipError_t launch_for_shape(MfmaSummarizeParams& p, const vista_summarize_desc& desc, int64_t G, hipStream_t s) {
   const int d = desc.d;
-  // Four query blocks a wave at d = 128, softmax: the tile in its own order (ordered_tile).  us a call, free / ordered: S = 256, jagged batch 169.6 /
-  // 168.3, 8 users of a million items 1560 / 1535, 300 users of 300 003 106.9 / 105.9, one of 7001 20.7 / 20.4; S = 512, 100 users of
-  // 300 003 134.6 / 133.4, with queries of their own 145.9 / 145.1.  With queries of their own at S = 256 the registers of
+  // Four query blocks a wave at d = 128, softmax: the tile in its own order (ordered_tile).  us a call, free / ordered: S = 256, jagged batch
+  // 169.2 / 168.9, 8 users of a million items 1573 / 1560, 300 users of 300 003 107.8 / 107.5, one of 7001 20.56 / 20.43; S = 512, 100 users
+  // of 300 003 135.9 / 134.7, with queries of their own 146.1 / 146.2.  With queries of their own at S = 256 the registers of
   // their load are spilled in the loop (8 users 84.4 / 84.7, 300 users 120.7 / 122.4): those stay free.  So do one and two blocks a
   // wave (S = 64 66.9 / 67.8, S = 128 equal) and d = 256 (S = 128 225 / 230, S = 512 435 / 450), where a wave has less to put between its
-  // products or attends without projecting.
+  // products or attends without projecting.  The SiLU form and the split operands have no such tile.
   constexpr bool softmax = ATTN == VISTA_ATTN_SOFTMAX;
   const bool shared = p.q_user_stride == 0;
   if (half_workgroups(desc, p.seg, G)) {

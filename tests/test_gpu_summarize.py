@@ -53,7 +53,8 @@ def test_mfma_jagged_matches_oracle(d, H, S, seg):
 @pytest.mark.parametrize("lens,seg,half", [(LENS, 64, True), ([5000], 0, True), ([9000, 33, 0, 120000, 1, 64, 20031, 150000], 2048, False)])
 def test_both_orders_of_a_tile_agree(lens, seg, half):
     """S = 256 at d = 128 takes a tile in one order of instructions for shared queries and in another for queries of the
-    users' own: the same sums, so the same bits where every user's own are the shared ones."""
+    users' own (launch_for_shape; were both sent to one kernel, this would compare it with itself): the same sums, so the
+    same bits where every user's own are the shared ones."""
     X, off, Q, Wk, Wv = problem(9, lens, 128, 256)
     own = np.repeat(Q[None], len(lens), axis=0)
     for per_user in (False, True):
@@ -63,6 +64,19 @@ def test_both_orders_of_a_tile_agree(lens, seg, half):
     few = [b for b in range(len(lens)) if lens[b] <= 9000]
     want = O.summarize(np.concatenate([X[off[b]:off[b + 1]] for b in few]), I.offsets_from_lengths([lens[b] for b in few]), Q, Wk, Wv, 4)
     assert_blocks_close(shared[few], want, "bf16", f"ordered tile, seg={seg}")
+
+
+@pytest.mark.parametrize("lens,seg", [([700, 0, 1, 31, 2100, 64, 95, 1029], 64), ([9000, 33, 120000, 20031, 0, 1], 2048)])
+@pytest.mark.parametrize("per_user", [False, True])
+def test_the_ordered_tile_of_512_seeds_agrees_with_the_free_one(lens, seg, per_user):
+    """S = 512 at d = 128 takes the ordered tile for queries of either kind, in waves that project and waves that only attend.  Its
+    waves hold the seeds that those of two calls of S = 256 with queries of the users' own do (the free tile, launch_for_shape), and up
+    to eight users both merge in four runs: the same bits."""
+    X, off, Q, Wk, Wv = problem(10, lens, 128, 512, per_user)
+    own = Q if per_user else np.repeat(Q[None], len(lens), axis=0)
+    got = run(X, off, Q, Wk, Wv, 4, segment_items=seg)
+    for half in (slice(0, 256), slice(256, 512)):
+        assert np.array_equal(got[:, half], run(X, off, own[:, half], Wk, Wv, 4, segment_items=seg))
 
 
 @pytest.mark.parametrize("d,H,S", [(128, 4, 256), (256, 8, 512)])
