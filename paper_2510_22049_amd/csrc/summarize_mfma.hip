@@ -5,8 +5,8 @@
 //   1. the X tile (32 x D bf16) goes from HBM straight into LDS (direct
 //      global->LDS loads, three tiles deep, no stop in registers);
 //   2. wave "K" of a pair forms K_h^T = (scale*log2e W_k,h)^T X^T, wave "V" forms
-//      V_h = X W_v,h -- D / 16 32x32x16 MFMAs each, weights held in registers (as LDS operands only in
-//      the widest SPLIT shape and with four query blocks a wave at d = 256) -- and both hand the bf16
+//      V_h = X W_v,h -- D / 16 32x32x16 MFMAs each, weights held in registers (as LDS operands only
+//      with four query blocks a wave at d = 256) -- and both hand the bf16
 //      result to their partner through LDS;
 //   3. each wave owns half of the S queries: for every block of 32 queries
 //      S^T = K_h Q_h^T (items x queries), p = 2^(s - m), O^T += V_h^T P^T.
@@ -24,17 +24,6 @@
 // (Sixteen waves of two query blocks and 128 registers each, four to a SIMD, were 7 to 10 %
 // slower than eight of four: twice the operand reads from LDS and idle attend-only waves.)
 //
-// SPLIT.  The fixed seed counts keep K, V and the softmax weights as bf16 operands.  Any other seed
-// count (and d = 64) computes with them in fp32, as one thread per query on the vector unit did
-// before: each is three bf16 terms, 24 bits.  Scores take three products (the seeds are bf16
-// already), P V six, the scale is applied to the fp32 keys.  Error of the result before its bf16
-// rounding against fp64 (2-norm; d = 64 to 256, scores up to 6 / 25 / 100): 0.3-0.8 / 0.5-1.7 /
-// 0.7-1.2 e-6, one thread per query 0.4-1.6 / 0.6-7.5 / 0.8-1.5 e-6; two terms were 1.3-3.4 /
-// 6.1-8.2 / 9.5-15 e-6 and 20 to 30 % faster, and are not enough for that reason.  More than four
-// times the matrix work of the plain operands and ten more vector instructions per weight pair;
-// against one thread per query: 48 users, 300 007 items, d = 64, S = 100 from 10 500 to 68 us,
-// 3 users, 20 000 items, d = 256, S = 100 from 2 717 to 37 us.
-//
 // Softmax reference.  Scores are kept in base-2 units.  While every score of a
 // tile is provably inside [-60, 60] (Cauchy-Schwarz: |q| |k| <= 60) the
 // reference maximum stays at the constant 0 and no per-score subtraction or
@@ -44,166 +33,45 @@
 //
 // Each piece ends with one partial record (O, l, m) per head; merge_mfma_kernel
 // combines a user's records in ascending segment order.
-#include <math.h>
-
-#include "common.hpp"
+#include "stage1_mfma.hpp"
 
 namespace vista {
 
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(2))) float f32x2;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef __attribute__((ext_vector_type(4))) short i16x4;
-
-constexpr int kTile = kTileItems;    // items per tile
 constexpr float kSafeBound2 = 3600.f;  // (60)^2: |q|^2 |k|^2 below this keeps 2^s in range
-// SPLIT: values up to 2^40 (squared, half a column of a tile) meet weights up to 2^60 with room for any history;
-// a tile beyond, or with an infinite or NaN value, takes the running maximum and an fp32 product.
-constexpr float kLarge2 = 1.2089258196146292e24f;
-// A record: [four O registers][lane][4], then [lane][l, m]: five stores of 8 or 16 bytes a lane and block, and two loads a
-// record in a wave of the merge, which is bound by the latency of the longest user's records.  (A register a row, 18 stores and
-// six loads of 4 bytes, and the maximum moved record by record, measured together: one user of 7001 items 21.1 -> 20.7 us a call, jagged
-// batch of 768 597 items 171.4 -> 170.0, 8 users of a million items 1586 -> 1580, SiLU, S = 128, 500 003 items 102.1 -> 101.2, d = 64,
-// S = 100, 300 007 items 67.0 -> 66.4.  The merge alone is slower by it where every compute unit reads: 32 768 blocks over 14 M items of
-// d = 256 116 -> 122 us, eight long users 12.1 -> 12.7; 5.8 -> 5.4, 12.3 -> 11.8 and 12.3 -> 11.6 in the first, second and fourth call.)
-constexpr int kRecFloats = 18 * 64;
-constexpr int kRecSums = 16 * 64;    // where l and m are
-
-struct MfmaSummarizeParams {
-  const uint16_t* X;
-  const int64_t* offsets;
-  const uint16_t* Q;
-  int64_t q_user_stride;
-  const uint16_t* Wk;
-  const uint16_t* Wv;
-  float* partials;
-  int B, S, H;
-  int nqb;        // query blocks = ceil(S / 32)
-  int wph;        // waves per head (the workgroup has HPW wph of them)
-  int64_t N;
-  int seg;
-  int nhg;        // head groups = H / HPW
-  float c;        // scale * log2(e)
-  float* Ks;      // self term: K', V' of the seeds, formed beside the history, or null
-  float* Vs;
-  int64_t self_rows;
-};
-
-union Pack8 {
-  bf16x8 v;
-  uint4 u;
-  uint16_t h[8];
-  uint32_t w[4];
-};
-
-__device__ __forceinline__ uint32_t cvt_pk_bf16(float a, float b) {
-  f32x2 f = {a, b};
-  bf16x2 r = __builtin_convertvector(f, bf16x2);
-  return __builtin_bit_cast(uint32_t, r);
-}
 
 __device__ __forceinline__ float dot2_ones(uint32_t pk, float acc) {
   const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
   return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk), ones, acc, false);
 }
 
-// acc + 0: NaN if either number of the pair is infinite or NaN
-__device__ __forceinline__ float dot2_zero(uint32_t pk, float acc) {
-  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk), bf16x2{}, acc, false);
-}
-
-__device__ __forceinline__ float dot2_self(uint32_t pk, float acc) {
-  const bf16x2 v = __builtin_bit_cast(bf16x2, pk);
-  return __builtin_amdgcn_fdot2_f32_bf16(v, v, acc, false);
-}
-
-// An instruction whose result is pinned comes before whatever is pinned later in the program.
-template <typename T>
-__device__ __forceinline__ void pin(T& v) { asm volatile("" : "+v"(v)); }
-
-// LDS-only workgroup barrier: global loads in flight (the X prefetch) stay in flight.
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-// Register i of a lane in half hf holds row 4 hf + acc_row0(i) of the 32x32 accumulator.
-__device__ __forceinline__ constexpr int acc_row0(int i) { return 8 * (i / 4) + (i % 4); }
-
-// One 32-wide operand of a tile: the two k-halves of its bf16 value and, where values are kept whole
-// (SPLIT), of the two bf16 terms that make up the rest of their 24 bits.
-template <bool SPLIT>
+// One 32-wide operand of a tile: the two k-halves of its bf16 value.
 struct Operand {
   Pack8 hi[2];
-  Pack8 mid[SPLIT ? 2 : 1];
-  Pack8 lo[SPLIT ? 2 : 1];
 };
 
-// fp32 pair (a, b) as three bf16 pairs: 8 + 8 + 8 bits, nothing is left of finite values below 2^127
-__device__ __forceinline__ void split_pk(float a, float b, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
-  hi = cvt_pk_bf16(a, b);
-  a -= __uint_as_float(hi << 16);
-  b -= __uint_as_float(hi & 0xFFFF0000u);
-  mid = cvt_pk_bf16(a, b);
-  lo = cvt_pk_bf16(a - __uint_as_float(mid << 16), b - __uint_as_float(mid & 0xFFFF0000u));
-}
-
-// The same for any pair: the leading terms are cut off instead of rounded, so that a value beyond the largest
-// bf16 number stays finite, and an infinite or NaN value leaves no rest.
-__device__ __forceinline__ void split_pk_any(float a, float b, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
-  const uint32_t ha = __float_as_uint(a) & 0xFFFF0000u, hb = __float_as_uint(b) & 0xFFFF0000u;
-  uint32_t low;
-  split_pk(__builtin_isfinite(a) ? a - __uint_as_float(ha) : 0.f, __builtin_isfinite(b) ? b - __uint_as_float(hb) : 0.f, mid, lo, low);
-  hi = (ha >> 16) | hb;
-}
-
-// acc += A B with A = hi (+ mid + lo) and B exact (bf16)
-template <bool SPLIT>
-__device__ __forceinline__ f32x16 mma_exact_b(const Operand<SPLIT>& a, const bf16x8 (&b)[2], f32x16 acc) {
+// acc += K Q
+__device__ __forceinline__ f32x16 mma_exact_b(const Operand& a, const bf16x8 (&b)[2], f32x16 acc) {
   acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi[0].v, b[0], acc, 0, 0, 0);
   acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi[1].v, b[1], acc, 0, 0, 0);
-  if constexpr (SPLIT) {
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.mid[q].v, b[q], acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.lo[q].v, b[q], acc, 0, 0, 0);
-    }
-  }
   return acc;
 }
 
-// acc += A B, both hi (+ mid + lo); mid and lo are at most 2^-8 and 2^-16 of hi, so what is left out (mid lo, lo lo) is 2^-24
-template <bool SPLIT>
-__device__ __forceinline__ f32x16 mma(const Operand<SPLIT>& a, const Operand<SPLIT>& b, f32x16 acc) {
+// acc += A B
+__device__ __forceinline__ f32x16 mma(const Operand& a, const Operand& b, f32x16 acc) {
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi[q].v, b.hi[q].v, acc, 0, 0, 0);
-    if constexpr (SPLIT) {
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.mid[q].v, b.hi[q].v, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi[q].v, b.mid[q].v, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.lo[q].v, b.hi[q].v, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.mid[q].v, b.mid[q].v, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi[q].v, b.lo[q].v, acc, 0, 0, 0);
-    }
-  }
+  for (int q = 0; q < 2; ++q) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi[q].v, b.hi[q].v, acc, 0, 0, 0);
   return acc;
 }
 
-// One block of 32 queries against one tile of 32 items.  `general`, `masked` and `large`
+// One block of 32 queries against one tile of 32 items.  `general` and `masked`
 // are wave-uniform; the MFMAs sit on the common path so the accumulators keep
-// one register assignment whichever route a tile takes.  large (SPLIT): the tile has
-// values of any size, infinite ones included: the second product in fp32 (a term 0 of a
-// weight times an infinite value would be NaN), rows past the piece left out of it.
-template <bool SPLIT>
-__device__ __forceinline__ void attend_block(const Operand<SPLIT>& k, const Operand<SPLIT>& v,
+// one register assignment whichever route a tile takes.
+__device__ __forceinline__ void attend_block(const Operand& k, const Operand& v,
                                              const bf16x8 (&q)[2], f32x16& o, float& l, float& m, bool general,
-                                             bool masked, int nvl, bool large) {
+                                             bool masked, int nvl) {
   // nvl = valid items of the tile minus 4 hf: register i is valid iff acc_row0(i) < nvl
   f32x16 s = {0};
-  s = mma_exact_b<SPLIT>(k, q, s);
+  s = mma_exact_b(k, q, s);
   if (general) {
 #pragma unroll
     for (int i = 0; i < 16; ++i)
@@ -228,52 +96,25 @@ __device__ __forceinline__ void attend_block(const Operand<SPLIT>& k, const Oper
     for (int i = 0; i < 16; ++i)
       if (acc_row0(i) >= nvl) s[i] = 0.f;
   }
-  if constexpr (SPLIT) {
-    if (large) {
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        auto term = [&](const Pack8& w) __attribute__((always_inline)) { return __uint_as_float(uint32_t(w.h[i % 8]) << 16); };
-        const float vi = term(v.hi[i / 8]) + (term(v.mid[i / 8]) + term(v.lo[i / 8]));
-        o = __builtin_amdgcn_mfma_f32_32x32x2f32(acc_row0(i) < nvl ? vi : 0.f, s[i], o, 0, 0, 0);
-        l += s[i];
-      }
-      return;
-    }
-  }
-  Operand<SPLIT> p;
+  Operand p;
 #pragma unroll
   for (int i = 0; i < 16; i += 2) {
-    if constexpr (SPLIT) {
-      split_pk(s[i], s[i + 1], p.hi[i / 8].w[(i % 8) / 2], p.mid[i / 8].w[(i % 8) / 2], p.lo[i / 8].w[(i % 8) / 2]);
-      l += s[i] + s[i + 1];
-    } else {
-      const uint32_t pk = cvt_pk_bf16(s[i], s[i + 1]);
-      l = dot2_ones(pk, l);
-      p.hi[i / 8].w[(i % 8) / 2] = pk;
-    }
+    const uint32_t pk = cvt_pk_bf16(s[i], s[i + 1]);
+    l = dot2_ones(pk, l);
+    p.hi[i / 8].w[(i % 8) / 2] = pk;
   }
-  o = mma<SPLIT>(v, p, o);
+  o = mma(v, p, o);
 }
-
-template <int V>
-struct Int { static constexpr int value = V; };
-
-constexpr int kXBuf = 3;             // ring depth of the X tiles and of the projected tiles in LDS
-// The split operands are three times as large, and two slots are enough (two workgroups then still fit a
-// compute unit): a tile is published into the slot of the one whose operands every wave has read, one
-// tile ago, and the barrier in between orders the two.
-constexpr int kvbuf_slots(bool split) { return split ? 2 : kXBuf; }
 
 // Shared memory of one workgroup.  WREG: a projecting wave keeps its D x 32 weight operands in
 // registers (D / 4 of them) instead of in LDS, which halves the operand reads of a projection: with the
 // weights in LDS at D = 256, 32 users and 500 000 items took 242 us instead of 222 at S = 128 and 308
 // instead of 296 at S = 256.
-template <int D, int HPW, bool WREG, bool SPLIT>
+template <int D, int HPW, bool WREG>
 struct SummarizeLds {
   uint4 xbuf[kXBuf][(D / 8) * 32];    // X tiles: [16-byte chunk][item], filled by direct global->LDS loads
-  uint4 kvbuf[kvbuf_slots(SPLIT)][HPW][2][SPLIT ? 6 : 2][64];   // projected tiles: [ring slot][head][K|V][(term, )half of the 16 registers][lane]
-  float knorm[kvbuf_slots(SPLIT)][HPW][64];   // squared norm of the scaled key rows (half per lane)
-  float vnorm[SPLIT ? 2 : 1][SPLIT ? HPW : 1][SPLIT ? 64 : 1];   // SPLIT: that of the value columns
+  uint4 kvbuf[kXBuf][HPW][2][2][64];  // projected tiles: [ring slot][head][K|V][half of the 16 registers][lane]
+  float knorm[kXBuf][HPW][64];        // squared norm of the scaled key rows (half per lane)
   uint4 wop[WREG ? 1 : HPW * 2 * (D / 16) * 64];   // projection weights as MFMA operands: [head][K|V][k-slice][lane]
 };
 
@@ -288,8 +129,8 @@ struct SummarizeLds {
 // denominator, no norm test; the key weights then carry -scale*log2(e), so a score leaves the
 // MFMA as t = -s log2(e) and SiLU(s) = -ln(2) t / (1 + 2^t); the weight handed to the second
 // product is t / (1 + 2^t) and the constant joins the 1/L_b of the merge.
-template <int D, int NQB, int HPW, int FW, bool WREG, bool SPLIT, bool ALLF, int ROLE, int ATTN, bool ORDERED>
-__device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, SummarizeLds<D, HPW, WREG, SPLIT>& sm,
+template <int D, int NQB, int HPW, int FW, bool WREG, bool ALLF, int ROLE, int ATTN, bool ORDERED>
+__device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, SummarizeLds<D, HPW, WREG>& sm,
                                                int64_t g, int h, int hl, int qblock, int64_t seg_begin,
                                                int64_t seg_end) {
   constexpr bool PROJ = ROLE < 2;        // this wave projects
@@ -355,7 +196,7 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
         for (int q = 0; q < 2; ++q)
 #pragma unroll
           for (int j = 0; j < 8; ++j) sel[q].h[j] = (l32 == 16 * q + 8 * hf + j) ? 0x3F80 : 0;
-        const float c = ROLE || SPLIT ? 1.f : p.c;
+        const float c = ROLE ? 1.f : p.c;
 #pragma unroll
         for (int b = 0; b < KS / 2; ++b) {
           f32x16 t = {0};
@@ -374,7 +215,7 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
             const uint16_t w = W[(16 * ks + 8 * hf + j) * D + 32 * h + l32];
-            t.h[j] = ROLE || SPLIT ? w : f32_to_bf16_bits(__uint_as_float(uint32_t(w) << 16) * p.c);
+            t.h[j] = ROLE ? w : f32_to_bf16_bits(__uint_as_float(uint32_t(w) << 16) * p.c);
           }
           if constexpr (WREG) {
 #pragma unroll
@@ -447,7 +288,6 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
   float l[NQB], m[NQB];
   // plain tiles keep their share of the denominators in lacc (register qb % 4 of either accumulator);
   // the general route folds it into l first
-  // (SPLIT adds its fp32 weights into l directly)
   constexpr int NLA = (NQB + 3) / 4;     // pairs of accumulators: one register of each per query block
   constexpr int NLR = NQB < 4 ? NQB : 4;
   f32x4 lacc[NLA][2];
@@ -514,45 +354,21 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
   // hand the projected tile to the partner waves: bf16 operand halves (+ key norms)
   auto publish = [&](int buf, const f32x16& acc) __attribute__((always_inline)) {
     if constexpr (PROJ) {
-      Operand<SPLIT> r;
+      Operand r;
       float n2 = 0.f;
 #pragma unroll
       for (int i = 0; i < 16; i += 2) {
-        uint32_t pk;
-        if constexpr (SPLIT) {
-          const float c = ROLE ? 1.f : p.c;      // the keys' scale, in fp32
-          split_pk(acc[i] * c, acc[i + 1] * c, pk, r.mid[i / 8].w[(i % 8) / 2], r.lo[i / 8].w[(i % 8) / 2]);
-        } else {
-          pk = cvt_pk_bf16(acc[i], acc[i + 1]);
-        }
-        if ((ROLE == 0 && !SILU) || SPLIT) n2 = dot2_self(pk, n2);
+        const uint32_t pk = cvt_pk_bf16(acc[i], acc[i + 1]);
+        if (ROLE == 0 && !SILU) n2 = dot2_self(pk, n2);
         r.hi[i / 8].w[(i % 8) / 2] = pk;
       }
-      if constexpr (SPLIT) {
-        if (__builtin_amdgcn_ballot_w64(!(n2 <= kLarge2))) {
 #pragma unroll
-          for (int i = 0; i < 16; i += 2) {
-            const float c = ROLE ? 1.f : p.c;
-            split_pk_any(acc[i] * c, acc[i + 1] * c, r.hi[i / 8].w[(i % 8) / 2], r.mid[i / 8].w[(i % 8) / 2], r.lo[i / 8].w[(i % 8) / 2]);
-          }
-        }
-        if (ROLE == 1) sm.vnorm[buf][hl][lane] = n2;
-      }
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        sm.kvbuf[buf][hl][WR][q][lane] = r.hi[q].u;
-        if constexpr (SPLIT) {
-          sm.kvbuf[buf][hl][WR][2 + q][lane] = r.mid[q].u;
-          sm.kvbuf[buf][hl][WR][4 + q][lane] = r.lo[q].u;
-        }
-      }
+      for (int q = 0; q < 2; ++q) sm.kvbuf[buf][hl][WR][q][lane] = r.hi[q].u;
       if (ROLE == 0 && !SILU) sm.knorm[buf][hl][lane] = n2;
     }
   };
-  float vn2 = 0.f;          // SPLIT: squared norm of half a value column of the tile being attended over
   auto unsafe_tile = [&](float kn2) __attribute__((always_inline)) {
     if constexpr (SILU) return false;
-    if constexpr (SPLIT) return __builtin_amdgcn_ballot_w64(!(kn2 * qmax2 <= kSafeBound2 && vn2 <= kLarge2)) != 0;
     return __builtin_amdgcn_ballot_w64(kn2 * qmax2 > kSafeBound2) != 0;
   };
 
@@ -566,77 +382,62 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
   // Common case: a full tile, bounded scores, another tile behind it.  Straight-line
   // code (one scheduling region per tile): two projection MFMAs of the next tile ride
   // along with every query block of this one.
-  Operand<SPLIT> kk, vv;    // K/V operands of the tile being attended over
+  Operand kk, vv;    // K/V operands of the tile being attended over
   float kn2 = 0.f;          // its squared key norm (this lane's item)
   // Operands of tile t+1 (ring slot i1) come out of LDS while tile t is still being worked on,
   // into the registers tile t has just finished with: K (and the norms) once the last scores
   // of the tile are issued, V after its last P.V product.  They were published one tile ago
   // and the barrier at the start of tile t made them visible, so by the next barrier they
   // are in registers and the next tile starts without a round trip to LDS.
-  auto read_operand = [&](Operand<SPLIT>& r, int i1, int which) __attribute__((always_inline)) {
+  auto read_operand = [&](Operand& r, int i1, int which) __attribute__((always_inline)) {
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      r.hi[q].u = sm.kvbuf[i1][hl][which][q][lane];
-      if constexpr (SPLIT) {
-        r.mid[q].u = sm.kvbuf[i1][hl][which][2 + q][lane];
-        r.lo[q].u = sm.kvbuf[i1][hl][which][4 + q][lane];
-      }
-    }
+    for (int q = 0; q < 2; ++q) r.hi[q].u = sm.kvbuf[i1][hl][which][q][lane];
   };
   auto read_k = [&](int i1) __attribute__((always_inline)) {
     read_operand(kk, i1, 0);
     if constexpr (!SILU) kn2 = sm.knorm[i1][hl][lane] + sm.knorm[i1][hl][lane ^ 32];
-    if constexpr (SPLIT) vn2 = sm.vnorm[i1][hl][lane];
   };
   auto read_v = [&](int i1) __attribute__((always_inline)) {
     read_operand(vv, i1, 1);
   };
-  int odd = 0;              // tile index mod 2
   // slots of tiles t+1 and t+2 in a ring of the X tiles and of the operands, r = tile index mod 3
   struct Slots { int x2, kv1, kv2; };
   auto slots = [&](int r) __attribute__((always_inline)) {
     const int i1 = r == kXBuf - 1 ? 0 : r + 1, i2 = i1 == kXBuf - 1 ? 0 : i1 + 1;
-    return SPLIT ? Slots{i2, odd ^ 1, odd} : Slots{i2, i1, i2};
+    return Slots{i2, i1, i2};
   };
   auto free_tile = [&](int r) __attribute__((always_inline)) {
     const Slots at = slots(r);
     f32x16 acc = {0};
     // scores run one query block ahead of the exponentials that consume them
     f32x16 nx = {0};
-    nx = mma_exact_b<SPLIT>(kk, qop[0], nx);
+    nx = mma_exact_b(kk, qop[0], nx);
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb) {
       if (qb == NQB - 1) read_k(at.kv1);     // the last scores of this tile are already issued
       const f32x16 sc = nx;
       if (qb + 1 < NQB) {
         const f32x16 z = {0};
-        nx = mma_exact_b<SPLIT>(kk, qop[qb + 1], z);
+        nx = mma_exact_b(kk, qop[qb + 1], z);
       }
       if (qb * KPB < KS) project(at.x2, qb * KPB, qb * KPB + KPB < KS ? qb * KPB + KPB : KS, acc);
-      Operand<SPLIT> pp;
-      float lsum[2] = {0.f, 0.f};
+      Operand pp;
 #pragma unroll
       for (int i = 0; i < 16; i += 2) {
         float ea = __builtin_amdgcn_exp2f(sc[i]), eb = __builtin_amdgcn_exp2f(sc[i + 1]);
-        if constexpr (SPLIT) lsum[(i / 2) & 1] += ea + eb;
         if constexpr (SILU) {
           ea = sc[i] * __builtin_amdgcn_rcpf(1.f + ea);
           eb = sc[i + 1] * __builtin_amdgcn_rcpf(1.f + eb);
         }
-        if constexpr (SPLIT)
-          split_pk(ea, eb, pp.hi[i / 8].w[(i % 8) / 2], pp.mid[i / 8].w[(i % 8) / 2], pp.lo[i / 8].w[(i % 8) / 2]);
-        else
-          pp.hi[i / 8].w[(i % 8) / 2] = cvt_pk_bf16(ea, eb);
+        pp.hi[i / 8].w[(i % 8) / 2] = cvt_pk_bf16(ea, eb);
       }
       // The denominator on the matrix core: a 4x4x4 product (16 blocks, one per four lanes)
       // whose A block has ones in row qb % 4 adds a lane's own four packed weights into register
       // qb % 4 of that lane -- the lane-local partial sum a chain of adds would form, taken over
       // the bf16 weights the numerator uses.  It issues like one plain vector instruction for four
       // weights; two accumulators take turns so that consecutive products do not wait for each
-      // other.  (SPLIT: the fp32 weights are added as they are; three terms would be twelve products.)
-      if constexpr (SPLIT) {
-        l[qb] += lsum[0] + lsum[1];
-      } else if constexpr (!SILU) {
+      // other.
+      if constexpr (!SILU) {
         const i16x4 sel = __builtin_bit_cast(i16x4, onesrow[qb % 4]);
 #pragma unroll
         for (int part = 0; part < 4; ++part) {
@@ -646,7 +447,7 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
           a = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(sel, __builtin_bit_cast(i16x4, pw), a, 0, 0, 0);
         }
       }
-      o[qb] = mma<SPLIT>(vv, pp, o[qb]);
+      o[qb] = mma(vv, pp, o[qb]);
     }
     read_v(at.kv1);
     publish(at.kv2, acc);
@@ -655,7 +456,7 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
   // exponentials run beside it (four products and sixteen v_exp_f32 take what the exponentials do alone); products in a row wait for the
   // pipe.  Left to itself the compiler ends a tile in runs of ten and more of them.  So the second product of a block and its denominators
   // wait for the exponentials of the next block, and a pair is packed a few instructions behind its exponentials.
-  static_assert(!ORDERED || (!SILU && !SPLIT), "ordered_tile forms softmax weights as one bf16 term");
+  static_assert(!ORDERED || !SILU, "ordered_tile forms softmax weights");
   auto ordered_tile = [&](int r) __attribute__((always_inline)) {
     const Slots at = slots(r);
     f32x16 acc = {0};
@@ -748,20 +549,18 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
   auto slow_tile = [&](int r, int nvalid, bool unsafe) __attribute__((always_inline)) {
     const Slots at = slots(r);
     const int nvl = nvalid - 4 * hf;
-    if constexpr (!SPLIT) {
 #pragma unroll
-      for (int qb = 0; qb < NQB; ++qb) {
-        l[qb] += lacc[qb / 4][0][qb % 4] + lacc[qb / 4][1][qb % 4];
-        lacc[qb / 4][0][qb % 4] = lacc[qb / 4][1][qb % 4] = 0.f;
-      }
+    for (int qb = 0; qb < NQB; ++qb) {
+      l[qb] += lacc[qb / 4][0][qb % 4] + lacc[qb / 4][1][qb % 4];
+      lacc[qb / 4][0][qb % 4] = lacc[qb / 4][1][qb % 4] = 0.f;
     }
     if constexpr (SILU) {
       // pointwise form: scores, weights (rows past the piece's end get weight 0), second product
 #pragma unroll
       for (int qb = 0; qb < NQB; ++qb) {
         f32x16 sc = {0};
-        sc = mma_exact_b<SPLIT>(kk, qop[qb], sc);
-        Operand<SPLIT> pp;
+        sc = mma_exact_b(kk, qop[qb], sc);
+        Operand pp;
 #pragma unroll
         for (int i = 0; i < 16; i += 2) {
           float wa = sc[i] * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(sc[i]));
@@ -770,7 +569,7 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
           if (acc_row0(i + 1) >= nvl) wb = 0.f;
           pp.hi[i / 8].w[(i % 8) / 2] = cvt_pk_bf16(wa, wb);
         }
-        o[qb] = mma<SPLIT>(vv, pp, o[qb]);
+        o[qb] = mma(vv, pp, o[qb]);
       }
       mode = 1;
     } else {
@@ -781,10 +580,9 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
     }
     mode = general ? 2 : 1;
     const bool masked = nvalid < kTile;
-    const bool large = SPLIT && __builtin_amdgcn_ballot_w64(!(vn2 <= kLarge2)) != 0;
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb)
-      attend_block<SPLIT>(kk, vv, qop[qb], o[qb], l[qb], m[qb], general, masked, nvl, large);
+      attend_block(kk, vv, qop[qb], o[qb], l[qb], m[qb], general, masked, nvl);
     }
     read_k(at.kv1);
     read_v(at.kv1);
@@ -822,7 +620,7 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
   };
 
   // Tile t lives in ring slot t mod 3, as raw rows (xbuf) and, projected, as operands
-  // (kvbuf; SPLIT: slot t mod 2).  While tile t is attended over, tile t+2 is projected and published, the
+  // (kvbuf).  While tile t is attended over, tile t+2 is projected and published, the
   // operands of tile t+1 move into registers, the rows of tile t+3 land and those of tile
   // t+4 are requested into the slot whose rows (tile t+1) were projected one tile ago.
   // ---- prologue: tiles 0, 1, 2 requested; 0 and 1 landed, projected and published
@@ -898,7 +696,6 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
         drain = false;
         ++n;
         r = r == kXBuf - 1 ? 0 : r + 1;
-        odd ^= 1;
         unsafe = unsafe_tile(kn2);
         plain = !unsafe;
       }
@@ -914,7 +711,6 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
       --ca.tiles_left;
       ca.row += kTile;
       r = r == kXBuf - 1 ? 0 : r + 1;
-      odd ^= 1;
       unsafe = unsafe_tile(kn2);
       plain = is_plain();
     }
@@ -935,73 +731,9 @@ __device__ __forceinline__ void summarize_wave(const MfmaSummarizeParams& p, Sum
       drain = true;
     }
     r = r == kXBuf - 1 ? 0 : r + 1;
-    odd ^= 1;
     if (!ca.valid) break;
     unsafe = unsafe_tile(kn2);
     plain = is_plain();
-  }
-}
-
-// Self term: K' = Q W_k and V' = Q W_v of the seeds in fp32 (bf16 inputs, products exact, fp32 sums).
-// A unit is 32 seeds x 32 channels of both, formed by one wave: the seeds' rows read once as the A operand, the
-// weights 16 bytes a lane and turned by the matrix core as in the main kernel.
-__device__ __forceinline__ void self_kv_unit(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Wk,
-                                             const uint16_t* __restrict__ Wv, float* __restrict__ Ks,
-                                             float* __restrict__ Vs, int64_t rows, int d, int64_t unit) {
-  const int nc = d / 32;
-  const int64_t r0 = unit / nc * 32;
-  const int c0 = int(unit % nc) * 32;
-  if (r0 >= rows) return;
-  const int lane = threadIdx.x & 63, hf = lane >> 5, l32 = lane & 31;
-  const int64_t qrow = r0 + l32 < rows ? r0 + l32 : rows - 1;   // rows past the end repeat the last; not stored
-  const uint16_t* q = Q + qrow * d + 8 * hf;
-  const int wrow = (l32 & 16) | ((l32 & 4) << 1) | ((l32 & 8) >> 1) | (l32 & 3);
-  const uint16_t* src[2] = {Wk + wrow * d + c0 + 8 * hf, Wv + wrow * d + c0 + 8 * hf};
-  Pack8 sel[2];
-#pragma unroll
-  for (int e = 0; e < 2; ++e)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) sel[e].h[j] = (l32 == 16 * e + 8 * hf + j) ? 0x3F80 : 0;
-  f32x16 acc[2] = {{0}, {0}};
-#pragma unroll 2
-  for (int k = 0; k < d; k += 32) {
-    float rest = 0.f;
-    Pack8 x[2], raw[2][2];
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      x[e].u = *reinterpret_cast<const uint4*>(q + k + 16 * e);
-#pragma unroll
-      for (int m = 0; m < 2; ++m) raw[m][e].u = *reinterpret_cast<const uint4*>(src[m] + k * d + 16 * e);
-    }
-#pragma unroll
-    for (int m = 0; m < 2; ++m) {
-      f32x16 t = {0};
-      t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(raw[m][0].v, sel[0].v, t, 0, 0, 0);
-      t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(raw[m][1].v, sel[1].v, t, 0, 0, 0);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) rest = dot2_zero(raw[m][e / 4].w[e % 4], rest);
-      const bool finite = __builtin_amdgcn_ballot_w64(rest != 0.f) == 0;     // (else not turned: see summarize_wave)
-#pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        Pack8 w;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) w.w[j] = cvt_pk_bf16(t[8 * e + 2 * j], t[8 * e + 2 * j + 1]);
-        if (!finite) {
-          const uint16_t* W = (m ? Wv : Wk) + int64_t(k + 16 * e + 8 * hf) * d + c0 + l32;
-#pragma unroll
-          for (int j = 0; j < 8; ++j) w.h[j] = W[j * d];
-        }
-        acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[e].v, w.v, acc[m], 0, 0, 0);
-      }
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int64_t r = r0 + acc_row0(i) + 4 * hf;
-    if (r < rows) {
-      Ks[r * d + c0 + l32] = acc[0][i];
-      Vs[r * d + c0 + l32] = acc[1][i];
-    }
   }
 }
 
@@ -1010,9 +742,9 @@ __device__ __forceinline__ void self_kv_unit(const uint16_t* __restrict__ Q, con
 // NQB query blocks to a projecting wave, NQA to one that only attends.  OCC: waves on a SIMD that the registers have to leave
 // room for, as far as the workgroups that fit the LDS can fill them (the two-wave workgroups of D = 256, S = 64 cannot, and take
 // 295 registers).
-template <int D, int NQB, int NQA, int HPW, int FW, bool WREG, bool SPLIT, int MAXT, int ATTN, int OCC, bool ORDERED>
+template <int D, int NQB, int NQA, int HPW, int FW, bool WREG, int MAXT, int ATTN, int OCC, bool ORDERED>
 __global__ __launch_bounds__(MAXT, OCC) void summarize_mfma_kernel(MfmaSummarizeParams p) {
-  __shared__ SummarizeLds<D, HPW, WREG, SPLIT> sm;
+  __shared__ SummarizeLds<D, HPW, WREG> sm;
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform, kept scalar
   const int hl = wave / p.wph;
@@ -1046,11 +778,11 @@ __global__ __launch_bounds__(MAXT, OCC) void summarize_mfma_kernel(MfmaSummarize
   }
   // All roles run the same sequence of barriers; only the MFMA operand order differs.
   if (slot == 0)
-    summarize_wave<D, NQB, HPW, FW, WREG, SPLIT, (!SPLIT && MAXT == 64 * FW), 0, ATTN, ORDERED>(p, sm, g, h, hl, 0, seg_begin, seg_end);
+    summarize_wave<D, NQB, HPW, FW, WREG, MAXT == 64 * FW, 0, ATTN, ORDERED>(p, sm, g, h, hl, 0, seg_begin, seg_end);
   else if (slot == 1)
-    summarize_wave<D, NQB, HPW, FW, WREG, SPLIT, (!SPLIT && MAXT == 64 * FW), 1, ATTN, ORDERED>(p, sm, g, h, hl, NQB, seg_begin, seg_end);
+    summarize_wave<D, NQB, HPW, FW, WREG, MAXT == 64 * FW, 1, ATTN, ORDERED>(p, sm, g, h, hl, NQB, seg_begin, seg_end);
   else if constexpr (MAXT != HPW * 128)      // (two waves per head: there is no third slot)
-    summarize_wave<D, NQA, HPW, FW, WREG, SPLIT, (!SPLIT && MAXT == 64 * FW), 2, ATTN, ORDERED>(p, sm, g, h, hl, 2 * NQB + (slot - 2) * NQA, seg_begin, seg_end);
+    summarize_wave<D, NQA, HPW, FW, WREG, MAXT == 64 * FW, 2, ATTN, ORDERED>(p, sm, g, h, hl, 2 * NQB + (slot - 2) * NQA, seg_begin, seg_end);
 }
 
 // Merge of a user's partial records in a fixed order, so the result is bitwise reproducible.
@@ -1390,13 +1122,13 @@ size_t mfma_summarize_workspace(const vista_summarize_desc& d, int seg) {
   return kHeaderBytes + plan_bytes(G) + ((partial_bytes(d, seg) + 255) & ~size_t(255)) + 2 * self_kv_bytes(d);
 }
 
-template <int D, int NQB, int HPW, int FW, bool WREG, bool SPLIT, int MAXT, int ATTN, int NQA = NQB, int OCC = MAXT / 256, bool ORDERED = false>
+template <int D, int NQB, int HPW, int FW, bool WREG, int MAXT, int ATTN, int NQA = NQB, int OCC = MAXT / 256, bool ORDERED = false>
 static hipError_t launch_main(MfmaSummarizeParams& p, int wph, int64_t G, hipStream_t s) {
   p.wph = wph;
   p.nhg = p.H / HPW;
   const int64_t groups = (G + 7) / 8;
   const int64_t blocks = groups * 8 * p.nhg;
-  return launch(summarize_mfma_kernel<D, NQB, NQA, HPW, FW, WREG, SPLIT, MAXT, ATTN, OCC, ORDERED>, dim3(unsigned(blocks)),
+  return launch(summarize_mfma_kernel<D, NQB, NQA, HPW, FW, WREG, MAXT, ATTN, OCC, ORDERED>, dim3(unsigned(blocks)),
                 dim3(HPW * wph * 64), 0, s, p);
 }
 
@@ -1413,16 +1145,16 @@ static hipError_t launch_for_shape(MfmaSummarizeParams& p, const vista_summarize
   const bool shared = p.q_user_stride == 0;
   if (half_workgroups(desc, p.seg, G)) {
     if (d == 128) {
-      if (p.nqb <= 2) return launch_main<128, 1, 2, 4, true, false, 256, ATTN, 1, 2>(p, 2, G, s);
-      if (p.nqb <= 4) return launch_main<128, 2, 2, 4, true, false, 256, ATTN, 2, 2>(p, 2, G, s);
-      if (p.nqb <= 8 && shared) return launch_main<128, 4, 2, 4, true, false, 256, ATTN, 4, 2, softmax>(p, 2, G, s);
-      if (p.nqb <= 8) return launch_main<128, 4, 2, 4, true, false, 256, ATTN, 4, 2>(p, 2, G, s);
-      return launch_main<128, 4, 1, 4, true, false, 256, ATTN, 4, 2, softmax>(p, 4, G, s);
+      if (p.nqb <= 2) return launch_main<128, 1, 2, 4, true, 256, ATTN, 1, 2>(p, 2, G, s);
+      if (p.nqb <= 4) return launch_main<128, 2, 2, 4, true, 256, ATTN, 2, 2>(p, 2, G, s);
+      if (p.nqb <= 8 && shared) return launch_main<128, 4, 2, 4, true, 256, ATTN, 4, 2, softmax>(p, 2, G, s);
+      if (p.nqb <= 8) return launch_main<128, 4, 2, 4, true, 256, ATTN, 4, 2>(p, 2, G, s);
+      return launch_main<128, 4, 1, 4, true, 256, ATTN, 4, 2, softmax>(p, 4, G, s);
     }
-    if (p.nqb <= 2) return launch_main<256, 1, 1, 2, true, false, 128, ATTN, 1, 2>(p, 2, G, s);
-    if (p.nqb <= 4) return launch_main<256, 1, 1, 4, true, false, 256, ATTN, 1, 2>(p, 4, G, s);
-    if (p.nqb <= 8) return launch_main<256, 2, 1, 4, true, false, 256, ATTN, 2, 2>(p, 4, G, s);
-    return launch_main<256, 2, 1, 4, true, false, 256, ATTN, 6, 2>(p, 4, G, s);
+    if (p.nqb <= 2) return launch_main<256, 1, 1, 2, true, 128, ATTN, 1, 2>(p, 2, G, s);
+    if (p.nqb <= 4) return launch_main<256, 1, 1, 4, true, 256, ATTN, 1, 2>(p, 4, G, s);
+    if (p.nqb <= 8) return launch_main<256, 2, 1, 4, true, 256, ATTN, 2, 2>(p, 4, G, s);
+    return launch_main<256, 2, 1, 4, true, 256, ATTN, 6, 2>(p, 4, G, s);
   }
   if (d == 128) {
     // SiLU's two transcendentals a score leave the vector unit the bound: one block a wave feeds it better than
@@ -1430,24 +1162,24 @@ static hipError_t launch_for_shape(MfmaSummarizeParams& p, const vista_summarize
     // at S = 64 eight waves hold one block each as it is).  Sixteen waves of two blocks lose to eight of four:
     // 149 -> 182 us at S = 256, 251 -> 281 at 512; at d = 256 364 -> 361 and, S = 512, 337 -> 356.
     if constexpr (ATTN == VISTA_ATTN_SILU)
-      if (p.nqb == 4) return launch_main<128, 1, 4, 8, true, false, 1024, ATTN>(p, 4, G, s);
-    if (p.nqb <= 2) return launch_main<128, 1, 4, 8, true, false, 512, ATTN>(p, 2, G, s);
-    if (p.nqb <= 4) return launch_main<128, 2, 4, 8, true, false, 512, ATTN>(p, 2, G, s);
-    if (p.nqb <= 8 && shared) return launch_main<128, 4, 4, 8, true, false, 512, ATTN, 4, 2, softmax>(p, 2, G, s);
-    if (p.nqb <= 8) return launch_main<128, 4, 4, 8, true, false, 512, ATTN>(p, 2, G, s);
-    return launch_main<128, 4, 2, 8, true, false, 512, ATTN, 4, 2, softmax>(p, 4, G, s);
+      if (p.nqb == 4) return launch_main<128, 1, 4, 8, true, 1024, ATTN>(p, 4, G, s);
+    if (p.nqb <= 2) return launch_main<128, 1, 4, 8, true, 512, ATTN>(p, 2, G, s);
+    if (p.nqb <= 4) return launch_main<128, 2, 4, 8, true, 512, ATTN>(p, 2, G, s);
+    if (p.nqb <= 8 && shared) return launch_main<128, 4, 4, 8, true, 512, ATTN, 4, 2, softmax>(p, 2, G, s);
+    if (p.nqb <= 8) return launch_main<128, 4, 4, 8, true, 512, ATTN>(p, 2, G, s);
+    return launch_main<128, 4, 2, 8, true, 512, ATTN, 4, 2, softmax>(p, 4, G, s);
   }
   // Two workgroups of four waves on a compute unit: their barriers are not in step (209 -> 167 us over 500 000 items,
   // SiLU form 143 -> 112 over 300 000; with the weights in LDS there was room for one).
-  if (p.nqb <= 2) return launch_main<256, 1, 2, 4, true, false, 256, ATTN, 1, 2>(p, 2, G, s);
-  if (p.nqb <= 4) return launch_main<256, 1, 2, 8, true, false, 512, ATTN>(p, 4, G, s);
-  if (p.nqb <= 8) return launch_main<256, 2, 2, 8, true, false, 512, ATTN>(p, 4, G, s);
+  if (p.nqb <= 2) return launch_main<256, 1, 2, 4, true, 256, ATTN, 1, 2>(p, 2, G, s);
+  if (p.nqb <= 4) return launch_main<256, 1, 2, 8, true, 512, ATTN>(p, 4, G, s);
+  if (p.nqb <= 8) return launch_main<256, 2, 2, 8, true, 512, ATTN>(p, 4, G, s);
   // At S = 512 either four blocks a wave, the weights in LDS, or 2 + 2 + 6 + 6, which leaves the projecting waves registers for
   // the weights.  Softmax: 421 -> 413 us over 500 000 items, two layers over 14 M items with the rest of the path 22.8 -> 22.35
   // ms.  SiLU keeps four each: its vector work is three times as long in a wave of six blocks as beside it (100 000 items in segments
   // of 4096 250 us against 261, 300 000 of 8192 481 against 505, 262 144 at the default 278 against 284).
   if constexpr (ATTN == VISTA_ATTN_SILU) {
-    return launch_main<256, 4, 2, 8, false, false, 512, ATTN>(p, 4, G, s);
+    return launch_main<256, 4, 2, 8, false, 512, ATTN>(p, 4, G, s);
   } else {
     // The waves of six blocks are late at every change of user, more so where they load the queries anew: 0.5 to 1 us a change
     // with shared queries, 1.5 to 3 with queries of their own, against 2 % of the call.  So short histories and short users
@@ -1456,26 +1188,9 @@ static hipError_t launch_for_shape(MfmaSummarizeParams& p, const vista_summarize
     // 96.0 / 96.2; 32 of 40 000 76.0 / 78.5, of 160 000 168 / 167; 200 of 160 000 269 / 274, of 1 280 000 1164 / 1139.
     const bool own = p.q_user_stride != 0;
     if (p.N < (own ? 65536 : 24576) || p.N < (own ? 4096 : 1024) * int64_t(p.B))
-      return launch_main<256, 4, 2, 8, false, false, 512, ATTN>(p, 4, G, s);
-    return launch_main<256, 2, 2, 8, true, false, 512, ATTN, 6>(p, 4, G, s);
+      return launch_main<256, 4, 2, 8, false, 512, ATTN>(p, 4, G, s);
+    return launch_main<256, 2, 2, 8, true, 512, ATTN, 6>(p, 4, G, s);
   }
-}
-
-static hipError_t launch_split(MfmaSummarizeParams& p, int d, int64_t G, hipStream_t s) {
-  constexpr int A = VISTA_ATTN_SOFTMAX;
-  const int w1 = p.nqb < 4 ? 4 : p.nqb, w2 = p.nqb < 3 ? 2 : (p.nqb + 1) / 2;   // waves per head at one, two query blocks
-  if (d == 64) {
-    if (p.nqb <= 2) return launch_main<64, 1, 2, 4, true, true, 512, A>(p, 2, G, s);
-    if (p.nqb <= 8) return launch_main<64, 2, 2, 4, true, true, 512, A>(p, w2, G, s);
-    return launch_main<64, 2, 1, 4, true, true, 512, A>(p, w2, G, s);
-  }
-  if (d == 128) {
-    if (p.nqb <= 2) return launch_main<128, 1, 2, 4, true, true, 512, A>(p, 2, G, s);
-    if (p.nqb <= 8) return launch_main<128, 2, 2, 4, true, true, 512, A>(p, w2, G, s);
-    return launch_main<128, 2, 1, 4, true, true, 512, A>(p, w2, G, s);
-  }
-  if (p.nqb <= 8) return launch_main<256, 1, 1, 4, true, true, 512, A>(p, w1, G, s);
-  return launch_main<256, 2, 1, 4, false, true, 512, A>(p, w2, G, s);
 }
 
 template <bool SILU, int RG>

@@ -1,5 +1,5 @@
 """GPU parity of the matrix-core path with split operands (bf16 softmax shapes outside the fixed seed
-counts): K, V and weights keep their 24 bits as three bf16 terms, so what separates a result from the
+counts): K, V and weights keep 22 bits and a sign as two fp16 terms, or are fp32, so what separates a result from the
 oracle is the rounding of the bf16 output and of fp32 sums."""
 import numpy as np
 import pytest
@@ -291,3 +291,49 @@ def test_items_at_minus_infinity_leave_the_softmax(dtype, d, H, S, rows, seg):
     want = O.summarize(np.delete(X, slice(*rows), axis=0), np.array([0, L - gone, L + 50 - gone]), Q, Wk, Wv, H)
     # at fixed bf16 operands (S of 64, 128, 256, 512) the path's own tolerance, else that of fp32 sums
     check(host64(out), want, (2e-2 if dtype == "bf16" and S in (128, 256) else 1e-4))
+
+
+def record_error(X, Q, Wk, Wv, H):
+    """One user, one segment: the largest error of a head's result before its bf16 rounding (2-norm against fp64), from the
+    partial record (registers [4][lane][4], row 8 (i / 4) + i % 4 + 4 (lane / 32), column lane % 32; then [lane][l, m])."""
+    (L, d), S = X.shape, Q.shape[0]
+    dh, nqb, seg = d // H, (S + 31) // 32, (L + 31) // 32 * 32
+    out = torch.empty((1, S, d), device="cuda", dtype=torch.bfloat16)
+    ws = V.vista_summarize(dev(X, "bf16"), torch.tensor([0, L], device="cuda"), dev(Q, "bf16"), dev(Wk, "bf16"), dev(Wv, "bf16"), out,
+                           H=H, segment_items=seg)
+    rec = ws[512:512 + H * nqb * 4608].view(torch.float32).cpu().double().numpy().reshape(H, nqb, 1152)
+    o = rec[:, :, :1024].reshape(H, nqb, 4, 2, 32, 4).transpose(0, 1, 4, 2, 3, 5).reshape(H, nqb * 32, dh)
+    got = o / rec[:, :, 1024::2].reshape(H, nqb, 2, 32)[:, :, 0].reshape(H, nqb * 32, 1)
+    heads = lambda m: (m.astype(np.float64)).reshape(-1, H, dh).transpose(1, 0, 2)
+    s = heads(Q) @ heads(X.astype(np.float64) @ Wk).transpose(0, 2, 1) * dh ** -0.5
+    w = np.exp(s - s.max(axis=2, keepdims=True))
+    want = w @ heads(X.astype(np.float64) @ Wv) / w.sum(axis=2, keepdims=True)
+    return (np.linalg.norm(got[:, :S] - want, axis=(1, 2)) / np.linalg.norm(want, axis=(1, 2))).max()
+
+
+# plain tiles, references of a row's own, fp32 for what fp16 terms do not hold (both ends), and queries beyond them
+@pytest.mark.parametrize("x,q,w", [(1, 1, 1), (1, 4, 1), (1, 16, 1), (0.02, 50, 1), (30, 0.03, 1), (1, 1, 0.01), (1e-5, 1, 1), (400, 0.003, 1),
+                                   (0.01, 80, 1), (3e4, 1e-3, 1e-3)])
+@pytest.mark.parametrize("d,H,S", [(64, 2, 33), (128, 4, 100), (256, 8, 40)])
+def test_split_keeps_fp32_precision_at_every_scale(d, H, S, x, q, w):
+    """Operands are right to 2^-23 of their size, products and sums in fp32: against scores of a hundred 2^-23 becomes 2^-17 of
+    a weight, averaged over the items that share it; 2^-19 covers all of these scales (three bf16 terms: up to 1.8e-6)."""
+    g = np.random.default_rng(S)
+    r = lambda shape, s: I.round_to((g.normal(size=shape) * s).astype(np.float32), "bf16")
+    assert record_error(r((900, d), x), r((S, d), q), r((d, d), w * d ** -0.5), r((d, d), w * d ** -0.5), H) <= 2.0 ** -19
+
+
+@pytest.mark.parametrize("d,H,S,per_user", [(64, 2, 100, False), (128, 4, 40, True), (256, 8, 300, False)])
+@pytest.mark.parametrize("seg", [0, 512])
+def test_split_histories_that_change_their_scale(d, H, S, per_user, seg):
+    """Users of very different sizes in one segment, and histories that start small and grow, so that a piece leaves the flat
+    reference and then fp16 behind, and all-negative rows: every user keeps its own tolerance."""
+    lens = [200, 330, 90, 31, 400, 64, 150]
+    X, off, Q, Wk, Wv = problem(21, d, S, per_user, lens=lens)
+    X[off[1]:off[2]] *= np.linspace(0.25, 8, lens[1])[:, None]
+    X[off[2]:off[3]] *= 2.0 ** -17
+    X[off[4]:off[5]] += 1.5 * X[off[4]]                            # a common direction: some seeds score below -10 throughout
+    X[off[5]] *= 2.0 ** 9
+    X[off[6] + 100:] *= 2.0 ** 12
+    X = I.round_to(X, "bf16")
+    check(run(X, off, Q, Wk, Wv, H, segment_items=seg), O.summarize(X, off, Q, Wk, Wv, H), 4e-3)     # (as for the running maximum)
