@@ -1028,7 +1028,7 @@ static int64_t short_limit(const vista_summarize_desc& d) {
   if (silu && d.S == 128) return 65536;
   return d.S == 256 ? 229376 : d.S == 512 ? 98304 : 131072;
 }
-static bool short_history(const vista_summarize_desc& d) {
+static bool short_history(const vista_summarize_desc& d, int64_t limit) {
   const bool silu = d.attn == VISTA_ATTN_SILU, own = d.q_user_stride != 0;
   const int64_t few = d.d == 128 ? 12288 : d.S < 256 ? 4096 : 6144;
   int64_t user;
@@ -1038,21 +1038,47 @@ static bool short_history(const vista_summarize_desc& d) {
     user = d.S == 128 ? (own ? 768 : 320) : 128;
   else
     user = d.S == 512 ? (own ? 1024 : 768) : own ? 640 : 384;
-  return d.total_items <= few || d.total_items + user * int64_t(d.B - 1) <= short_limit(d);
+  return d.total_items <= few || d.total_items + user * int64_t(d.B - 1) <= limit;
+}
+static bool short_history(const vista_summarize_desc& d) { return short_history(d, short_limit(d)); }
+
+// The shortest of these go to workgroups of one head with half the query blocks a wave (or, of one block, half the waves), in
+// segments that make one workgroup a compute unit: a tile takes half the time again, and a wave's code, which such a call walks
+// cold, is half as long.  Beyond, rows are fetched and users are changed once more for nothing, the sooner the more users there are;
+// with some way to the limit above, where halves are no better than whole ones.  us a call, halves / one head: d = 128, S = 256, one
+// user of 2000 items 16.6 / 13.9, of 7001 20.3 / 17.5, of 30 000 30.0 / 24.5, of 64 000 37 / 37; 64 users of 8000 in all 28.5 / 24.2, of 48 000
+// 36.3 / 35.6; S = 128, SiLU, one user of 15 000 19.5 / 15.6, 300 of 20 000 4 to 9 % faster, of 32 000 8 to 11 % slower; S = 64, 64 users of
+// 12 000 3 % faster, of 32 000 11 % slower; S = 512, 30 users of 60 000 52.4 / 47.1; d = 256, S = 512, one user of 7001 34.5 / 30.8, 8 of 8000 19 %
+// faster, 300 of 20 000 6 % slower.  (At d = 256 up to S = 128 a half already is one head of one block a wave.)
+static bool one_head_history(const vista_summarize_desc& d) {
+  const bool silu = d.attn == VISTA_ATTN_SILU;
+  if ((d.d == 256 && d.S < 256) || !short_history(d, short_limit(d) / 8 * 7)) return false;
+  if (d.d == 256 || d.S == 512) return true;
+  const double few = d.S == 64 ? 16384 : d.S == 128 ? (silu ? 53248 : 49152) : silu ? 40960 : 57344;
+  return double(d.total_items) <= few * (0.4 + 0.6 * 32.0 / (double(d.B) + 31.0));
 }
 
-// Head groups (workgroups per segment; half: of half the heads each) and workgroups resident on a compute unit, as launched below.
-static int head_groups(const vista_summarize_desc& d, bool half) {
+// How the heads of a segment are shared out.
+enum class Heads { kWhole, kHalf, kOne };
+
+// Head groups (workgroups per segment) and workgroups resident on a compute unit, as launched below.
+static int head_groups(const vista_summarize_desc& d, Heads heads) {
   const int nqb = (d.S + 31) / 32;
-  if (mfma_summarize_supported(d)) return (d.d == 256 ? 4 : nqb > 8 ? 2 : 1) * (half ? 2 : 1);
+  if (mfma_summarize_supported(d))
+    return heads == Heads::kOne ? d.H : (d.d == 256 ? 4 : nqb > 8 ? 2 : 1) * (heads == Heads::kHalf ? 2 : 1);
   if (d.d == 256) return 8;
   return nqb > 8 ? d.H : d.H / 2;
 }
 static int resident_workgroups(const vista_summarize_desc& d) {
   // Two fit, but two cold starts on a compute unit have to pay: a segment of 768 items for one does it with the split
   // operands (d = 64, S = 100: 60 000 items in 29.7 us with one, 33.7 with two, 200 000 in 52.5 and 51.9), 2048 at d = 256.
-  if (mfma_split_supported(d)) return d.d != 256 && d.S <= 128 && d.total_items > 768 * 256 / head_groups(d, false) ? 2 : 1;
+  if (mfma_split_supported(d)) return d.d != 256 && d.S <= 128 && d.total_items > 768 * 256 / head_groups(d, Heads::kWhole) ? 2 : 1;
   return d.d == 256 && d.S == 64 && d.total_items > 131072 ? 2 : 1;
+}
+
+static Heads fitted_heads(const vista_summarize_desc& d) {
+  if (!mfma_summarize_supported(d)) return Heads::kWhole;
+  return one_head_history(d) ? Heads::kOne : short_history(d) ? Heads::kHalf : Heads::kWhole;
 }
 
 // Segment size of the matrix-core kernels where the caller leaves it open: the history is cut so that
@@ -1064,14 +1090,14 @@ static int resident_workgroups(const vista_summarize_desc& d) {
 // at 96 and 20.8 at 128.
 int mfma_summarize_segment(const vista_summarize_desc& d) {
   const int64_t N = d.total_items;
-  const bool half = mfma_summarize_supported(d) && short_history(d);
-  const int64_t units = 256 * resident_workgroups(d) / head_groups(d, half);
+  const Heads heads = fitted_heads(d);
+  const int64_t units = 256 * resident_workgroups(d) / head_groups(d, heads);
   constexpr int64_t kMost = 32768, kLeast = 128;
   int64_t k = (N + units * kMost - 1) / (units * kMost);
   if (k < 1) k = 1;
   int64_t s = (N + units * k - 1) / (units * k);
   s = (s + 31) / 32 * 32;
-  if (half && d.d == 128 && d.S < 512) {
+  if (heads == Heads::kHalf && d.d == 128 && d.S < 512) {
     // Few workgroups: a longer segment is more tiles for each, a shorter one more records to write and merge, so the
     // best length goes with the square root: 1.5 sqrt(N), which is beyond both the least length and an even share of the
     // chip from 9200 to 28 700 items.  (15 000 items, d = 128, S = 256: 27.7 us at 128, 24.8 at 192, 24.3 at 256; 30 000: 34.4 at
@@ -1082,20 +1108,24 @@ int mfma_summarize_segment(const vista_summarize_desc& d) {
   return int(s < kLeast ? kLeast : s);
 }
 
-// Whether G segments go to workgroups of half the heads.  Segments fitted here follow short_history.  Where the caller names their
+// How the heads of G segments are shared out.  Segments fitted here follow fitted_heads; one head a workgroup is for them alone, as
+// halves hold their queries in the waves that whole workgroups do and so leave the score bound at the same tiles.  Where the caller names their
 // size, or the workspace leaves the base schedule, both kinds walk the same tiles of the same users, and halves win while each has
 // a compute unit.  At d = 128 two of them share one, and in a short history nothing is lost beyond (a user is a record and a ragged tile
 // of it, 128 items).  Half / whole, mean over 1 to 200 users and segments of 64 to 4096 items: softmax, d = 128, S = 256, 60 halves 0.73, 240
 // 0.75, 500 0.95; S = 512, 120 0.77, 240 0.80; S = 128 in segments of 8192, 260 1.06; d = 256, S = 256, 64 halves 0.83, 240 0.86, 480 1.05; S = 512
 // 0.82, 0.86, 1.02.  At d = 256 up to 288 are well in segments of up to 256 (0.84 to 0.99), 1.1 to 1.2 in longer ones; S = 64 is 0.99 for 240,
 // 1.04 in long segments.
-static bool half_workgroups(const vista_summarize_desc& d, int seg, int64_t G) {
-  if (!mfma_summarize_supported(d)) return false;
-  if (seg == mfma_summarize_segment(d)) return short_history(d);
+static Heads heads_of_workgroups(const vista_summarize_desc& d, int seg, int64_t G) {
+  if (!mfma_summarize_supported(d)) return Heads::kWhole;
+  if (seg == mfma_summarize_segment(d)) {
+    const Heads heads = fitted_heads(d);
+    return heads == Heads::kOne && d.segment_items > 0 ? Heads::kHalf : heads;
+  }
   const bool few = d.total_items + 128 * int64_t(d.B) <= short_limit(d);
-  const int64_t halves = G * head_groups(d, true);
-  if (d.d == 128) return few || halves <= 256;
-  return few ? halves <= 288 : halves <= 256 && d.S != 64;
+  const int64_t halves = G * head_groups(d, Heads::kHalf);
+  const bool half = d.d == 128 ? few || halves <= 256 : few ? halves <= 288 : halves <= 256 && d.S != 64;
+  return half ? Heads::kHalf : Heads::kWhole;
 }
 
 // Whether the seeds' own keys and values are formed beside the history.  With workgroups on nearly every compute unit the
@@ -1107,7 +1137,7 @@ static bool half_workgroups(const vista_summarize_desc& d, int seg, int64_t G) {
 // users (32) 47.5 / 67.9.  Split operands: d = 64, S = 100, 63 workgroups, 32 users (3) 35.4 / 31.8; 250, 128 users (3) 43.6 / 38.7;
 // d = 256, S = 200, 256, 32 users (6) 103.2 / 95.5.  Of 1152 calls five take the kernel in front where beside is 5 to 13 % faster.
 static bool self_beside_history(const vista_summarize_desc& d, int seg, int64_t G, int64_t rows) {
-  const int64_t units = (rows + 31) / 32 * (d.d / 32), groups = G * head_groups(d, half_workgroups(d, seg, G));
+  const int64_t units = (rows + 31) / 32 * (d.d / 32), groups = G * head_groups(d, heads_of_workgroups(d, seg, G));
   return units <= (groups >= 240 ? 64 : 4) * groups;
 }
 
@@ -1143,7 +1173,18 @@ static hipError_t launch_for_shape(MfmaSummarizeParams& p, const vista_summarize
   // products or attends without projecting.  The SiLU form and the split operands have no such tile.
   constexpr bool softmax = ATTN == VISTA_ATTN_SOFTMAX;
   const bool shared = p.q_user_stride == 0;
-  if (half_workgroups(desc, p.seg, G)) {
+  const Heads heads = heads_of_workgroups(desc, p.seg, G);
+  if (heads == Heads::kOne) {
+    if (d == 128) {
+      if (p.nqb <= 2) return launch_main<128, 1, 1, 2, true, 128, ATTN, 1, 2>(p, 2, G, s);
+      if (p.nqb <= 4) return launch_main<128, 1, 1, 4, true, 256, ATTN, 1, 2>(p, 4, G, s);
+      if (p.nqb <= 8) return launch_main<128, 2, 1, 4, true, 256, ATTN, 2, 2>(p, 4, G, s);
+      return launch_main<128, 2, 1, 8, true, 512, ATTN, 2, 2>(p, 8, G, s);
+    }
+    if (p.nqb <= 8) return launch_main<256, 1, 1, 8, true, 512, ATTN, 1, 2>(p, 8, G, s);
+    return launch_main<256, 2, 1, 8, true, 512, ATTN, 2, 2>(p, 8, G, s);
+  }
+  if (heads == Heads::kHalf) {
     if (d == 128) {
       if (p.nqb <= 2) return launch_main<128, 1, 2, 4, true, 256, ATTN, 1, 2>(p, 2, G, s);
       if (p.nqb <= 4) return launch_main<128, 2, 2, 4, true, 256, ATTN, 2, 2>(p, 2, G, s);

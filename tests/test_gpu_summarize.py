@@ -370,3 +370,28 @@ def test_whole_workgroups_on_the_edges(form, d, H, S, edge):
         # the 10^6 there are; between two items of equal weight and opposite value that is 0.25 x 0.03 x 2 of the largest value
         slack = 0.015 if edge == "mixed" and not silu else 0.0
         assert np.all(np.isfinite(among)) and block_errors(among, want).max() <= 2e-2 + slack, f"{form} d={d} S={S} {edge}"
+
+
+@pytest.mark.parametrize("form,d,H,S", [(f, *s) for f in ("softmax", "silu") for s in ((128, 4, 64), (128, 4, 128), (128, 4, 256), (128, 4, 512),
+                                                                                          (256, 8, 256), (256, 8, 512))])
+@pytest.mark.parametrize("edge", ["shared", "own", "self", "mixed"])
+def test_workgroups_of_one_head(form, d, H, S, edge):
+    """Short histories whose segment size is left open take one head a workgroup, a named size halves: both right by the
+    oracle, and where no score leaves the bound (or the form has none) the same bits in segments of the same size.  Ragged users, runs
+    of empty ones, a single item, users that end on tiles and segments."""
+    lens = [1, 0, 0, 33, 128, 700, 31, 1027, 64, 95] + [9, 0, 4] * 5
+    silu = form == "silu"
+    X, off, Q, Wk, Wv = problem(70 + S, lens, d, S, per_user=edge == "own")
+    if edge == "mixed":
+        X[40:300] = bf(X[40:300] * 4.8)    # |q| |k| up to 68 on both sides of 60; bf16 keys cost 2^-9 of a score, up to 0.017 of the block here
+    attn = V.VISTA_ATTN_SILU if silu else V.VISTA_ATTN_SOFTMAX
+    kw = dict(attn=attn, self_term=edge == "self")
+    fitted = V.vista_summarize_call_segment_items(V.summarize_desc(len(lens), S, d, H, V.VISTA_BF16, int(off[-1]), edge == "own", attn=attn,
+                                                                   self_term=edge == "self"))
+    got, halves = run(X, off, Q, Wk, Wv, H, **kw), run(X, off, Q, Wk, Wv, H, segment_items=fitted, **kw)
+    want = (O.summarize_silu if silu else O.summarize)(X, off, Q, Wk, Wv, H, self_term=edge == "self")
+    assert_blocks_close(got, want, "bf16", f"one head, {form} d={d} S={S} {edge}")
+    assert_blocks_close(halves, want, "bf16", f"halves, {form} d={d} S={S} {edge}")
+    assert all(np.all(got[b] == 0) for b in range(len(lens)) if lens[b] == 0)
+    if silu or edge != "mixed":
+        assert np.array_equal(got, halves)
