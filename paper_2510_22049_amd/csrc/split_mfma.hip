@@ -12,8 +12,9 @@
 // the terms where fp16 has its bits.  Keys or values that it does not hold (too large, infinite, NaN, or so small
 // that the second term is lost) are handed over as fp32, and the rest of that user's piece is computed in fp32.
 // Three bf16 terms an operand (24 bits) took three and six products and twice the vector instructions a
-// split: 48 users, 300 007 items, d = 64, S = 100 66.2 -> 55.2 us a call, 1 200 028 items 202 -> 154, d = 256 1104 -> 836,
-// d = 256, S = 500 2783 -> 2007.  Error of the result before its bf16 rounding against fp64 (2-norm; d = 64 to 256, one user
+// split: 48 users, 300 007 items, d = 64, S = 100 66.2 -> 55.2 us a call (one head a workgroup 51.9), 1 200 028 items 202 -> 154,
+// d = 256 1104 -> 836, d = 256, S = 500 2783 -> 2007; a piece's first tile, which takes its reference, costs more than before: many users of
+// some 80 to 180 items at d = 256 2 to 4 %.  Error of the result before its bf16 rounding against fp64 (2-norm; d = 64 to 256, one user
 // of 700 and of 3001 items, scores up to 6 / 25 / 100): 2.7-3.4 and 5.3-5.7 / 3.9-4.9 and 5.5-6.8 / 5.3-8.0 and 5.7-9.3 e-7; three bf16
 // terms 3.6-4.4 and 6.3-7.1 / 6.6-7.1 and 10-18 / 11-14 and 10-15 e-7.  (Two bf16 terms, 16 bits, were ten times that.)
 // What such a wave spends its time on is vector issue: a product keeps the matrix pipe for 32 clocks, in which some
@@ -249,7 +250,7 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
     if constexpr (ROLE == 1) {
       float part[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
+      for (int ks = 0; ks < KS; ks += KS / 4) {        // (64 rows of them: a power of two is all that is wanted)
         Pack8 w;
         if constexpr (WREG) w.v = wreg[ks]; else w.u = sm.wop[((hl * 2 + WR) * KS + ks) * 64 + lane];
 #pragma unroll
@@ -259,8 +260,9 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
       n2 += __shfl_xor(n2, 32, 64);
       const int e = (int(__float_as_uint(n2) >> 23) - 127) >> 1;       // floor of log2 of the norm
       const bool usual = n2 >= 8.6361686e-37f && n2 <= 1.1579209e36f;   // about 2^-120 .. 2^120; no column of zeros, nothing infinite or NaN
-      vscale = usual ? __uint_as_float(uint32_t(127 + 7 - e) << 23) : 1.f;
-      if (hf == 0) reinterpret_cast<float*>(sm.vunit[hl])[l32] = usual ? __uint_as_float(uint32_t(127 - 7 + e) << 23) : 1.f;
+      constexpr int kNorm = D == 64 ? 7 : 6;       // (the rest of the rows make it 1.4, 2 times as large)
+      vscale = usual ? __uint_as_float(uint32_t(127 + kNorm - e) << 23) : 1.f;
+      if (hf == 0) reinterpret_cast<float*>(sm.vunit[hl])[l32] = usual ? __uint_as_float(uint32_t(127 - kNorm + e) << 23) : 1.f;
     }
   };
 
@@ -387,13 +389,13 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
   auto publish_pairs = [&](int buf, const f32x16& acc, Operand& r, float n2) __attribute__((always_inline)) {
     if constexpr (PROJ) {
       bool raw = __builtin_amdgcn_ballot_w64(!(n2 <= kHalfMost2)) != 0;
-      if (ROLE == 1 && __builtin_amdgcn_ballot_w64(n2 < kValueLeast2)) {      // (nothing but zeros is well kept)
+      if (ROLE == 1 && __builtin_expect(__builtin_amdgcn_ballot_w64(n2 < kValueLeast2) != 0, 0)) {      // (nothing but zeros is well kept)
         float any = 0.f;
 #pragma unroll
         for (int i = 0; i < 16; ++i) any = fmaxf(any, fabsf(acc[i]));
         raw = raw || __builtin_amdgcn_ballot_w64(n2 < kValueLeast2 && any > 0.f) != 0;
       }
-      if (raw) {         // fp32 as it is, four registers where a term's half would be
+      if (__builtin_expect(raw, 0)) {         // fp32 as it is, four registers where a term's half would be
 #pragma unroll
         for (int i = 0; i < 16; ++i)
           (i < 8 ? r.hi[i / 4] : r.lo[(i / 4) & 1]).w[i % 4] = __float_as_uint(ROLE ? acc[i] : acc[i] * p.c);
@@ -565,11 +567,11 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
     const Slots at = slots(r);
     const int nvl = nvalid - 4 * hf;
     const bool raw_keys = __builtin_amdgcn_ballot_w64(kn2 == INFINITY) != 0, raw_values = __builtin_amdgcn_ballot_w64(vraw > 0.f) != 0;
-    if (mode != 2 && (raw_keys || raw_values || wide_queries)) {
+    if (__builtin_expect(mode != 2 && (raw_keys || raw_values || wide_queries), 0)) {
       scale_values();
       mode = 2;
     }
-    if (mode == 2) {
+    if (__builtin_expect(mode == 2, 0)) {
       const float unit = reinterpret_cast<const float*>(sm.vunit[hl])[l32];
 #pragma unroll
       for (int qb = 0; qb < NQB; ++qb) {
@@ -591,19 +593,22 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
           for (int i = 0; i < 16; ++i)
             if (acc_row0(i) >= nvl) sc[qb][i] = -INFINITY;
       }
+      bool moved = false;
+      if (mode == 0 || unsafe) {           // (the ragged end of a piece with a reference is within it)
 #pragma unroll
-      for (int qb = 0; qb < NQB; ++qb) {
-        float t[2] = {sc[qb][0], sc[qb][1]};
+        for (int qb = 0; qb < NQB; ++qb) {
+          float t[2] = {sc[qb][0], sc[qb][1]};
 #pragma unroll
-        for (int i = 2; i < 16; ++i) t[i & 1] = fmaxf(t[i & 1], sc[qb][i]);
-        top[qb] = fmaxf(t[0], t[1]);
+          for (int i = 2; i < 16; ++i) t[i & 1] = fmaxf(t[i & 1], sc[qb][i]);
+          top[qb] = fmaxf(t[0], t[1]);
+        }
+#pragma unroll
+        for (int qb = 0; qb < NQB; ++qb) {
+          top[qb] = fmaxf(top[qb], __shfl_xor(top[qb], 32, 64));
+          raise |= top[qb] - m[qb] > kTopWeight;
+        }
+        moved = __builtin_amdgcn_ballot_w64(raise) != 0;
       }
-#pragma unroll
-      for (int qb = 0; qb < NQB; ++qb) {
-        top[qb] = fmaxf(top[qb], __shfl_xor(top[qb], 32, 64));
-        raise |= top[qb] - m[qb] > kTopWeight;
-      }
-      const bool moved = __builtin_amdgcn_ballot_w64(raise) != 0;
       if (moved) {
         bool low = !(qmax2 * kn2 <= kFlatScore * kFlatScore);
 #pragma unroll
@@ -793,9 +798,9 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
 }
 
 
-// NQB query blocks a wave; the first FW waves fetch X.
+// NQB query blocks a wave; the first FW waves fetch X.  At d = 64 a wave of one block has 168 registers, so that three fit a SIMD.
 template <int D, int NQB, int HPW, int FW, bool WREG>
-__global__ __launch_bounds__(512, 2) void split_mfma_kernel(MfmaSummarizeParams p) {
+__global__ __launch_bounds__(512, D == 64 && NQB == 1 ? 3 : 2) void split_mfma_kernel(MfmaSummarizeParams p) {
   __shared__ SplitLds<D, HPW, WREG> sm;
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform, kept scalar
@@ -841,8 +846,13 @@ hipError_t launch_kernel(MfmaSummarizeParams& p, int wph, int64_t G, hipStream_t
 
 }  // namespace
 
-hipError_t launch_split(MfmaSummarizeParams& p, int d, int64_t G, hipStream_t s) {
+hipError_t launch_split(MfmaSummarizeParams& p, int d, bool one_head, int64_t G, hipStream_t s) {
   const int w1 = p.nqb < 4 ? 4 : p.nqb, w2 = p.nqb < 3 ? 2 : (p.nqb + 1) / 2;   // waves per head at one, two query blocks
+  if (one_head) {
+    const int w = p.nqb < 2 ? 2 : p.nqb;
+    if (d == 64) return w < 4 ? launch_kernel<64, 1, 1, 2, true>(p, w, G, s) : launch_kernel<64, 1, 1, 4, true>(p, w, G, s);
+    return w < 4 ? launch_kernel<128, 1, 1, 2, true>(p, w, G, s) : launch_kernel<128, 1, 1, 4, true>(p, w, G, s);
+  }
   if (d == 64) {
     if (p.nqb <= 2) return launch_kernel<64, 1, 2, 4, true>(p, 2, G, s);
     if (p.nqb <= 8) return launch_kernel<64, 2, 2, 4, true>(p, w2, G, s);

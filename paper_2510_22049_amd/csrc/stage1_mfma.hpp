@@ -150,7 +150,7 @@ __device__ __forceinline__ void self_kv_unit(const uint16_t* __restrict__ Q, con
   }
 }
 
-// The kernels of the shapes whose operands are kept whole (split_mfma.hip).
-hipError_t launch_split(MfmaSummarizeParams& p, int d, int64_t G, hipStream_t s);
+// The kernels of the shapes whose operands are kept whole (split_mfma.hip); one_head: a head a workgroup (d = 64, 128, S <= 256).
+hipError_t launch_split(MfmaSummarizeParams& p, int d, bool one_head, int64_t G, hipStream_t s);
 
 }  // namespace vista

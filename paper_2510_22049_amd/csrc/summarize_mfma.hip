@@ -1064,19 +1064,41 @@ enum class Heads { kWhole, kHalf, kOne };
 // Head groups (workgroups per segment) and workgroups resident on a compute unit, as launched below.
 static int head_groups(const vista_summarize_desc& d, Heads heads) {
   const int nqb = (d.S + 31) / 32;
+  if (heads == Heads::kOne) return d.H;
   if (mfma_summarize_supported(d))
-    return heads == Heads::kOne ? d.H : (d.d == 256 ? 4 : nqb > 8 ? 2 : 1) * (heads == Heads::kHalf ? 2 : 1);
+    return (d.d == 256 ? 4 : nqb > 8 ? 2 : 1) * (heads == Heads::kHalf ? 2 : 1);
   if (d.d == 256) return 8;
   return nqb > 8 ? d.H : d.H / 2;
 }
-static int resident_workgroups(const vista_summarize_desc& d) {
+static int resident_workgroups(const vista_summarize_desc& d, Heads heads) {
+  // One head, split operands: another one shares the compute unit where its segment would be longer than 512 items, a third (d = 64, waves
+  // of 168 registers) than 800; eight waves have it to themselves (d = 64, S = 100, 48 users of 300 007 items 54.6 us with two, 52.4 with three;
+  // S = 200 in segments of 1216 84, of 2368 81; d = 128, S = 100, 60 000 items in segments of 512 33.7, of 1024 36).
+  if (heads == Heads::kOne && mfma_split_supported(d)) {
+    const int64_t alone = d.total_items * d.H / 256;
+    return d.S > 128 || alone <= 512 ? 1 : d.d == 64 && alone > 1600 ? 3 : 2;
+  }
   // Two fit, but two cold starts on a compute unit have to pay: a segment of 768 items for one does it with the split
   // operands (d = 64, S = 100: 60 000 items in 29.7 us with one, 33.7 with two, 200 000 in 52.5 and 51.9), 2048 at d = 256.
   if (mfma_split_supported(d)) return d.d != 256 && d.S <= 128 && d.total_items > 768 * 256 / head_groups(d, Heads::kWhole) ? 2 : 1;
   return d.d == 256 && d.S == 64 && d.total_items > 131072 ? 2 : 1;
 }
 
+// Split operands: one head a workgroup and one block a wave, three to eight waves, beside two heads and two blocks.  us a call, two
+// heads / one: d = 64, S = 100, one user of 7001 items 18.4 / 14.9, 30 users of 3000 27.0 / 18.2, 48 of 300 007 55 to 60 / 52.4, of 600 000
+// 87 / 83 to 89; S = 200, 30 of 15 000 30.8 / 24.7, 48 of 200 000 67.7 / 62.6, of 600 000 136 / 153; d = 128, S = 100, one of 15 000 25.0 / 20.4, 48 of
+// 200 000 75.3 / 72.2, of 600 000 163 / 179; S = 250, 30 of 7001 34.0 / 25.0, of 60 000 55.0 / 49.9, of 120 000 76 / 86.  One and two blocks in all
+// make two waves, which is worth it in short histories: d = 64, S = 20, one of 15 000 16.4 / 15.8, 30 of 30 000 18.1 / 18.4; d = 128, S = 40, 30 of
+// 7001 23.0 / 20.9, of 15 000 21.4 / 22.2.
+static bool one_head_split(const vista_summarize_desc& d) {
+  const int64_t nqb = (d.S + 31) / 32, N = d.total_items;
+  if (d.d == 256 || nqb > 8) return false;
+  if (nqb <= 2) return N <= (d.d == 64 ? 16384 : 8192);
+  return d.d == 64 ? N * nqb <= 2200000 : N * (nqb < 4 ? 16 : nqb * nqb) <= 3800000;
+}
+
 static Heads fitted_heads(const vista_summarize_desc& d) {
+  if (mfma_split_supported(d)) return one_head_split(d) ? Heads::kOne : Heads::kWhole;
   if (!mfma_summarize_supported(d)) return Heads::kWhole;
   return one_head_history(d) ? Heads::kOne : short_history(d) ? Heads::kHalf : Heads::kWhole;
 }
@@ -1091,7 +1113,7 @@ static Heads fitted_heads(const vista_summarize_desc& d) {
 int mfma_summarize_segment(const vista_summarize_desc& d) {
   const int64_t N = d.total_items;
   const Heads heads = fitted_heads(d);
-  const int64_t units = 256 * resident_workgroups(d) / head_groups(d, heads);
+  const int64_t units = 256 * resident_workgroups(d, heads) / head_groups(d, heads);
   constexpr int64_t kMost = 32768, kLeast = 128;
   int64_t k = (N + units * kMost - 1) / (units * kMost);
   if (k < 1) k = 1;
@@ -1117,6 +1139,7 @@ int mfma_summarize_segment(const vista_summarize_desc& d) {
 // 0.82, 0.86, 1.02.  At d = 256 up to 288 are well in segments of up to 256 (0.84 to 0.99), 1.1 to 1.2 in longer ones; S = 64 is 0.99 for 240,
 // 1.04 in long segments.
 static Heads heads_of_workgroups(const vista_summarize_desc& d, int seg, int64_t G) {
+  if (mfma_split_supported(d)) return d.segment_items == 0 && seg == mfma_summarize_segment(d) ? fitted_heads(d) : Heads::kWhole;
   if (!mfma_summarize_supported(d)) return Heads::kWhole;
   if (seg == mfma_summarize_segment(d)) {
     const Heads heads = fitted_heads(d);
@@ -1281,7 +1304,7 @@ vista_status mfma_summarize(const SummarizeArgs& a) {
   const int64_t merge_blocks = int64_t(d.B) * d.H * p.nqb;
   if ((a.G + 7) / 8 * 8 * 8 > 0x7FFFFFFF || merge_blocks > 0x7FFFFFFF) return VISTA_ERR_UNSUPPORTED;
   if (a.G > 0) {
-    const hipError_t e = mfma_split_supported(d) ? launch_split(p, d.d, a.G, a.stream)
+    const hipError_t e = mfma_split_supported(d) ? launch_split(p, d.d, heads_of_workgroups(d, a.seg, a.G) == Heads::kOne, a.G, a.stream)
                          : silu          ? launch_for_shape<VISTA_ATTN_SILU>(p, d, a.G, a.stream)
                                          : launch_for_shape<VISTA_ATTN_SOFTMAX>(p, d, a.G, a.stream);
     if (e != hipSuccess) return VISTA_ERR_HIP;

@@ -337,3 +337,23 @@ def test_split_histories_that_change_their_scale(d, H, S, per_user, seg):
     X[off[6] + 100:] *= 2.0 ** 12
     X = I.round_to(X, "bf16")
     check(run(X, off, Q, Wk, Wv, H, segment_items=seg), O.summarize(X, off, Q, Wk, Wv, H), 4e-3)     # (as for the running maximum)
+
+
+@pytest.mark.parametrize("d,H,S,limit", [(64, 2, 40, 16384), (64, 2, 256, 275000), (128, 4, 33, 8192), (128, 4, 96, 237500), (128, 4, 250, 59375)])
+@pytest.mark.parametrize("beyond", [0, 1])
+@pytest.mark.parametrize("self_term", [False, True])
+def test_both_sides_of_one_head_a_workgroup(d, H, S, limit, beyond, self_term):
+    """Up to these many items a split call takes workgroups of one head, beyond of two: ragged users, one without items, and
+    the same again in segments of a named size, which keep two heads.  (The longest user by its first eight queries.)"""
+    lens = [1, 0, 33, 700, 64]
+    lens.insert(3, limit + beyond - sum(lens))
+    X, off, Q, Wk, Wv = problem(31, d, S, lens=lens)
+    got = run(X, off, Q, Wk, Wv, H, self_term=self_term)
+    assert np.all(got[1] == 0)
+    few = [0, 2, 4, 5]
+    Xs = np.concatenate([X[off[b]:off[b + 1]] for b in few])
+    check(got[few], O.summarize(Xs, I.offsets_from_lengths([lens[b] for b in few]), Q, Wk, Wv, H, self_term=self_term), 1e-4)
+    check(got[3:4, :8], O.summarize(X[off[3]:off[4]], np.array([0, lens[3]]), Q[:8], Wk, Wv, H, self_term=self_term), 1e-4)
+    named = run(X, off, Q, Wk, Wv, H, self_term=self_term, segment_items=2048)
+    top = np.abs(got).reshape(6, -1).max(axis=1)[:, None, None]
+    assert np.all(np.abs(got - named) <= 2.0 ** -7 * np.abs(got) + 1e-5 * top)      # at most the next bf16 number
