@@ -99,3 +99,28 @@ def test_users_are_isolated(dtype, form):
     after = run()
     for b in (0, 2, 4):
         assert np.array_equal(before[b], after[b])
+
+
+@pytest.mark.parametrize("H,d,S", [(1, 64, 16), (1, 64, 64), (2, 128, 33), (4, 64, 49), (3, 144, 17)])
+@pytest.mark.parametrize("form,dtype", [("softmax", "f32"), ("silu", "f32"), ("softmax", "bf16")])
+@pytest.mark.parametrize("lens", [[1], [16], [31], [1024], LENS, [8, 8, 8, 8, 24, 200, 15, 17]])
+def test_segments_of_32_items(H, d, S, form, dtype, lens):
+    """The smallest calls: eight waves a workgroup, two for the same queries, whose halves of a tile may hold different users,
+    none of a user's items or a single one.  An infinite row of one user leaves the others their bits."""
+    r = draw(S + len(lens), dtype)
+    off, B, silu = I.offsets_from_lengths(lens), len(lens), form == "silu"
+    X, Q, Wk, Wv = r((off[-1], d)), r((S, d)), r((d, d), d ** -0.5), r((d, d), d ** -0.5)
+    attn = V.VISTA_ATTN_SILU if silu else V.VISTA_ATTN_SOFTMAX
+
+    def call(X):
+        out = torch.full((B, S, d), float("nan"), device="cuda", dtype=torch_dtype(dtype))
+        V.vista_summarize(dev(X, dtype), torch.from_numpy(off).cuda(), dev(Q, dtype), dev(Wk, dtype), dev(Wv, dtype), out, H=H, segment_items=32, attn=attn)
+        return host64(out)
+
+    got = call(X)
+    check(got, (O.summarize_silu if silu else O.summarize)(X, off, Q, Wk, Wv, H), dtype)
+    if B > 1:
+        bad = int(np.argmax(lens))
+        X[off[bad]:off[bad + 1]] = np.inf
+        after, rest = call(X), np.arange(B) != bad
+        assert np.array_equal(after[rest], got[rest])
