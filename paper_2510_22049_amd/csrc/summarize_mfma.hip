@@ -1001,7 +1001,7 @@ bool mfma_summarize_supported(const vista_summarize_desc& d) {
 }
 
 // The other bf16 softmax shapes of the same head width: any seed count, K, V and weights as split
-// operands (three bf16 terms, 24 bits).
+// operands (split_mfma.hip).
 bool mfma_split_supported(const vista_summarize_desc& d) {
   if (d.dtype != VISTA_BF16 || d.attn != VISTA_ATTN_SOFTMAX || mfma_summarize_supported(d)) return false;
   return (d.d == 64 && d.H == 2) || (d.d == 128 && d.H == 4) || (d.d == 256 && d.H == 8);
