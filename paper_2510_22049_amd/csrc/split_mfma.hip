@@ -614,7 +614,7 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
 #pragma unroll
         for (int qb = 0; qb < NQB; ++qb) low |= top[qb] < 0.f;
         const bool flat = mode == 0 && __builtin_amdgcn_ballot_w64(low) == 0;
-        safe2 = flat ? kFlatScore * kFlatScore / qmax2 : -1.f;         // (no queries but zeros: infinite, and raw values still are not below)
+        safe2 = flat ? fminf(kFlatScore * kFlatScore / qmax2, 1e30f) : -1.f;     // (finite also for queries of zeros: raw tiles are not below it)
 #pragma unroll
         for (int qb = 0; qb < NQB; ++qb) {
           const float mq = flat ? kFlat : top[qb] - m[qb] > kTopWeight ? top[qb] - kBestWeight : m[qb];

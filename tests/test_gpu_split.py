@@ -357,3 +357,13 @@ def test_both_sides_of_one_head_a_workgroup(d, H, S, limit, beyond, self_term):
     named = run(X, off, Q, Wk, Wv, H, self_term=self_term, segment_items=2048)
     top = np.abs(got).reshape(6, -1).max(axis=1)[:, None, None]
     assert np.all(np.abs(got - named) <= 2.0 ** -7 * np.abs(got) + 1e-5 * top)      # at most the next bf16 number
+
+
+@pytest.mark.parametrize("d,H", [(64, 2), (128, 4), (256, 8)])
+@pytest.mark.parametrize("seg", [0, 256])
+def test_split_queries_of_zeros_beside_values_that_fp16_does_not_hold(d, H, seg):
+    """No score leaves any bound, whatever the keys: tiles handed over as fp32 are still not taken for fp16 terms."""
+    X, off, Q, Wk, Wv = problem(41, d, 40, lens=[300, 128])
+    X[70:75] *= 2.0 ** 20
+    Q[:] = 0.0
+    check(run(X, off, Q, Wk, Wv, H, segment_items=seg), O.summarize(X, off, Q, Wk, Wv, H), 1e-4)
