@@ -179,7 +179,8 @@ size_t vista_summarize_workspace_bytes(const vista_summarize_desc* desc);
  *
  * Supported: bf16 with (d, H) = (128, 4) or (256, 8), S in {64, 128, 256, 512} (MFMA path);
  * bf16 softmax with (d, H) = (64, 2), (128, 4) or (256, 8) and any other S (MFMA path whose K, V
- * and weights are two fp16 terms, 22 bits and a sign, or fp32 where these do not hold them; history 16-byte, queries and out 8-byte aligned, else the
+ * and weights are two fp16 terms, 22 bits and a sign, with a user's items of a segment formed again in fp32 where these leave too little of
+ * a row; history 16-byte, queries and out 8-byte aligned, else the
  * plain path); any dtype with d/H <= 64, d <= 512, S <= 512 (softmax and SiLU at a head width that is
  * a multiple of 16 on the fp32 matrix instructions, tensors aligned to four elements; else the plain
  * path, one thread per query).

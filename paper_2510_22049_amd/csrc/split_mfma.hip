@@ -8,15 +8,20 @@
 // The fixed seed counts keep K, V and the softmax weights as bf16 operands.  Any other seed
 // count (and d = 64) keeps them whole, as one thread per query on the vector unit did before: each is
 // two fp16 terms, 22 bits and a sign.  Scores take two products (the seeds are bf16, one fp16 term), P V
-// three, the scale is applied to the fp32 keys, and a power of two per channel and per kind of operand puts
-// the terms where fp16 has its bits.  Keys or values that it does not hold (too large, infinite, NaN, or so small
-// that the second term is lost) are handed over as fp32, and the rest of that user's piece is computed in fp32.
-// Three bf16 terms an operand (24 bits) took three and six products and twice the vector instructions a
-// split: 48 users, 300 007 items, d = 64, S = 100 66.2 -> 55.2 us a call (one head a workgroup 51.9), 1 200 028 items 202 -> 154,
-// d = 256 1104 -> 836, d = 256, S = 500 2783 -> 2007; a piece's first tile, which takes its reference, costs more than before: many users of
-// some 80 to 180 items at d = 256 2 to 4 %.  Error of the result before its bf16 rounding against fp64 (2-norm; d = 64 to 256, one user
-// of 700 and of 3001 items, scores up to 6 / 25 / 100): 2.7-3.4 and 5.3-5.7 / 3.9-4.9 and 5.5-6.8 / 5.3-8.0 and 5.7-9.3 e-7; three bf16
-// terms 3.6-4.4 and 6.3-7.1 / 6.6-7.1 and 10-18 / 11-14 and 10-15 e-7.  (Two bf16 terms, 16 bits, were ten times that.)
+// three, the scale is applied to the fp32 keys.  fp16 has these bits from 2^-3 to 2^16 only, so everything is brought there by powers of two, which
+// change no bit: queries and keys by a unit of the seeds, values by their column of W_v and by the first tile of a user's piece, weights by
+// a whole-number reference of each row's own, which is one more product (ones times -m).  That is 19 binary places, and a row may need
+// others: its items of large weight may have no value, its own values may be small beside its neighbours'.  So what the terms leave of a row at most
+// is held against what the row came to when a piece ends, and a piece with a row that is not known to 2^-19 by that, with keys, values or queries outside fp16,
+// infinite or NaN, is formed again in fp32 (pieces_in_fp32), by the wave that found it.
+// us a call, 48 users, 300 007 items, d = 64, S = 100, three bf16 terms / two fp16 terms: unit scale 66.2 / 56.1, items 0.7 of whose variance is common to a user
+// 66.1 / 56.1, seeds 3 times as large 76.8 / 59.2, items 300 times, seeds 1 / 300 66.1 / 55.9; 1 200 028 items 199 / 150, d = 256 1102 / 845, d = 256, S = 500
+// 2706 / 2066.  Users of some 80 to 180 items at d = 256, S = 100 to 200 are 4 to 8 % slower, 101 / 109 and 87 / 91: the check, and every other tile a ragged one.  A reference that all rows
+// share (2^-4, scores up to 19.75 and every row's best on the first tile not below 0, else tile by tile with a look for the maximum) was 53.2 at unit scale, 65.4 and
+// 67.9 in the second and third call, and gave rows wrong by 33 % where an item without a value scored 19 above the others.
+// Error of the result before its bf16 rounding against fp64 (2-norm; d = 64 to 256, one user
+// of 700 and of 3001 items, scores up to 6 / 25 / 100): 3.0-3.7 and 5.2-5.7 / 3.8-5.2 and 5.6-7.3 / 5.3-8.9 and 7.2-9.8 e-7; three bf16
+// terms 3.7-4.3 and 6.3-7.6 / 5.8-8.1 and 9.7-14 / 8.0-14 and 12-16 e-7.  (Two bf16 terms, 16 bits, were ten times that.)
 // What such a wave spends its time on is vector issue: a product keeps the matrix pipe for 32 clocks, in which some
 // six plain vector instructions or three exponentials go beside it, so a tile stands in an order that pairs them.
 #include "stage1_mfma.hpp"
@@ -28,19 +33,20 @@ typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
 
 namespace {
 
-constexpr int kTile = kTileItems;    // items per tile
-// Keys are published 8 times as large, queries divided by that: at unit scale both sit where fp16 has all their bits.
-constexpr float kKeyUnit = 8.f;
 constexpr float kHalfMost2 = 4.29e9f;            // 65 500^2: squared sums below keep every term finite in fp16
-constexpr float kValueLeast2 = 9.765625e-4f;     // (2^-5)^2: half a column of values below has its second terms among fp16's coarse subnormals
-constexpr float kQueryMost2 = 4096.f;            // (2^6)^2, of a query so divided, beyond which it is taken in fp32: a key's last bit, 2^-25, times it stays below 2^-19
-// Weights are 2^(s - m).  fp16 ends at 2^16 and has its 22 bits (two terms) down to 2^-3, its last one at 2^-24.  While scores are
-// within kFlatScore (by |q| |k|) and every row's best on a piece's first tile is at least 0, m is kFlat for all of them, which the
-// products take for nothing as what they add to.  Otherwise m is each row's own, its best weight near the top.
-constexpr float kFlat = 4.f;
+constexpr float kQueryMost2 = 4096.f;            // (2^6)^2, of a query in its unit, beyond which it is taken in fp32: a key's last bit, 2^-25, times it stays below 2^-19
+constexpr float kKeyMost2 = 8100.f;              // 90^2: a query's numbers below 2^-17 lose up to 2^-25 each, which meets keys of at most this
+// Weights are 2^(s - m), m a whole number of each row's own that puts its best weight to 2^12..2^13 when it is taken and is raised when a weight
+// would pass 2^kTopWeight (fp16 ends at 2^16).  A plain tile has scores within +-kPlainScore (by |q| |k|), so that m - s is within fp32's exponents.
 constexpr float kTopWeight = 15.75f;
-constexpr float kFlatScore = kTopWeight + kFlat;
-constexpr float kBestWeight = 14.f;
+constexpr float kBestWeight = 12.f;
+constexpr float kFirstReference = -8.f, kFirstBest = 8.f;      // a piece begins with this one, which stays where the first tile's best weight is 2^8 to 2^kTopWeight
+constexpr float kPlainScore = 54.f;
+// What fp16 terms leave of a weight is at most 2^-25 (weights from 2^-3 up have 22 bits and a sign).  So over a piece of n items a row's sum is
+// wrong by at most 2^-25 sum |v| <= 2^-25 (n sum |v|^2)^1/2, and a row that is not 2^19 times that is not known well enough: (2^-6)^2.
+// Of a value at most 2^-25 is left too, which matters where a row's own values are small beside the others of their columns: its mean has to be
+// 2^-6.5, or a quarter of what n values of the mean size (2^-3.5 at least) come to where they point anywhere: (2^-6.5)^2, (2^-3.5)^2, (2^-2)^2.
+constexpr float kWeightsLost2 = 2.4414062e-4f, kValuesLost2 = 1.2207031e-4f, kValueMean2 = 7.8125e-3f, kMeanLost2 = 0.0625f;
 
 // One 32-wide operand of a tile: the two k-halves of its two fp16 terms, 22 bits and a sign.
 struct Operand {
@@ -95,46 +101,47 @@ __device__ __forceinline__ f32x16 mma(const Operand& a, const Operand& b, f32x16
   return acc;
 }
 
-// Register i of a split or raw operand as fp32, a lane's operand i of 32x32x2 products.
-__device__ __forceinline__ float whole(const Operand& a, int i, bool raw, float unit) {
-  const uint32_t hw = a.hi[i / 8].w[(i % 8) / 2], lw = a.lo[i / 8].w[(i % 8) / 2];
-  const uint32_t two = __float_as_uint((i & 1 ? f16_hi(hw) + f16_hi(lw) : f16_lo(hw) + f16_lo(lw)) * unit);
-  const uint32_t one = (i < 8 ? a.hi[i / 4] : a.lo[(i / 4) & 1]).w[i % 4], mask = raw ? ~0u : 0u;
-  return __uint_as_float((one & mask) | (two & ~mask));
+// v of lane i with that of another lane of the same sixteen, in registers: 1, 2, then those in reverse order of eight and of sixteen.
+template <int CTRL>
+__device__ __forceinline__ uint32_t turned(uint32_t v) { return uint32_t(__builtin_amdgcn_update_dpp(int(v), int(v), CTRL, 0xF, 0xF, false)); }
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+  v = max(v, turned<0xB1>(v));
+  v = max(v, turned<0x4E>(v));
+  v = max(v, turned<0x141>(v));
+  v = max(v, turned<0x140>(v));
+  const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  v = max(r[0], r[1]);
+  const auto h = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return max(h[0], h[1]);
+}
+// of this lane and the one in the other half
+__device__ __forceinline__ float half_sum(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float half_max(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float wave_sum(float v) {
+  auto other = [](float x, auto ctrl) { return __uint_as_float(turned<decltype(ctrl)::value>(__float_as_uint(x))); };
+  v += other(v, Int<0xB1>{});
+  v += other(v, Int<0x4E>{});
+  v += other(v, Int<0x141>{});
+  v += other(v, Int<0x140>{});
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return half_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
 }
 
-// One block with everything in fp32, for keys, values and queries of any size, infinite and NaN ones included (row: the lane's
-// half of its query).  Rows past the piece are left out of the product, not only given weight 0: they may be infinite.
-__device__ __forceinline__ void attend_block_wide(const Operand& k, bool raw_keys, const Operand& v, bool raw_values,
-                                                  float value_unit, const uint16_t* row, f32x16& o, float& l, float& m, int nvl) {
-  f32x16 s = {0};
+// Largest of a lane's sixteen, three a time.
+__device__ __forceinline__ float max16(const f32x16& s) {
+  float t[2] = {s[0], s[1]};
 #pragma unroll
-  for (int i = 0; i < 16; ++i)
-    s = __builtin_amdgcn_mfma_f32_32x32x2f32(whole(k, i, raw_keys, 1.f / kKeyUnit), __uint_as_float(uint32_t(row[acc_row0(i)]) << 16), s, 0, 0, 0);
-#pragma unroll
-  for (int i = 0; i < 16; ++i)
-    if (acc_row0(i) >= nvl) s[i] = -INFINITY;
-  float tmax = s[0];
-#pragma unroll
-  for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, s[i]);
-  tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
-  const float mnew = fmaxf(m, tmax);
-  const float alpha = __builtin_amdgcn_exp2f(m - mnew);
-  l *= alpha;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) o[i] *= alpha;
-  m = mnew;
-  f32x16 t = {0};          // sums of the tile first: weights of nearly one, added to thousands one by one, would all be rounded the same way
-  float lsum[2] = {0.f, 0.f};
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const float e = acc_row0(i) < nvl ? __builtin_amdgcn_exp2f(s[i] - mnew) : 0.f;
-    t = __builtin_amdgcn_mfma_f32_32x32x2f32(acc_row0(i) < nvl ? whole(v, i, raw_values, value_unit) : 0.f, e, t, 0, 0, 0);
-    lsum[i & 1] += e;
+  for (int i = 2; i < 14; i += 4) {
+    t[0] = fmaxf(fmaxf(t[0], s[i]), s[i + 2]);
+    t[1] = fmaxf(fmaxf(t[1], s[i + 1]), s[i + 3]);
   }
-  l += lsum[0] + lsum[1];
-#pragma unroll
-  for (int i = 0; i < 16; ++i) o[i] += t[i];
+  return fmaxf(fmaxf(t[0], t[1]), fmaxf(s[14], s[15]));
 }
 
 // Shared memory of one workgroup.  WREG: a projecting wave keeps its D x 32 weight operands in registers instead of in LDS.
@@ -144,11 +151,136 @@ template <int D, int HPW, bool WREG>
 struct SplitLds {
   uint4 xbuf[kXBuf][(D / 8) * 32];    // X tiles: [16-byte chunk][item], filled by direct global->LDS loads
   uint4 kvbuf[2][HPW][2][4][64];      // projected tiles: [slot][head][K|V][term, half of the 16 registers][lane]
-  float knorm[2][HPW][64];            // squared norm of the scaled key rows (half per lane); infinite for raw keys
-  float vraw[2][HPW][64];             // infinite for raw values, else 0
-  float4 vunit[HPW][8];               // a channel's published values times this are its values
+  float knorm[2][HPW][64];            // squared norm of the scaled key rows (half per lane); infinite where fp16 does not hold them
+  float vnorm[2][HPW][64];            // that of the value columns, infinite too
+  int4 vunit[HPW][8];                 // a channel's published values times two to this and its piece's unit are its values
+  int punit[4][HPW];                  // units of four pieces, by their number: the one attended over and the two that may be published beside it
+  int redo;                           // some wave has records to form again
   uint4 wop[WREG ? 1 : HPW * 2 * (D / 16) * 64];   // projection weights as MFMA operands: [head][K|V][k-slice][lane]
 };
+
+// Partial records of a finished piece; slot = segment + user.
+template <int NQB>
+__device__ __forceinline__ void write_record(const MfmaSummarizeParams& p, int64_t slot, int h, int block, int lane, const f32x16 (&o)[NQB],
+                                             const float (&l)[NQB], const float (&m)[NQB]) {
+  char* rec = reinterpret_cast<char*>(p.partials + ((slot * p.H + h) * p.nqb + block) * kRecFloats);
+  const uint32_t lane_off = uint32_t(lane) * 16;
+#pragma unroll
+  for (int qb = 0; qb < NQB; ++qb) {
+    if (block + qb >= p.nqb) break;                    // a block past the last query has no record
+    char* r = rec + size_t(qb) * kRecFloats * 4;       // scalar
+#pragma unroll
+    for (int i = 0; i < 16; i += 4)
+      *reinterpret_cast<float4*>(r + i * 256 + lane_off) = make_float4(o[qb][i], o[qb][i + 1], o[qb][i + 2], o[qb][i + 3]);
+    *reinterpret_cast<float2*>(r + kRecSums * 4 + lane_off / 2) = make_float2(half_sum(l[qb]), m[qb]);
+  }
+}
+
+// The pieces whose records a wave has marked (m NaN) once more, with everything in fp32 and a running maximum: for keys, values and queries of any
+// size, infinite and NaN ones included, and for rows that two fp16 terms leave too little of.  Each wave by itself, from memory; only the weights
+// stand in LDS, where the tiles were.
+template <int D, int NQB, int HPW, bool WREG>
+__device__ __forceinline__ void pieces_in_fp32(const MfmaSummarizeParams& p, SplitLds<D, HPW, WREG>& sm, int64_t g, int h, int hl, int qblock,
+                                                int64_t seg_begin, int64_t seg_end) {
+  constexpr int KS = D / 16, kOps = HPW * 2 * KS * 64;       // [head][K|V][k-slice][lane]
+  static_assert(sizeof(uint4) * kOps <= sizeof(sm.xbuf) + sizeof(sm.kvbuf), "the flag that all waves look at is behind the tiles");
+  uint4* w = reinterpret_cast<uint4*>(&sm);
+  const int lane = threadIdx.x & 63, hf = lane >> 5, l32 = lane & 31;
+#pragma unroll 1
+  for (int e = threadIdx.x; e < kOps; e += blockDim.x) {
+    const int ks = (e >> 6) % KS, m = (e >> 6) / KS % 2, head = (e >> 6) / (2 * KS);
+    const uint16_t* W = (m ? p.Wv : p.Wk) + (16 * ks + 8 * hf) * D + 32 * (h - hl + head) + l32;
+    Pack8 t;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) t.h[j] = W[j * D];
+    w[e] = t.u;
+  }
+  lds_barrier();
+  w += hl * 2 * KS * 64 + lane;
+  f32x16 o[NQB];
+  float l[NQB], m[NQB];
+  auto reset = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int qb = 0; qb < NQB; ++qb) {
+      o[qb] = f32x16{0};
+      l[qb] = 0.f;
+      m[qb] = kLowest;
+    }
+  };
+  reset();
+  TileCursor c;
+  c.init(p.offsets, p.B, find_user_wave(p.offsets, p.B, seg_begin), seg_begin, seg_end);
+  bool marked = false, first = true;
+#pragma unroll 1
+  while (c.valid) {
+    if (first) {
+      const float* rec = p.partials + (((g + c.user) * p.H + h) * p.nqb + (qblock < p.nqb ? qblock : 0)) * kRecFloats;
+      const float at = __hip_atomic_load(rec + kRecSums + 2 * lane + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      marked = qblock < p.nqb && __builtin_amdgcn_ballot_w64(__builtin_isnan(at)) != 0;
+    }
+    if (!marked) {                                       // to the piece's last tile
+      c.skip(c.tiles_left - 1);
+      c.advance(p.offsets, p.B, seg_end);
+      continue;
+    }
+    const int rows = c.rows(), nvl = rows - 4 * hf;      // register i holds a row of the piece iff acc_row0(i) < nvl
+    const uint16_t* x = p.X + (c.row + (l32 < rows ? l32 : rows - 1)) * D + 8 * hf;
+    f32x16 k = {0}, v = {0};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      Pack8 t, wk, wv;
+      t.u = *reinterpret_cast<const uint4*>(x + 16 * ks);
+      wk.u = w[ks * 64];
+      wv.u = w[(KS + ks) * 64];
+      k = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wk.v, t.v, k, 0, 0, 0);
+      v = __builtin_amdgcn_mfma_f32_32x32x16_bf16(t.v, wv.v, v, 0, 0, 0);
+    }
+#pragma unroll
+    for (int qb = 0; qb < NQB; ++qb) {
+      int q = qblock * 32 + qb * 32 + l32;
+      if (q > p.S - 1) q = p.S - 1;
+      const uint16_t* row = p.Q + p.q_user_stride * c.user + int64_t(q) * D + 32 * h + 4 * hf;
+      f32x16 s = {0};
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        s = __builtin_amdgcn_mfma_f32_32x32x2f32(k[i] * p.c, __uint_as_float(uint32_t(row[acc_row0(i)]) << 16), s, 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (acc_row0(i) >= nvl) s[i] = -INFINITY;
+      float top = s[0];
+#pragma unroll
+      for (int i = 1; i < 16; ++i) top = fmaxf(top, s[i]);
+      top = half_max(top);
+      const float mnew = fmaxf(m[qb], top);
+      const float alpha = __builtin_amdgcn_exp2f(m[qb] - mnew);
+      l[qb] *= alpha;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) o[qb][i] *= alpha;
+      m[qb] = mnew;
+      // rows past the piece are left out of the product, not only given weight 0: they may be infinite.  Sums of the tile first: weights of
+      // nearly one, added to thousands one by one, would all be rounded the same way
+      f32x16 t = {0};
+      float lsum[2] = {0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const float e = acc_row0(i) < nvl ? __builtin_amdgcn_exp2f(s[i] - mnew) : 0.f;
+        t = __builtin_amdgcn_mfma_f32_32x32x2f32(acc_row0(i) < nvl ? v[i] : 0.f, e, t, 0, 0, 0);
+        lsum[i & 1] += e;
+      }
+      l[qb] += lsum[0] + lsum[1];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) o[qb][i] += t[i];
+    }
+    const bool last = c.tiles_left == 1;
+    const int user = c.user;
+    c.advance(p.offsets, p.B, seg_end);
+    first = last;
+    if (last) {
+      write_record<NQB>(p, g + user, h, qblock, lane, o, l, m);
+      reset();
+    }
+  }
+}
 
 // Body of one wave; ROLE 0 forms K^T, ROLE 1 forms V, ROLE 2 forms nothing and only attends.
 template <int D, int NQB, int HPW, int FW, bool WREG, int ROLE>
@@ -166,6 +298,7 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
   const int lane = tid & 63;
   const int hf = lane >> 5;
   const int l32 = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
   // Projection weights of this wave's head as MFMA operands, in registers or parked in LDS
   // (each wave reads back only what it wrote).  Element j of slice ks is
@@ -243,33 +376,52 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
     }
   };
 
-  // A channel's values are published times a power of two that brings the norm of its column of W_v to 2^7..2^8, so that
-  // the values of histories at unit scale sit in the middle of fp16's range whatever the weights' own size.
-  float vscale = 1.f;
+  // A channel's values are published times two powers of two that bring them to some 2^4 whatever the size of the weights and of a user's
+  // items: by the norm of its column of W_v, and by 2^4, or, where the first tile of a piece has numbers above 2^8
+  // by that or none above 1, by what takes its largest to 2^6: what fp16 cuts off, 2^-25, is then below what fp32 sums of a channel are known to.
+  float vchannel = 1.f, vscale = 1.f;
+  bool odd_column = false;           // weights too large or too small for that, or not finite
   auto settle_values = [&]() __attribute__((always_inline)) {
     if constexpr (ROLE == 1) {
       float part[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int ks = 0; ks < KS; ks += KS / 4) {        // (64 rows of them: a power of two is all that is wanted)
+      for (int ks = 0; ks < KS; ++ks) {
         Pack8 w;
         if constexpr (WREG) w.v = wreg[ks]; else w.u = sm.wop[((hl * 2 + WR) * KS + ks) * 64 + lane];
 #pragma unroll
         for (int j = 0; j < 4; ++j) part[j] = dot2_self(w.w[j], part[j]);
       }
       float n2 = (part[0] + part[1]) + (part[2] + part[3]);
-      n2 += __shfl_xor(n2, 32, 64);
+      n2 = half_sum(n2);
       const int e = (int(__float_as_uint(n2) >> 23) - 127) >> 1;       // floor of log2 of the norm
       const bool usual = n2 >= 8.6361686e-37f && n2 <= 1.1579209e36f;   // about 2^-120 .. 2^120; no column of zeros, nothing infinite or NaN
-      constexpr int kNorm = D == 64 ? 7 : 6;       // (the rest of the rows make it 1.4, 2 times as large)
-      vscale = usual ? __uint_as_float(uint32_t(127 + kNorm - e) << 23) : 1.f;
-      if (hf == 0) reinterpret_cast<float*>(sm.vunit[hl])[l32] = usual ? __uint_as_float(uint32_t(127 - kNorm + e) << 23) : 1.f;
+      vchannel = usual ? __uint_as_float(uint32_t(127 - e) << 23) : 1.f;
+      odd_column = !usual && n2 != 0.f;
+      if (hf == 0) reinterpret_cast<int*>(sm.vunit[hl])[l32] = usual ? e : 0;
+    }
+  };
+  int pieces_out = 0;                // pieces published so far
+  auto start_piece = [&](const f32x16& acc) __attribute__((always_inline)) {
+    if constexpr (ROLE == 1) {
+      float most[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < 16; ++i) most[i % 4] = fmaxf(most[i % 4], fabsf(acc[i]));
+      const float mine = fmaxf(fmaxf(most[0], most[1]), fmaxf(most[2], most[3])) * vchannel;
+      int up = 4;
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(mine <= 256.f)) != 0 || __builtin_amdgcn_ballot_w64(mine >= 1.f) == 0, 0)) {
+        const uint32_t top = wave_max(__float_as_uint(mine) & 0x7FFFFFFFu);
+        if (top >= 0x20000000u && top < 0x5F800000u) up = 6 - (int(top >> 23) - 127);      // 2^-63 .. 2^64
+      }
+      vscale = ldexpf(vchannel, up);
+      if (lane == 0) sm.punit[pieces_out & 3][hl] = -up;
+      ++pieces_out;
     }
   };
 
   const int qbase = qblock * 32;         // first query of this wave
   bf16x8 qop[NQB][2];                    // (once settled, the bits of fp16 numbers)
   float qmax2 = 0.f;
-  bool wide_queries = false;             // queries beyond what fp16 terms take
+  float qunit = 1.f, kunit = 1.f;        // queries are taken times the first, keys times the second, its inverse
   auto request_queries = [&](int user) __attribute__((always_inline)) {
     const char* Qb = reinterpret_cast<const char*>(p.Q + p.q_user_stride * user + 32 * h) + 8 * hf;
 #pragma unroll
@@ -288,8 +440,26 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
       }
     }
   };
+  // The unit of shared queries, the same for all waves of a head: a power of two that brings the largest number of eight rows to 1..2; keys are
+  // published by the inverse.  Users' own queries are taken as they are.
+  uint2 qsome = make_uint2(0, 0);
+  auto request_some = [&]() __attribute__((always_inline)) {
+    qsome = *reinterpret_cast<const uint2*>(p.Q + int64_t((lane >> 3) * p.S >> 3) * D + 32 * h + 4 * (lane & 7));
+  };
+  auto settle_unit = [&]() __attribute__((always_inline)) {
+    const uint32_t a = qsome.x & 0x7FFF7FFFu, b = qsome.y & 0x7FFF7FFFu;
+    const uint32_t top = wave_max(max(max(a & 0xFFFFu, a >> 16), max(b & 0xFFFFu, b >> 16)));
+    int e = int(top >> 7) - 127;
+    if (top == 0 || e > 100) e = 0;              // (an infinite or NaN one too)
+    if (e < -100) e = -100;
+    kunit = __uint_as_float(uint32_t(127 + e) << 23);
+    qunit = __uint_as_float(uint32_t(127 - e) << 23);
+  };
+  bool coarse = false;                   // some query number lost bits
+  float bound2 = 0.f;                    // keys of no larger squared norm have scores within kPlainScore
+  bool lost_queries = false;             // queries beyond what fp16 terms take
   auto settle_queries = [&]() __attribute__((always_inline)) {
-    float worst = 0.f;
+    float worst = 0.f, rest = 0.f;
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb) {
       float n2 = 0.f;
@@ -299,20 +469,21 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
         t.v = qop[qb][part];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const float a = __uint_as_float(t.w[j] << 16) * (1.f / kKeyUnit), b = __uint_as_float(t.w[j] & 0xFFFF0000u) * (1.f / kKeyUnit);
+          const float a = __uint_as_float(t.w[j] << 16) * qunit, b = __uint_as_float(t.w[j] & 0xFFFF0000u) * qunit;
           n2 = fmaf(a, a, n2);
           n2 = fmaf(b, b, n2);
           t.w[j] = cvt_pk_f16(a, b);
+          rest = fmaxf(rest, fmaxf(fabsf(a - f16_lo(t.w[j])), fabsf(b - f16_hi(t.w[j]))));
         }
         qop[qb][part] = t.v;
       }
-      n2 += __shfl_xor(n2, 32, 64);
+      n2 = half_sum(n2);
       worst = n2 <= kQueryMost2 ? fmaxf(worst, n2) : INFINITY;
     }
-#pragma unroll
-    for (int off = 16; off >= 1; off >>= 1) worst = fmaxf(worst, __shfl_xor(worst, off, 64));
-    qmax2 = worst;
-    wide_queries = __builtin_amdgcn_ballot_w64(qmax2 == INFINITY) != 0;
+    qmax2 = __uint_as_float(wave_max(__float_as_uint(worst)));     // (not negative)
+    lost_queries = __builtin_amdgcn_ballot_w64(qmax2 == INFINITY) != 0;
+    coarse = __builtin_amdgcn_ballot_w64(rest != 0.f) != 0;
+    bound2 = fminf(kPlainScore * kPlainScore / qmax2, coarse ? kKeyMost2 : kHalfMost2);
   };
 
   // ---- the segment as one stream of tiles (TileCursor: scalar state, offsets read through
@@ -323,20 +494,39 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
     c.init(p.offsets, p.B, find_user_wave(p.offsets, p.B, seg_begin), seg_begin, seg_end);
   };
   auto cursor_advance = [&](Cursor& c) __attribute__((always_inline)) { c.advance(p.offsets, p.B, seg_end); };
+  // whether the tile it then names is the first of a piece
+  auto cursor_enters = [&](Cursor& c) __attribute__((always_inline)) {
+    const bool last = c.tiles_left == 1;
+    cursor_advance(c);
+    return last && c.valid ? 1 : 0;
+  };
 
   f32x16 o[NQB];
   float l[NQB], m[NQB];
-  int mode = 0;                  // 0 fresh piece, 1 reference m, 2 fp32 operands and a running maximum, to the piece's end
-  float safe2 = -1.f;            // with the flat reference: keys of no larger squared norm are within kFlatScore
+  int mode = 0;                  // 0 fresh piece, 1 reference m, 2 not for fp16 terms: nothing more is done for the piece, its record is formed again
+  bool redo = false;             // this wave has such records
+  float safe2 = -1.f;            // bound2, or less than any where a row's m is out of the way
+  float vsum = 0.f;              // this lane's share of the squared norms of the values so far
+  int tiles = 0;                 // of the piece so far
+  // scores come out of the matrix core less m: one more product, of ones at k = 0 with -m there (fp16 holds whole numbers to 2048)
+  Pack8 ones, mop[NQB];
+  ones.u = make_uint4(hf == 0 ? 0x3C00u : 0u, 0u, 0u, 0u);
+  auto set_reference = [&](int qb) __attribute__((always_inline)) {
+    mop[qb].u = make_uint4(hf == 0 ? cvt_pk_f16(-m[qb], 0.f) : 0u, 0u, 0u, 0u);
+  };
   auto reset_state = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) o[qb][i] = 0.f;
       l[qb] = 0.f;
-      m[qb] = kLowest;
+      m[qb] = kFirstReference;
+      set_reference(qb);
     }
     mode = 0;
+    safe2 = bound2;
+    vsum = 0.f;
+    tiles = 0;
   };
 
   // HBM -> LDS movement of X without a stop in registers (global_load_lds, 16 bytes
@@ -344,7 +534,6 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
   // xbuf[t % 3]; the rows of tile t+3 are requested at the top of tile t into the
   // buffer tile t has vacated and must have landed by the end of tile t+1, so a
   // load has two tile periods.  Rows past the piece are clamped to its last row.
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   auto fetch_rows = [&](const char* base, int last, int xb) __attribute__((always_inline)) {   // last: last valid row
     if (wave >= FW) return;
 #pragma unroll
@@ -381,27 +570,22 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
   };
   // hand the projected tile to the partner waves: operands (+ key norms), a pair of registers at a time
   auto publish_pair = [&](const f32x16& acc, int i, Operand& r, float& n2) __attribute__((always_inline)) {
-    const float c = ROLE ? vscale : p.c * kKeyUnit;        // the keys' scale, in fp32
+    const float c = ROLE ? vscale : p.c * kunit;           // the keys' scale, in fp32
     uint32_t& pk = r.hi[i / 8].w[(i % 8) / 2];
     split_pk(acc[i] * c, acc[i + 1] * c, pk, r.lo[i / 8].w[(i % 8) / 2]);
     n2 = dot2_self_f16(pk, n2);
   };
   auto publish_pairs = [&](int buf, const f32x16& acc, Operand& r, float n2) __attribute__((always_inline)) {
     if constexpr (PROJ) {
-      bool raw = __builtin_amdgcn_ballot_w64(!(n2 <= kHalfMost2)) != 0;
-      if (ROLE == 1 && __builtin_expect(__builtin_amdgcn_ballot_w64(n2 < kValueLeast2) != 0, 0)) {      // (nothing but zeros is well kept)
+      bool lost = !(n2 <= kHalfMost2) || (ROLE == 1 && odd_column);
+      if (ROLE == 1 && __builtin_expect(__builtin_amdgcn_ballot_w64(n2 == 0.f) != 0, 0)) {      // (nothing but zeros is well kept)
         float any = 0.f;
 #pragma unroll
         for (int i = 0; i < 16; ++i) any = fmaxf(any, fabsf(acc[i]));
-        raw = raw || __builtin_amdgcn_ballot_w64(n2 < kValueLeast2 && any > 0.f) != 0;
+        lost |= n2 == 0.f && any > 0.f;
       }
-      if (__builtin_expect(raw, 0)) {         // fp32 as it is, four registers where a term's half would be
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-          (i < 8 ? r.hi[i / 4] : r.lo[(i / 4) & 1]).w[i % 4] = __float_as_uint(ROLE ? acc[i] : acc[i] * p.c);
-      }
-      if (ROLE == 0) sm.knorm[buf][hl][lane] = raw ? INFINITY : n2;
-      else sm.vraw[buf][hl][lane] = raw ? INFINITY : 0.f;
+      if (lost) n2 = INFINITY;
+      if (ROLE == 0) sm.knorm[buf][hl][lane] = n2; else sm.vnorm[buf][hl][lane] = n2;
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
         sm.kvbuf[buf][hl][WR][q][lane] = r.hi[q].u;
@@ -418,12 +602,15 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
       publish_pairs(buf, acc, r, n2);
     }
   };
-  float vraw = 0.f;         // infinite where the values of the tile being attended over are raw
-  auto unsafe_tile = [&](float kn2) __attribute__((always_inline)) { return __builtin_amdgcn_ballot_w64(!(kn2 + vraw <= safe2)) != 0; };
+  float vn2 = 0.f;          // squared norm of half a value column of the tile being attended over
+  auto unsafe_tile = [&](float kn2) __attribute__((always_inline)) { return __builtin_amdgcn_ballot_w64(!(kn2 <= safe2)) != 0; };
 
   // everything the workgroup starts from is requested before any of it is waited for
   request_weights();
-  if (p.q_user_stride == 0) request_queries(0);
+  if (p.q_user_stride == 0) {
+    request_some();
+    request_queries(0);
+  }
   Cursor ca, cf;
   cursor_init(ca);
   cf = ca;
@@ -448,7 +635,7 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
   auto read_k = [&](int i1) __attribute__((always_inline)) {
     read_operand(kk, i1, 0);
     kn2 = sm.knorm[i1][hl][lane] + sm.knorm[i1][hl][lane ^ 32];
-    vraw = sm.vraw[i1][hl][lane];
+    vn2 = sm.vnorm[i1][hl][lane];
   };
   auto read_v = [&](int i1) __attribute__((always_inline)) {
     read_operand(vv, i1, 1);
@@ -460,7 +647,7 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
     const int i1 = r == kXBuf - 1 ? 0 : r + 1, i2 = i1 == kXBuf - 1 ? 0 : i1 + 1;
     return Slots{i2, odd ^ 1, odd};
   };
-  f32x16 nx = {0};          // scores of the first block of the tile to come
+  f32x16 nx = {0};          // scores less m of the first block of the tile to come, where that is a plain one
   // the next n slices of a projection, the operand of the one behind them requested
   auto project_some = [&](int buf, int n, int& ks, Pack8& xr, f32x16& acc) __attribute__((always_inline)) {
     if constexpr (PROJ) {
@@ -477,19 +664,27 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
       }
     }
   };
+  // product j of five; the reference last, so that the sums before it are of the scores' own size
+  auto score_product = [&](int qb, int j, const f32x16& s) __attribute__((always_inline)) {
+    if (j == 4) return mfma_f16(ones.v, mop[qb].v, s);
+    return mfma_f16((j < 2 ? kk.lo[j & 1] : kk.hi[j & 1]).v, qop[qb][j & 1], j ? s : f32x16{0});
+  };
+  // which of the tiles t + 2, t + 3 and t + 4, from the lowest bit, are the first of their piece
+  int firsts = 0;
   // A plain tile, in an order of its own (pin): every pair of exponentials, its split and its sum stand between two products, those of the
   // next block's scores, of the block before with the values and of the projection.  A tile ends with the first scores of the next
   // one (nx) and its last block's products, beside the projected tile's own split.
-  auto fast_tile = [&](int r) __attribute__((always_inline)) {
+  // Where a weight would leave fp16's range, or a piece's first tile has none in the middle of it, the row's reference is moved before the exponentials.
+  // straight: no piece starts within the tiles on their way.
+  auto fast_tile = [&](int r, auto straight) __attribute__((always_inline)) {
     const Slots at = slots(r);
     f32x16 acc = {0};
     int ks = 0;
     Pack8 xr;
     if constexpr (PROJ) xr.u = sm.xbuf[at.x2][hf * 32 + l32];
     Operand before;      // weights of the block before
-    const f32x16 flat = {-kFlat, -kFlat, -kFlat, -kFlat, -kFlat, -kFlat, -kFlat, -kFlat, -kFlat, -kFlat, -kFlat, -kFlat, -kFlat, -kFlat, -kFlat, -kFlat};
     auto score = [&](int qb, int j, f32x16& s) __attribute__((always_inline)) {
-      s = mfma_f16((j < 2 ? kk.lo[j & 1] : kk.hi[j & 1]).v, qop[qb][j & 1], j ? s : flat);
+      s = score_product(qb, j, s);
       pin(s);
     };
     auto second = [&](int qb, const Operand& w, int j) __attribute__((always_inline)) {
@@ -497,10 +692,26 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
       o[qb] = mfma_f16((j % 3 == 0 ? vv.lo[q] : vv.hi[q]).v, (j % 3 == 1 ? w.lo[q] : w.hi[q]).v, o[qb]);
       pin(o[qb]);
     };
+    vsum += vn2;
+    ++tiles;
     if (NQB == 1) read_k(at.kv1);
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb) {
-      const f32x16 sc = nx;
+      f32x16 sc = nx;
+      float top = max16(sc);
+      const float low = mode == 0 ? kFirstBest : -INFINITY;
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(top > kTopWeight || top < low) != 0, 0)) {
+        top = half_max(top);
+        const float by = top > kTopWeight || top < low ? floorf(top) - kBestWeight : 0.f, alpha = __builtin_amdgcn_exp2f(-by);
+        m[qb] += by;
+        l[qb] *= alpha;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          sc[i] -= by;
+          o[qb][i] *= alpha;
+        }
+        set_reference(qb);
+      }
       f32x16 nn;
       float ev[16], lsum[2] = {0.f, 0.f};
       Operand cur;
@@ -524,7 +735,7 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
           pin(lsum[0]);
           pin(lsum[1]);
         }
-        if (more && (st & 1)) score(qb + 1, st / 2, nn);
+        if (more && ((st & 1) || st == 8)) score(qb + 1, st / 2, nn);
         if (qb > 0 && st < 6) second(qb - 1, before, st);
         if (!more && st > 5) second(qb, cur, st - 6);
         if (st < 8) project_some(at.x2, ((qb * 8 + st + 1) * KS) / (NQB * 8) - ((qb * 8 + st) * KS) / (NQB * 8), ks, xr, acc);
@@ -533,54 +744,70 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
       before = cur;
       if (more) nx = nn;
     }
+    if constexpr (!decltype(straight)::value) {
+      if (firsts & 1) start_piece(acc);
+    }
     Operand pub;
     float n2 = 0.f;
 #pragma unroll
     for (int st = 0; st < 8; ++st) {
       if (st < 3) second(NQB - 1, before, 3 + st);
-      else if (st < 7) score(0, st - 3, nx);
+      else score(0, st - 3, nx);
       if constexpr (PROJ) {
         publish_pair(acc, 2 * st, pub, n2);
         pin(n2);
       }
     }
+    mode = 1;
     read_v(at.kv1);
     if constexpr (PROJ) publish_pairs(at.kv2, acc, pub, n2);
   };
 
   // the accumulators in the values' own units
+  int pieces_done = 0;
   auto scale_values = [&]() __attribute__((always_inline)) {
+    const int unit = sm.punit[pieces_done & 3][hl];
 #pragma unroll
     for (int g4 = 0; g4 < 4; ++g4) {
-      const float4 u = sm.vunit[hl][2 * g4 + hf];      // channels 8 g4 + 4 hf + 0..3: rows of registers 4 g4..
+      const int4 u = sm.vunit[hl][2 * g4 + hf];        // channels 8 g4 + 4 hf + 0..3: rows of registers 4 g4..
 #pragma unroll
       for (int qb = 0; qb < NQB; ++qb) {
-        o[qb][4 * g4] *= u.x;
-        o[qb][4 * g4 + 1] *= u.y;
-        o[qb][4 * g4 + 2] *= u.z;
-        o[qb][4 * g4 + 3] *= u.w;
+        o[qb][4 * g4] = ldexpf(o[qb][4 * g4], u.x + unit);
+        o[qb][4 * g4 + 1] = ldexpf(o[qb][4 * g4 + 1], u.y + unit);
+        o[qb][4 * g4 + 2] = ldexpf(o[qb][4 * g4 + 2], u.z + unit);
+        o[qb][4 * g4 + 3] = ldexpf(o[qb][4 * g4 + 3], u.w + unit);
       }
     }
   };
+  // whether every row of this wave is known well enough (the accumulators in the terms' units)
+  auto rows_known = [&]() __attribute__((always_inline)) {
+    const float v2 = wave_sum(vsum);
+    const float n = 32.f * float(tiles);
+    const float by_l = v2 == 0.f ? 0.f : v2 >= kValueMean2 * n ? fminf(kValuesLost2, kMeanLost2 * v2 / (n * n)) : kValuesLost2;
+    const float by_n = kWeightsLost2 * n * v2;
+    bool bad = !(v2 < INFINITY);
+#pragma unroll
+    for (int qb = 0; qb < NQB; ++qb) {
+      float part[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < 16; ++i) part[i % 4] = fmaf(o[qb][i], o[qb][i], part[i % 4]);
+      const float o2 = half_sum((part[0] + part[1]) + (part[2] + part[3])), ls = half_sum(l[qb]);
+      bad |= !(o2 >= by_n && o2 >= by_l * ls * ls && o2 < INFINITY);
+    }
+    return __builtin_amdgcn_ballot_w64(bad) == 0;
+  };
   // Any tile: ragged tail, scores beyond the bound, last tile of the segment.
-  auto slow_tile = [&](int r, int nvalid, bool unsafe) __attribute__((always_inline)) {
+  auto slow_tile = [&](int r, int nvalid) __attribute__((always_inline)) {
     const Slots at = slots(r);
     const int nvl = nvalid - 4 * hf;
-    const bool raw_keys = __builtin_amdgcn_ballot_w64(kn2 == INFINITY) != 0, raw_values = __builtin_amdgcn_ballot_w64(vraw > 0.f) != 0;
-    if (__builtin_expect(mode != 2 && (raw_keys || raw_values || wide_queries), 0)) {
-      scale_values();
-      mode = 2;
-    }
-    if (__builtin_expect(mode == 2, 0)) {
-      const float unit = reinterpret_cast<const float*>(sm.vunit[hl])[l32];
+    if (__builtin_expect(lost_queries || __builtin_amdgcn_ballot_w64(!(kn2 < INFINITY) || (coarse && kn2 > kKeyMost2)) != 0, 0)) mode = 2;
+    if (__builtin_expect(mode != 2, 1)) {
+      if (mode == 0) {
 #pragma unroll
-      for (int qb = 0; qb < NQB; ++qb) {
-        int q = qbase + qb * 32 + l32;
-        if (q > p.S - 1) q = p.S - 1;
-        attend_block_wide(kk, raw_keys, vv, raw_values, unit, p.Q + p.q_user_stride * ca.user + int64_t(q) * D + 32 * h + 4 * hf,
-                          o[qb], l[qb], m[qb], nvl);
+        for (int qb = 0; qb < NQB; ++qb) m[qb] = kLowest;
       }
-    } else {
+      vsum += vn2;
+      ++tiles;
       f32x16 sc[NQB];
       float top[NQB];
       bool raise = false;
@@ -593,37 +820,27 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
           for (int i = 0; i < 16; ++i)
             if (acc_row0(i) >= nvl) sc[qb][i] = -INFINITY;
       }
-      bool moved = false;
-      if (mode == 0 || unsafe) {           // (the ragged end of a piece with a reference is within it)
 #pragma unroll
-        for (int qb = 0; qb < NQB; ++qb) {
-          float t[2] = {sc[qb][0], sc[qb][1]};
+      for (int qb = 0; qb < NQB; ++qb) top[qb] = max16(sc[qb]);
 #pragma unroll
-          for (int i = 2; i < 16; ++i) t[i & 1] = fmaxf(t[i & 1], sc[qb][i]);
-          top[qb] = fmaxf(t[0], t[1]);
-        }
-#pragma unroll
-        for (int qb = 0; qb < NQB; ++qb) {
-          top[qb] = fmaxf(top[qb], __shfl_xor(top[qb], 32, 64));
-          raise |= top[qb] - m[qb] > kTopWeight;
-        }
-        moved = __builtin_amdgcn_ballot_w64(raise) != 0;
+      for (int qb = 0; qb < NQB; ++qb) {
+        top[qb] = half_max(top[qb]);
+        raise |= top[qb] - m[qb] > kTopWeight;
       }
-      if (moved) {
-        bool low = !(qmax2 * kn2 <= kFlatScore * kFlatScore);
-#pragma unroll
-        for (int qb = 0; qb < NQB; ++qb) low |= top[qb] < 0.f;
-        const bool flat = mode == 0 && __builtin_amdgcn_ballot_w64(low) == 0;
-        safe2 = flat ? fminf(kFlatScore * kFlatScore / qmax2, 1e30f) : -1.f;     // (finite also for queries of zeros: raw tiles are not below it)
+      if (__builtin_amdgcn_ballot_w64(raise) != 0) {
+        bool out = false;
 #pragma unroll
         for (int qb = 0; qb < NQB; ++qb) {
-          const float mq = flat ? kFlat : top[qb] - m[qb] > kTopWeight ? top[qb] - kBestWeight : m[qb];
+          const float mq = top[qb] - m[qb] > kTopWeight ? floorf(top[qb]) - kBestWeight : m[qb];
           const float alpha = __builtin_amdgcn_exp2f(m[qb] - mq);      // 0 on a piece's first tile (m lowest)
           l[qb] *= alpha;
 #pragma unroll
           for (int i = 0; i < 16; ++i) o[qb][i] *= alpha;
           m[qb] = mq;
+          set_reference(qb);
+          out |= !(fabsf(mq) <= kPlainScore + kBestWeight + 1.f);
         }
+        safe2 = __builtin_amdgcn_ballot_w64(out) != 0 ? -1.f : bound2;
       }
 #pragma unroll
       for (int qb = 0; qb < NQB; ++qb) {
@@ -643,29 +860,24 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
     }
     read_k(at.kv1);
     read_v(at.kv1);
-    nx = mma_scores(kk, qop[0], f32x16{0} - kFlat);     // (of no use, and not used, where the next tile is no plain one)
     // the tile two ahead (past the end of the segment: a repeat of its last tile, never used)
     f32x16 acc = {0};
     project(at.x2, 0, KS, acc);
+    if (firsts & 1) start_piece(acc);
     publish(at.kv2, acc);
   };
 
   // partial record of a finished piece: slot = segment + user
   auto write_partial = [&](int user) __attribute__((always_inline)) {
-    const int64_t slot = g + user;
-    if (mode != 2) scale_values();
-    char* rec = reinterpret_cast<char*>(p.partials + ((slot * p.H + h) * p.nqb + (qbase / 32)) * kRecFloats);
-    const uint32_t lane_off = uint32_t(lane) * 16;
+    if (mode == 2 || !rows_known()) {
+      redo = true;
 #pragma unroll
-    for (int qb = 0; qb < NQB; ++qb) {
-      if (qbase / 32 + qb >= p.nqb) break;               // a block past the last query has no record
-      char* r = rec + size_t(qb) * kRecFloats * 4;       // scalar
-#pragma unroll
-      for (int i = 0; i < 16; i += 4)
-        *reinterpret_cast<float4*>(r + i * 256 + lane_off) = make_float4(o[qb][i], o[qb][i + 1], o[qb][i + 2], o[qb][i + 3]);
-      *reinterpret_cast<float2*>(r + kRecSums * 4 + lane_off / 2) =
-          make_float2(l[qb] + __shfl_xor(l[qb], 32, 64), m[qb]);
+      for (int qb = 0; qb < NQB; ++qb) m[qb] = NAN;
+    } else {
+      scale_values();
     }
+    ++pieces_done;
+    write_record<NQB>(p, g + user, h, qbase / 32, lane, o, l, m);
   };
 
   if (!ca.valid) return;               // only with invalid offsets (whole workgroup)
@@ -684,28 +896,32 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
   // t+4 are requested into the slot whose rows (tile t+1) were projected one tile ago.
   // ---- prologue: tiles 0, 1, 2 requested; 0 and 1 landed, projected and published
   fetch(cf, 0);
-  cursor_advance(cf);
+  const int first1 = cursor_enters(cf);
   fetch(cf, 1);
-  cursor_advance(cf);
+  firsts = cursor_enters(cf);
   fetch(cf, 2);
-  cursor_advance(cf);
+  firsts |= cursor_enters(cf) << 1;
   if (p.q_user_stride != 0) request_queries(ca.user);
   settle_weights();
   settle_values();
+  if (p.q_user_stride == 0) settle_unit();
   settle_queries();
+  safe2 = bound2;
   wait_vm(Int<CPT>{});
   lds_barrier();
   {
     f32x16 acc = {0};
     project(0, 0, KS, acc);
+    start_piece(acc);
     publish(0, acc);
     f32x16 acc1 = {0};
     project(1, 0, KS, acc1);
+    if (first1) start_piece(acc1);
     publish(1, acc1);
   }
   lds_barrier();              // slot 0's rows are projected by everyone, its operands are visible
   fetch(cf, 0);               // tile 3
-  cursor_advance(cf);
+  firsts |= cursor_enters(cf) << 2;
   read_k(0);
   read_v(0);
   wait_vm(Int<CPT>{});        // tile 2 has landed
@@ -724,7 +940,7 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
   auto end_of_tile = [&]() __attribute__((always_inline)) {
     if (drain) wait_vm(Int<0>{}); else wait_vm(Int<CPT>{});
     drain = false;
-    cursor_advance(cf);
+    firsts = (firsts >> 1) | (cursor_enters(cf) << 2);
   };
   // Start of a tile: the barrier, then the request for tile t+4.
   auto begin_tile = [&]() __attribute__((always_inline)) {
@@ -734,13 +950,17 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
   // whether the tile whose operands are in registers is a plain one
   bool unsafe = unsafe_tile(kn2);
   auto is_plain = [&]() __attribute__((always_inline)) {
-    return !(ca.tiles_left == 1 || mode != 1 || unsafe);
+    return !(ca.tiles_left == 1 || mode == 2 || unsafe);
   };
   bool plain = is_plain();
+  auto first_scores = [&]() __attribute__((always_inline)) {       // a plain tile behind another one has them already
+#pragma unroll
+    for (int j = 0; j < 5; ++j) nx = score_product(0, j, nx);
+  };
+  if (plain) first_scores();
   for (;;) {
-    // Plain tiles while the tile being requested is a full one of the same piece: no cursor in the loop.  Its
-    // branches and state moves are on every wave between two barriers; without this loop 8 users of a
-    // million items take 1720 us instead of 1652, two layers at d = 256 27.4 ms instead of 24.0.
+    // Plain tiles while the tile being requested is a full one of the same piece: no cursor in the loop, whose
+    // branches and state moves would be on every wave between two barriers.
     if (plain) {
       const int run = cf.straight(ca);
       const char* base = reinterpret_cast<const char*>(p.X) + cf.row * (D * 2);
@@ -749,7 +969,7 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
         lds_barrier();
         fetch_rows(base, kTile - 1, r == kXBuf - 1 ? 0 : r + 1);
         base += kTile * D * 2;
-        fast_tile(r);
+        fast_tile(r, Int<1>{});
         if (drain) wait_vm(Int<0>{}); else wait_vm(Int<CPT>{});
         drain = false;
         ++n;
@@ -764,7 +984,7 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
     }
     while (__builtin_expect(plain, 1)) {
       begin_tile();
-      fast_tile(r);
+      fast_tile(r, Int<0>{});
       end_of_tile();
       --ca.tiles_left;
       ca.row += kTile;
@@ -776,7 +996,7 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
     begin_tile();
     const bool last_in_piece = ca.tiles_left == 1;
     const int nvalid = last_in_piece ? ca.tail : kTile;
-    slow_tile(r, nvalid, unsafe);
+    slow_tile(r, nvalid);
     end_of_tile();
     const int done_user = ca.user;
     cursor_advance(ca);
@@ -786,6 +1006,7 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
       if (p.q_user_stride != 0 && ca.valid) {
         request_queries(ca.user);
         settle_queries();
+        safe2 = bound2;
       }
       drain = true;
     }
@@ -794,7 +1015,9 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
     if (!ca.valid) break;
     unsafe = unsafe_tile(kn2);
     plain = is_plain();
+    if (plain) first_scores();
   }
+  if (redo) sm.redo = 1;
 }
 
 
@@ -828,12 +1051,17 @@ __global__ __launch_bounds__(512, D == 64 && NQB == 1 ? 3 : 2) void split_mfma_k
       self_kv_unit(p.Q, p.Wk, p.Wv, p.Ks, p.Vs, p.self_rows, D, u);
   }
   // All roles run the same sequence of barriers; only the MFMA operand order differs.
+  const int qblock = slot * NQB;
+  if (threadIdx.x == 0) sm.redo = 0;      // (set behind the first tile's barrier at the earliest)
   if (slot == 0)
-    split_wave<D, NQB, HPW, FW, WREG, 0>(p, sm, g, h, hl, 0, seg_begin, seg_end);
+    split_wave<D, NQB, HPW, FW, WREG, 0>(p, sm, g, h, hl, qblock, seg_begin, seg_end);
   else if (slot == 1)
-    split_wave<D, NQB, HPW, FW, WREG, 1>(p, sm, g, h, hl, NQB, seg_begin, seg_end);
+    split_wave<D, NQB, HPW, FW, WREG, 1>(p, sm, g, h, hl, qblock, seg_begin, seg_end);
   else
-    split_wave<D, NQB, HPW, FW, WREG, 2>(p, sm, g, h, hl, slot * NQB, seg_begin, seg_end);
+    split_wave<D, NQB, HPW, FW, WREG, 2>(p, sm, g, h, hl, qblock, seg_begin, seg_end);
+  __builtin_amdgcn_s_waitcnt(0x0F70);     // rows still on their way to LDS, records
+  lds_barrier();
+  if (__builtin_expect(sm.redo != 0, 0)) pieces_in_fp32<D, NQB, HPW, WREG>(p, sm, g, h, hl, qblock, seg_begin, seg_end);
 }
 
 template <int D, int NQB, int HPW, int FW, bool WREG>

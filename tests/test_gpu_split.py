@@ -1,6 +1,6 @@
 """GPU parity of the matrix-core path with split operands (bf16 softmax shapes outside the fixed seed
-counts): K, V and weights keep 22 bits and a sign as two fp16 terms, or are fp32, so what separates a result from the
-oracle is the rounding of the bf16 output and of fp32 sums."""
+counts): K, V and weights keep 22 bits and a sign as two fp16 terms, a piece in which these leave too little of a row is formed again
+in fp32, so what separates a result from the oracle is the rounding of the bf16 output and of fp32 sums."""
 import numpy as np
 import pytest
 import torch
@@ -293,22 +293,27 @@ def test_items_at_minus_infinity_leave_the_softmax(dtype, d, H, S, rows, seg):
     check(host64(out), want, (2e-2 if dtype == "bf16" and S in (128, 256) else 1e-4))
 
 
-def record_error(X, Q, Wk, Wv, H):
-    """One user, one segment: the largest error of a head's result before its bf16 rounding (2-norm against fp64), from the
+def records(X, Q, Wk, Wv, H, named=True):
+    """One user, one segment: every head's rows [H, S, dh] before their bf16 rounding and in fp64, from the
     partial record (registers [4][lane][4], row 8 (i / 4) + i % 4 + 4 (lane / 32), column lane % 32; then [lane][l, m])."""
     (L, d), S = X.shape, Q.shape[0]
     dh, nqb, seg = d // H, (S + 31) // 32, (L + 31) // 32 * 32
     out = torch.empty((1, S, d), device="cuda", dtype=torch.bfloat16)
     ws = V.vista_summarize(dev(X, "bf16"), torch.tensor([0, L], device="cuda"), dev(Q, "bf16"), dev(Wk, "bf16"), dev(Wv, "bf16"), out,
-                           H=H, segment_items=seg)
+                           H=H, segment_items=seg if named else 0)
     rec = ws[512:512 + H * nqb * 4608].view(torch.float32).cpu().double().numpy().reshape(H, nqb, 1152)
     o = rec[:, :, :1024].reshape(H, nqb, 4, 2, 32, 4).transpose(0, 1, 4, 2, 3, 5).reshape(H, nqb * 32, dh)
     got = o / rec[:, :, 1024::2].reshape(H, nqb, 2, 32)[:, :, 0].reshape(H, nqb * 32, 1)
     heads = lambda m: (m.astype(np.float64)).reshape(-1, H, dh).transpose(1, 0, 2)
     s = heads(Q) @ heads(X.astype(np.float64) @ Wk).transpose(0, 2, 1) * dh ** -0.5
     w = np.exp(s - s.max(axis=2, keepdims=True))
-    want = w @ heads(X.astype(np.float64) @ Wv) / w.sum(axis=2, keepdims=True)
-    return (np.linalg.norm(got[:, :S] - want, axis=(1, 2)) / np.linalg.norm(want, axis=(1, 2))).max()
+    return got[:, :S], w @ heads(X.astype(np.float64) @ Wv) / w.sum(axis=2, keepdims=True)
+
+
+def record_error(X, Q, Wk, Wv, H):
+    """The largest error of a head's result (2-norm)."""
+    got, want = records(X, Q, Wk, Wv, H)
+    return (np.linalg.norm(got - want, axis=(1, 2)) / np.linalg.norm(want, axis=(1, 2))).max()
 
 
 # plain tiles, references of a row's own, fp32 for what fp16 terms do not hold (both ends), and queries beyond them
@@ -339,7 +344,8 @@ def test_split_histories_that_change_their_scale(d, H, S, per_user, seg):
     check(run(X, off, Q, Wk, Wv, H, segment_items=seg), O.summarize(X, off, Q, Wk, Wv, H), 4e-3)     # (as for the running maximum)
 
 
-@pytest.mark.parametrize("d,H,S,limit", [(64, 2, 40, 16384), (64, 2, 256, 275000), (128, 4, 33, 8192), (128, 4, 96, 237500), (128, 4, 250, 59375)])
+@pytest.mark.parametrize("d,H,S,limit", [(64, 2, 40, 16384), (64, 2, 256, 275000), (128, 4, 33, 8192), (128, 4, 96, 237500), (128, 4, 250, 59375),
+                                           (64, 2, 255, 162500), (128, 4, 95, 125000), (128, 4, 249, 31250)])
 @pytest.mark.parametrize("beyond", [0, 1])
 @pytest.mark.parametrize("self_term", [False, True])
 def test_both_sides_of_one_head_a_workgroup(d, H, S, limit, beyond, self_term):
@@ -367,3 +373,77 @@ def test_split_queries_of_zeros_beside_values_that_fp16_does_not_hold(d, H, seg)
     X[70:75] *= 2.0 ** 20
     Q[:] = 0.0
     check(run(X, off, Q, Wk, Wv, H, segment_items=seg), O.summarize(X, off, Q, Wk, Wv, H), 1e-4)
+
+
+def row_errors(X, Q, Wk, Wv, H, named):
+    got, want = records(X, Q, Wk, Wv, H, named)
+    return np.linalg.norm(got - want, axis=2) / np.linalg.norm(want, axis=2)
+
+
+@pytest.mark.parametrize("d,H,S", [(64, 2, 33), (128, 4, 100), (128, 4, 300), (256, 8, 40), (256, 8, 257)])
+@pytest.mark.parametrize("score", [2.0, 10.4, 15.0, 18.2, 19.4, 30.0, 50.0, 100.0])
+@pytest.mark.parametrize("L,spread,named", [(99, 0.0, False), (99, 0.05, True), (3000, 0.0, True), (3000, 0.3, True)])
+def test_split_weights_far_below_a_row_s_best_count(d, H, S, score, L, spread, named):
+    """A history that begins with a row of zeros (score 0, value 0) and goes on with items that score 2^-score: they alone make
+    the result, row by row.  fp32 sums: 2^-19 where keys have 22 bits and a sign, and 2^-22 of the score in the exponent, the same for
+    all items of a row."""
+    g = np.random.default_rng(S)
+    bf = lambda x: I.round_to(np.asarray(x, dtype=np.float32), "bf16")
+    Wk, Wv = np.zeros((d, d), np.float32), bf(np.abs(g.normal(size=(d, d))) * d ** -0.5)
+    Wk[0], Wv[0] = 1.0, 0.0                                      # channel 0 makes the keys, the others the values
+    X = bf(np.abs(g.normal(size=(L, d))))
+    X[:, 0] = bf(score / (32 ** 0.5 * 1.4427) * (1 + spread * g.normal(size=L) / score))
+    X[0] = 0.0
+    Q = bf(-1.0 - g.integers(0, 2, size=(S, 1)) / 64 + np.zeros((S, d)))
+    assert row_errors(X, Q, Wk, Wv, H, named).max() <= 2.0 ** -19 + score * 2.0 ** -22
+
+
+@pytest.mark.parametrize("d,H,S", [(64, 2, 33), (128, 4, 100), (256, 8, 300)])
+@pytest.mark.parametrize("k,q,x", [(1000, 3e-4, 1), (3000, 1e-4, 1), (4000, 1e-5, 1), (1, 3e-4, 60), (1, 1e-6, 1), (1e-6, 1e6, 1), (1e4, 3e-6, 30)])
+@pytest.mark.parametrize("named", [True, False])
+def test_split_small_queries_meet_large_keys(d, H, S, k, q, x, named):
+    """Scores of ordinary size from operands that are not: as at every scale, and in rows."""
+    g = np.random.default_rng(S)
+    r = lambda shape, s: I.round_to((g.normal(size=shape) * s).astype(np.float32), "bf16")
+    X, Q, Wk, Wv = r((128, d), x), r((S, d), q), r((d, d), k * d ** -0.5), r((d, d), d ** -0.5)
+    Q[1] *= 2.0 ** -10                                            # and a row of much smaller ones among them
+    assert row_errors(X, Q, Wk, Wv, H, named).max() <= 2.0 ** -18.5     # (a row instead of all rows of a head)
+
+
+@pytest.mark.parametrize("d,H,S", [(64, 2, 100), (128, 4, 33), (256, 8, 40)])
+@pytest.mark.parametrize("small", [8, 12, 16, 24, 40])
+@pytest.mark.parametrize("L,named", [(100, False), (800, True)])
+def test_split_a_small_value_among_large_ones(d, H, S, small, L, named):
+    """The item that all of the weight goes to has values 2^-small of the others': 2^-16 of the result at most, where two fp16 terms
+    are cut off below, the others' part of it being 2^-60."""
+    g = np.random.default_rng(S)
+    bf = lambda x: I.round_to(np.asarray(x, dtype=np.float32), "bf16")
+    Wk, Wv = np.zeros((d, d), np.float32), bf(g.normal(size=(d, d)) * d ** -0.5)
+    Wk[0], Wv[0] = 1.0, 0.0
+    X = bf(g.normal(size=(L, d)))
+    X[:, 0] = -13.0
+    X[70, 1:] *= 2.0 ** -small
+    X[70, 0] = 0.0
+    assert row_errors(X, bf(np.ones((S, d))), Wk, Wv, H, named).max() <= 2.0 ** -16
+
+
+@pytest.mark.parametrize("d,H,S", [(64, 2, 40), (128, 4, 100), (256, 8, 100)])
+@pytest.mark.parametrize("times", [2.0 ** 12, 2.0 ** 90, float("inf")])
+def test_split_a_user_s_own_queries_beyond_fp16(d, H, S, times):
+    """Large queries of one user, over small keys, are his alone: the others keep their bits."""
+    lens = [40, 300, 90, 3, 200]
+    X, off, Q, Wk, Wv = problem(17, d, S, per_user=True, lens=lens)
+    before = run(X, off, Q, Wk, Wv, H)
+    with np.errstate(invalid="ignore"):
+        Q[1] = Q[1] * times
+    if np.isfinite(times):
+        X[off[1]:off[2]] *= 2.0 ** -12
+    out = torch.full((5, S, d), float("nan"), device="cuda", dtype=torch.bfloat16)
+    V.vista_summarize(dev(X, "bf16"), torch.from_numpy(off).cuda(), dev(Q, "bf16"), dev(Wk, "bf16"), dev(Wv, "bf16"), out, H=H)
+    got = host64(out)
+    for b in (0, 2, 3, 4):
+        assert np.array_equal(before[b], got[b])
+    if times == 2.0 ** 12:
+        check(got[1:2], O.summarize(X[off[1]:off[2]], np.array([0, lens[1]]), Q[1:2], Wk, Wv, H), 1e-4)
+    elif times == 2.0 ** 90:                                       # every weight goes to the best item
+        check(got[1:2], O.summarize(X[off[1]:off[2]], np.array([0, lens[1]]), Q[1:2], Wk, Wv, H), 1e-4)
