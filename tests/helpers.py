@@ -82,28 +82,50 @@ def always_short(d, S):
     return 12288 if d == 128 else 4096 if S < 256 else 6144
 
 
-def is_short_history(form, d, S, N, B, own_queries=False):
-    return N <= always_short(d, S) or N + user_as_items(form, d, S, own_queries) * (B - 1) <= short_history_limit(form, d, S)
+def is_short_history(form, d, S, N, B, own_queries=False, limit=None):
+    limit = short_history_limit(form, d, S) if limit is None else limit
+    return N <= always_short(d, S) or N + user_as_items(form, d, S, own_queries) * (B - 1) <= limit
+
+
+def takes_one_head(form, d, S, N, B, own_queries=False):
+    """The shortest of these go to workgroups of one head, where the call leaves the segment size open."""
+    if (d == 256 and S < 256) or not is_short_history(form, d, S, N, B, own_queries, short_history_limit(form, d, S) // 8 * 7):
+        return False
+    if d == 256 or S == 512:
+        return True
+    few = 16384 if S == 64 else {"softmax": 49152, "silu": 53248}[form] if S == 128 else {"softmax": 57344, "silu": 40960}[form]
+    return N <= few * (0.4 + 0.6 * 32.0 / (B + 31.0))
 
 
 def fitted_segment(form, d, S, N, B, own_queries=False):
     """Segment size of those kernels before any limit of the workspace (histories of up to 131 072 items)."""
-    units = 256 // (4 if d == 256 else 2 if S == 512 else 1)
+    whole = 4 if d == 256 else 2 if S == 512 else 1                  # groups of heads
+    share = lambda groups: -(-(-(-N // (256 // groups))) // 32) * 32
+    if takes_one_head(form, d, S, N, B, own_queries):
+        return max(128, share(8 if d == 256 else 4))
     if not is_short_history(form, d, S, N, B, own_queries):
-        return max(128, -(-(-(-N // units)) // 32) * 32)
+        return max(128, share(whole))
     by_root = (int(1.5 * N ** 0.5) + 16) // 32 * 32 if d == 128 and S < 512 else 0
-    return max(128, -(-(-(-N // (units // 2))) // 32) * 32, by_root)
+    return max(128, share(2 * whole), by_root)
 
 
-def takes_half_workgroups(form, off, d, H, S, own_queries=False, segment_items=0):
+def workgroups_taken(form, off, d, H, S, own_queries=False, segment_items=0):
     """Which kind of workgroup a call of those kernels takes, as the library's rules put it: at the fitted segment size as
-    above, at another one (named, or the base schedule's where the workspace has a limit) by the number of workgroups."""
+    above (named, halves in place of one head), at another one (named, or the base schedule's where the workspace has a limit) by
+    the number of workgroups."""
     B, N = len(off) - 1, int(off[-1])
     desc = V.summarize_desc(B, S, d, H, V.VISTA_BF16, N, own_queries, segment_items=segment_items,
                             attn=V.VISTA_ATTN_SILU if form == "silu" else V.VISTA_ATTN_SOFTMAX)
     seg = V.vista_summarize_call_segment_items(desc)
     if seg == fitted_segment(form, d, S, N, B, own_queries):
-        return is_short_history(form, d, S, N, B, own_queries)
+        if takes_one_head(form, d, S, N, B, own_queries):
+            return "half" if segment_items else "one"
+        return "half" if is_short_history(form, d, S, N, B, own_queries) else "whole"
     few = N + 128 * B <= short_history_limit(form, d, S)
     halves = -(-N // seg) * (8 if d == 256 else 4 if S == 512 else 2)
-    return few or halves <= 256 if d == 128 else halves <= 288 if few else halves <= 256 and S != 64
+    half = few or halves <= 256 if d == 128 else halves <= 288 if few else halves <= 256 and S != 64
+    return "half" if half else "whole"
+
+
+def takes_half_workgroups(form, off, d, H, S, own_queries=False, segment_items=0):
+    return workgroups_taken(form, off, d, H, S, own_queries, segment_items) == "half"

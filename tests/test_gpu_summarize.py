@@ -6,7 +6,8 @@ import torch
 from oracle import vista_oracle as O
 from paper_2510_22049_amd import binding as V
 from paper_2510_22049_amd import inputs as I
-from tests.helpers import assert_blocks_close, block_errors, dev, host64, is_short_history, short_history_limit, takes_half_workgroups, user_as_items
+from tests.helpers import (assert_blocks_close, block_errors, dev, host64, is_short_history, short_history_limit, takes_half_workgroups, user_as_items,
+                           workgroups_taken)
 
 pytestmark = pytest.mark.gpu
 
@@ -50,7 +51,7 @@ def test_mfma_jagged_matches_oracle(d, H, S, seg):
     assert np.all(got[1] == 0) and np.all(got[8] == 0)
 
 
-@pytest.mark.parametrize("lens,seg,half", [(LENS, 64, True), ([5000], 0, True), ([9000, 33, 0, 120000, 1, 64, 20031, 150000], 2048, False)])
+@pytest.mark.parametrize("lens,seg,half", [(LENS, 64, True), ([5000], 128, True), ([9000, 33, 0, 120000, 1, 64, 20031, 150000], 2048, False)])
 def test_both_orders_of_a_tile_agree(lens, seg, half):
     """S = 256 at d = 128 takes a tile in one order of instructions for shared queries and in another for queries of the
     users' own (launch_for_shape; were both sent to one kernel, this would compare it with itself): the same sums, so the
@@ -388,6 +389,7 @@ def test_workgroups_of_one_head(form, d, H, S, edge):
     kw = dict(attn=attn, self_term=edge == "self")
     fitted = V.vista_summarize_call_segment_items(V.summarize_desc(len(lens), S, d, H, V.VISTA_BF16, int(off[-1]), edge == "own", attn=attn,
                                                                    self_term=edge == "self"))
+    assert workgroups_taken(form, off, d, H, S, edge == "own") == "one" and workgroups_taken(form, off, d, H, S, edge == "own", fitted) == "half"
     got, halves = run(X, off, Q, Wk, Wv, H, **kw), run(X, off, Q, Wk, Wv, H, segment_items=fitted, **kw)
     want = (O.summarize_silu if silu else O.summarize)(X, off, Q, Wk, Wv, H, self_term=edge == "self")
     assert_blocks_close(got, want, "bf16", f"one head, {form} d={d} S={S} {edge}")
@@ -395,3 +397,5 @@ def test_workgroups_of_one_head(form, d, H, S, edge):
     assert all(np.all(got[b] == 0) for b in range(len(lens)) if lens[b] == 0)
     if silu or edge != "mixed":
         assert np.array_equal(got, halves)
+    elif S > 64:                           # half the blocks a wave: a bound on scores of other queries, which is left at other tiles
+        assert not np.array_equal(got, halves)

@@ -6,7 +6,7 @@ import pytest
 
 from paper_2510_22049_amd import binding as V
 from paper_2510_22049_amd import inputs as I
-from tests.helpers import always_short, fitted_segment, is_short_history, short_history_limit, user_as_items
+from tests.helpers import always_short, fitted_segment, is_short_history, short_history_limit, takes_one_head, user_as_items
 
 
 def desc(B, N, seg=0, S=256, d=128, H=4):
@@ -148,3 +148,23 @@ def test_where_a_history_is_short(form, d, H, S, own):
             assert V.vista_summarize_call_segment_items(q) == (seg if fits else base), (B, N)
             told += fits and seg != fitted_segment(form, d, S, N, 10 ** 6 if N <= edge else 0, own)
     assert told >= 4
+
+
+@pytest.mark.parametrize("form", ["softmax", "silu"])
+@pytest.mark.parametrize("S", [64, 128, 256])
+@pytest.mark.parametrize("own", [False, True])
+def test_where_a_workgroup_takes_one_head(form, S, own):
+    """At d = 128 the heads of a segment are four workgroups instead of two or one, so the segments that fill the chip are longer: the
+    size tells on which side of the limit a call is.  (At d = 256 and at 512 seeds halves are as many.)"""
+    told = 0
+    for B in (1, 2, 5, 17, 64, 200):
+        lo, hi = 1024, 10 ** 6                                        # takes_one_head falls once
+        assert takes_one_head(form, 128, S, lo, B, own) and not takes_one_head(form, 128, S, hi, B, own)
+        while hi - lo > 1:
+            mid = (lo + hi) // 2
+            lo, hi = (mid, hi) if takes_one_head(form, 128, S, mid, B, own) else (lo, mid)
+        for N in (lo - 999, lo, hi, hi + 999):
+            q = V.summarize_desc(B, S, 128, 4, V.VISTA_BF16, N, own, attn=V.VISTA_ATTN_SILU if form == "silu" else V.VISTA_ATTN_SOFTMAX)
+            assert V.vista_summarize_call_segment_items(q) == fitted_segment(form, 128, S, N, B, own), (B, N)
+        told += fitted_segment(form, 128, S, lo, B, own) != fitted_segment(form, 128, S, hi, B, own)
+    assert told >= 3
