@@ -318,7 +318,7 @@ def main() -> None:
         "roofline": mfma_roofline(
             flop_item, items_per_s, cal, traffic=traffic.get("summarize_mfma"),
             traffic_source="profiles/hbm_traffic_pmc.txt (default segment size)" if traffic else None,
-            kernel="summarize_mfma_kernel<128, 4, 4, 4, 8, true, false, 512, softmax, 2, true>", algorithmic_bytes=N * c1.d * 2,
+            kernel="summarize_mfma_kernel<128, 4, 4, 4, 8, true, 512, softmax, 2, true>", algorithmic_bytes=N * c1.d * 2,
             note="duration = one whole vista_summarize call (summarize_mfma + merge kernels, HIP events on the "
                  "launch stream); the kernel-only average is in profiles/",
             co_bound={"bound": "alu", "what": "the tile loop's own instruction mix, registers only (per query block "
@@ -339,7 +339,7 @@ def main() -> None:
         ms, med = time_steps(lambda: step1(attn, w_), a.steps, a.warmup)
         ips = N / (ms * 1e-3)
         if leg == "silu":
-            roof = mfma_roofline(flop_item, ips, cal, kernel="summarize_mfma_kernel<128, 4, 4, 4, 8, true, false, 512, silu, 2, false>",
+            roof = mfma_roofline(flop_item, ips, cal, kernel="summarize_mfma_kernel<128, 4, 4, 4, 8, true, 512, silu, 2, false>",
                                  note="same flop count as the softmax form; two transcendentals per score (2^t, 1/x)")
         else:
             fl = 4 * c1.d * c1.d + 4 * c1.d * (c1.d // c1.H)       # projections + SiLU(K)^T V per head

@@ -85,7 +85,7 @@ __device__ __forceinline__ constexpr int acc_row0(int i) { return 8 * (i / 4) + 
 template <int V>
 struct Int { static constexpr int value = V; };
 
-constexpr int kXBuf = 3;             // ring depth of the X tiles and of the projected tiles in LDS
+constexpr int kXBuf = 3;             // ring depth of the X tiles in LDS (and of the projected tiles in the plain kernels)
 
 // Self term: K' = Q W_k and V' = Q W_v of the seeds in fp32 (bf16 inputs, products exact, fp32 sums).
 // A unit is 32 seeds x 32 channels of both, formed by one wave: the seeds' rows read once as the A operand, the

@@ -1072,14 +1072,15 @@ static int head_groups(const vista_summarize_desc& d, Heads heads) {
 }
 static int resident_workgroups(const vista_summarize_desc& d, Heads heads) {
   // One head, split operands: another one shares the compute unit where its segment would be longer than 512 items, a third (d = 64, waves
-  // of 168 registers) than 800; eight waves have it to themselves (d = 64, S = 100, 48 users of 300 007 items 54.6 us with two, 52.4 with three;
-  // S = 200 in segments of 1216 84, of 2368 81; d = 128, S = 100, 60 000 items in segments of 512 33.7, of 1024 36).
+  // of 168 registers) than 1600; eight waves have it to themselves.  us a call with one / two / three: d = 64, S = 100, 48 users of 300 007 items 71.9 / 57.3
+  // / 55.1, of 100 000 38.0 / 34.6 / 34.4, of 60 000 31.0 / 29.8 / 31.1; S = 200, 180 000 64.3 / 67.2 / 74.0; d = 128, S = 100, 120 000 70.2 / 55.9 / 66.7,
+  // 60 000 47.1 / 40.3 / 46.9; S = 250, 30 000 36.8 / 44.7 / 52.1.
   if (heads == Heads::kOne && mfma_split_supported(d)) {
     const int64_t alone = d.total_items * d.H / 256;
     return d.S > 128 || alone <= 512 ? 1 : d.d == 64 && alone > 1600 ? 3 : 2;
   }
   // Two fit, but two cold starts on a compute unit have to pay: a segment of 768 items for one does it with the split
-  // operands (d = 64, S = 100: 60 000 items in 29.7 us with one, 33.7 with two, 200 000 in 52.5 and 51.9), 2048 at d = 256.
+  // operands (d = 64, S = 40: 60 000 items in 23.8 us with one, 24.5 with two, 100 000 in 26.4 and 28.0, 200 000 in 37.2 and 33.3), 2048 at d = 256.
   if (mfma_split_supported(d)) return d.d != 256 && d.S <= 128 && d.total_items > 768 * 256 / head_groups(d, Heads::kWhole) ? 2 : 1;
   return d.d == 256 && d.S == 64 && d.total_items > 131072 ? 2 : 1;
 }
@@ -1193,7 +1194,7 @@ static hipError_t launch_for_shape(MfmaSummarizeParams& p, const vista_summarize
   // of 300 003 135.9 / 134.7, with queries of their own 146.1 / 146.2.  With queries of their own at S = 256 the registers of
   // their load are spilled in the loop (8 users 84.4 / 84.7, 300 users 120.7 / 122.4): those stay free.  So do one and two blocks a
   // wave (S = 64 66.9 / 67.8, S = 128 equal) and d = 256 (S = 128 225 / 230, S = 512 435 / 450), where a wave has less to put between its
-  // products or attends without projecting.  The SiLU form and the split operands have no such tile.
+  // products or attends without projecting.  The SiLU form has no such tile.
   constexpr bool softmax = ATTN == VISTA_ATTN_SOFTMAX;
   const bool shared = p.q_user_stride == 0;
   const Heads heads = heads_of_workgroups(desc, p.seg, G);
