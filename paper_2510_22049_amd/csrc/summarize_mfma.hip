@@ -1088,14 +1088,16 @@ static int resident_workgroups(const vista_summarize_desc& d, Heads heads) {
 // Split operands: one head a workgroup and one block a wave, three to eight waves, beside two heads and two blocks.  us a call, two
 // heads / one: d = 64, S = 100, 30 users of 30 000 items 25.4 / 23.4, of 150 000 41.8 / 40.5, 48 of 300 007 55.3 to 55.8 / 55.0 to 55.9, of 450 000 70.6 / 71.6, of 600 000
 // 85.8 / 87.6; S = 200, 30 of 60 000 40.0 / 35.7, of 200 000 65.4 / 65.2, of 300 007 83.1 / 89.6; d = 128, S = 100, 30 of 60 000 43.1 / 41.4, of
-// 120 000 55.4 / 55.9, of 200 000 73.8 / 77.7; S = 250, one of 15 000 30.4 / 24.6, 30 of 30 000 40.0 / 37.4, of 60 000 51.1 / 53.0.  One and two blocks in all
+// 120 000 55.4 / 55.9, of 200 000 73.8 / 77.7; S = 205, one of 53 749 45.4 / 40.7; S = 250, one of 15 000 30.4 / 24.6, of 55 300 46.6 / 43.6, 30 of 30 000
+// 40.0 / 37.4, of 55 000 55.3 / 50.7, of 60 000 51.1 / 53.0.  One and two blocks in all
 // make two waves, which is worth it in short histories: d = 64, S = 40, one of 15 000 17.7 / 16.9, 30 of 30 000 20.3 / 21.8; d = 128, S = 40, 30 of
 // 7001 24.1 / 22.7, of 15 000 21.7 / 24.8.
 static bool one_head_split(const vista_summarize_desc& d) {
   const int64_t nqb = (d.S + 31) / 32, N = d.total_items;
   if (d.d == 256 || nqb > 8) return false;
   if (nqb <= 2) return N <= (d.d == 64 ? 16384 : 8192);
-  return d.d == 64 ? N * nqb <= 1300000 : N * (nqb < 4 ? 16 : nqb * nqb) <= 2000000;
+  if (d.d == 64) return N * nqb <= 1300000;
+  return N <= 125000 && double(N) * (double(nqb) * sqrt(double(nqb))) <= 1500000.0;
 }
 
 static Heads fitted_heads(const vista_summarize_desc& d) {

@@ -345,7 +345,7 @@ def test_split_histories_that_change_their_scale(d, H, S, per_user, seg):
 
 
 @pytest.mark.parametrize("d,H,S,limit", [(64, 2, 40, 16384), (64, 2, 256, 275000), (128, 4, 33, 8192), (128, 4, 96, 237500), (128, 4, 250, 59375),
-                                           (64, 2, 255, 162500), (128, 4, 95, 125000), (128, 4, 249, 31250)])
+                                           (64, 2, 255, 162500), (128, 4, 95, 125000), (128, 4, 249, 66291), (128, 4, 205, 80992)])
 @pytest.mark.parametrize("beyond", [0, 1])
 @pytest.mark.parametrize("self_term", [False, True])
 def test_both_sides_of_one_head_a_workgroup(d, H, S, limit, beyond, self_term):
