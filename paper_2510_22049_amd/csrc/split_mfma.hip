@@ -966,6 +966,9 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
       const char* base = reinterpret_cast<const char*>(p.X) + cf.row * (D * 2);
       int n = 0;
       while (n < run && plain) {
+        // The loop's head on a cache line: d = 128, 300 007 items, S = 300 212 -> 200 us a call, S = 400 232 -> 228, S = 100 and 200 the same; d = 256 loses
+        // (S = 100 317 -> 323), d = 64 is the same.
+        if constexpr (D == 128) asm volatile(".p2align 6");
         lds_barrier();
         fetch_rows(base, kTile - 1, r == kXBuf - 1 ? 0 : r + 1);
         base += kTile * D * 2;
