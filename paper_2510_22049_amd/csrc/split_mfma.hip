@@ -45,8 +45,9 @@ constexpr float kPlainScore = 54.f;
 // What fp16 terms leave of a weight is at most 2^-25 (weights from 2^-3 up have 22 bits and a sign).  So over a piece of n items a row's sum is
 // wrong by at most 2^-25 sum |v| <= 2^-25 (n sum |v|^2)^1/2, and a row that is not 2^19 times that is not known well enough: (2^-6)^2.
 // Of a value at most 2^-25 is left too, which matters where a row's own values are small beside the others of their columns: its mean has to be
-// 2^-6.5, or a quarter of what n values of the mean size (2^-3.5 at least) come to where they point anywhere: (2^-6.5)^2, (2^-3.5)^2, (2^-2)^2.
-constexpr float kWeightsLost2 = 2.4414062e-4f, kValuesLost2 = 1.2207031e-4f, kValueMean2 = 7.8125e-3f, kMeanLost2 = 0.0625f;
+// 2^-2.5, which is 2^20 times sqrt(32) of these, or a quarter of what n values of the mean size (2^-0.5 at least; 2^7.5 is usual) come to where
+// they point anywhere, as what is left of them does: (2^-2.5)^2, (2^-0.5)^2, (2^-2)^2.
+constexpr float kWeightsLost2 = 2.4414062e-4f, kValuesLost2 = 0.03125f, kValueMean2 = 0.5f, kMeanLost2 = 0.0625f;
 
 // One 32-wide operand of a tile: the two k-halves of its two fp16 terms, 22 bits and a sign.
 struct Operand {

@@ -414,8 +414,8 @@ def test_split_small_queries_meet_large_keys(d, H, S, k, q, x, named):
 @pytest.mark.parametrize("small", [8, 12, 16, 24, 40])
 @pytest.mark.parametrize("L,named", [(100, False), (800, True)])
 def test_split_a_small_value_among_large_ones(d, H, S, small, L, named):
-    """The item that all of the weight goes to has values 2^-small of the others': 2^-16 of the result at most, where two fp16 terms
-    are cut off below, the others' part of it being 2^-60."""
+    """The item that all of the weight goes to has values 2^-small of the others', whose part of the result is 2^-60: the result is known
+    as any other, to 2^-20 where two fp16 terms are cut off below and to fp32 sums of d products, some 2^-21."""
     g = np.random.default_rng(S)
     bf = lambda x: I.round_to(np.asarray(x, dtype=np.float32), "bf16")
     Wk, Wv = np.zeros((d, d), np.float32), bf(g.normal(size=(d, d)) * d ** -0.5)
@@ -424,7 +424,7 @@ def test_split_a_small_value_among_large_ones(d, H, S, small, L, named):
     X[:, 0] = -13.0
     X[70, 1:] *= 2.0 ** -small
     X[70, 0] = 0.0
-    assert row_errors(X, bf(np.ones((S, d))), Wk, Wv, H, named).max() <= 2.0 ** -16
+    assert row_errors(X, bf(np.ones((S, d))), Wk, Wv, H, named).max() <= 2.0 ** -19
 
 
 @pytest.mark.parametrize("d,H,S", [(64, 2, 40), (128, 4, 100), (256, 8, 100)])
