@@ -9,7 +9,7 @@
 // count (and d = 64) keeps them whole, as one thread per query on the vector unit did before: each is
 // two fp16 terms, 22 bits and a sign.  Scores take two products (the seeds are bf16, one fp16 term), P V
 // three, the scale is applied to the fp32 keys.  fp16 has these bits from 2^-3 to 2^16 only, so everything is brought there by powers of two, which
-// change no bit: queries and keys by a unit of the seeds, values by their column of W_v and by the first tile of a user's piece, weights by
+// change no bit: queries and keys by a unit of the seeds (users' own: of each user's), values by their column of W_v and by the first tile of a user's piece, weights by
 // a whole-number reference of each row's own, which is one more product (ones times -m).  That is 19 binary places, and a row may need
 // others: its items of large weight may have no value, its own values may be small beside its neighbours'.  So what the terms leave of a row at most
 // is held against what the row came to when a piece ends, and a piece with a row that is not known to 2^-19 by that, with keys, values or queries outside fp16,
@@ -156,6 +156,7 @@ struct SplitLds {
   float vnorm[2][HPW][64];            // that of the value columns, infinite too
   int4 vunit[HPW][8];                 // a channel's published values times two to this and its piece's unit are its values
   int punit[4][HPW];                  // units of four pieces, by their number: the one attended over and the two that may be published beside it
+  int qunit[4][HPW];                  // and of users' own queries: two to this is what they are divided by
   int redo;                           // some wave has records to form again
   uint4 wop[WREG ? 1 : HPW * 2 * (D / 16) * 64];   // projection weights as MFMA operands: [head][K|V][k-slice][lane]
 };
@@ -401,8 +402,31 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
       if (hf == 0) reinterpret_cast<int*>(sm.vunit[hl])[l32] = usual ? e : 0;
     }
   };
+  // The unit of the queries, the same for all waves of a head: a power of two that brings the largest number of eight rows to 1..2; keys are published
+  // by the inverse.  Users' own queries have units of their own, which the K wave forms two tiles ahead with the piece's first keys.
+  const bool own = p.q_user_stride != 0;
+  float qunit = 1.f, kunit = 1.f;        // queries are taken times the first, keys times the second, the inverse of their user's
+  uint2 qsome = make_uint2(0, 0);
+  auto request_some = [&](int user) __attribute__((always_inline)) {
+    qsome = *reinterpret_cast<const uint2*>(p.Q + p.q_user_stride * user + int64_t((lane >> 3) * p.S >> 3) * D + 32 * h + 4 * (lane & 7));
+  };
+  auto unit_of_some = [&]() __attribute__((always_inline)) {
+    const uint32_t a = qsome.x & 0x7FFF7FFFu, b = qsome.y & 0x7FFF7FFFu;
+    const uint32_t top = wave_max(max(max(a & 0xFFFFu, a >> 16), max(b & 0xFFFFu, b >> 16)));
+    const int e = int(top >> 7) - 127;
+    return top == 0 || e > 100 ? 0 : e < -100 ? -100 : e;        // (0 for an infinite or NaN one too)
+  };
+  auto power_of_two = [](int e) __attribute__((always_inline)) { return __uint_as_float(uint32_t(127 + e) << 23); };
   int pieces_out = 0;                // pieces published so far
   auto start_piece = [&](const f32x16& acc) __attribute__((always_inline)) {
+    if constexpr (ROLE == 0) {
+      if (own) {
+        const int e = unit_of_some();
+        kunit = power_of_two(e);
+        if (lane == 0) sm.qunit[pieces_out & 3][hl] = e;
+        ++pieces_out;
+      }
+    }
     if constexpr (ROLE == 1) {
       float most[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -422,7 +446,6 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
   const int qbase = qblock * 32;         // first query of this wave
   bf16x8 qop[NQB][2];                    // (once settled, the bits of fp16 numbers)
   float qmax2 = 0.f;
-  float qunit = 1.f, kunit = 1.f;        // queries are taken times the first, keys times the second, its inverse
   auto request_queries = [&](int user) __attribute__((always_inline)) {
     const char* Qb = reinterpret_cast<const char*>(p.Q + p.q_user_stride * user + 32 * h) + 8 * hf;
 #pragma unroll
@@ -440,21 +463,6 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
         qop[qb][part] = t.v;
       }
     }
-  };
-  // The unit of shared queries, the same for all waves of a head: a power of two that brings the largest number of eight rows to 1..2; keys are
-  // published by the inverse.  Users' own queries are taken as they are.
-  uint2 qsome = make_uint2(0, 0);
-  auto request_some = [&]() __attribute__((always_inline)) {
-    qsome = *reinterpret_cast<const uint2*>(p.Q + int64_t((lane >> 3) * p.S >> 3) * D + 32 * h + 4 * (lane & 7));
-  };
-  auto settle_unit = [&]() __attribute__((always_inline)) {
-    const uint32_t a = qsome.x & 0x7FFF7FFFu, b = qsome.y & 0x7FFF7FFFu;
-    const uint32_t top = wave_max(max(max(a & 0xFFFFu, a >> 16), max(b & 0xFFFFu, b >> 16)));
-    int e = int(top >> 7) - 127;
-    if (top == 0 || e > 100) e = 0;              // (an infinite or NaN one too)
-    if (e < -100) e = -100;
-    kunit = __uint_as_float(uint32_t(127 + e) << 23);
-    qunit = __uint_as_float(uint32_t(127 - e) << 23);
   };
   bool coarse = false;                   // some query number lost bits
   float bound2 = 0.f;                    // keys of no larger squared norm have scores within kPlainScore
@@ -608,8 +616,8 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
 
   // everything the workgroup starts from is requested before any of it is waited for
   request_weights();
-  if (p.q_user_stride == 0) {
-    request_some();
+  if (!own) {
+    request_some(0);
     request_queries(0);
   }
   Cursor ca, cf;
@@ -671,7 +679,7 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
     return mfma_f16((j < 2 ? kk.lo[j & 1] : kk.hi[j & 1]).v, qop[qb][j & 1], j ? s : f32x16{0});
   };
   // which of the tiles t + 2, t + 3 and t + 4, from the lowest bit, are the first of their piece
-  int firsts = 0;
+  int firsts = 0, user2 = 0, user3 = 0, user4 = 0;      // and whose they are
   // A plain tile, in an order of its own (pin): every pair of exponentials, its split and its sum stand between two products, those of the
   // next block's scores, of the block before with the values and of the projection.  A tile ends with the first scores of the next
   // one (nx) and its last block's products, beside the projected tile's own split.
@@ -899,13 +907,23 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
   fetch(cf, 0);
   const int first1 = cursor_enters(cf);
   fetch(cf, 1);
+  const int user1 = cf.user;
   firsts = cursor_enters(cf);
+  user2 = cf.user;
   fetch(cf, 2);
   firsts |= cursor_enters(cf) << 1;
-  if (p.q_user_stride != 0) request_queries(ca.user);
+  user3 = cf.user;
+  if (own) {
+    request_some(ca.user);
+    request_queries(ca.user);
+  }
   settle_weights();
   settle_values();
-  if (p.q_user_stride == 0) settle_unit();
+  {
+    const int e = unit_of_some();
+    kunit = power_of_two(e);
+    qunit = power_of_two(-e);
+  }
   settle_queries();
   safe2 = bound2;
   wait_vm(Int<CPT>{});
@@ -917,12 +935,16 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
     publish(0, acc);
     f32x16 acc1 = {0};
     project(1, 0, KS, acc1);
-    if (first1) start_piece(acc1);
+    if (first1) {
+      if (own && ROLE == 0) request_some(user1);
+      start_piece(acc1);
+    }
     publish(1, acc1);
   }
   lds_barrier();              // slot 0's rows are projected by everyone, its operands are visible
   fetch(cf, 0);               // tile 3
   firsts |= cursor_enters(cf) << 2;
+  user4 = cf.user;
   read_k(0);
   read_v(0);
   wait_vm(Int<CPT>{});        // tile 2 has landed
@@ -942,11 +964,16 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
     if (drain) wait_vm(Int<0>{}); else wait_vm(Int<CPT>{});
     drain = false;
     firsts = (firsts >> 1) | (cursor_enters(cf) << 2);
+    user2 = user3;
+    user3 = user4;
+    user4 = cf.user;
   };
   // Start of a tile: the barrier, then the request for tile t+4.
   auto begin_tile = [&]() __attribute__((always_inline)) {
     lds_barrier();
     fetch(cf, r == kXBuf - 1 ? 0 : r + 1);
+    if constexpr (ROLE == 0)
+      if (own && (firsts & 1)) request_some(user2);
   };
   // whether the tile whose operands are in registers is a plain one
   bool unsafe = unsafe_tile(kn2);
@@ -1007,8 +1034,9 @@ __device__ __forceinline__ void split_wave(const MfmaSummarizeParams& p, SplitLd
     if (last_in_piece) {
       write_partial(done_user);
       reset_state();
-      if (p.q_user_stride != 0 && ca.valid) {
+      if (own && ca.valid) {
         request_queries(ca.user);
+        qunit = power_of_two(-sm.qunit[pieces_done & 3][hl]);
         settle_queries();
         safe2 = bound2;
       }

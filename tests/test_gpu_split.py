@@ -368,7 +368,7 @@ def test_both_sides_of_one_head_a_workgroup(d, H, S, limit, beyond, self_term):
 @pytest.mark.parametrize("d,H", [(64, 2), (128, 4), (256, 8)])
 @pytest.mark.parametrize("seg", [0, 256])
 def test_split_queries_of_zeros_beside_values_that_fp16_does_not_hold(d, H, seg):
-    """No score leaves any bound, whatever the keys: tiles handed over as fp32 are still not taken for fp16 terms."""
+    """No score leaves any bound, whatever the keys: values and keys that fp16 does not hold are seen all the same."""
     X, off, Q, Wk, Wv = problem(41, d, 40, lens=[300, 128])
     X[70:75] *= 2.0 ** 20
     Q[:] = 0.0
@@ -425,6 +425,19 @@ def test_split_a_small_value_among_large_ones(d, H, S, small, L, named):
     X[70, 1:] *= 2.0 ** -small
     X[70, 0] = 0.0
     assert row_errors(X, bf(np.ones((S, d))), Wk, Wv, H, named).max() <= 2.0 ** -19
+
+
+@pytest.mark.parametrize("d,H,S", [(64, 2, 33), (64, 2, 100), (128, 4, 100), (256, 8, 300)])
+@pytest.mark.parametrize("seg", [0, 64, 2048])
+def test_split_users_whose_own_queries_differ_in_scale(d, H, S, seg):
+    """Pieces of one tile and of many, each user's queries of another size over items of the inverse: a unit for each piece, formed
+    two tiles ahead.  (Scores as at unit scale: 1e-4 of the block.)"""
+    lens = [1, 40, 700, 0, 31, 32, 33, 5, 64, 300, 2, 95]
+    X, off, Q, Wk, Wv = problem(S, d, S, per_user=True, lens=lens)
+    for b, e in enumerate([0, 9, -9, 3, -14, 14, 0, -7, 30, -30, 5, 11]):
+        Q[b] *= 2.0 ** e
+        X[off[b]:off[b + 1]] *= 2.0 ** -e
+    check(run(X, off, Q, Wk, Wv, H, segment_items=seg), O.summarize(X, off, Q, Wk, Wv, H), 1e-4)
 
 
 @pytest.mark.parametrize("d,H,S", [(64, 2, 40), (128, 4, 100), (256, 8, 100)])
